@@ -239,7 +239,7 @@ int actq_allocate_bits(const float* w, const int64_t* D, int64_t M,
  * round trip between the statistics and the quantizer (Sec. 4.3 runs the
  * allocator inside the training step).  The result equals actq_allocate_bits
  * bit for bit: the greedy's answer is fixed by the price of its last move, which
- * one workgroup finds by radix selection over the 64-bit price patterns; moves
+ * one workgroup finds by narrowing a bracket of 64-bit price patterns; moves
  * of exactly that price are applied in (i, step) order.  It also writes the byte
  * offsets that actq_packed_bytes would compute for the chosen widths.
  *

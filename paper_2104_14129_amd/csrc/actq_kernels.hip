@@ -1753,22 +1753,38 @@ __global__ __launch_bounds__(kSensMaxBlock) void sample_sensitivity_kernel(const
 //
 // The greedy applies moves (item i, step r of the width ladder) in ascending order of
 // (price, i, r) until enough bits are freed, and an item's prices never decrease along the
-// ladder.  Its result is therefore fixed by the price of the last applied move: every move
-// strictly cheaper is applied, and the moves of exactly that price are applied in (i, r)
-// order until the budget holds.  That price is found by a radix selection over the 64-bit
-// patterns of the prices (non-negative doubles order like their bit patterns), eight passes
-// of eight bits, each a 256-bin histogram of freed bits; ties are then resolved with a
-// prefix sum in item order, and a second prefix sum turns the widths into byte offsets.
-// One workgroup does all of it out of LDS.  The prices of a thread's first item stay in
-// registers (all of them when M <= the workgroup size); those of further items are
-// recomputed in every pass.  Three histograms rotate so that a pass needs one barrier:
-// while pass p accumulates into one, every wavefront has already scanned the previous one
-// for itself and the third one is being cleared for the pass after.
+// ladder.  Its result is therefore fixed by the price of the last applied move, the threshold:
+// every move strictly cheaper is applied, and the moves of exactly that price are applied in
+// (i, r) order until the budget holds.  One workgroup finds the threshold and works out of LDS;
+// a prefix sum then turns the widths into byte offsets.
+//
+// What bounds it: one workgroup has one compute unit, so the number of (binary64) divisions, LDS
+// atomics and barriers is the time.  A radix selection over the 64-bit patterns of all prices
+// (eight passes of eight bits) took 154 us for 13,568 items with all eight widths, 101 us with
+// {1, 2, 4, 8}, and 10 us for 128 items.  Hence:
+//   * select_price narrows a bracket [lo, hi] of price patterns, starting from the smallest and
+//     the largest candidate instead of from 64 free bits, and stops as soon as at most 64
+//     candidates are left: mostly one histogram instead of eight;
+//   * a small problem (allocate_bits_small_kernel) has one move per thread and every price in LDS;
+//   * a large one (allocate_bits_kernel) does not price its moves at all at first.  A price is
+//     (w / D) * c_r to within a few units in the last place, so a histogram of the ITEMS over
+//     w / D gives bounds of the bits freed below any price t: sum_r dw_r * (elements of the items
+//     with w / D < t / c_r).  A search over t on that table leaves a bracket that holds the
+//     threshold and, typically, one or two hundred of the 95,000 moves; only those are priced
+//     exactly, and the widths of all other items follow from comparing w / D with t / c_r.
+// The order of w / D is taken from the upper 32 bits of its binary64 pattern (20 bits of mantissa),
+// computed to within one unit.  Every comparison on it leaves a margin of two units: what passes is
+// cheaper (dearer) by one unit at least, 2^-21, and the rounding errors of t / c_r and of the price
+// are below 2^-50.  What lies inside the margin is decided by exact prices.  Both the bits freed
+// below the bracket and the widths of the items are taken per bin of the table, not per item.
 
 constexpr int kAllocBlock = 1024;
 constexpr int kAllocWavesMax = kAllocBlock / kWave;
 constexpr int kMaxSteps = 7;
-constexpr int kAllocCached = 11;  // items per thread whose (w, D) the allocator keeps in registers
+constexpr int kSmallMoves = 2048;     // the small kernel: moves, at most two per thread
+constexpr int kAllocBins = 4096;      // bins of the large kernel's table over w / D
+constexpr int kAllocList = 1024;      // exactly priced moves the large kernel keeps in LDS
+constexpr int kAllocQuads = 4;        // quadruples of consecutive items per thread kept in registers: 16,384 items in all
 
 struct AllocArgs {
     int64_t M;
@@ -1776,6 +1792,8 @@ struct AllocArgs {
     const int64_t* D_items;  // per-item element counts, or null
     int64_t budget_bits;
     Ladder lad;
+    double inverse[kMaxSteps];   // 1 / lad.price[r]
+    uint32_t width_nibbles;      // lad.width[k] in bits 4 k .. 4 k + 3
 };
 
 // DPP row_shr:K with zero fill: lane i of a row of 16 receives lane i - K, or 0 when there is none.
@@ -1787,6 +1805,14 @@ __device__ __forceinline__ uint64_t row_shift_right(uint64_t v)
     return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
+template <int CTRL>
+__device__ __forceinline__ uint64_t dpp_u64(uint64_t v)
+{
+    const uint32_t lo = dpp_u32<CTRL>(static_cast<uint32_t>(v));
+    const uint32_t hi = dpp_u32<CTRL>(static_cast<uint32_t>(v >> 32));
+    return (static_cast<uint64_t>(hi) << 32) | lo;
+}
+
 __device__ __forceinline__ uint64_t read_lane(uint64_t v, int src)
 {
     const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(v)), src));
@@ -1794,14 +1820,21 @@ __device__ __forceinline__ uint64_t read_lane(uint64_t v, int src)
     return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
-// Inclusive prefix sum over the 64 lanes: four shift-and-add steps inside each row of 16,
-// then the totals of the preceding rows, read from the rows' last lanes.
-__device__ __forceinline__ uint64_t wave_inclusive_scan(uint64_t v, int lane)
+// Inclusive prefix sum inside each row of sixteen lanes.
+__device__ __forceinline__ uint64_t row_inclusive_scan(uint64_t v)
 {
     v += row_shift_right<1>(v);
     v += row_shift_right<2>(v);
     v += row_shift_right<4>(v);
     v += row_shift_right<8>(v);
+    return v;
+}
+
+// Inclusive prefix sum over the 64 lanes: the rows' own, then the totals of the preceding rows,
+// read from the rows' last lanes.
+__device__ __forceinline__ uint64_t wave_inclusive_scan(uint64_t v, int lane)
+{
+    v = row_inclusive_scan(v);
     const uint64_t t0 = read_lane(v, 15), t1 = read_lane(v, 31), t2 = read_lane(v, 47);
     const int row = lane >> 4;
     uint64_t before = 0;
@@ -1811,163 +1844,105 @@ __device__ __forceinline__ uint64_t wave_inclusive_scan(uint64_t v, int lane)
     return v + before;
 }
 
-// Exclusive prefix sum over the workgroup in thread order; `total` receives the sum.
-__device__ __forceinline__ uint64_t block_exclusive_scan(uint64_t v, uint64_t* wave_totals, uint64_t& total)
+struct Add { template <typename V> __device__ V operator()(V a, V b) const { return a + b; } };
+struct Min { template <typename V> __device__ V operator()(V a, V b) const { return a < b ? a : b; } };
+struct Max { template <typename V> __device__ V operator()(V a, V b) const { return a > b ? a : b; } };
+
+// Reduction over each row of sixteen lanes, in every lane of it.
+template <typename Op>
+__device__ __forceinline__ uint64_t row_reduce(uint64_t v, Op op)
 {
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    v = op(v, dpp_u64<kDppXor1>(v));
+    v = op(v, dpp_u64<kDppXor2>(v));
+    v = op(v, dpp_u64<kDppHalfMirror>(v));
+    v = op(v, dpp_u64<kDppXor8>(v));
+    return v;
+}
+
+template <typename Op>
+__device__ __forceinline__ uint32_t wave_reduce(uint32_t v, Op op)
+{
+    v = op(v, dpp_u32<kDppXor1>(v));
+    v = op(v, dpp_u32<kDppXor2>(v));
+    v = op(v, dpp_u32<kDppHalfMirror>(v));
+    v = op(v, dpp_u32<kDppXor8>(v));
+    const auto lane = [&](int src) { return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), src)); };
+    return op(op(lane(0), lane(16)), op(lane(32), lane(48)));
+}
+
+template <typename Op>
+__device__ __forceinline__ uint64_t wave_reduce(uint64_t v, Op op)
+{
+    v = row_reduce(v, op);
+    return op(op(read_lane(v, 0), read_lane(v, 16)), op(read_lane(v, 32), read_lane(v, 48)));
+}
+
+// Second half of a reduction over the workgroup, behind a barrier: the wavefronts' results.
+template <typename Op>
+__device__ __forceinline__ uint64_t combine_waves(const uint64_t* of_wave, int waves, uint64_t identity, Op op)
+{
+    const int k = threadIdx.x & 15;
+    return read_lane(row_reduce(k < waves ? of_wave[k] : identity, op), 0);
+}
+
+// Exclusive prefix sum over the workgroup in thread order; `total` receives the sum.  One barrier;
+// `of_wave` (one entry per wavefront) must not be in use by anything else until the next barrier.
+__device__ __forceinline__ uint64_t block_exclusive_scan(uint64_t v, uint64_t* of_wave, uint64_t& total)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int waves = blockDim.x >> 6;
     const uint64_t incl = wave_inclusive_scan(v, lane);
-    if (lane == kWave - 1) wave_totals[wave] = incl;
+    if (lane == kWave - 1) of_wave[wave] = incl;
     __syncthreads();
-    uint64_t before = 0, all = 0;
-    for (int k = 0; k < waves; ++k) {
-        const uint64_t t = wave_totals[k];
-        before += k < wave ? t : 0;
-        all += t;
-    }
-    __syncthreads();
-    total = all;
-    return before + incl - v;
+    const int k = lane & 15;
+    const uint64_t own = k < waves ? of_wave[k] : 0;
+    const uint64_t upto = row_inclusive_scan(own);
+    total = read_lane(upto, 15);
+    return read_lane(upto, wave) - read_lane(own, wave) + incl - v;
 }
 
 // price of one step of item (w, D): two separately rounded double operations; -0.0 becomes +0.0
-__device__ __forceinline__ uint64_t price_bits(double w, double D, double step_price)
+__device__ __forceinline__ uint64_t price_bits(float w, int64_t D, double step_price)
 {
-    const double key = (w * step_price) / D + 0.0;
+    const double key = (static_cast<double>(w) * step_price) / static_cast<double>(D) + 0.0;
     return static_cast<uint64_t>(__double_as_longlong(key));
 }
 
-__device__ __forceinline__ uint64_t price_bits(float w, int64_t D, double step_price)
-{
-    return price_bits(static_cast<double>(w), static_cast<double>(D), step_price);
-}
+// The threshold among candidate moves: its price pattern, the bits freed by all cheaper moves of
+// the problem, and how many moves have exactly this price.
+struct Threshold {
+    uint64_t price, below, ties;
+};
 
-template <int CACHED>
-__global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float* __restrict__ w, AllocArgs a,
-                                                                    uint8_t* __restrict__ bits,
-                                                                    uint64_t* __restrict__ offsets,
-                                                                    int64_t* __restrict__ result)
+constexpr int kSelectBins = 256;
+
+struct SelectLds {
+    uint64_t hist[2][kSelectBins];   // both cleared by the caller, as is `count`
+    uint64_t key[kWave], amount[kWave];
+    uint32_t count[2];
+};
+
+// `each(f)` calls f(price, bits freed) for the thread's candidates.  All candidates of the workgroup:
+// n of them (n >= 1) with prices in [lo, hi]; the moves that are not candidates are either cheaper
+// than the threshold (they free `below` bits) or dearer.  Uniform over the workgroup, and so is
+// every branch around the barriers.
+template <typename Each>
+__device__ Threshold select_price(const Each& each, uint64_t n, uint64_t lo, uint64_t hi, uint64_t need, uint64_t below,
+                                  SelectLds& s)
 {
-    __shared__ uint64_t hist[3][256];
-    __shared__ uint64_t wave_totals[kAllocWavesMax];
-    __shared__ int width[8];      // the ladder, in LDS because lanes index it independently
-    __shared__ double price[8];
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    const int threads = blockDim.x;
-    const int steps = a.lad.count - 1;
-    if (tid < 8) {
-        width[tid] = a.lad.width[tid];
-        price[tid] = tid < 7 ? a.lad.price[tid] : 0.0;
-    }
-    for (int k = tid; k < 3 * 256; k += threads) (&hist[0][0])[k] = 0;
-    __syncthreads();
-    const int widest = width[0], narrowest = width[steps];
-
-    // Totals and validation.  The first CACHED items of every thread stay in registers, as the
-    // two doubles their prices are computed from (an empty or invalid slot has D = 0), so that the
-    // eight passes below run from registers: a pass that reloads its items pays one memory round
-    // trip per item and thread.  The first item also keeps its prices.  (CACHED is 1 when every
-    // thread has at most one item, which keeps the kernel of the small problem small.)
-    uint64_t my_elems = 0;
-    bool bad = false;
-    double cached_w[CACHED], cached_D[CACHED];   // D < 2^34 is exact in a double
-#pragma unroll
-    for (int j = 0; j < CACHED; ++j) {
-        const int64_t i = tid + static_cast<int64_t>(j) * threads;
-        const bool live = i < a.M;
-        const float wi = live ? w[i] : 0.0f;
-        const int64_t Di = live ? (a.D_items ? a.D_items[i] : a.D) : 0;
-        const bool ok = live && valid_sensitivity_bits(__float_as_uint(wi)) && Di > 0 && Di < (int64_t(1) << 34);
-        bad = bad || (live && !ok);
-        cached_w[j] = static_cast<double>(wi);
-        cached_D[j] = ok ? static_cast<double>(Di) : 0.0;
-        my_elems += ok ? static_cast<uint64_t>(Di) : 0;
-    }
-    uint64_t first_key[kMaxSteps];
-#pragma unroll
-    for (int r = 0; r < kMaxSteps; ++r)
-        first_key[r] = (r < steps && cached_D[0] != 0.0) ? price_bits(cached_w[0], cached_D[0], price[r])
-                                                  : ~uint64_t(0);
-    for (int64_t i = tid + static_cast<int64_t>(CACHED) * threads; i < a.M; i += threads) {
-        const float wi = w[i];
-        const int64_t Di = a.D_items ? a.D_items[i] : a.D;
-        if (!valid_sensitivity_bits(__float_as_uint(wi)) || Di <= 0 || Di >= (int64_t(1) << 34)) bad = true;
-        else my_elems += static_cast<uint64_t>(Di);
-    }
-    const bool invalid = __syncthreads_or(bad ? 1 : 0) != 0;
-    uint64_t elems;
-    block_exclusive_scan(my_elems, wave_totals, elems);
-    const uint64_t budget = static_cast<uint64_t>(a.budget_bits);
-    const bool loose = !invalid && elems * widest <= budget;
-    const bool infeasible = !invalid && elems * narrowest > budget;
-    const int64_t status = invalid ? ACTQ_EINVAL : (infeasible ? ACTQ_EINFEASIBLE : ACTQ_OK);
-
-    uint64_t threshold = 0, below = 0, need = 0;
-    const bool search = !invalid && !loose && !infeasible;
-    if (search) {
-        need = elems * widest - budget;  // bits that must be freed, > 0
-        uint64_t prefix = 0;
-        uint32_t alive[(CACHED + 3) / 4];   // one byte per cached item: which of its moves are still in play
-#pragma unroll
-        for (int k = 0; k < (CACHED + 3) / 4; ++k) alive[k] = ~0u;
-        for (int pass = 7; pass >= 0; --pass) {
-            uint64_t* h = hist[pass % 3];
-            const int shift = 8 * pass;
-            // A lane adds up the moves it sends to one bin in a row and issues one atomic per run:
-            // in the first passes (sign and exponent bits) nearly every price falls into the same
-            // one or two bins, and 64 lanes adding to one LDS address are served one after another.
-            uint32_t run_bin = 0;
-            uint64_t run_sum = 0;
-            const auto add = [&](uint32_t bin, uint64_t freed) {
-                if (bin != run_bin && run_sum) {
-                    __hip_atomic_fetch_add(&h[run_bin], run_sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    run_sum = 0;
-                }
-                run_bin = bin;
-                run_sum += freed;
-            };
-            // first item: cached prices
-            if (cached_D[0] != 0.0) {
-#pragma unroll
-                for (int r = 0; r < kMaxSteps; ++r) {
-                    if (r >= steps) continue;
-                    const uint64_t key = first_key[r];
-                    if (pass == 7 || (key >> (shift + 8)) == prefix)
-                        add(static_cast<uint32_t>(key >> shift) & 255u, static_cast<uint64_t>(cached_D[0]) * (width[r] - width[r + 1]));
-                }
-            }
-            // further cached items: prices recomputed from registers, but only for the moves whose
-            // price still matches the digits found so far -- a move that fell out of the prefix in
-            // one pass stays out, and after two passes few are left
-#pragma unroll
-            for (int j = 1; j < CACHED; ++j) {
-                if (static_cast<int64_t>(j) * threads >= a.M) break;   // uniform
-                constexpr uint32_t kAll = (1u << kMaxSteps) - 1u;
-                const int field = 8 * (j % 4);
-                uint32_t in_play = (alive[j / 4] >> field) & kAll;
-                if (cached_D[j] == 0.0 || in_play == 0) continue;
-                const uint64_t Dj = static_cast<uint64_t>(cached_D[j]);
-                for (int r = 0; r < steps; ++r) {
-                    if (!((in_play >> r) & 1u)) continue;
-                    const uint64_t key = price_bits(cached_w[j], cached_D[j], price[r]);
-                    if (pass == 7 || (key >> (shift + 8)) == prefix)
-                        add(static_cast<uint32_t>(key >> shift) & 255u, Dj * (width[r] - width[r + 1]));
-                    else
-                        in_play &= ~(1u << r);
-                }
-                alive[j / 4] = (alive[j / 4] & ~(kAll << field)) | (in_play << field);
-            }
-            for (int64_t i = tid + static_cast<int64_t>(CACHED) * threads; i < a.M; i += threads) {
-                const float wi = w[i];
-                const int64_t Di = a.D_items ? a.D_items[i] : a.D;
-                for (int r = 0; r < steps; ++r) {
-                    const uint64_t key = price_bits(wi, Di, price[r]);
-                    if (pass == 7 || (key >> (shift + 8)) == prefix)
-                        add(static_cast<uint32_t>(key >> shift) & 255u, static_cast<uint64_t>(Di) * (width[r] - width[r + 1]));
-                }
-            }
-            if (run_sum)
-                __hip_atomic_fetch_add(&h[run_bin], run_sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    for (int turn = 0;; turn ^= 1) {
+        if (lo == hi) return Threshold{lo, below, n};
+        if (n > kWave) {
+            const uint64_t span = hi - lo;
+            const int bits = 64 - __builtin_clzll(span);
+            const int shift = bits > 8 ? bits - 8 : 0;   // (span >> shift) < 256
+            uint64_t* h = s.hist[turn];
+            each([&](uint64_t key, uint64_t freed) {
+                if (key >= lo && key <= hi)
+                    __hip_atomic_fetch_add(&h[(key - lo) >> shift], freed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            });
             __syncthreads();
             // Every wavefront finds, for itself, the bin in which the running sum of freed bits
             // first reaches `need`.  Exactly one lane holds it.
@@ -1978,90 +1953,696 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
             uint64_t run = below + incl - mine;
             const bool winner = run < need && run + mine >= need;
             int digit = 4 * lane;
+            bool found = false;
 #pragma unroll
-            for (int k = 0; k < 3; ++k)
-                if (winner && run + hb[k] < need) { run += hb[k]; ++digit; }
-                else break;
+            for (int k = 0; k < 3; ++k) {
+                found = found || run + hb[k] >= need;
+                if (!found) { run += hb[k]; ++digit; }
+            }
             const uint64_t vote = __ballot(winner);
             const int src = vote ? __builtin_ctzll(vote) : 0;
             digit = __builtin_amdgcn_readlane(digit, src);
             below = read_lane(run, src);
-            prefix = (prefix << 8) | static_cast<uint64_t>(digit);
-            // the histogram of the pass before this one is free again: clear it for the pass after the next
-            uint64_t* stale = hist[(pass + 1) % 3];
-            for (int k = tid; k < 256; k += threads) stale[k] = 0;
+            const uint64_t top = lo + ((static_cast<uint64_t>(digit) + 1) << shift) - 1;
+            lo += static_cast<uint64_t>(digit) << shift;
+            hi = top < hi && top >= lo ? top : hi;
         }
-        threshold = prefix;
+        // what is left, counted, and listed if it is little
+        each([&](uint64_t key, uint64_t freed) {
+            if (key >= lo && key <= hi) {
+                const uint32_t at = __hip_atomic_fetch_add(&s.count[turn], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (at < kWave) {
+                    s.key[at] = key;
+                    s.amount[at] = freed;
+                }
+            }
+        });
+        // the other turn's words: all threads are past the barrier behind their last use
+        for (int k = tid; k < kSelectBins; k += blockDim.x) s.hist[turn ^ 1][k] = 0;
+        if (tid == 0) s.count[turn ^ 1] = 0;
+        __syncthreads();
+        n = s.count[turn];
+        if (n <= kWave) break;
+    }
+    // at most one move per lane: sums over the cheaper and over the not dearer ones of the list
+    const bool live = lane < static_cast<int>(n);
+    const uint64_t key = live ? s.key[lane] : ~uint64_t(0);
+    uint64_t cheaper = 0, upto = 0, ties = 0;
+    for (int k = 0; k < static_cast<int>(n); ++k) {
+        const uint64_t other = s.key[k], freed = s.amount[k];
+        cheaper += other < key ? freed : 0;
+        upto += other <= key ? freed : 0;
+        ties += other == key ? 1 : 0;
+    }
+    const uint64_t vote = __ballot(live && below + cheaper < need && below + upto >= need);
+    const int src = vote ? __builtin_ctzll(vote) : 0;
+    return Threshold{read_lane(key, src), below + read_lane(cheaper, src), read_lane(ties, src)};
+}
+
+__device__ __forceinline__ bool valid_item(float w, int64_t D)
+{
+    return valid_sensitivity_bits(__float_as_uint(w)) && D > 0 && D < (int64_t(1) << 34);
+}
+
+__device__ __forceinline__ uint64_t stream_bytes(int64_t D, int width)
+{
+    return (static_cast<uint64_t>(D) + kGroup - 1) / kGroup * 32u * static_cast<uint64_t>(width);
+}
+
+// What the totals decide before any search.
+struct AllocVerdict {
+    bool search, loose;
+    uint64_t need;    // bits that must be freed, > 0 if there is a search
+    int64_t status;
+};
+
+__device__ __forceinline__ AllocVerdict alloc_verdict(uint64_t elems, bool invalid, const AllocArgs& a)
+{
+    const uint64_t budget = static_cast<uint64_t>(a.budget_bits);
+    const uint64_t widest = static_cast<uint64_t>(a.lad.width[0]), narrowest = static_cast<uint64_t>(a.lad.width[a.lad.count - 1]);
+    AllocVerdict v;
+    v.loose = !invalid && elems * widest <= budget;
+    const bool infeasible = !invalid && elems * narrowest > budget;
+    v.search = !invalid && !v.loose && !infeasible;
+    v.need = elems * widest - budget;
+    v.status = invalid ? ACTQ_EINVAL : (infeasible ? ACTQ_EINFEASIBLE : ACTQ_OK);
+    return v;
+}
+
+// Width and price of rung k for an index that differs between lanes: the widths are nibbles of one
+// word, the prices are picked from scalar registers.
+__device__ __forceinline__ int ladder_width(const AllocArgs& a, int k) { return static_cast<int>((a.width_nibbles >> (4 * k)) & 15u); }
+
+__device__ __forceinline__ double ladder_price(const Ladder& lad, int k)
+{
+    double v = lad.price[0];
+#pragma unroll
+    for (int j = 1; j < kMaxSteps; ++j) v = k == j ? lad.price[j] : v;
+    return v;
+}
+
+// M <= 1024 and M * steps <= kSmallMoves: every price in LDS, at most two per thread, an item per thread.
+__global__ __launch_bounds__(kAllocBlock) void allocate_bits_small_kernel(const float* __restrict__ w, AllocArgs a,
+                                                                          uint8_t* __restrict__ bits,
+                                                                          uint64_t* __restrict__ offsets,
+                                                                          int64_t* __restrict__ result)
+{
+    __shared__ uint64_t key[kSmallMoves], amount[kSmallMoves];   // move r * M + i
+    __shared__ SelectLds sel;
+    __shared__ uint64_t wave_elems[kAllocWavesMax], wave_lo[kAllocWavesMax], wave_hi[kAllocWavesMax], wave_bad[kAllocWavesMax];
+    __shared__ uint64_t wave_ties[kAllocWavesMax], wave_bytes[kAllocWavesMax];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    const int threads = blockDim.x, waves = threads >> 6;
+    const int M = static_cast<int>(a.M), steps = a.lad.count - 1, moves = M * steps;
+    const bool live = tid < M;
+    const float wi = live ? w[tid] : 0.0f;
+    int64_t Di = live ? (a.D_items ? a.D_items[tid] : a.D) : 0;
+    uint64_t lo = ~uint64_t(0), hi = 0;
+    for (int e = tid; e < moves; e += threads) {
+        const int r = static_cast<int>(static_cast<uint32_t>(e) / static_cast<uint32_t>(M)), i = e - r * M;
+        const float wm = w[i];
+        int64_t Dm = a.D_items ? a.D_items[i] : a.D;
+        if (!valid_item(wm, Dm)) Dm = 1;   // the whole problem is invalid then, and nothing is searched
+        const uint64_t k = price_bits(wm, Dm, ladder_price(a.lad, r));
+        key[e] = k;
+        amount[e] = static_cast<uint64_t>(Dm) * static_cast<uint64_t>(ladder_width(a, r) - ladder_width(a, r + 1));
+        lo = k < lo ? k : lo;
+        hi = k > hi ? k : hi;
+    }
+    for (int k = tid; k < 2 * kSelectBins; k += threads) (&sel.hist[0][0])[k] = 0;
+    if (tid < 2) sel.count[tid] = 0;
+    const bool ok = live && valid_item(wi, Di);
+    const uint64_t e64 = wave_reduce(ok ? static_cast<uint64_t>(Di) : uint64_t(0), Add());
+    lo = wave_reduce(lo, Min());
+    hi = wave_reduce(hi, Max());
+    const uint64_t bad = __ballot(live && !ok);
+    if (lane == 0) {
+        wave_elems[wave] = e64;
+        wave_lo[wave] = lo;
+        wave_hi[wave] = hi;
+        wave_bad[wave] = bad;
+    }
+    __syncthreads();
+    const uint64_t elems = combine_waves(wave_elems, waves, 0, Add());
+    const bool invalid = combine_waves(wave_bad, waves, 0, Max()) != 0;
+    const AllocVerdict v = alloc_verdict(elems, invalid, a);
+    Threshold t = {0, 0, 0};
+    if (v.search) {
+        const auto each = [&](auto f) {
+            for (int e = tid; e < moves; e += threads) f(key[e], amount[e]);
+        };
+        t = select_price(each, static_cast<uint64_t>(moves), combine_waves(wave_lo, waves, ~uint64_t(0), Min()),
+                         combine_waves(wave_hi, waves, 0, Max()), v.need, 0, sel);
+    }
+    if (Di <= 0 || Di >= (int64_t(1) << 34)) Di = live ? 1 : 0;   // invalid input: stay memory-safe
+    int rung = v.loose ? 0 : steps, ties = 0;
+    if (v.search && live) {
+        rung = 0;
+        for (int r = 0; r < steps; ++r) {
+            const uint64_t k = key[r * M + tid];
+            rung += k < t.price ? 1 : 0;
+            ties += k == t.price ? 1 : 0;
+        }
+    }
+    if (t.ties > 1) {
+        // the moves at the threshold in (item, step) order, until the budget holds
+        const uint64_t rest = v.need - t.below;
+        uint64_t unused;
+        uint64_t freed = block_exclusive_scan(static_cast<uint64_t>(Di) * static_cast<uint64_t>(ladder_width(a, rung) - ladder_width(a, rung + ties)),
+                                              wave_ties, unused);
+        for (; ties > 0 && freed < rest; --ties, ++rung)
+            freed += static_cast<uint64_t>(Di) * static_cast<uint64_t>(ladder_width(a, rung) - ladder_width(a, rung + 1));
+    } else {
+        rung += ties;   // the one move at the threshold is applied
+    }
+    const int b = ladder_width(a, rung);
+    uint64_t total;
+    const uint64_t off = block_exclusive_scan(live ? stream_bytes(Di, b) : 0, wave_bytes, total);
+    if (live) {
+        bits[tid] = static_cast<uint8_t>(b);
+        offsets[tid] = off;
+    }
+    if (tid == 0) {
+        result[0] = static_cast<int64_t>(total);
+        result[1] = v.status;
+    }
+}
+
+// Upper 32 bits of the binary64 pattern of w / D, one unit off at most: the reciprocal of D in binary32
+// (relative error below 2^-22 with the rounding of D) is four times finer than a unit, and costs a
+// tenth of a binary64 division.  A valid sensitivity is not negative; -0.0 counts as 0.
+__device__ __forceinline__ uint32_t ratio_of(float w, int64_t D)
+{
+    const float d = __builtin_fmaf(static_cast<float>(static_cast<uint32_t>(D >> 32)), 4294967296.0f, static_cast<float>(static_cast<uint32_t>(D)));
+    const double q = static_cast<double>(w) * static_cast<double>(__builtin_amdgcn_rcpf(d));
+    return static_cast<uint32_t>(static_cast<uint64_t>(__double_as_longlong(q)) >> 32) & 0x7fffffffu;
+}
+
+// Upper 32 bits of (price with the upper 32 bits `t` and zeros below) / c_r.
+__device__ __forceinline__ uint32_t ratio_at(uint64_t price, double inverse)
+{
+    return static_cast<uint32_t>(static_cast<uint64_t>(__double_as_longlong(__longlong_as_double(static_cast<long long>(price)) * inverse)) >> 32);
+}
+
+// For a bracket [lo, hi) of prices: how item ratios compare with lo / c_r and hi / c_r, every r.
+// A step r of an item is certainly cheaper than lo if ratio + 2 < below[r], and certainly not
+// cheaper than hi if ratio > above[r].
+struct RatioBracket {
+    uint32_t below[kMaxSteps], above[kMaxSteps];
+};
+
+__device__ __forceinline__ void make_bracket(uint64_t lo, uint64_t hi, const AllocArgs& a, RatioBracket& b)
+{
+#pragma unroll
+    for (int r = 0; r < kMaxSteps; ++r) {
+        const bool step = r + 1 < a.lad.count;
+        // a ladder with fewer steps: the unused ones are never cheaper (`above` is not looked at)
+        b.below[r] = step ? static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(ratio_at(lo, a.inverse[r])))) : 0u;
+        b.above[r] = step ? static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(ratio_at(hi, a.inverse[r])))) + 2u : 0u;
+    }
+}
+
+// For items with ratios in [least, most]: the steps before `first` are cheaper than the bracket for all
+// of them, steps [first, last) are undecided.
+__device__ __forceinline__ void bracket_steps(const RatioBracket& b, int steps, uint32_t least, uint32_t most, int& first, int& last)
+{
+    first = 0;
+    last = 0;
+#pragma unroll
+    for (int r = 0; r < kMaxSteps; ++r) {
+        first += most + 2u < b.below[r] ? 1 : 0;
+        last += r < steps && least <= b.above[r] ? 1 : 0;
+    }
+}
+
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef int64_t i64x2_a8 __attribute__((ext_vector_type(2), aligned(8)));
+
+// Any M.  A thread's items come in quadruples of consecutive ones, 4096 items per round; the
+// bins (ratios, before there are bins) and element counts of the first kAllocQuads rounds stay in registers.
+// M >= 4: the small kernel takes everything up to kSmallMoves / 7 items.
+__global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float* __restrict__ w, AllocArgs a,
+                                                                    uint8_t* __restrict__ bits,
+                                                                    uint64_t* __restrict__ offsets,
+                                                                    int64_t* __restrict__ result)
+{
+    constexpr int kQ = 4, kCached = kAllocQuads * kQ;
+    constexpr int64_t kRound = int64_t(kAllocBlock) * kQ;
+    __shared__ uint64_t table[kAllocBins + 1];   // elements of the items per bin of w / D, then their prefix sums
+    __shared__ uint32_t step_class[kAllocBins / 4];   // per bin, a byte: bracket_steps' `first`, and 8 if any step is undecided
+    __shared__ uint64_t list_key[kAllocList], list_amount[kAllocList];
+    __shared__ SelectLds sel;
+    __shared__ uint64_t wave_a[kAllocWavesMax], wave_b[kAllocWavesMax], wave_c[kAllocWavesMax], wave_d[kAllocWavesMax];
+    __shared__ uint64_t wave_round[2][kAllocWavesMax], wave_bytes[kAllocQuads * kAllocWavesMax];
+    __shared__ uint32_t list_count, bracket_lo, bracket_hi;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int waves = kAllocWavesMax;
+    const int steps = a.lad.count - 1;
+    const int64_t M = a.M;
+    const auto item = [&](int j) { return (j / kQ) * kRound + tid * kQ + j % kQ; };
+    const auto elements = [&](int64_t i) { return a.D_items ? a.D_items[i] : a.D; };
+
+    for (int k = tid; k <= kAllocBins; k += kAllocBlock) table[k] = 0;
+    for (int k = tid; k < 2 * kSelectBins; k += kAllocBlock) (&sel.hist[0][0])[k] = 0;
+    if (tid < 2) sel.count[tid] = 0;
+    if (tid == 0) list_count = 0;
+
+    // Ratios, totals and validation.  An empty slot has D = 0 and the largest ratio.
+    constexpr uint32_t kNone = 0x7fffffffu;
+    uint32_t ratio[kCached];
+    int64_t size[kCached];
+    uint64_t my_elems = 0;
+    uint32_t lo_ratio = kNone, hi_ratio = 0;   // over the positive ratios
+    bool bad = false;
+    float weight[kCached];
+    // Whole quadruples per load (a load instruction costs its 64 addresses, not its bytes); one that
+    // reaches past the end is taken from the last four items and shifted into place below.
+#pragma unroll
+    for (int k = 0; k < kAllocQuads; ++k) {
+        const int64_t i0 = item(k * kQ), at = i0 < M - kQ ? i0 : M - kQ;
+        const f32x4_a4 x = *reinterpret_cast<const f32x4_a4*>(w + at);
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) weight[k * kQ + q] = x[q];
+    }
+    if (a.D_items) {
+#pragma unroll
+        for (int k = 0; k < kAllocQuads; ++k) {
+            const int64_t i0 = item(k * kQ), at = i0 < M - kQ ? i0 : M - kQ;
+            const i64x2_a8 x = *reinterpret_cast<const i64x2_a8*>(a.D_items + at), y = *reinterpret_cast<const i64x2_a8*>(a.D_items + at + 2);
+            size[k * kQ] = x[0];
+            size[k * kQ + 1] = x[1];
+            size[k * kQ + 2] = y[0];
+            size[k * kQ + 3] = y[1];
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kCached; ++j) size[j] = a.D;
+    }
+#pragma unroll
+    for (int k = 0; k < kAllocQuads; ++k) {
+        if ((k + 1) * kRound > M) {
+            const int64_t past = item(k * kQ) - (M - kQ);   // 1, 2, 3: the quadruple is shifted by that much; from 4 on it is empty
+#pragma unroll
+            for (int q = 0; q < kQ; ++q) {
+                const int j = k * kQ + q;
+#pragma unroll
+                for (int p = 1; p + q < kQ; ++p) {
+                    weight[j] = past == p ? weight[j + p] : weight[j];
+                    size[j] = past == p ? size[j + p] : size[j];
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < kCached; ++j) {
+        const bool live = item(j) < M;
+        const bool ok = live && valid_item(weight[j], size[j]);
+        bad = bad || (live && !ok);
+        ratio[j] = ok ? ratio_of(weight[j], size[j]) : kNone;
+        size[j] = ok ? size[j] : 0;
+        my_elems += static_cast<uint64_t>(size[j]);
+        if (ok && ratio[j] != 0) {
+            lo_ratio = ratio[j] < lo_ratio ? ratio[j] : lo_ratio;
+            hi_ratio = ratio[j] > hi_ratio ? ratio[j] : hi_ratio;
+        }
+        if (j % kQ == kQ - 1) __builtin_amdgcn_sched_barrier(0);   // a quadruple at a time: the temporaries stay in registers
+    }
+    // items beyond the registers: recomputed in every pass
+    const auto further = [&](auto f) {
+        for (int64_t base = kAllocQuads * kRound; base < M; base += kRound)
+            for (int q = 0; q < kQ; ++q) {
+                const int64_t i = base + tid * kQ + q;
+                if (i < M) f(i, w[i], elements(i));
+            }
+    };
+    further([&](int64_t, float wi, int64_t Di) {
+        if (!valid_item(wi, Di)) { bad = true; return; }
+        my_elems += static_cast<uint64_t>(Di);
+        const uint32_t u = ratio_of(wi, Di);
+        if (u != 0) {
+            lo_ratio = u < lo_ratio ? u : lo_ratio;
+            hi_ratio = u > hi_ratio ? u : hi_ratio;
+        }
+    });
+    {
+        const uint64_t e = wave_reduce(my_elems, Add()), l = wave_reduce(lo_ratio, Min()), h = wave_reduce(hi_ratio, Max());
+        const uint64_t any_bad = __ballot(bad);
+        if (lane == 0) {
+            wave_a[wave] = e;
+            wave_b[wave] = l;
+            wave_c[wave] = h;
+            wave_d[wave] = any_bad;
+        }
+    }
+    __syncthreads();
+    const uint64_t elems = combine_waves(wave_a, waves, 0, Add());
+    const uint32_t first_ratio = static_cast<uint32_t>(combine_waves(wave_b, waves, kNone, Min()));
+    const uint32_t last_ratio = static_cast<uint32_t>(combine_waves(wave_c, waves, 0, Max()));   // 0: every price is 0
+    const bool invalid = combine_waves(wave_d, waves, 0, Max()) != 0;
+    const AllocVerdict v = alloc_verdict(elems, invalid, a);
+
+    Threshold t = {0, 0, 0};
+    RatioBracket br;
+    // the bins of the table: bin 0 the ratio 0, then equal steps from the smallest positive ratio
+    const uint32_t span = last_ratio > first_ratio ? last_ratio - first_ratio : 0u;
+    int shift = span ? 32 - __builtin_clz(span) - 12 : 0;
+    shift = shift > 0 ? shift : 0;
+    if ((span >> shift) > static_cast<uint32_t>(kAllocBins - 2)) ++shift;
+    const auto bin_of = [&](uint32_t u) {   // an empty slot's ratio gives some bin, too
+        const uint32_t bin = u == 0 ? 0u : 1u + ((u - first_ratio) >> shift);
+        return bin < static_cast<uint32_t>(kAllocBins) ? bin : static_cast<uint32_t>(kAllocBins - 1);
+    };
+    uint64_t hb[4] = {0, 0, 0, 0};   // elements of the items in bins 4 tid .. 4 tid + 3
+    // step_class of the thread's four bins for the bracket `br`; returns the bits freed by the steps that are cheaper than it
+    const auto classify = [&]() {
+        uint32_t classes = 0;
+        uint64_t freed = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t bin = static_cast<uint32_t>(4 * tid + k);
+            const uint32_t least = bin == 0 ? 0u : first_ratio + ((bin - 1u) << shift);
+            const uint32_t most = bin == 0 ? 0u : least + ((1u << shift) - 1u);
+            int first, last;
+            bracket_steps(br, steps, least, most, first, last);
+            classes |= static_cast<uint32_t>(first | (first < last ? 8 : 0)) << (8 * k);
+            freed += hb[k] * static_cast<uint64_t>(a.lad.width[0] - ladder_width(a, first));
+        }
+        step_class[tid] = classes;
+        return freed;
+    };
+    const auto class_of = [&](uint32_t bin) { return static_cast<uint32_t>(reinterpret_cast<const uint8_t*>(step_class)[bin]); };
+    if (v.search) {
+        const auto add_item = [&](uint32_t bin, int64_t D) {
+            __hip_atomic_fetch_add(&table[bin], static_cast<uint64_t>(D), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        };
+#pragma unroll
+        for (int j = 0; j < kCached; ++j) {
+            ratio[j] = bin_of(ratio[j]);   // bins from here on
+            if (size[j] != 0) add_item(ratio[j], size[j]);
+        }
+        further([&](int64_t, float wi, int64_t Di) { add_item(bin_of(ratio_of(wi, Di)), Di); });
+        __syncthreads();
+        uint64_t mine = 0, total;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) { hb[k] = table[4 * tid + k]; mine += hb[k]; }
+        uint64_t run = block_exclusive_scan(mine, wave_round[0], total);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            table[4 * tid + k] = run;   // elements of the items in the bins before this one
+            run += hb[k];
+        }
+        if (tid == kAllocBlock - 1) table[kAllocBins] = run;
+        __syncthreads();
+
+        // ---- the bracket: wavefront 0 evaluates both bounds of the bits freed below 64 prices at a time
+        if (wave == 0) {
+            // price patterns' upper halves; nothing positive is cheaper than `start`, nothing is dearer than `end`
+            const uint64_t lowest = static_cast<uint64_t>(first_ratio) << 32, highest = static_cast<uint64_t>(last_ratio + 1) << 32;
+            const uint32_t p_lo = static_cast<uint32_t>(static_cast<uint64_t>(__double_as_longlong(__longlong_as_double(static_cast<long long>(lowest)) * a.lad.price[0])) >> 32);
+            const uint32_t p_hi = static_cast<uint32_t>(static_cast<uint64_t>(__double_as_longlong(__longlong_as_double(static_cast<long long>(highest)) * ladder_price(a.lad, steps - 1))) >> 32);
+            const uint32_t start = last_ratio ? (p_lo > 4u ? p_lo - 4u : 0u) : 0u, end = last_ratio ? p_hi + 4u : 4u;
+            uint32_t lo = 0, hi = end, left = start, right = end;
+            for (int round = 0; round < 4; ++round) {
+                const uint32_t width = right - left;
+                const uint32_t p = left + static_cast<uint32_t>(static_cast<uint64_t>(width) * static_cast<uint32_t>(lane) / 63u);
+                uint64_t most = 0, least = 0;   // bits freed by the moves cheaper than p: upper and lower bound
+#pragma unroll
+                for (int r = 0; r < kMaxSteps; ++r) {
+                    if (r >= steps) continue;
+                    const uint32_t u = ratio_at(static_cast<uint64_t>(p) << 32, a.inverse[r]);
+                    const uint64_t dw = static_cast<uint64_t>(a.lad.width[r] - a.lad.width[r + 1]);
+                    // items of ratio < u - 2 only: whole bins before the one that holds it
+                    const uint32_t x = u > 2u ? u - 2u : 0u;
+                    uint32_t b_least = x <= first_ratio ? 1u : 1u + ((x - first_ratio) >> shift);
+                    b_least = x == 0 ? 0u : (b_least < static_cast<uint32_t>(kAllocBins) ? b_least : static_cast<uint32_t>(kAllocBins));
+                    // every item of ratio <= u + 2: whole bins up to the one that holds it
+                    const uint32_t y = u + 2u;
+                    uint32_t b_most = y < first_ratio ? 1u : 2u + ((y - first_ratio) >> shift);
+                    b_most = b_most < static_cast<uint32_t>(kAllocBins) ? b_most : static_cast<uint32_t>(kAllocBins);
+                    least += dw * table[b_least];
+                    most += dw * table[b_most];
+                }
+                const uint64_t not_yet = __ballot(most < v.need), enough = __ballot(least >= v.need);
+                if (not_yet) lo = left + static_cast<uint32_t>(static_cast<uint64_t>(width) * static_cast<uint32_t>(63 - __builtin_clzll(not_yet)) / 63u);
+                if (enough) hi = left + static_cast<uint32_t>(static_cast<uint64_t>(width) * static_cast<uint32_t>(__builtin_ctzll(enough)) / 63u);
+                left = lo > start ? lo : start;
+                right = hi;
+                // finer than a bin the table cannot tell
+                if (((right - left) >> shift) == 0u || right - left > width / 2u) break;
+            }
+            if (lane == 0) {
+                bracket_lo = lo;
+                bracket_hi = hi;
+            }
+        }
+        __syncthreads();
+
+        // ---- the undecided moves, priced exactly
+        make_bracket(static_cast<uint64_t>(bracket_lo) << 32, static_cast<uint64_t>(bracket_hi) << 32, a, br);
+        uint64_t my_below = classify();
+        __syncthreads();
+        uint32_t undecided = 0;   // of the items in registers: those in a bin with undecided steps
+#pragma unroll
+        for (int j = 0; j < kCached; ++j) undecided |= size[j] != 0 && (class_of(ratio[j]) & 8u) ? 1u << j : 0u;
+        // every undecided move of this thread: f(price, bits freed); before(D, class) once per item that is looked at
+        const auto walk_items = [&](auto f, auto before) {
+            const auto moves_of = [&](float wi, int64_t Di, uint32_t cls, uint32_t u) {
+                int first, last;
+                bracket_steps(br, steps, u, u, first, last);
+                before(Di, static_cast<int>(cls & 7u), first);
+                for (int r = first; r < last; ++r)
+                    f(price_bits(wi, Di, ladder_price(a.lad, r)),
+                      static_cast<uint64_t>(Di) * static_cast<uint64_t>(ladder_width(a, r) - ladder_width(a, r + 1)));
+            };
+            for (uint32_t m = undecided; m != 0; m &= m - 1) {
+                const int64_t i = item(__builtin_ctz(m));
+                const float wi = w[i];
+                const int64_t Di = elements(i);
+                const uint32_t u = ratio_of(wi, Di);
+                moves_of(wi, Di, class_of(bin_of(u)), u);
+            }
+            further([&](int64_t, float wi, int64_t Di) {
+                const uint32_t u = ratio_of(wi, Di), cls = class_of(bin_of(u));
+                if (cls & 8u) moves_of(wi, Di, cls, u);
+            });
+        };
+        const auto walk = [&](auto f) { walk_items(f, [](int64_t, int, int) {}); };
+        uint64_t lo = ~uint64_t(0), hi = 0;
+        walk_items([&](uint64_t key, uint64_t freed) {
+            const uint32_t at = __hip_atomic_fetch_add(&list_count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (at < kAllocList) {
+                list_key[at] = key;
+                list_amount[at] = freed;
+            }
+            lo = key < lo ? key : lo;
+            hi = key > hi ? key : hi;
+        }, [&](int64_t Di, int of_bin, int of_item) {   // cheaper steps of the item beyond those counted with its bin
+            my_below += static_cast<uint64_t>(Di) * static_cast<uint64_t>(ladder_width(a, of_bin) - ladder_width(a, of_item));
+        });
+        {
+            const uint64_t b = wave_reduce(my_below, Add());
+            lo = wave_reduce(lo, Min());
+            hi = wave_reduce(hi, Max());
+            if (lane == 0) {
+                wave_a[wave] = b;
+                wave_b[wave] = lo;
+                wave_c[wave] = hi;
+            }
+        }
+        __syncthreads();
+        const uint64_t below = combine_waves(wave_a, waves, 0, Add());
+        lo = combine_waves(wave_b, waves, ~uint64_t(0), Min());
+        hi = combine_waves(wave_c, waves, 0, Max());
+        const uint64_t n = list_count;
+        if (n <= kAllocList) {
+            const auto each = [&](auto f) {
+                for (int e = tid; e < static_cast<int>(n); e += kAllocBlock) f(list_key[e], list_amount[e]);
+            };
+            t = select_price(each, n, lo, hi, v.need, below, sel);
+        } else {
+            t = select_price(walk, n, lo, hi, v.need, below, sel);   // many (nearly) equal prices
+        }
+        make_bracket(t.price, t.price, a, br);
+        __syncthreads();   // step_class has been read by everyone
+        classify();
+        __syncthreads();
     }
 
-    // Widths, then offsets, in item order.  A round gives every thread Q consecutive items, so the
-    // two workgroup prefix sums (ties at the threshold, then bytes) run over thread totals: once
-    // per Q * threads items.  The barriers of those sums, not the arithmetic, are what a round costs.
-    uint64_t tie_carry = 0, byte_carry = 0;
-    const uint64_t rest = need - below;  // bits still to free among the moves priced exactly at the threshold
-    const auto assign = [&](auto items_per_thread) {
-        constexpr int Q = decltype(items_per_thread)::value;
-        for (int64_t base = 0; base < a.M; base += static_cast<int64_t>(threads) * Q) {
-            const int64_t i0 = base + static_cast<int64_t>(tid) * Q;
-            int64_t Dq[Q];
-            int rung[Q], ties[Q];
-            bool live[Q];
-            uint64_t tie_bits[Q], tie_sum = 0;
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                const int64_t i = i0 + q;
-                live[q] = i < a.M;
-                const float wi = live[q] ? w[i] : 0.0f;
-                int64_t Di = live[q] ? (a.D_items ? a.D_items[i] : a.D) : 0;
-                if (Di <= 0 || Di >= (int64_t(1) << 34)) Di = live[q] ? 1 : 0;  // invalid input: stay memory-safe
-                Dq[q] = Di;
-                rung[q] = loose ? 0 : steps;
-                ties[q] = 0;
-                if (search && live[q]) {
-                    rung[q] = 0;
-                    for (int r = 0; r < steps; ++r) {
-                        const uint64_t key = price_bits(wi, Di, price[r]);
-                        rung[q] += key < threshold ? 1 : 0;
-                        ties[q] += key == threshold ? 1 : 0;
-                    }
-                }
-                tie_bits[q] = static_cast<uint64_t>(Di) * (width[rung[q]] - width[rung[q] + ties[q]]);
-                tie_sum += tie_bits[q];
-            }
-            uint64_t tie_total;
-            uint64_t before = tie_carry + block_exclusive_scan(tie_sum, wave_totals, tie_total);
-            tie_carry += tie_total;
-            uint64_t my_bytes[Q], byte_sum = 0;
-            int b[Q];
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                uint64_t freed = before;      // by the tie moves of all items before this one
-                before += tie_bits[q];
-                for (; ties[q] > 0 && freed < rest; --ties[q], ++rung[q])
-                    freed += static_cast<uint64_t>(Dq[q]) * (width[rung[q]] - width[rung[q] + 1]);
-                b[q] = width[rung[q]];
-                const uint64_t groups = (static_cast<uint64_t>(Dq[q]) + kGroup - 1) / kGroup;
-                my_bytes[q] = live[q] ? groups * 32u * b[q] : 0;
-                byte_sum += my_bytes[q];
-            }
-            uint64_t byte_total;
-            uint64_t off = byte_carry + block_exclusive_scan(byte_sum, wave_totals, byte_total);
-            byte_carry += byte_total;
-#pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                if (live[q]) {
-                    bits[i0 + q] = static_cast<uint8_t>(b[q]);
-                    offsets[i0 + q] = off;
-                }
-                off += my_bytes[q];
-            }
+    // ---- widths, then offsets, in item order
+    const auto settle = [&](float wi, int64_t Di, int& rung, int& ties) {   // an item near the threshold
+        int first, last;
+        const uint32_t u = ratio_of(wi, Di);
+        bracket_steps(br, steps, u, u, first, last);
+        rung = first;
+        ties = 0;
+        for (int r = first; r < last; ++r) {
+            const uint64_t key = price_bits(wi, Di, ladder_price(a.lad, r));
+            rung += key < t.price ? 1 : 0;
+            ties += key == t.price ? 1 : 0;
         }
     };
-    if (a.M <= threads) assign(std::integral_constant<int, 1>());
-    else assign(std::integral_constant<int, 4>());
+    const uint64_t rest = v.need - t.below;   // bits still to free among the moves priced exactly at the threshold
+    uint64_t tie_carry = 0, byte_carry = 0;
+    // rungs and tied moves of the items in registers, four bits each
+    uint64_t rungs = 0, tied = 0;
+    if (v.search) {
+        uint32_t near = 0;
+#pragma unroll
+        for (int j = 0; j < kCached; ++j) {
+            const uint32_t cls = class_of(ratio[j]);
+            near |= size[j] != 0 && (cls & 8u) ? 1u << j : 0u;
+            rungs |= static_cast<uint64_t>(cls & 7u) << (4 * j);
+        }
+        for (uint32_t m = near; m != 0; m &= m - 1) {
+            const int j = __builtin_ctz(m);
+            const int64_t i = item(j);
+            int rung, ties;
+            settle(w[i], elements(i), rung, ties);
+            if (t.ties == 1) { rung += ties; ties = 0; }   // the one move at the threshold is applied
+            rungs = (rungs & ~(uint64_t(15) << (4 * j))) | (static_cast<uint64_t>(rung) << (4 * j));
+            tied |= static_cast<uint64_t>(ties) << (4 * j);
+        }
+    } else if (!v.loose) {
+        rungs = 0x1111111111111111ull * static_cast<uint64_t>(steps);
+    }
+    const auto apply_ties = [&](int64_t Di, int& rung, int ties, uint64_t freed) {
+        for (; ties > 0 && freed < rest; --ties, ++rung)
+            freed += static_cast<uint64_t>(Di) * static_cast<uint64_t>(ladder_width(a, rung) - ladder_width(a, rung + 1));
+    };
+    const auto tie_bits = [&](int64_t Di, int rung, int ties) {
+        return static_cast<uint64_t>(Di) * static_cast<uint64_t>(ladder_width(a, rung) - ladder_width(a, rung + ties));
+    };
+    if (t.ties > 1) {
+#pragma unroll
+        for (int k = 0; k < kAllocQuads; ++k) {
+            if (k * kRound >= M) break;
+            uint64_t of_item[kQ], sum = 0, total;
+#pragma unroll
+            for (int q = 0; q < kQ; ++q) {
+                const int j = k * kQ + q;
+                of_item[q] = tie_bits(size[j], static_cast<int>(rungs >> (4 * j)) & 15, static_cast<int>(tied >> (4 * j)) & 15);
+                sum += of_item[q];
+            }
+            uint64_t before = tie_carry + block_exclusive_scan(sum, wave_round[k & 1], total);
+            tie_carry += total;
+#pragma unroll
+            for (int q = 0; q < kQ; ++q) {
+                const int j = k * kQ + q;
+                int rung = static_cast<int>(rungs >> (4 * j)) & 15;
+                apply_ties(size[j], rung, static_cast<int>(tied >> (4 * j)) & 15, before);
+                before += of_item[q];
+                rungs = (rungs & ~(uint64_t(15) << (4 * j))) | (static_cast<uint64_t>(rung) << (4 * j));
+            }
+        }
+    }
+    const bool word_stores = (reinterpret_cast<uintptr_t>(bits) & 3u) == 0;
+    const auto store_quad = [&](int64_t i0, uint32_t widths, const uint64_t (&at)[kQ]) {
+        if (i0 + kQ <= M && word_stores) {
+            *reinterpret_cast<uint32_t*>(bits + i0) = widths;
+            i64x2_a8 x, y;
+            x[0] = static_cast<int64_t>(at[0]);
+            x[1] = static_cast<int64_t>(at[1]);
+            y[0] = static_cast<int64_t>(at[2]);
+            y[1] = static_cast<int64_t>(at[3]);
+            *reinterpret_cast<i64x2_a8*>(offsets + i0) = x;
+            *reinterpret_cast<i64x2_a8*>(offsets + i0 + 2) = y;
+            return;
+        }
+#pragma unroll
+        for (int q = 0; q < kQ; ++q)
+            if (i0 + q < M) {
+                bits[i0 + q] = static_cast<uint8_t>(widths >> (8 * q));
+                offsets[i0 + q] = at[q];
+            }
+    };
+    // the byte sums of all rounds in registers go through one barrier
+    {
+        uint64_t upto[kAllocQuads], own[kAllocQuads];
+#pragma unroll
+        for (int k = 0; k < kAllocQuads; ++k) {
+            own[k] = 0;
+#pragma unroll
+            for (int q = 0; q < kQ; ++q) {
+                const int j = k * kQ + q;
+                int64_t Di = size[j];
+                if (invalid) {   // invalid input: stay memory-safe, with the sizes as they are where they can be
+                    const int64_t i = item(j);
+                    Di = i < M ? elements(i) : 0;
+                    if (Di <= 0 || Di >= (int64_t(1) << 34)) Di = i < M ? 1 : 0;
+                    size[j] = Di;
+                }
+                own[k] += stream_bytes(Di, ladder_width(a, static_cast<int>(rungs >> (4 * j)) & 15));
+            }
+            upto[k] = wave_inclusive_scan(own[k], lane);
+            if (lane == kWave - 1) wave_bytes[k * kAllocWavesMax + wave] = upto[k];
+        }
+        __syncthreads();
+        const uint64_t of_wave = wave_bytes[lane];   // row k of the lanes: round k
+        const uint64_t scan = row_inclusive_scan(of_wave);
+#pragma unroll
+        for (int k = 0; k < kAllocQuads; ++k) {
+            uint64_t off = byte_carry + read_lane(scan, 16 * k + wave) - read_lane(of_wave, 16 * k + wave) + upto[k] - own[k];
+            byte_carry += read_lane(scan, 16 * k + 15);
+            uint64_t at[kQ];
+            uint32_t widths = 0;
+#pragma unroll
+            for (int q = 0; q < kQ; ++q) {
+                const int j = k * kQ + q;
+                const int b = ladder_width(a, static_cast<int>(rungs >> (4 * j)) & 15);
+                widths |= static_cast<uint32_t>(b) << (8 * q);
+                at[q] = off;
+                off += stream_bytes(size[j], b);
+            }
+            store_quad(item(k * kQ), widths, at);
+        }
+    }
+    // items beyond the registers, round by round
+    for (int64_t base = kAllocQuads * kRound; base < M; base += kRound) {
+        int64_t D4[kQ];
+        int rung[kQ], ties[kQ];
+        uint64_t tie4[kQ], sum = 0, total;
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) {
+            const int64_t i = base + tid * kQ + q;
+            D4[q] = i < M ? elements(i) : 0;
+            if (D4[q] <= 0 || D4[q] >= (int64_t(1) << 34)) D4[q] = i < M ? 1 : 0;
+            rung[q] = v.loose ? 0 : steps;
+            ties[q] = 0;
+            if (v.search && i < M) {
+                const float wi = w[i];
+                const uint32_t cls = class_of(bin_of(ratio_of(wi, D4[q])));
+                rung[q] = static_cast<int>(cls & 7u);
+                if (cls & 8u) settle(wi, D4[q], rung[q], ties[q]);
+            }
+            tie4[q] = tie_bits(D4[q], rung[q], ties[q]);
+            sum += tie4[q];
+        }
+        uint64_t before = tie_carry + block_exclusive_scan(sum, wave_round[0], total);
+        tie_carry += total;
+        uint64_t bytes = 0;
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) {
+            apply_ties(D4[q], rung[q], ties[q], before);
+            before += tie4[q];
+            bytes += stream_bytes(D4[q], ladder_width(a, rung[q]));
+        }
+        uint64_t off = byte_carry + block_exclusive_scan(bytes, wave_round[1], total);
+        byte_carry += total;
+        uint64_t at[kQ];
+        uint32_t widths = 0;
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) {
+            const int b = ladder_width(a, rung[q]);
+            widths |= static_cast<uint32_t>(b) << (8 * q);
+            at[q] = off;
+            off += stream_bytes(D4[q], b);
+        }
+        store_quad(base + tid * kQ, widths, at);
+    }
     if (tid == 0) {
         result[0] = static_cast<int64_t>(byte_carry);
-        result[1] = status;
+        result[1] = v.status;
     }
 }
 
@@ -2267,11 +2848,19 @@ int launch_allocate_bits(const float* w, const int64_t* D_items, int64_t D, int6
     a.D_items = D_items;
     a.budget_bits = budget_bits;
     a.lad = lad;
-    // a workgroup no larger than the problem: barriers and scans get cheaper with fewer wavefronts
-    const int64_t lanes = (M + kWave - 1) / kWave * kWave;
-    const int block = static_cast<int>(lanes < kAllocBlock ? lanes : kAllocBlock);
-    if (M <= block) allocate_bits_kernel<1><<<1, block, 0, static_cast<hipStream_t>(stream)>>>(w, a, bits, offsets, result);
-    else allocate_bits_kernel<kAllocCached><<<1, block, 0, static_cast<hipStream_t>(stream)>>>(w, a, bits, offsets, result);
+    for (int r = 0; r < kMaxSteps; ++r) a.inverse[r] = r + 1 < lad.count ? 1.0 / lad.price[r] : 0.0;
+    a.width_nibbles = 0;
+    for (int k = 0; k < lad.count; ++k) a.width_nibbles |= static_cast<uint32_t>(lad.width[k]) << (4 * k);
+    const int64_t moves = M * (lad.count - 1);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    if (M <= kAllocBlock && moves <= kSmallMoves) {
+        // a thread per move up to the largest workgroup: the (binary64) division of a move is most of its cost
+        const int64_t most = moves > M ? moves : M;
+        const int64_t lanes = (most + kWave - 1) / kWave * kWave;
+        allocate_bits_small_kernel<<<1, static_cast<unsigned>(lanes < kAllocBlock ? lanes : kAllocBlock), 0, s>>>(w, a, bits, offsets, result);
+    } else {
+        allocate_bits_kernel<<<1, kAllocBlock, 0, s>>>(w, a, bits, offsets, result);
+    }
     return check_launch("actq_allocate_bits_device");
 }
 

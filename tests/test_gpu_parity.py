@@ -463,6 +463,48 @@ def test_device_allocator_equals_the_greedy(case):
     _check_alloc(w, D, max(budget, 0), widths, uniform)
 
 
+def _spread(rng, M, law):
+    if law == "wide":          # ratios over 60 decades: the bins over w / D are as coarse as they get
+        return np.exp(rng.uniform(np.log(1e-30), np.log(1e30), M)).astype(np.float32)
+    if law == "close":         # more undecided moves than the kernel lists, all prices different
+        return (1.0 + np.arange(M) * 2.0 ** -22).astype(np.float32)
+    if law == "few":           # a handful of values: many ties at the threshold, and some free items
+        return rng.choice(np.array([0.0, 1e-45, 1.0, 1.0000001, 3.0], dtype=np.float32), M)
+    return np.full(M, {"zero": 0.0, "one": 1.0}[law], dtype=np.float32)
+
+
+# items around the limits of the two kernels: 2048 moves and 1024 items (one workgroup of single
+# moves), rounds of 4096 items, 16,384 items in registers; remainders of the quadruples
+@pytest.mark.parametrize("law", ["wide", "close", "few", "zero", "one"])
+@pytest.mark.parametrize("M,widths", [(292, 0x1FE), (293, 0x1FE), (682, 0x116), (683, 0x116), (1024, 0x102), (1025, 0x102), (4096, 0x116),
+                                      (4097, 0x1FE), (4099, 0x106), (16384, 0x116), (16385, 0x116), (16390, 0x1FE)])
+def test_device_allocator_at_the_limits_of_its_kernels(M, widths, law):
+    rng = np.random.default_rng(M)
+    w = _spread(rng, M, law)
+    D = np.full(M, 25088, dtype=np.int64) if law == "close" else rng.choice([1, 256, 25088, 802816, 2 ** 34 - 1], M).astype(np.int64)
+    lo = min(b for b in range(1, 9) if widths >> b & 1)
+    # the host allocator (a heap, checked against the oracle elsewhere) is the reference at these sizes
+    for mean in (lo + 0.003, 2.0, 6.7):
+        budget = int(mean * float(D.sum()))
+        want = B.allocate_bits(w, D, budget, widths)
+        got, offs, total, status = _device_alloc(w, D, budget, widths, False)
+        assert status == 0 and np.array_equal(got, want), (mean, np.flatnonzero(got != want)[:6])
+        per = ((D + 255) // 256) * 32 * want.astype(np.int64)
+        assert np.array_equal(offs, np.concatenate([[0], np.cumsum(per)[:-1]])) and total == int(per.sum())
+
+
+def test_device_allocator_writes_widths_at_any_byte_address():
+    M = 5003
+    w = synth.lognormal_sensitivities(M, seed=3)
+    D = np.full(M, 1000, dtype=np.int64)
+    want = B.allocate_bits(w, D, 2 * M * 1000)
+    wd = torch.from_numpy(np.concatenate([[0.0], w]).astype(np.float32)).cuda()[1:]    # 4 bytes past an aligned address
+    buf = torch.full((M + 9,), 0xA5, dtype=torch.uint8, device="cuda:0")
+    bits, offs, res = B.allocate_bits_device(wd, torch.from_numpy(D).cuda(), 2 * M * 1000, bits=buf[1:1 + M])
+    assert np.array_equal(bits.cpu().numpy(), want) and int(res[1]) == 0
+    assert buf[0] == 0xA5 and (buf[1 + M:] == 0xA5).all()
+
+
 def test_device_allocator_edges():
     M = 300
     rng = np.random.default_rng(1)
