@@ -408,6 +408,55 @@ def test_variance_sweep_per_group_against_per_tensor():
         assert se_pt > 10 * se_pg
 
 
+# ----------------------------------------------------------------------------- samples that end inside a group
+
+# tiles of four groups, runs of eight, the 16-byte pieces (4 or 8 elements) and the lanes' stretches (16, 32) and what
+# is left of them; samples aligned to 2, 4, 8, 16, 64 and 128 bytes; one tile, many tiles, several XCD runs
+@pytest.mark.parametrize("N,D", [(5, 1), (3, 2), (7, 3), (4, 7), (3, 17), (9, 31), (2, 33), (2, 255), (3, 1023), (3, 1025), (2, 1024 + 16),
+                                 (3, 2047), (3, 2049), (2, 2048 + 64), (5, 3 * 1024 + 8), (70, 256 * 33 + 5), (9, 64 * 57 * 57), (40, 3 * 75 * 75)])
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+@pytest.mark.parametrize("noise_bits,hf", [(16, 0), (24, 0), (16, 1), (24, 1), (16, 2), (24, 2)])
+def test_ragged_samples_in_every_mode(N, D, dtype, noise_bits, hf):
+    rng = np.random.default_rng(N * 31 + D)
+    x = (rng.standard_normal((N, D)) * np.exp(rng.uniform(-3, 3, (N, 1))) - 0.25).astype(dtype)
+    bits = ((np.arange(N) + D) % 8 + 1).astype(np.uint8)
+    if hf == B.ACTQ_HDR_F32:
+        _round_trip(x, bits, seed=D, tag=N, noise_bits=noise_bits, out_dtypes=(torch.float32, torch.float16))
+    elif hf == B.ACTQ_HDR_BF16:
+        _round_trip_bf16(x, bits, seed=D, tag=N, noise_bits=noise_bits, out_dtypes=(torch.float32, torch.float16))
+    else:
+        run = GpuRun(x, bits, hf=hf)
+        zr = oracle.tensor_stats(x)
+        run.header.copy_(torch.from_numpy(zr))
+        packed, _ = run.quantize(D, N, noise_bits)
+        opacked, ooff = oracle.quantize_pack_tensor(x, bits, zr, D, N, noise_bits=noise_bits)
+        assert np.array_equal(packed, opacked)
+        for dt, npdt in ((torch.float32, np.float32), (torch.float16, np.float16)):
+            want = oracle.unpack_dequantize_tensor(opacked, zr, bits, ooff, N, D, out_dtype=npdt)
+            assert np.array_equal(run.dequantize(dt).view(np.uint8), want.view(np.uint8))
+
+
+@pytest.mark.parametrize("b", [2, 3, 4, 5, 6, 7, 8])
+def test_binary16_overshoot_with_the_bfloat16_header(b):
+    """A group range that bfloat16 holds exactly and whose scaled maximum lies one ulp above B, on the elements
+    with the largest noise: the kernel that clamps for b = 8 only equals the oracle, which always clamps."""
+    Bq = np.float32((1 << b) - 1)
+    cands = np.arange(0x3800, 0x4000, 8, dtype=np.uint16).view(np.float16)      # eight significant bits
+    c32 = cands.astype(np.float32)
+    r = cands[np.flatnonzero((c32 * (Bq / c32).astype(np.float32)).astype(np.float32) > Bq)[0]]
+    D = 1 << 18
+    hits = [d for d in range(D) if oracle.noise(321, 0, 0, d, 16) >= 1.0 - 2.0 ** -16]
+    assert hits
+    x = np.zeros((1, D), dtype=np.float16)
+    x[0, 1::2] = np.float16(float(r) / 2)
+    for d in hits:
+        x[0, d] = r
+        g = d // 256
+        if x[0, g * 256:(g + 1) * 256].min() != 0.0:
+            x[0, g * 256 + (1 if d % 256 == 0 else 0)] = 0.0
+    _round_trip_bf16(x, np.array([b], dtype=np.uint8), 321, 0, 16)
+
+
 # ----------------------------------------------------------------------------- device allocator
 
 def _oracle_alloc(w, D, budget, widths):
