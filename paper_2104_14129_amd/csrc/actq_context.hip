@@ -330,14 +330,13 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_backward_kernel(const uint8_
 }
 
 // ------------------------------------------------------------------------------------
-// Backward fast path for the common geometries: square window K in {2, 3}, stride S in {1, 2},
-// dilation 1, any legal padding.  With one element per lane the backward kernel is bound by
+// Backward path for square windows K in {2, 3}, stride S in {1, 2}, dilation 1, any legal padding, where the
+// row kernels further down do not apply or lose.  With one element per lane the kernel above is bound by
 // instruction issue, not by HBM (a wavefront that produces 256 bytes can afford only about two
 // dozen vector instructions), so here a lane produces four consecutive elements of a row: the
 // index arithmetic, the row checks and the loads of the neighbouring outputs are shared, and
 // the result leaves as one 128-bit (binary16: 64-bit) store.  The arithmetic and its order are
-// those of the kernel above.  (The same regrouping of the forward kernel was measured slower:
-// four windows per lane spread every load of the wavefront over four times as many cache lines.)
+// those of the kernel above.
 
 template <typename T>
 struct Quad;
@@ -419,6 +418,420 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_backward_quad_kernel(const u
     }
 }
 
+// ------------------------------------------------------------------------------------
+// Pools of any extent with the windows networks use: stride 2 with K = 3 (padding 0 or 1) or K = 2
+// (padding 0), and stride 1 with K = 3 and padding 1; dilation 1, rows of any length and alignment.
+// What bounds these kernels is memory (input once, output and positions once); one element per lane
+// costs three to five times that in address cycles (the texture addresser takes a wavefront's 64
+// addresses in 16 clocks whatever the width of the load).  So a lane owns 16 bytes of an input row (E
+// columns, from column E c; at the alignment of an element, rows of odd length start anywhere) and the
+// NO = E / S output columns that lie over them.  The lanes run over (plane, row, c) flattened, so the
+// neighbouring lanes hold the columns to the left and right, and the one column that a window needs
+// from there comes by a wavefront shift; the wavefront's edge lane takes it through the scalar data path.
+// Columns past the end of a row are read (they belong to the next row) and ignored; the wavefront that
+// would read past the tensor's end goes element by element.
+// Against one output (forward) and four inputs (backward) per lane: 3x3 / 2 / 1 on binary16 [4096, 113, 113]
+// 74 -> 29 us forward and 122 -> 31 us backward, binary32 87 -> 47 and 150 -> 49 us.
+struct RowPool {
+    uint32_t chunks;              // lanes per row
+    FastDiv by_chunks, by_rows;   // by_rows: division by the rows (forward: output rows; backward: stretches of S input rows) of a plane
+    uint32_t rows;
+    uint32_t total;               // lanes in all
+    int64_t elems;                // elements of the tensor that is read
+};
+
+// Stretches of E elements and of NO elements and positions.
+template <typename T, int S>
+struct RowVec;
+template <>
+struct RowVec<float, 1> {
+    typedef float in __attribute__((ext_vector_type(4), aligned(4)));
+    typedef in out;
+    typedef uint32_t codes __attribute__((aligned(1)));
+};
+template <>
+struct RowVec<float, 2> {
+    typedef float in __attribute__((ext_vector_type(4), aligned(4)));
+    typedef float out __attribute__((ext_vector_type(2), aligned(4)));
+    typedef uint16_t codes __attribute__((aligned(1)));
+};
+template <>
+struct RowVec<_Float16, 1> {
+    typedef _Float16 in __attribute__((ext_vector_type(8), aligned(2)));
+    typedef in out;
+    typedef uint64_t codes __attribute__((aligned(1)));
+};
+template <>
+struct RowVec<_Float16, 2> {
+    typedef _Float16 in __attribute__((ext_vector_type(8), aligned(2)));
+    typedef _Float16 out __attribute__((ext_vector_type(4), aligned(2)));
+    typedef uint32_t codes __attribute__((aligned(1)));
+};
+
+template <typename V>
+__device__ __forceinline__ V load_uniform(const V* p)
+{
+    typedef const V __attribute__((address_space(4))) * constant_ptr;
+    return *(constant_ptr)(reinterpret_cast<uintptr_t>(p));
+}
+
+// One element at a wavefront-uniform address, as (part of) the aligned 32-bit word around it.
+template <typename V>
+__device__ __forceinline__ V load_uniform_element(const V* p)
+{
+    const uintptr_t at = reinterpret_cast<uintptr_t>(p);
+    const uint32_t word = load_uniform(reinterpret_cast<const uint32_t*>(at & ~uintptr_t(3))) >> (8 * static_cast<uint32_t>(at & 3u));
+    V v;
+    __builtin_memcpy(&v, &word, sizeof(V));
+    return v;
+}
+
+// A word from the lane to the left / right; the wavefront's edge lane keeps garbage.
+__device__ __forceinline__ uint32_t from_lane(uint32_t w, bool left)
+{
+    constexpr int kWaveShiftRight1 = 0x138, kWaveShiftLeft1 = 0x130;
+    return static_cast<uint32_t>(left ? __builtin_amdgcn_update_dpp(0, static_cast<int>(w), kWaveShiftRight1, 0xf, 0xf, false)
+                                      : __builtin_amdgcn_update_dpp(0, static_cast<int>(w), kWaveShiftLeft1, 0xf, 0xf, false));
+}
+
+__device__ __forceinline__ int64_t read_lane_i64(int64_t v, int lane)
+{
+    const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(static_cast<uint64_t>(v) & 0xffffffffu), lane));
+    const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(static_cast<uint64_t>(v) >> 32), lane));
+    return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
+}
+
+// What a word of memory becomes in the kernels: positions are words as they are, gradients binary32 patterns.
+struct PositionWord {
+    static __device__ __forceinline__ uint32_t of(uint8_t v) { return v; }
+};
+template <typename T>
+struct GradientWord {
+    static __device__ __forceinline__ uint32_t of(T v) { return __float_as_uint(static_cast<float>(v)); }
+};
+
+// The word `own` of the lane to the left (LEFT) or right.  The wavefront's edge lane takes it from memory,
+// element `at` of p, if its neighbour exists (`inside`).
+template <bool LEFT, typename WORD, typename V, typename M>
+__device__ __forceinline__ V neighbour(V own, bool inside, const M* p, int64_t at)
+{
+    constexpr int kEdge = LEFT ? 0 : kWave - 1;
+    const int64_t edge_at = read_lane_i64(at, kEdge);
+    V from_edge = 0;
+    if (__builtin_amdgcn_readlane(static_cast<int>(inside), kEdge) != 0) from_edge = WORD::of(load_uniform_element(p + edge_at));
+    const V shifted = static_cast<V>(from_lane(own, LEFT));
+    return (threadIdx.x & (kWave - 1)) == kEdge ? from_edge : shifted;
+}
+
+// The first `count` (1 .. N - 1) of N values or positions, as pieces of 4, 2 and 1: at most three stores.
+template <int N, typename T, typename V>
+__device__ __forceinline__ void store_first(T* dst, V v, int count)
+{
+    typedef T pair __attribute__((ext_vector_type(2), aligned(sizeof(T))));
+    typedef T quad __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+    T t0 = v[0], t1 = v[1];
+    if constexpr (N == 8) {
+        if (count & 4) {
+            quad w;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) w[k] = v[k];
+            *reinterpret_cast<quad*>(dst) = w;
+            dst += 4;
+        }
+        t0 = count & 4 ? v[4] : t0;
+        t1 = count & 4 ? v[5] : t1;
+    }
+    T last = t0;
+    if constexpr (N >= 4) {
+        if (count & 2) {
+            pair w;
+            w[0] = t0;
+            w[1] = t1;
+            *reinterpret_cast<pair*>(dst) = w;
+            dst += 2;
+        }
+        const T second = N == 8 && (count & 4) ? v[N == 8 ? 6 : 2] : v[2];
+        last = count & 2 ? second : t0;
+    }
+    if (count & 1) *dst = last;
+}
+
+__device__ __forceinline__ void store_first_codes(uint8_t* dst, uint64_t codes, int count)
+{
+    typedef uint32_t word __attribute__((aligned(1)));
+    typedef uint16_t half __attribute__((aligned(1)));
+    if (count & 4) {
+        *reinterpret_cast<word*>(dst) = static_cast<uint32_t>(codes);
+        dst += 4;
+        codes >>= 32;
+    }
+    if (count & 2) {
+        *reinterpret_cast<half*>(dst) = static_cast<uint16_t>(codes);
+        dst += 2;
+        codes >>= 16;
+    }
+    if (count & 1) *dst = static_cast<uint8_t>(codes);
+}
+
+// How the forward kernel carries a value: as its bit pattern (a selection of floating-point values by their
+// comparison becomes a maximum instruction, which returns +0 where the first of two zeros is -0).
+// Binary16 at stride 2 is widened to binary32 first: every value is compared twice or more, and a
+// comparison of halves has to extract them (32 -> 29 us at 3x3 / 2 / 1 on [4096, 113, 113]); at stride 1 the
+// registers of three widened rows cost more (70 -> 85 us).
+template <typename T, int S>
+struct Carrier;
+template <int S>
+struct Carrier<float, S> {
+    typedef uint32_t raw;
+    typedef uint32_t type;
+    static __device__ __forceinline__ type of(raw u) { return u; }
+    static __device__ __forceinline__ float value(type u) { return __uint_as_float(u); }
+    static __device__ __forceinline__ raw back(type u) { return u; }
+};
+template <>
+struct Carrier<_Float16, 1> {
+    typedef uint16_t raw;
+    typedef uint16_t type;
+    static __device__ __forceinline__ type of(raw u) { return u; }
+    static __device__ __forceinline__ _Float16 value(type u)
+    {
+        _Float16 h;
+        __builtin_memcpy(&h, &u, 2);
+        return h;
+    }
+    static __device__ __forceinline__ raw back(type u) { return u; }
+};
+template <>
+struct Carrier<_Float16, 2> {
+    typedef uint16_t raw;
+    typedef uint32_t type;
+    static __device__ __forceinline__ type of(raw u)
+    {
+        uint32_t w = __float_as_uint(static_cast<float>(Carrier<_Float16, 1>::value(u)));   // exact
+        asm("" : "+v"(w));   // a pattern, not a value, to the compiler
+        return w;
+    }
+    static __device__ __forceinline__ float value(type u) { return __uint_as_float(u); }
+    static __device__ __forceinline__ raw back(type u)
+    {
+        asm("" : "+v"(u));
+        const _Float16 h = static_cast<_Float16>(__uint_as_float(u));
+        raw r;
+        __builtin_memcpy(&r, &h, 2);
+        return r;
+    }
+};
+
+// Forward.  Rows and columns outside the image read as the nearest ones inside (their addresses are
+// clamped).  A copy to the right of or below its original never wins, because only a larger value
+// replaces the running maximum; one to the left or above wins in its original's place, and the
+// position moves to the original (which is the first of the equal values inside the image).
+template <typename T, int K, int P, int S>
+__global__ __launch_bounds__(kBlock) void maxpool2d_forward_rows_kernel(const T* __restrict__ x, Pool g, RowPool q,
+                                                                        T* __restrict__ y, uint8_t* __restrict__ argmax)
+{
+    typedef Carrier<T, S> C;
+    typedef typename C::raw raw;
+    typedef raw vec_in __attribute__((ext_vector_type(16 / sizeof(T)), aligned(sizeof(T))));
+    typedef raw vec_out __attribute__((ext_vector_type(16 / sizeof(T) / S), aligned(sizeof(T))));
+    typedef typename RowVec<T, S>::codes vec_codes;
+    constexpr int E = 16 / sizeof(T), NO = E / S;
+    constexpr bool kLeft = P == 1, kRight = K == 3 && (P == 0 || S == 1);   // columns needed from the neighbours
+    const uint32_t idx = blockIdx.x * kBlock + threadIdx.x;
+    const bool live = idx < q.total;
+    const uint32_t id = live ? idx : q.total - 1;   // every lane takes part in the shift
+    const uint32_t strip = fastdiv(id, q.by_chunks);           // output row over all planes
+    const uint32_t c = id - strip * q.chunks;
+    const uint32_t plane = fastdiv(strip, q.by_rows);
+    const int32_t i = static_cast<int32_t>(strip - plane * q.rows);
+    int64_t at[K];   // the lane's first element of every window row
+#pragma unroll
+    for (int a = 0; a < K; ++a) {
+        const int32_t r = min(max(S * i - P + a, 0), g.H - 1);
+        at[a] = (static_cast<int64_t>(plane) * g.H + r) * g.W + static_cast<int64_t>(E) * c;
+    }
+    const raw* xr = reinterpret_cast<const raw*>(x);
+    raw* yr = reinterpret_cast<raw*>(y);
+    typename C::type v[K][E + 2];   // slot 1 + t: column E c + t; slots 0 and E + 1: the neighbours' columns
+    if (__any(at[K - 1] + E > q.elems)) {
+#pragma unroll
+        for (int a = 0; a < K; ++a)
+#pragma unroll
+            for (int t = 0; t < E; ++t) v[a][1 + t] = C::of(xr[min(at[a] + t, q.elems - 1)]);
+    } else {
+        vec_in w[K];
+#pragma unroll
+        for (int a = 0; a < K; ++a) w[a] = *reinterpret_cast<const vec_in*>(xr + at[a]);
+#pragma unroll
+        for (int a = 0; a < K; ++a)
+#pragma unroll
+            for (int t = 0; t < E; ++t) v[a][1 + t] = C::of(w[a][t]);
+    }
+    if (kLeft) {
+#pragma unroll
+        for (int a = 0; a < K; ++a) {
+            v[a][0] = neighbour<true, C>(v[a][E], c > 0, xr, at[a] - 1);
+            v[a][0] = c > 0 ? v[a][0] : v[a][1];   // the padded column
+        }
+    }
+    if (kRight) {
+#pragma unroll
+        for (int a = 0; a < K; ++a) v[a][E + 1] = neighbour<false, C>(v[a][1], c + 1 < q.chunks, xr, at[a] + E);
+    }
+    const int32_t j0 = NO * static_cast<int32_t>(c);
+    vec_out out;
+    uint64_t codes = 0;
+#pragma unroll
+    for (int e = 0; e < NO; ++e) {
+        // column S (j0 + e) - P + b = E c - 1 + slot
+        constexpr int kFirst = 1 - P;
+        const bool past = P == 1 && S * (j0 + e) + 1 >= g.W;   // the window's last column is padding
+        typename C::type best = v[0][S * e + kFirst];
+        uint32_t best_k = 0;
+#pragma unroll
+        for (int a = 0; a < K; ++a)
+#pragma unroll
+            for (int b = 0; b < K; ++b) {
+                if (a == 0 && b == 0) continue;
+                typename C::type val = v[a][S * e + b + kFirst];
+                if (P == 1 && b == K - 1) val = past ? v[a][S * e + b - 1 + kFirst] : val;
+                const bool take = C::value(val) > C::value(best);
+                best = take ? val : best;
+                best_k = take ? static_cast<uint32_t>(a * K + b) : best_k;
+            }
+        if (P == 1) {
+            if (e == 0) best_k += c == 0 && (best_k == 0 || best_k == 3 || best_k == 6) ? 1u : 0u;
+            best_k += i == 0 && best_k < K ? K : 0u;
+        }
+        out[e] = C::back(best);
+        codes |= static_cast<uint64_t>(best_k) << (8 * e);
+    }
+    const int left = g.OW - j0;   // output columns from j0 on
+    if (!live || left <= 0) return;
+    const int64_t o = static_cast<int64_t>(strip) * g.OW + j0;
+    if (left >= NO) {
+        if (sizeof(T) == 4) {   // non-temporal: 50 -> 46 us on [4096, 111, 120]; binary16 is 2 % slower with it
+            __builtin_nontemporal_store(out, reinterpret_cast<vec_out*>(yr + o));
+            __builtin_nontemporal_store(static_cast<vec_codes>(codes), reinterpret_cast<vec_codes*>(argmax + o));
+        } else {
+            *reinterpret_cast<vec_out*>(yr + o) = out;
+            *reinterpret_cast<vec_codes*>(argmax + o) = static_cast<vec_codes>(codes);
+        }
+    } else {
+        store_first<NO>(yr + o, out, left);
+        store_first_codes(argmax + o, codes, left);
+    }
+}
+
+// Backward.  A lane produces E columns of S input rows, S q + rr.  The output rows whose windows reach
+// them are q (K = 2), q and q + 1 (stride 2, padding 1), q - 1 and q (stride 2, K = 3, padding 0), and
+// q - 1 .. q + 1 (stride 1).  The additions run over ascending output row, then column.
+// NT: non-temporal stores.
+template <typename T, int K, int P, int S, bool NT>
+__global__ __launch_bounds__(kBlock) void maxpool2d_backward_rows_kernel(const uint8_t* __restrict__ argmax,
+                                                                         const T* __restrict__ grad_y, Pool g, RowPool q,
+                                                                         T* __restrict__ grad_x)
+{
+    typedef typename RowVec<T, S>::in vec_in;
+    typedef typename RowVec<T, S>::out vec_out;
+    typedef typename RowVec<T, S>::codes vec_codes;
+    constexpr int E = 16 / sizeof(T), NO = E / S;
+    constexpr int MR = S == 1 ? 3 : (K == 3 ? 2 : 1);                  // output rows
+    constexpr int kFirstRow = K == 3 && (P == 0 || S == 1) ? -1 : 0;   // the first of them, relative to q
+    constexpr bool kLeft = K == 3 && (P == 0 || S == 1), kRight = P == 1;
+    constexpr uint32_t kNone = 0x100;                                  // no window position
+    const uint32_t idx = blockIdx.x * kBlock + threadIdx.x;
+    const bool live = idx < q.total;
+    const uint32_t id = live ? idx : q.total - 1;
+    const uint32_t strip = fastdiv(id, q.by_chunks);           // stretch of S input rows over all planes
+    const uint32_t c = id - strip * q.chunks;
+    const uint32_t plane = fastdiv(strip, q.by_rows);
+    const int32_t stretch = static_cast<int32_t>(strip - plane * q.rows);
+    const int32_t j0 = NO * static_cast<int32_t>(c);
+    uint32_t gy[MR][NO + 2];     // slot 1 + t: output column j0 + t
+    uint32_t code[MR][NO + 2];
+    int64_t at[MR];
+    bool row_ok[MR];
+#pragma unroll
+    for (int u = 0; u < MR; ++u) {
+        const int32_t i = stretch + kFirstRow + u;
+        row_ok[u] = i >= 0 && i < g.OH;
+        at[u] = (static_cast<int64_t>(plane) * g.OH + min(max(i, 0), g.OH - 1)) * g.OW + j0;
+    }
+    if (__any(at[MR - 1] + NO > q.elems)) {
+#pragma unroll
+        for (int u = 0; u < MR; ++u)
+#pragma unroll
+            for (int t = 0; t < NO; ++t) {
+                const int64_t o = min(at[u] + t, q.elems - 1);
+                gy[u][1 + t] = GradientWord<T>::of(grad_y[o]);
+                code[u][1 + t] = argmax[o];
+            }
+    } else {
+        vec_out w[MR];
+        uint64_t cw[MR];
+#pragma unroll
+        for (int u = 0; u < MR; ++u) {
+            w[u] = *reinterpret_cast<const vec_out*>(grad_y + at[u]);
+            cw[u] = *reinterpret_cast<const vec_codes*>(argmax + at[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < MR; ++u)
+#pragma unroll
+            for (int t = 0; t < NO; ++t) {
+                gy[u][1 + t] = GradientWord<T>::of(w[u][t]);
+                code[u][1 + t] = static_cast<uint32_t>(cw[u] >> (8 * t)) & 0xffu;
+            }
+    }
+#pragma unroll
+    for (int u = 0; u < MR; ++u) {
+        // the neighbours' columns first, as stored; then what does not exist is no position
+        const bool left_there = c > 0 && j0 - 1 < g.OW, right_there = c + 1 < q.chunks && j0 + NO < g.OW;
+        if (kLeft) {
+            gy[u][0] = neighbour<true, GradientWord<T>>(gy[u][NO], left_there, grad_y, at[u] - 1);
+            code[u][0] = neighbour<true, PositionWord>(code[u][NO], left_there, argmax, at[u] - 1);
+            code[u][0] = row_ok[u] && left_there ? code[u][0] : kNone;
+        }
+        if (kRight) {
+            gy[u][NO + 1] = neighbour<false, GradientWord<T>>(gy[u][1], right_there, grad_y, at[u] + NO);
+            code[u][NO + 1] = neighbour<false, PositionWord>(code[u][1], right_there, argmax, at[u] + NO);
+            code[u][NO + 1] = row_ok[u] && right_there ? code[u][NO + 1] : kNone;
+        }
+#pragma unroll
+        for (int t = 0; t < NO; ++t) code[u][1 + t] = row_ok[u] && j0 + t < g.OW ? code[u][1 + t] : kNone;
+    }
+    const int left = g.W - E * static_cast<int32_t>(c);   // input columns from the lane's first on, > 0
+#pragma unroll
+    for (int rr = 0; rr < S; ++rr) {
+        vec_in out;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            float acc = 0.0f;
+#pragma unroll
+            for (int u = 0; u < MR; ++u) {                          // ascending output row
+                const int a = rr + P - S * (kFirstRow + u);         // row of input row S q + rr in its window
+                if (a < 0 || a >= K) continue;
+#pragma unroll
+                for (int t = kLeft ? -1 : 0; t < NO + (kRight ? 1 : 0); ++t) {   // ascending output column
+                    const int b = e + P - S * t;
+                    if (b < 0 || b >= K) continue;
+                    acc += code[u][1 + t] == static_cast<uint32_t>(a * K + b) ? __uint_as_float(gy[u][1 + t]) : 0.0f;  // + 0 changes nothing
+                }
+            }
+            out[e] = static_cast<T>(acc);
+        }
+        const int32_t r = S * stretch + rr;
+        if (!live || r >= g.H) continue;
+        T* dst = grad_x + (static_cast<int64_t>(plane) * g.H + r) * g.W + static_cast<int64_t>(E) * c;
+        if (left >= E) {
+            if (NT) __builtin_nontemporal_store(out, reinterpret_cast<vec_in*>(dst));
+            else *reinterpret_cast<vec_in*>(dst) = out;
+        } else {
+            store_first<E>(dst, out, left);
+        }
+    }
+}
+
 }  // namespace
 
 int launch_relu_forward(const void* x, int dtype, int64_t n, void* y, uint8_t* mask, void* stream)
@@ -472,346 +885,21 @@ static Pool make_pool(const PoolShape& p, int64_t planes, int64_t per_plane, dim
     return g;
 }
 
-// Forward fast path for stride 2, square windows K in {2, 3}, padding <= 1, dilation 1, rows a
-// multiple of four long.  The vector memory pipeline moves 64 bytes per clock and compute unit
-// whatever the width of the load, so nine 32-bit loads per output (16 clocks each for a
-// wavefront) keep it busier than HBM.  Here a lane produces two neighbouring outputs from one
-// aligned 128-bit load per window row plus at most one 32-bit load on either side: three times
-// fewer load cycles per output.  Window positions and their order are those of the kernel above.
-template <typename T, int K>
-__global__ __launch_bounds__(kBlock) void maxpool2d_forward_pair_kernel(const T* __restrict__ x, int64_t planes, Pool g,
-                                                                        QuadGeometry q, T* __restrict__ y,
-                                                                        uint8_t* __restrict__ argmax)
-{
-    typedef typename Quad<T>::vec vec4;
-    const int64_t plane = static_cast<int64_t>(blockIdx.z) * g.grid_y + blockIdx.y;
-    const uint32_t idx = blockIdx.x * kBlock + threadIdx.x;
-    if (plane >= planes || idx >= static_cast<uint32_t>(g.OH * q.quads_per_row)) return;  // pairs per row here
-    const int32_t i = static_cast<int32_t>(fastdiv(idx, q.by_quads));
-    const int32_t m = static_cast<int32_t>(idx) - i * q.quads_per_row;   // outputs 2m and 2m + 1
-    const T* xp = x + plane * g.H * g.W;
-    const int32_t r0 = 2 * i - g.ph;
-    const int32_t c4 = 4 * m;                  // first column of the aligned quad
-    // slot t holds input column c4 - 1 + t: slot 0 the left neighbour, 1..4 the quad, 5 the right neighbour
-    float v[K][6];
-    bool col_ok[6], row_ok[K];
-#pragma unroll
-    for (int t = 0; t < 6; ++t) col_ok[t] = c4 - 1 + t >= 0 && c4 - 1 + t < g.W;
-    const bool quad_ok = c4 + 3 < g.W;
-#pragma unroll
-    for (int a = 0; a < K; ++a) {
-        const int32_t r = r0 + a;
-        row_ok[a] = r >= 0 && r < g.H;
-        const T* row = xp + min(max(r, 0), g.H - 1) * g.W;
-        if (quad_ok) {
-            const vec4 w = *reinterpret_cast<const vec4*>(row + c4);
-            v[a][1] = static_cast<float>(w[0]); v[a][2] = static_cast<float>(w[1]);
-            v[a][3] = static_cast<float>(w[2]); v[a][4] = static_cast<float>(w[3]);
-        } else {
-#pragma unroll
-            for (int t = 1; t < 5; ++t) v[a][t] = static_cast<float>(row[min(c4 - 1 + t, g.W - 1)]);
-        }
-        v[a][0] = static_cast<float>(row[max(c4 - 1, 0)]);
-        v[a][5] = static_cast<float>(row[min(c4 + 4, g.W - 1)]);
-    }
-    float best[2];
-    uint32_t best_k[2];
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-        bool have = false;
-        best[e] = 0.0f;
-        best_k[e] = 0;
-#pragma unroll
-        for (int a = 0; a < K; ++a)
-#pragma unroll
-            for (int b = 0; b < K; ++b) {
-                // column 2 * (2m + e) - pw + b = c4 + 2e - pw + b: slot 2e + b + 1 - pw, pw in {0, 1}
-                const float val = g.pw ? v[a][2 * e + b] : v[a][2 * e + b + 1];
-                const bool ok = row_ok[a] && (g.pw ? col_ok[2 * e + b] : col_ok[2 * e + b + 1]);
-                const bool take = ok && (!have || val > best[e]);
-                best[e] = take ? val : best[e];
-                best_k[e] = take ? static_cast<uint32_t>(a * K + b) : best_k[e];
-                have = have || ok;
-            }
-    }
-    const int64_t o = plane * g.OH * g.OW + i * g.OW + 2 * m;
-    if (2 * m + 1 < g.OW) {   // OW is even on this path, so this always holds; kept as the guard of the pair store
-        typedef T pair __attribute__((ext_vector_type(2)));
-        pair out;
-        out[0] = static_cast<T>(best[0]);
-        out[1] = static_cast<T>(best[1]);
-        __builtin_nontemporal_store(out, reinterpret_cast<pair*>(y + o));
-        __builtin_nontemporal_store(static_cast<uint16_t>(best_k[0] | (best_k[1] << 8)), reinterpret_cast<uint16_t*>(argmax + o));
-    }
-}
+constexpr int kPoolBwdBlock = 256;   // threads per block of the streaming backward kernel [128 .. 1024 alike]
 
-// The same with four outputs per lane when the rows allow it (input rows a multiple of eight and
-// output rows a multiple of four long): two aligned 128-bit loads and at most one 32-bit load per
-// window row serve four windows.
-template <typename T, int K, int P>
-__global__ __launch_bounds__(kBlock) void maxpool2d_forward_four_kernel(const T* __restrict__ x, int64_t planes, Pool g,
-                                                                        QuadGeometry q, T* __restrict__ y,
-                                                                        uint8_t* __restrict__ argmax)
-{
-    typedef typename Quad<T>::vec vec4;
-    const int64_t plane = static_cast<int64_t>(blockIdx.z) * g.grid_y + blockIdx.y;
-    const uint32_t idx = blockIdx.x * kBlock + threadIdx.x;
-    if (plane >= planes || idx >= static_cast<uint32_t>(g.OH * q.quads_per_row)) return;
-    const int32_t i = static_cast<int32_t>(fastdiv(idx, q.by_quads));
-    const int32_t m = static_cast<int32_t>(idx) - i * q.quads_per_row;   // outputs 4m .. 4m+3
-    const T* xp = x + plane * g.H * g.W;
-    const int32_t r0 = 2 * i - P;
-    const int32_t c8 = 8 * m;                  // slot t holds input column c8 - 1 + t
-    float v[K][9];
-    bool row_ok[K];
-    const bool left_ok = c8 >= 1;
-#pragma unroll
-    for (int a = 0; a < K; ++a) {
-        const int32_t r = r0 + a;
-        row_ok[a] = r >= 0 && r < g.H;
-        const T* row = xp + min(max(r, 0), g.H - 1) * g.W;
-        const vec4 w0 = *reinterpret_cast<const vec4*>(row + c8);
-        const vec4 w1 = *reinterpret_cast<const vec4*>(row + c8 + 4);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            v[a][1 + t] = static_cast<float>(w0[t]);
-            v[a][5 + t] = static_cast<float>(w1[t]);
-        }
-        v[a][0] = P ? static_cast<float>(row[max(c8 - 1, 0)]) : 0.0f;
-    }
-    vec4 out;
-    uint32_t codes = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        bool have = false;
-        float best = 0.0f;
-        uint32_t best_k = 0;
-#pragma unroll
-        for (int a = 0; a < K; ++a)
-#pragma unroll
-            for (int b = 0; b < K; ++b) {
-                constexpr int kShift = 1 - P;
-                const int t = 2 * e + b + kShift;  // column 2 * (4m + e) - P + b = c8 - 1 + t
-                const bool ok = row_ok[a] && (t > 0 || left_ok);
-                const bool take = ok && (!have || v[a][t] > best);
-                best = take ? v[a][t] : best;
-                best_k = take ? static_cast<uint32_t>(a * K + b) : best_k;
-                have = have || ok;
-            }
-        out[e] = static_cast<T>(best);
-        codes |= best_k << (8 * e);
-    }
-    const int64_t o = plane * g.OH * g.OW + i * g.OW + 4 * m;
-    __builtin_nontemporal_store(out, reinterpret_cast<vec4*>(y + o));
-    __builtin_nontemporal_store(codes, reinterpret_cast<uint32_t*>(argmax + o));
-}
-
-// Forward path for the common down-sampling pools (3x3 / stride 2 / padding 1 and 2x2 / stride 2 /
-// padding 0 on even extents, H = 2 OH and W = 2 OW, rows a multiple of 16 bytes long).  Because
-// H = 2 OH, output row q = plane * OH + i of the whole tensor reads the rows 2q - P .. 2q - P + K - 1
-// of the whole input, so planes and rows flatten into one index.  A lane owns 16 bytes of an input
-// row (E = 4 or 8 columns) and R consecutive output rows; every load instruction of a wavefront then
-// covers whole cache lines (the window-per-lane kernels above touch each line from several
-// instructions, which makes the first-level cache, not HBM, the limit).  The one column to the left
-// of a lane's 16 bytes (P = 1) comes from the neighbouring lane by a wavefront shift; lane 0 takes
-// it through the scalar data path.
+// Backward path of its own for binary32 on even extents (3x3 / stride 2 / padding 1 and 2x2 / stride 2 /
+// padding 0, H = 2 OH and W = 2 OW, rows a multiple of 16 bytes long): planes and rows flatten into one
+// index without any row or column being special but at the ends of a plane, and every load and store is
+// aligned.
 struct StreamPool {
     uint32_t chunks_per_row;   // W / E
-    FastDiv by_chunks, by_rows;  // by_rows: division by OH / R
-    uint32_t rows_per_plane;   // OH / R
-    uint32_t total;            // planes * (OH / R) * chunks_per_row
+    FastDiv by_chunks, by_rows;  // by_rows: division by OH
+    uint32_t rows_per_plane;   // OH
+    uint32_t total;            // planes * OH * chunks_per_row
 };
 
-template <typename V>
-__device__ __forceinline__ V load_uniform(const V* p)
-{
-    typedef const V __attribute__((address_space(4))) * constant_ptr;
-    return *(constant_ptr)(reinterpret_cast<uintptr_t>(p));
-}
-
-__device__ __forceinline__ float from_left_lane(float v)
-{
-    constexpr int kWaveShiftRight1 = 0x138;
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kWaveShiftRight1, 0xf, 0xf, false));
-}
-
-#ifndef ACTQ_POOL_FWD_BLOCK
-#define ACTQ_POOL_FWD_BLOCK 256
-#endif
-#ifndef ACTQ_POOL_BWD_BLOCK
-#define ACTQ_POOL_BWD_BLOCK 256
-#endif
-constexpr int kPoolFwdBlock = ACTQ_POOL_FWD_BLOCK;   // threads per block of the streaming pooling kernels
-constexpr int kPoolBwdBlock = ACTQ_POOL_BWD_BLOCK;
-
-template <typename T, int K, int P, int R>
-__global__ __launch_bounds__(kPoolFwdBlock) void maxpool2d_forward_stream_kernel(const T* __restrict__ x, Pool g, StreamPool q,
-                                                                          T* __restrict__ y,
-                                                                          uint8_t* __restrict__ argmax)
-{
-    constexpr int E = 16 / sizeof(T);    // input columns per lane
-    constexpr int NO = E / 2;            // outputs per lane and output row
-    constexpr int NR = 2 * R + K - 2;    // input rows per lane
-    typedef T vec_in __attribute__((ext_vector_type(E)));
-    typedef T vec_out __attribute__((ext_vector_type(NO)));
-    const uint32_t idx = blockIdx.x * kPoolFwdBlock + threadIdx.x;
-    const bool live = idx < q.total;
-    // lanes past the end repeat the last lane's loads (every lane takes part in the shift) and store nothing
-    const uint32_t id = live ? idx : q.total - 1;
-    const uint32_t strip = fastdiv(id, q.by_chunks);            // plane * (OH / R) + i / R
-    const uint32_t c = id - strip * q.chunks_per_row;
-    const uint32_t plane = fastdiv(strip, q.by_rows);
-    const bool top = strip - plane * q.rows_per_plane == 0;     // the strip starts at output row 0 of its plane
-    const int64_t q0 = static_cast<int64_t>(strip) * R;         // first output row, counted over all planes
-    const bool left_ok = c > 0;
-    const int lane = threadIdx.x & (kWave - 1);
-    float v[NR][E + 1];   // slot 0: the column left of the lane's own, slots 1..E its own
-    bool row_ok[NR];
-#pragma unroll
-    for (int a = 0; a < NR; ++a) {
-        row_ok[a] = !(P == 1 && a == 0 && top);
-        // the row above the plane is padding: read the plane's first row instead and ignore it
-        const int64_t r = 2 * q0 - P + a + (row_ok[a] ? 0 : 1);
-        const T* row = x + r * g.W + static_cast<int64_t>(E) * c;
-        const vec_in w = *reinterpret_cast<const vec_in*>(row);
-#pragma unroll
-        for (int t = 0; t < E; ++t) v[a][1 + t] = static_cast<float>(w[t]);
-        v[a][0] = 0.0f;
-        if (P == 1) {
-            v[a][0] = from_left_lane(v[a][E]);
-            // lane 0 has no neighbour: its left column comes through the scalar data path, as the
-            // aligned 32-bit word that ends where the lane's own 16 bytes start
-            const uint32_t c_first = __builtin_amdgcn_readfirstlane(c);
-            const uint32_t r_lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(r));
-            const uint32_t r_hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(static_cast<uint64_t>(r) >> 32));
-            const int64_t r_first = static_cast<int64_t>((static_cast<uint64_t>(r_hi) << 32) | r_lo);
-            const T* first = x + r_first * g.W + static_cast<int64_t>(E) * c_first;
-            float edge = 0.0f;
-            if (c_first > 0) {
-                const uint32_t word = load_uniform(reinterpret_cast<const uint32_t*>(first) - 1);
-                if (sizeof(T) == 4) edge = __uint_as_float(word);
-                else {
-                    const uint16_t hi = static_cast<uint16_t>(word >> 16);
-                    _Float16 h;
-                    __builtin_memcpy(&h, &hi, 2);
-                    edge = static_cast<float>(h);
-                }
-            }
-            v[a][0] = lane == 0 ? edge : v[a][0];
-        }
-    }
-#pragma unroll
-    for (int rr = 0; rr < R; ++rr) {
-        vec_out out;
-        uint32_t codes = 0;
-#pragma unroll
-        for (int e = 0; e < NO; ++e) {
-            bool have = false;
-            float best = 0.0f;
-            uint32_t best_k = 0;
-#pragma unroll
-            for (int a = 0; a < K; ++a)
-#pragma unroll
-                for (int b = 0; b < K; ++b) {
-                    const int t = 2 * e + b + 1 - P;   // column 2 * (NO c + e) - P + b = E c - 1 + t
-                    const bool ok = row_ok[2 * rr + a] && (t > 0 || left_ok);
-                    const bool take = ok && (!have || v[2 * rr + a][t] > best);
-                    best = take ? v[2 * rr + a][t] : best;
-                    best_k = take ? static_cast<uint32_t>(a * K + b) : best_k;
-                    have = have || ok;
-                }
-            out[e] = static_cast<T>(best);
-            codes |= best_k << (8 * e);
-        }
-        if (!live) continue;
-        const int64_t o = (q0 + rr) * g.OW + static_cast<int64_t>(NO) * c;
-        __builtin_nontemporal_store(out, reinterpret_cast<vec_out*>(y + o));
-        if (NO == 2) __builtin_nontemporal_store(static_cast<uint16_t>(codes), reinterpret_cast<uint16_t*>(argmax + o));
-        else __builtin_nontemporal_store(codes, reinterpret_cast<uint32_t*>(argmax + o));
-    }
-}
-
-// Backward fast path for stride 2, square windows K in {2, 3}, padding P <= 1, dilation 1, input
-// rows a multiple of eight and output rows a multiple of four long.  A lane produces eight
-// consecutive inputs of a row.  The outputs whose window can contain one of them are the six
-// columns 4m-1 .. 4m+4 of one or two output rows: their gradients come in as one aligned 128-bit
-// load plus a 32-bit load on either side, their positions as one 32-bit load plus two bytes --
-// twelve loads for eight inputs instead of four loads per input.  Which window position an
-// output column would need for an input column is fixed at compile time; the order of the
-// additions is that of the kernels above (ascending output row, then column).
-template <typename T, int K, int P>
-__global__ __launch_bounds__(kBlock) void maxpool2d_backward_oct_kernel(const uint8_t* __restrict__ argmax,
-                                                                        const T* __restrict__ grad_y, int64_t planes,
-                                                                        Pool g, QuadGeometry q, T* __restrict__ grad_x)
-{
-    typedef typename Quad<T>::vec vec4;
-    constexpr int MR = (K - 1) / 2 + 1;   // output rows whose window can contain one input row
-    const int64_t plane = static_cast<int64_t>(blockIdx.z) * g.grid_y + blockIdx.y;
-    const uint32_t idx = blockIdx.x * kBlock + threadIdx.x;
-    if (plane >= planes || idx >= static_cast<uint32_t>(g.H * q.quads_per_row)) return;  // octets per row here
-    const int32_t r = static_cast<int32_t>(fastdiv(idx, q.by_quads));
-    const int32_t m = static_cast<int32_t>(idx) - r * q.quads_per_row;   // inputs 8m .. 8m+7
-    const uint8_t* ap = argmax + plane * g.OH * g.OW;
-    const T* gp = grad_y + plane * g.OH * g.OW;
-    const int32_t j4 = 4 * m;                 // slot t is output column j4 - 1 + t
-    const int32_t i_hi = (r + P) >> 1;
-    float gy[MR][6];
-    uint32_t code[MR][6];
-    int32_t row_code[MR];                     // a * K for the row, or a value no stored position can match
-    const bool quad_ok = j4 + 3 < g.OW;
-#pragma unroll
-    for (int u = 0; u < MR; ++u) {
-        const int32_t i = i_hi - u;
-        const int32_t a = r + P - 2 * i;      // >= 0
-        row_code[u] = (i >= 0 && i < g.OH && a < K) ? a * K : -1000;
-        const int32_t base = min(max(i, 0), g.OH - 1) * g.OW;
-        if (quad_ok) {
-            const vec4 w = *reinterpret_cast<const vec4*>(gp + base + j4);
-            const uint32_t c = *reinterpret_cast<const uint32_t*>(ap + base + j4);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                gy[u][1 + t] = static_cast<float>(w[t]);
-                code[u][1 + t] = (c >> (8 * t)) & 0xffu;
-            }
-        } else {
-#pragma unroll
-            for (int t = 1; t < 5; ++t) {
-                const int32_t j = j4 - 1 + t;
-                gy[u][t] = static_cast<float>(gp[base + min(j, g.OW - 1)]);
-                code[u][t] = j < g.OW ? static_cast<uint32_t>(ap[base + min(j, g.OW - 1)]) : 0xffffu;
-            }
-        }
-        gy[u][0] = static_cast<float>(gp[base + max(j4 - 1, 0)]);
-        code[u][0] = j4 >= 1 ? static_cast<uint32_t>(ap[base + max(j4 - 1, 0)]) : 0xffffu;
-        gy[u][5] = static_cast<float>(gp[base + min(j4 + 4, g.OW - 1)]);
-        code[u][5] = j4 + 4 < g.OW ? static_cast<uint32_t>(ap[base + min(j4 + 4, g.OW - 1)]) : 0xffffu;
-    }
-    T out[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        float acc = 0.0f;
-#pragma unroll
-        for (int u = MR - 1; u >= 0; --u)     // ascending output row
-#pragma unroll
-            for (int t = 0; t < 6; ++t) {     // ascending output column
-                constexpr int kOffset = P + 2;
-                const int b = e + kOffset - 2 * t;   // position of input column 8m+e in the window of column j4-1+t
-                if (b < 0 || b >= K) continue;
-                acc += static_cast<int32_t>(code[u][t]) == row_code[u] + b ? gy[u][t] : 0.0f;  // + 0 changes nothing
-            }
-        out[e] = static_cast<T>(acc);
-    }
-    T* dst = grad_x + plane * g.H * g.W + r * g.W + 8 * m;
-    vec4 lo, hi;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { lo[e] = out[e]; hi[e] = out[4 + e]; }
-    __builtin_nontemporal_store(lo, reinterpret_cast<vec4*>(dst));
-    __builtin_nontemporal_store(hi, reinterpret_cast<vec4*>(dst) + 1);
-}
-
-// Backward counterpart of the streaming forward kernel, for the same geometries.  A lane owns the
-// NO = E / 2 output columns of one output row q (counted over all planes) that lie over its 16
-// bytes of input columns, and produces the two input rows 2q and 2q + 1 there: every gradient and
+// A lane owns the NO = E / 2 output columns of one output row q (counted over all planes) that lie over its
+// 16 bytes of input columns, and produces the two input rows 2q and 2q + 1 there: every gradient and
 // position is loaded once per output row that needs it, in whole cache lines, and the results
 // leave as two 128-bit stores.  With a 3x3 window input row 2q + 1 also lies in the window of
 // output row q + 1, and the lane's last column in that of the first output column of the lane to
@@ -919,55 +1007,43 @@ static bool quad_geometry(const PoolShape& p) {
     return p.kh == p.kw && (p.kh == 2 || p.kh == 3) && p.sh == p.sw && (p.sh == 1 || p.sh == 2) && p.dh == 1 && p.dw == 1;
 }
 
+// The lanes of the row kernels: `rows` rows per plane of `columns` columns that lanes of E columns must cover;
+// false if a launch cannot hold them.
+static bool row_pool(int64_t planes, int64_t rows, int64_t columns, int E, int64_t elems, RowPool* q)
+{
+    const int64_t chunks = (columns + E - 1) / E, total = planes * rows * chunks;
+    if (total >= (int64_t(1) << 31)) return false;
+    q->chunks = static_cast<uint32_t>(chunks);
+    q->by_chunks = make_fastdiv(q->chunks);
+    q->by_rows = make_fastdiv(static_cast<uint32_t>(rows));
+    q->rows = static_cast<uint32_t>(rows);
+    q->total = static_cast<uint32_t>(total);
+    q->elems = elems;
+    return true;
+}
+
+static bool row_geometry(const PoolShape& p)
+{
+    if (p.kh != p.kw || p.sh != p.sw || p.ph != p.pw || p.dh != 1 || p.dw != 1) return false;
+    return p.sh == 2 ? (p.kh == 3 && p.ph <= 1) || (p.kh == 2 && p.ph == 0) : p.sh == 1 && p.kh == 3 && p.ph == 1;
+}
+
 template <typename T>
 static void maxpool_forward_typed(const T* x, int64_t planes, const PoolShape& p, T* y, uint8_t* argmax, hipStream_t s)
 {
     dim3 grid;
-    const bool pair_geometry = p.kh == p.kw && (p.kh == 2 || p.kh == 3) && p.sh == 2 && p.sw == 2 && p.dh == 1 &&
-                               p.dw == 1 && p.pw <= 1 && p.W % 4 == 0 && p.OW % 2 == 0 && aligned_to(x, 4 * sizeof(T)) &&
-                               aligned_to(y, 2 * sizeof(T)) && aligned_to(argmax, 2);
-    // all window columns of four outputs lie inside [8m - 1, 8m + 7]: K = 3 with P = 1, or K = 2 with P = 0
-    const bool four_geometry = pair_geometry && p.ph == p.pw && p.W % 8 == 0 && p.OW % 4 == 0 && 2 * p.OW == p.W &&
-                               ((p.kh == 3 && p.pw == 1) || (p.kh == 2 && p.pw == 0)) &&
-                               aligned_to(y, 4 * sizeof(T)) && aligned_to(argmax, 4);
-    // the flattened streaming path: even extents, whole 16-byte chunks per row, fewer than 2^31 lanes
     constexpr int kE = 16 / static_cast<int>(sizeof(T));
-    constexpr int kStreamRows = 1;
-    const bool stream_geometry = four_geometry && 2 * p.OH == p.H && p.W % kE == 0 && p.OH % kStreamRows == 0 &&
-                                 aligned_to(x, 16) &&
-                                 planes * (p.OH / kStreamRows) * (p.W / kE) < (int64_t(1) << 31);
-    if (stream_geometry) {
-        StreamPool q;
-        q.chunks_per_row = static_cast<uint32_t>(p.W / kE);
-        q.by_chunks = make_fastdiv(q.chunks_per_row);
-        q.rows_per_plane = static_cast<uint32_t>(p.OH / kStreamRows);
-        q.by_rows = make_fastdiv(q.rows_per_plane);
-        q.total = static_cast<uint32_t>(planes * q.rows_per_plane * q.chunks_per_row);
+    RowPool rows;
+    // the columns that lanes must hold: those over the outputs, and with K = 3 and no padding one more
+    const int64_t columns = static_cast<int64_t>(p.sw) * p.OW + (p.kh == 3 && p.ph == 0 ? 1 : 0);
+    if (row_geometry(p) && row_pool(planes, p.OH, columns, kE, planes * p.H * p.W, &rows)) {
         dim3 unused;
         const Pool g = make_pool(p, planes, 1, &unused);
-        const unsigned blocks = (q.total + kPoolFwdBlock - 1) / kPoolFwdBlock;
-        if (p.kh == 3) maxpool2d_forward_stream_kernel<T, 3, 1, kStreamRows><<<blocks, kPoolFwdBlock, 0, s>>>(x, g, q, y, argmax);
-        else maxpool2d_forward_stream_kernel<T, 2, 0, kStreamRows><<<blocks, kPoolFwdBlock, 0, s>>>(x, g, q, y, argmax);
-        return;
-    }
-    if (four_geometry) {
-        QuadGeometry q;
-        q.quads_per_row = p.OW / 4;
-        q.by_quads = make_fastdiv(static_cast<uint32_t>(q.quads_per_row));
-        q.vector_ok = 1;
-        const Pool g = make_pool(p, planes, static_cast<int64_t>(p.OH) * q.quads_per_row, &grid);
-        if (p.kh == 3) maxpool2d_forward_four_kernel<T, 3, 1><<<grid, kBlock, 0, s>>>(x, planes, g, q, y, argmax);
-        else maxpool2d_forward_four_kernel<T, 2, 0><<<grid, kBlock, 0, s>>>(x, planes, g, q, y, argmax);
-        return;
-    }
-    if (pair_geometry) {
-        QuadGeometry q;
-        q.quads_per_row = p.OW / 2;   // pairs of outputs per row
-        q.by_quads = make_fastdiv(static_cast<uint32_t>(q.quads_per_row));
-        q.vector_ok = 1;
-        const Pool g = make_pool(p, planes, static_cast<int64_t>(p.OH) * q.quads_per_row, &grid);
-        if (p.kh == 3) maxpool2d_forward_pair_kernel<T, 3><<<grid, kBlock, 0, s>>>(x, planes, g, q, y, argmax);
-        else maxpool2d_forward_pair_kernel<T, 2><<<grid, kBlock, 0, s>>>(x, planes, g, q, y, argmax);
+        const unsigned blocks = (rows.total + kBlock - 1) / kBlock;
+        if (p.sh == 1) maxpool2d_forward_rows_kernel<T, 3, 1, 1><<<blocks, kBlock, 0, s>>>(x, g, rows, y, argmax);
+        else if (p.kh == 2) maxpool2d_forward_rows_kernel<T, 2, 0, 2><<<blocks, kBlock, 0, s>>>(x, g, rows, y, argmax);
+        else if (p.ph == 1) maxpool2d_forward_rows_kernel<T, 3, 1, 2><<<blocks, kBlock, 0, s>>>(x, g, rows, y, argmax);
+        else maxpool2d_forward_rows_kernel<T, 3, 0, 2><<<blocks, kBlock, 0, s>>>(x, g, rows, y, argmax);
         return;
     }
     const Pool g = make_pool(p, planes, static_cast<int64_t>(p.OH) * p.OW, &grid);
@@ -981,14 +1057,10 @@ static void maxpool_backward_typed(const uint8_t* argmax, const T* grad_y, int64
                                    T* grad_x, hipStream_t s)
 {
     dim3 grid;
-    const bool oct_geometry = p.kh == p.kw && (p.kh == 2 || p.kh == 3) && p.sh == 2 && p.sw == 2 && p.dh == 1 &&
-                              p.dw == 1 && p.ph <= 1 && p.pw <= 1 && p.ph == p.pw && p.W % 8 == 0 && p.OW % 4 == 0 &&
-                              aligned_to(grad_x, 4 * sizeof(T)) && aligned_to(grad_y, 4 * sizeof(T)) &&
-                              aligned_to(argmax, 4);
     constexpr int kE = 16 / static_cast<int>(sizeof(T));
-    const bool stream_geometry = oct_geometry && 2 * p.OH == p.H && 2 * p.OW == p.W && p.W % kE == 0 &&
-                                 ((p.kh == 3 && p.pw == 1) || (p.kh == 2 && p.pw == 0)) && aligned_to(grad_x, 16) &&
-                                 aligned_to(grad_y, 8) && planes * p.OH * (p.W / kE) < (int64_t(1) << 31);
+    const bool stream_geometry = sizeof(T) == 4 && row_geometry(p) && p.sh == 2 && 2 * p.OH == p.H && 2 * p.OW == p.W && p.W % 8 == 0 &&
+                                 aligned_to(grad_x, 16) && aligned_to(grad_y, 16) && aligned_to(argmax, 4) &&
+                                 planes * p.OH * (p.W / kE) < (int64_t(1) << 31);
     if (stream_geometry) {
         StreamPool q;
         q.chunks_per_row = static_cast<uint32_t>(p.W / kE);
@@ -1003,18 +1075,30 @@ static void maxpool_backward_typed(const uint8_t* argmax, const T* grad_y, int64
         else maxpool2d_backward_stream_kernel<T, 2, 0><<<blocks, kPoolBwdBlock, 0, s>>>(argmax, grad_y, g, q, grad_x);
         return;
     }
-    if (oct_geometry) {
-        QuadGeometry q;
-        q.quads_per_row = p.W / 8;   // octets of inputs per row
-        q.by_quads = make_fastdiv(static_cast<uint32_t>(q.quads_per_row));
-        q.vector_ok = 1;
-        const Pool g = make_pool(p, planes, static_cast<int64_t>(p.H) * q.quads_per_row, &grid);
-#define ACTQ_POOL_OCT(K, P) maxpool2d_backward_oct_kernel<T, K, P><<<grid, kBlock, 0, s>>>(argmax, grad_y, planes, g, q, grad_x)
-        if (p.kh == 3 && p.pw == 1) ACTQ_POOL_OCT(3, 1);
-        else if (p.kh == 3) ACTQ_POOL_OCT(3, 0);
-        else if (p.pw == 1) ACTQ_POOL_OCT(2, 1);
-        else ACTQ_POOL_OCT(2, 0);
-#undef ACTQ_POOL_OCT
+    // Binary32, no overlap between the windows, aligned rows, planes that fill the blocks of a grid over planes: four
+    // inputs of one row per lane stay faster (44 against 49 us on [4096, 112, 116]; small planes: 73 against 53 us on
+    // [65536, 28, 28]).
+    const bool quad_rows = sizeof(T) == 4 && p.kh == 2 && p.sh == 2 && p.W % 4 == 0 && aligned_to(grad_x, 16) &&
+                           static_cast<int64_t>(p.H) * p.W >= 8192;
+    RowPool rows;
+    if (row_geometry(p) && !quad_rows && row_pool(planes, (static_cast<int64_t>(p.H) + p.sh - 1) / p.sh, p.W, kE, planes * p.OH * p.OW, &rows)) {
+        dim3 unused;
+        const Pool g = make_pool(p, planes, 1, &unused);
+        const unsigned blocks = (rows.total + kBlock - 1) / kBlock;
+        // Binary32 rows of odd alignment and a result that outgrows the caches (128 MiB of the 256): non-temporal stores
+        // (61 -> 48 us on [4096, 113, 113], 72 -> 54 us on [16384, 57, 57]; smaller results and aligned rows lose by them: 24
+        // against 28 us on [8192, 57, 57], 60 against 100 us on [65536, 28, 28]; binary16 loses 2 to 10 %).
+        const bool nt = sizeof(T) == 4 && p.W % 4 != 0 && planes * p.H * p.W >= (int64_t(128) << 18);
+#define ACTQ_POOL_ROWS(K, P, S)                                                                                              \
+    do {                                                                                                                    \
+        if (nt) maxpool2d_backward_rows_kernel<T, K, P, S, sizeof(T) == 4><<<blocks, kBlock, 0, s>>>(argmax, grad_y, g, rows, grad_x);  \
+        else maxpool2d_backward_rows_kernel<T, K, P, S, false><<<blocks, kBlock, 0, s>>>(argmax, grad_y, g, rows, grad_x);   \
+    } while (0)
+        if (p.sh == 1) ACTQ_POOL_ROWS(3, 1, 1);
+        else if (p.kh == 2) ACTQ_POOL_ROWS(2, 0, 2);
+        else if (p.ph == 1) ACTQ_POOL_ROWS(3, 1, 2);
+        else ACTQ_POOL_ROWS(3, 0, 2);
+#undef ACTQ_POOL_ROWS
         return;
     }
     if (quad_geometry(p)) {

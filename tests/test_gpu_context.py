@@ -131,6 +131,54 @@ def _pool_round_trip(x_np, g_np, H, W, k, s, p, d):
     assert _bits_equal(gx.cpu().numpy(), want)
 
 
+# rows of every remainder of a lane's 4 or 8 columns and 2, 4 or 8 outputs, odd and even extents, one-row and one-column
+# images, wavefronts that end in the middle of a row, several planes per wavefront, the tensor's last wavefront
+ROW_SHAPES = [((3,), 1, 1), ((5,), 1, 9), ((4,), 9, 1), ((2,), 3, 3), ((7,), 5, 6), ((3,), 8, 7), ((2, 3), 17, 8), ((3,), 16, 9), ((3,), 6, 10),
+              ((2,), 7, 11), ((3,), 4, 12), ((2,), 9, 13), ((2,), 10, 14), ((3,), 11, 15), ((3,), 12, 17), ((1,), 57, 57), ((3,), 33, 131),
+              ((2,), 5, 515), ((130,), 7, 7)]
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+@pytest.mark.parametrize("k,s,p", [(3, 2, 1), (3, 2, 0), (2, 2, 0), (3, 1, 1)])
+@pytest.mark.parametrize("shape", ROW_SHAPES)
+def test_maxpool_rows_of_any_extent(shape, k, s, p, dtype):
+    lead, H, W = shape
+    if H + 2 * p < k or W + 2 * p < k:
+        pytest.skip("the window does not fit")
+    rng = np.random.default_rng(H * 1000 + W)
+    # few values: many ties, which the first of a window wins, also at the padded edges; the lowest values there are
+    x = rng.integers(-3, 3, lead + (H, W)).astype(dtype)
+    x[rng.random(x.shape) < 0.1] = np.finfo(dtype).min
+    x[rng.random(x.shape) < 0.1] = -0.0
+    x[rng.random(x.shape) < 0.1] = np.finfo(dtype).smallest_subnormal
+    OH, OW = (H + 2 * p - k) // s + 1, (W + 2 * p - k) // s + 1
+    g = rng.standard_normal(lead + (OH, OW)).astype(dtype)
+    _pool_round_trip(x, g, H, W, (k, k), (s, s), (p, p), (1, 1))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("shape,k,s,p", [((2, 57, 57), 3, 2, 1), ((3, 30, 31), 3, 2, 0), ((2, 28, 27), 2, 2, 0), ((2, 19, 21), 3, 1, 1),
+                                         ((2, 16, 16), 3, 2, 1), ((2, 16, 24), 2, 2, 0)])
+def test_maxpool_at_any_element_address(shape, k, s, p, dtype):
+    """Tensors, positions and gradients that start one element (one byte) past an aligned address give what aligned ones give."""
+    def shifted(t):
+        buf = torch.full((t.numel() + 9,), 7, dtype=t.dtype, device="cuda:0")
+        buf[1:1 + t.numel()] = t.reshape(-1)
+        return buf, buf[1:1 + t.numel()].view(t.shape)
+    x = torch.randn(shape, device="cuda:0").to(dtype)
+    y, arg = B.maxpool2d_forward(x, (k, k), (s, s), (p, p))
+    g = torch.randn(y.shape, device="cuda:0").to(dtype)
+    gx = B.maxpool2d_backward(arg, g, shape[-2], shape[-1], (k, k), (s, s), (p, p))
+    ybuf, y1 = shifted(torch.zeros_like(y))
+    abuf, a1 = shifted(torch.zeros_like(arg))
+    gbuf, gx1 = shifted(torch.zeros_like(x))
+    B.maxpool2d_forward(shifted(x)[1], (k, k), (s, s), (p, p), (1, 1), y1, a1)
+    B.maxpool2d_backward(a1, shifted(g)[1], shape[-2], shape[-1], (k, k), (s, s), (p, p), (1, 1), gx1)
+    assert torch.equal(y1, y) and torch.equal(a1, arg) and torch.equal(gx1, gx)
+    for buf in (ybuf, abuf, gbuf):
+        assert buf[0] == 7 and (buf[-8:] == 7).all()
+
+
 @pytest.mark.parametrize("dtype", [np.float32, np.float16])
 @pytest.mark.parametrize("cfg", CONFIGS)
 def test_maxpool_configs(cfg, dtype):
