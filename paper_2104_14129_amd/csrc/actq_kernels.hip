@@ -1170,10 +1170,13 @@ struct MultiItem {
     uint32_t total_tiles;     // N * tiles
 };
 
+// The table travels by value in the kernel arguments; a table of one (most calls) is a launch of its own
+// kind, because 40 items are 3.2 kB of arguments, 0.5 us of the 4 us that a launch costs the host.
+template <int CAPACITY>
 struct MultiTable {
     uint32_t count;
     uint32_t first_sample;    // index of the launch's first sample in the noise counter
-    MultiItem item[kMaxMulti];
+    MultiItem item[CAPACITY];
 };
 
 // Linear work index of wavefront `wave` of block `bx`.  Blocks are handed to the eight XCDs in
@@ -1223,10 +1226,10 @@ __device__ __forceinline__ P* device_pointer(uintptr_t a)
 }
 
 // False: the wavefront has no work.  XCD_MAP: the order of wave_unit.
-template <int WAVES_PER_BLOCK, int XCD_MAP, int RUN = 1>
-__device__ __forceinline__ bool multi_cursor(const MultiTable& t, uint32_t wave, MultiCursor& c)
+template <int WAVES_PER_BLOCK, int XCD_MAP, int RUN, int CAPACITY>
+__device__ __forceinline__ bool multi_cursor(const MultiTable<CAPACITY>& t, uint32_t wave, MultiCursor& c)
 {
-    const MultiItem& it = t.item[blockIdx.y];
+    const MultiItem& it = t.item[CAPACITY == 1 ? 0 : blockIdx.y];
     const uint32_t lin = wave_unit<WAVES_PER_BLOCK, XCD_MAP, RUN>(blockIdx.x, wave);
     // tiles: low word the runs per sample, high word all runs of the tensor
     uint64_t tiles = (static_cast<uint64_t>(it.total_tiles) << 32) | it.tiles;
@@ -1257,13 +1260,13 @@ __device__ __forceinline__ void sample_width_offset(const MultiCursor& c, uint32
 
 
 // Sec. 4.1: Z = min, R = max - min per group; one tile of four groups per wavefront.
-template <typename T, bool RAGGED>
-__global__ __launch_bounds__(kGsBlock) void group_stats_multi_kernel(MultiTable t)
+template <typename T, bool RAGGED, int CAPACITY>
+__global__ __launch_bounds__(kGsBlock) void group_stats_multi_kernel(MultiTable<CAPACITY> t)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
     MultiCursor c;
-    if (!multi_cursor<kGsBlock / kWave, kGsXcdMap, kGsRun>(t, wave, c)) return;
+    if (!multi_cursor<kGsBlock / kWave, kGsXcdMap, kGsRun, CAPACITY>(t, wave, c)) return;
     const uint32_t ng = static_cast<uint32_t>((c.D + (kGroup - 1)) >> 8);
     const uint32_t g0 = c.tile * kTileGroups;
     const T* tile = device_pointer<const T>(c.x) + (static_cast<int64_t>(c.n) * static_cast<int64_t>(c.D) + (static_cast<int64_t>(g0) << 8));
@@ -1293,7 +1296,8 @@ __global__ __launch_bounds__(kGsBlock) void group_stats_multi_kernel(MultiTable 
     }
 }
 
-__device__ __forceinline__ QuantizeArgs quantize_args(const MultiTable& t, const MultiCursor& c, uint32_t k0, uint32_t k1, uint64_t tag,
+template <int CAPACITY>
+__device__ __forceinline__ QuantizeArgs quantize_args(const MultiTable<CAPACITY>& t, const MultiCursor& c, uint32_t k0, uint32_t k1, uint64_t tag,
                                                       uint8_t* packed, uint64_t capacity)
 {
     const uint64_t tensor_tag = tag + blockIdx.y;  // every tensor of the launch draws its own noise
@@ -1313,30 +1317,30 @@ __device__ __forceinline__ QuantizeArgs quantize_args(const MultiTable& t, const
 
 // Runs of kQpGroupsF16 groups (the table is built for runs of that length).  Eight wavefronts per SIMD
 // are asked for: the kernel lives on other wavefronts' issue slots while one waits for its loads.
-template <int HDR, bool RAGGED>
+template <int HDR, bool RAGGED, int CAPACITY>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void quantize_pack_run_kernel(
-    MultiTable t, uint32_t k0, uint32_t k1, uint64_t tag, uint8_t* __restrict__ packed, uint64_t capacity)
+    MultiTable<CAPACITY> t, uint32_t k0, uint32_t k1, uint64_t tag, uint8_t* __restrict__ packed, uint64_t capacity)
 {
     __shared__ u32x4 stage_all[kWavesPerBlock][kQpStageSlots];
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
     MultiCursor c;
-    if (!multi_cursor<kWavesPerBlock, kQpXcdMap, kQpRun>(t, wave, c)) return;
+    if (!multi_cursor<kWavesPerBlock, kQpXcdMap, kQpRun, CAPACITY>(t, wave, c)) return;
     quantize_run_f16<HDR, RAGGED>(device_pointer<const _Float16>(c.x) + static_cast<int64_t>(c.n) * static_cast<int64_t>(c.D), c.n,
                                   c.tile * kQpGroupsF16, c.D, static_cast<uint32_t>((c.D + (kGroup - 1)) >> 8), lane,
                                   quantize_args(t, c, k0, k1, tag, packed, capacity), stage_all[wave]);
 }
 
 // One tile of four groups per wavefront.
-template <typename T, int NOISE_BITS, int HDR, bool RAGGED>
+template <typename T, int NOISE_BITS, int HDR, bool RAGGED, int CAPACITY>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void quantize_pack_tile_kernel(
-    MultiTable t, uint32_t k0, uint32_t k1, uint64_t tag, uint8_t* __restrict__ packed, uint64_t capacity)
+    MultiTable<CAPACITY> t, uint32_t k0, uint32_t k1, uint64_t tag, uint8_t* __restrict__ packed, uint64_t capacity)
 {
     __shared__ u32x4 stage_all[kWavesPerBlock][kQpStageSlots];
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
     MultiCursor c;
-    if (!multi_cursor<kWavesPerBlock, kQpXcdMap, kQpRun>(t, wave, c)) return;
+    if (!multi_cursor<kWavesPerBlock, kQpXcdMap, kQpRun, CAPACITY>(t, wave, c)) return;
     quantize_tile<T, NOISE_BITS, HDR, RAGGED>(device_pointer<const T>(c.x) + static_cast<int64_t>(c.n) * static_cast<int64_t>(c.D), c.n,
                                               c.tile * kTileGroups, c.D, static_cast<uint32_t>((c.D + (kGroup - 1)) >> 8), lane,
                                               quantize_args(t, c, k0, k1, tag, packed, capacity), stage_all[wave]);
@@ -1347,8 +1351,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) 
 // a line meet in an L2.  Binary32, [256, 501860] at B = 2: 120 us with the order and the non-temporal stores of
 // whole groups, 118 with the runs, 110 with cached stores, 100 with both; whole lines ([256, 51744]): 13.0 us,
 // 12.3 with the runs, 13.1 with both.
-template <typename T, int HDR, int NG, int LAYOUT>
-__global__ __launch_bounds__(kDqBlock) void unpack_dequantize_multi_kernel(MultiTable t, const uint8_t* __restrict__ packed,
+template <typename T, int HDR, int NG, int LAYOUT, int CAPACITY>
+__global__ __launch_bounds__(kDqBlock) void unpack_dequantize_multi_kernel(MultiTable<CAPACITY> t, const uint8_t* __restrict__ packed,
                                                                            uint64_t capacity)
 {
     constexpr bool kRun = LAYOUT != kWholeGroups;
@@ -1357,7 +1361,7 @@ __global__ __launch_bounds__(kDqBlock) void unpack_dequantize_multi_kernel(Multi
     const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
     uint32_t* stage = stage_all[sizeof(T) == 4 ? wave : 0];
     MultiCursor c;
-    if (!multi_cursor<kDqBlock / kWave, kRun ? 0 : kDqXcdMap, kRun ? kDqRaggedRun : 1>(t, wave, c)) return;
+    if (!multi_cursor<kDqBlock / kWave, kRun ? 0 : kDqXcdMap, kRun ? kDqRaggedRun : 1, CAPACITY>(t, wave, c)) return;
     uint32_t b;
     uint64_t off;
     sample_width_offset(c, b, off);
@@ -2435,8 +2439,9 @@ static int quantize_groups_per_wave(int dtype, int noise_bits, int hdr)
     return quantize_by_runs(dtype, noise_bits, hdr) ? kQpGroupsF16 : kTileGroups;
 }
 
+template <int CAPACITY>
 static int make_multi_table(const char* who, const actq_tensor* tensors, int32_t count, int64_t N, int64_t first_sample,
-                            MultiTable* t, dim3* grid, int groups_per_wave, int waves_per_block, int run)
+                            MultiTable<CAPACITY>* t, dim3* grid, int groups_per_wave, int waves_per_block, int run)
 {
     t->count = static_cast<uint32_t>(count);
     t->first_sample = static_cast<uint32_t>(first_sample);
@@ -2467,18 +2472,22 @@ static int make_multi_table(const char* who, const actq_tensor* tensors, int32_t
     return ACTQ_OK;
 }
 
+// Launches with a table of CAPACITY items; ragged samples come as single tensors only.
+template <int CAPACITY>
 static int group_stats_launch(const char* who, const actq_tensor* tensors, int32_t count, int dtype, int64_t N, bool ragged, hipStream_t s)
 {
-    MultiTable t;
+    MultiTable<CAPACITY> t;
     dim3 grid;
     if (int rc = make_multi_table(who, tensors, count, N, 0, &t, &grid, kTileGroups, kGsBlock / kWave, kGsRun)) return rc;
-    if (dtype == ACTQ_F32) {
-        if (ragged) group_stats_multi_kernel<float, true><<<grid, kGsBlock, 0, s>>>(t);
-        else group_stats_multi_kernel<float, false><<<grid, kGsBlock, 0, s>>>(t);
-    } else {
-        if (ragged) group_stats_multi_kernel<_Float16, true><<<grid, kGsBlock, 0, s>>>(t);
-        else group_stats_multi_kernel<_Float16, false><<<grid, kGsBlock, 0, s>>>(t);
+    if constexpr (CAPACITY == 1) {
+        if (ragged) {
+            if (dtype == ACTQ_F32) group_stats_multi_kernel<float, true, 1><<<grid, kGsBlock, 0, s>>>(t);
+            else group_stats_multi_kernel<_Float16, true, 1><<<grid, kGsBlock, 0, s>>>(t);
+            return check_launch(who);
+        }
     }
+    if (dtype == ACTQ_F32) group_stats_multi_kernel<float, false, CAPACITY><<<grid, kGsBlock, 0, s>>>(t);
+    else group_stats_multi_kernel<_Float16, false, CAPACITY><<<grid, kGsBlock, 0, s>>>(t);
     return check_launch(who);
 }
 
@@ -2489,26 +2498,37 @@ struct QuantizeCall {
     uint64_t capacity;
 };
 
-template <typename T, int NOISE_BITS, int HDR>
-static void quantize_tile_launch(bool ragged, const MultiTable& t, dim3 grid, const QuantizeCall& c, hipStream_t s)
+template <typename T, int NOISE_BITS, int HDR, int CAPACITY>
+static void quantize_tile_launch(bool ragged, const MultiTable<CAPACITY>& t, dim3 grid, const QuantizeCall& c, hipStream_t s)
 {
     const uint32_t k0 = static_cast<uint32_t>(c.seed), k1 = static_cast<uint32_t>(c.seed >> 32);
-    if (ragged) quantize_pack_tile_kernel<T, NOISE_BITS, HDR, true><<<grid, kBlock, 0, s>>>(t, k0, k1, c.tag, c.packed, c.capacity);
-    else quantize_pack_tile_kernel<T, NOISE_BITS, HDR, false><<<grid, kBlock, 0, s>>>(t, k0, k1, c.tag, c.packed, c.capacity);
+    if constexpr (CAPACITY == 1) {
+        if (ragged) {
+            quantize_pack_tile_kernel<T, NOISE_BITS, HDR, true, 1><<<grid, kBlock, 0, s>>>(t, k0, k1, c.tag, c.packed, c.capacity);
+            return;
+        }
+    }
+    quantize_pack_tile_kernel<T, NOISE_BITS, HDR, false, CAPACITY><<<grid, kBlock, 0, s>>>(t, k0, k1, c.tag, c.packed, c.capacity);
 }
 
-template <int HDR>
-static void quantize_run_launch(bool ragged, const MultiTable& t, dim3 grid, const QuantizeCall& c, hipStream_t s)
+template <int HDR, int CAPACITY>
+static void quantize_run_launch(bool ragged, const MultiTable<CAPACITY>& t, dim3 grid, const QuantizeCall& c, hipStream_t s)
 {
     const uint32_t k0 = static_cast<uint32_t>(c.seed), k1 = static_cast<uint32_t>(c.seed >> 32);
-    if (ragged) quantize_pack_run_kernel<HDR, true><<<grid, kBlock, 0, s>>>(t, k0, k1, c.tag, c.packed, c.capacity);
-    else quantize_pack_run_kernel<HDR, false><<<grid, kBlock, 0, s>>>(t, k0, k1, c.tag, c.packed, c.capacity);
+    if constexpr (CAPACITY == 1) {
+        if (ragged) {
+            quantize_pack_run_kernel<HDR, true, 1><<<grid, kBlock, 0, s>>>(t, k0, k1, c.tag, c.packed, c.capacity);
+            return;
+        }
+    }
+    quantize_pack_run_kernel<HDR, false, CAPACITY><<<grid, kBlock, 0, s>>>(t, k0, k1, c.tag, c.packed, c.capacity);
 }
 
+template <int CAPACITY>
 static int quantize_launch(const char* who, const actq_tensor* tensors, int32_t count, int dtype, int64_t N, int64_t first_sample,
                            bool ragged, const QuantizeCall& c, hipStream_t s)
 {
-    MultiTable t;
+    MultiTable<CAPACITY> t;
     dim3 grid;
     const int per_wave = quantize_groups_per_wave(dtype, c.noise_bits, c.hdr);
     if (int rc = make_multi_table(who, tensors, count, N, first_sample, &t, &grid, per_wave, kWavesPerBlock, kQpRun)) return rc;
@@ -2534,19 +2554,27 @@ static int quantize_launch(const char* who, const actq_tensor* tensors, int32_t 
     return check_launch(who);
 }
 
-template <typename T, int NG, int HDR>
-static void dequantize_typed_launch(int layout, const MultiTable& t, dim3 grid, const uint8_t* pk, uint64_t capacity, hipStream_t s)
+template <typename T, int NG, int HDR, int CAPACITY>
+static void dequantize_typed_launch(int layout, const MultiTable<CAPACITY>& t, dim3 grid, const uint8_t* pk, uint64_t capacity, hipStream_t s)
 {
-    if (layout == kWholeGroups) unpack_dequantize_multi_kernel<T, HDR, NG, kWholeGroups><<<grid, kDqBlock, 0, s>>>(t, pk, capacity);
-    else if (layout == kRaggedLines) unpack_dequantize_multi_kernel<T, HDR, NG, kRaggedLines><<<grid, kDqBlock, 0, s>>>(t, pk, capacity);
-    else unpack_dequantize_multi_kernel<T, HDR, NG, kRagged><<<grid, kDqBlock, 0, s>>>(t, pk, capacity);
+    if constexpr (CAPACITY == 1) {
+        if (layout == kRaggedLines) {
+            unpack_dequantize_multi_kernel<T, HDR, NG, kRaggedLines, 1><<<grid, kDqBlock, 0, s>>>(t, pk, capacity);
+            return;
+        }
+        if (layout == kRagged) {
+            unpack_dequantize_multi_kernel<T, HDR, NG, kRagged, 1><<<grid, kDqBlock, 0, s>>>(t, pk, capacity);
+            return;
+        }
+    }
+    unpack_dequantize_multi_kernel<T, HDR, NG, kWholeGroups, CAPACITY><<<grid, kDqBlock, 0, s>>>(t, pk, capacity);
 }
 
-template <typename T, int NG>
+template <typename T, int NG, int CAPACITY>
 static int dequantize_launch(const char* who, const actq_tensor* tensors, int32_t count, const void* packed, uint64_t capacity, int hdr,
                              int64_t N, int layout, hipStream_t s)
 {
-    MultiTable t;
+    MultiTable<CAPACITY> t;
     dim3 grid;
     const int run = layout == kWholeGroups ? 1 : kDqRaggedRun;
     if (int rc = make_multi_table(who, tensors, count, N, 0, &t, &grid, NG, kDqBlock / kWave, run)) return rc;
@@ -2590,7 +2618,7 @@ int launch_group_stats(const void* x, int dtype, int64_t N, int64_t D, float* gm
         one.gmin = gmin + n0 * ng;
         one.grange = grange + n0 * ng;
         one.D = D;
-        return group_stats_launch("actq_group_stats", &one, 1, dtype, count, D % kGroup != 0, static_cast<hipStream_t>(stream));
+        return group_stats_launch<1>("actq_group_stats", &one, 1, dtype, count, D % kGroup != 0, static_cast<hipStream_t>(stream));
     });
 }
 
@@ -2607,7 +2635,7 @@ int launch_quantize_pack(const void* x, int dtype, int64_t N, int64_t D, const u
         one.bits = bits + n0;
         one.offsets = offsets + n0;
         one.D = D;
-        return quantize_launch("actq_quantize_pack", &one, 1, dtype, count, n0, D % kGroup != 0, call, static_cast<hipStream_t>(stream));
+        return quantize_launch<1>("actq_quantize_pack", &one, 1, dtype, count, n0, D % kGroup != 0, call, static_cast<hipStream_t>(stream));
     });
 }
 
@@ -2626,30 +2654,44 @@ int launch_unpack_dequantize(const void* packed, uint64_t capacity, const void* 
         one.bits = bits + n0;
         one.offsets = offsets + n0;
         one.D = D;
-        if (out_dtype == ACTQ_F32) return dequantize_launch<float, kDqGroupsF32>("actq_unpack_dequantize", &one, 1, packed, capacity, hdr, count, layout, s);
-        return dequantize_launch<_Float16, kDqGroupsF16>("actq_unpack_dequantize", &one, 1, packed, capacity, hdr, count, layout, s);
+        if (out_dtype == ACTQ_F32) return dequantize_launch<float, kDqGroupsF32, 1>("actq_unpack_dequantize", &one, 1, packed, capacity, hdr, count, layout, s);
+        return dequantize_launch<_Float16, kDqGroupsF16, 1>("actq_unpack_dequantize", &one, 1, packed, capacity, hdr, count, layout, s);
     });
 }
 
 int launch_group_stats_multi(const actq_tensor* tensors, int32_t count, int dtype, int64_t N, void* stream)
 {
-    return group_stats_launch("actq_group_stats_multi", tensors, count, dtype, N, false, static_cast<hipStream_t>(stream));
+    const char* who = "actq_group_stats_multi";
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    return count == 1 ? group_stats_launch<1>(who, tensors, count, dtype, N, false, s)
+                      : group_stats_launch<kMaxMulti>(who, tensors, count, dtype, N, false, s);
 }
 
 int launch_quantize_pack_multi(const actq_tensor* tensors, int32_t count, int dtype, int64_t N, uint64_t seed,
                                uint64_t tag, int noise_bits, void* packed, uint64_t capacity, int hdr, void* stream)
 {
+    const char* who = "actq_quantize_pack_multi";
+    hipStream_t s = static_cast<hipStream_t>(stream);
     const QuantizeCall call = {seed, tag, noise_bits, hdr, static_cast<uint8_t*>(packed), capacity};
-    return quantize_launch("actq_quantize_pack_multi", tensors, count, dtype, N, 0, false, call, static_cast<hipStream_t>(stream));
+    return count == 1 ? quantize_launch<1>(who, tensors, count, dtype, N, 0, false, call, s)
+                      : quantize_launch<kMaxMulti>(who, tensors, count, dtype, N, 0, false, call, s);
+}
+
+template <int CAPACITY>
+static int dequantize_multi(const actq_tensor* tensors, int32_t count, const void* packed, uint64_t capacity, int hdr, int64_t N,
+                            int out_dtype, hipStream_t s)
+{
+    const char* who = "actq_unpack_dequantize_multi";
+    if (out_dtype == ACTQ_F32) return dequantize_launch<float, kDqGroupsF32, CAPACITY>(who, tensors, count, packed, capacity, hdr, N, kWholeGroups, s);
+    return dequantize_launch<_Float16, kDqGroupsF16, CAPACITY>(who, tensors, count, packed, capacity, hdr, N, kWholeGroups, s);
 }
 
 int launch_unpack_dequantize_multi(const actq_tensor* tensors, int32_t count, const void* packed, uint64_t capacity,
                                    int hdr, int64_t N, int out_dtype, void* stream)
 {
-    const char* who = "actq_unpack_dequantize_multi";
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (out_dtype == ACTQ_F32) return dequantize_launch<float, kDqGroupsF32>(who, tensors, count, packed, capacity, hdr, N, kWholeGroups, s);
-    return dequantize_launch<_Float16, kDqGroupsF16>(who, tensors, count, packed, capacity, hdr, N, kWholeGroups, s);
+    return count == 1 ? dequantize_multi<1>(tensors, count, packed, capacity, hdr, N, out_dtype, s)
+                      : dequantize_multi<kMaxMulti>(tensors, count, packed, capacity, hdr, N, out_dtype, s);
 }
 
 int launch_allocate_bits(const float* w, const int64_t* D_items, int64_t D, int64_t M, int64_t budget_bits,

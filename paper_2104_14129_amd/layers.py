@@ -113,21 +113,18 @@ def compress(x: torch.Tensor, grad2: torch.Tensor | None = None) -> SavedContext
         narrowest = min(b for b in range(1, 9) if config.widths >> b & 1)
         if config.bits < narrowest:
             raise ValueError(f"an average of {config.bits} bits is below the narrowest allowed width {narrowest}")
-        gmin = torch.empty((N, ng), dtype=torch.float32, device=x.device)
-        grange = torch.empty((N, ng), dtype=torch.float32, device=x.device)
-        B.group_stats(x2, gmin, grange)
-        w = B.sample_sensitivity(grange, grad2)
         budget = int(config.bits * N * D)
-        c.bits, c.offsets, _ = B.allocate_bits_device(w, D, budget, config.widths)
         capacity = budget // 8 + N * (ng * G - D) + 32   # the budget in bytes plus the padding of ragged last groups
+        c.bits, c.offsets, c.packed, c.header = B.compress_mixed(x2, grad2, budget, config.widths, max(capacity, 32), config.seed,
+                                                                 next(_tags), config.noise_bits, c.hf)
     else:
         b = int(config.bits)
         if b != config.bits or not 1 <= b <= 8:
             raise ValueError("a fixed width must be an integer from 1 to 8")
         c.bits, c.offsets, capacity = _uniform_widths(N, D, b, x.device)
-    c.packed = torch.empty(max(capacity, 32), dtype=torch.uint8, device=x.device)
-    c.header = torch.empty(N * ng * 2, dtype=torch.int16 if c.hf == B.ACTQ_HDR_BF16 else torch.float32, device=x.device)
-    B.quantize_pack(x2, c.bits, c.offsets, c.packed, c.header, config.seed, next(_tags), config.noise_bits, hf=c.hf)
+        c.packed = torch.empty(max(capacity, 32), dtype=torch.uint8, device=x.device)
+        c.header = torch.empty(N * ng * 2, dtype=torch.int16 if c.hf == B.ACTQ_HDR_BF16 else torch.float32, device=x.device)
+        B.quantize_pack(x2, c.bits, c.offsets, c.packed, c.header, config.seed, next(_tags), config.noise_bits, hf=c.hf)
     if config.swap:
         _swap_out(c)
     return c

@@ -279,3 +279,16 @@ def test_layers_run_under_autocast():
     # 8-bit contexts of binary16-rounded activations: the gradients agree to binary16 accuracy
     for a, b in zip(*grads):
         assert torch.allclose(a, b, rtol=5e-2, atol=5e-3 * float(a.abs().max()))
+
+
+def test_calls_go_to_the_current_stream():
+    """The binding takes the stream that is current where the call is made, in any nesting of stream contexts."""
+    from paper_2104_14129_amd import binding as B
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    assert B._stream(None) == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(a):
+        assert B._stream(None) == a.cuda_stream
+        with torch.cuda.stream(b):
+            assert B._stream(None) == b.cuda_stream and B._stream(a) == a.cuda_stream
+        assert B._stream(None) == a.cuda_stream
+    assert B._stream(None) == torch.cuda.current_stream().cuda_stream
