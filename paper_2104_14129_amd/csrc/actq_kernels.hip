@@ -1174,8 +1174,8 @@ struct MultiItem {
 // kind, because 40 items are 3.2 kB of arguments, 0.5 us of the 4 us that a launch costs the host.
 template <int CAPACITY>
 struct MultiTable {
-    uint32_t count;
-    uint32_t first_sample;    // index of the launch's first sample in the noise counter
+    uint32_t first_sample;    // index of the table's first sample in the noise counter
+    uint32_t first_tile;      // of every tensor, where a launch starts
     MultiItem item[CAPACITY];
 };
 
@@ -1230,7 +1230,7 @@ template <int WAVES_PER_BLOCK, int XCD_MAP, int RUN, int CAPACITY>
 __device__ __forceinline__ bool multi_cursor(const MultiTable<CAPACITY>& t, uint32_t wave, MultiCursor& c)
 {
     const MultiItem& it = t.item[CAPACITY == 1 ? 0 : blockIdx.y];
-    const uint32_t lin = wave_unit<WAVES_PER_BLOCK, XCD_MAP, RUN>(blockIdx.x, wave);
+    const uint32_t lin = t.first_tile + wave_unit<WAVES_PER_BLOCK, XCD_MAP, RUN>(blockIdx.x, wave);
     // tiles: low word the runs per sample, high word all runs of the tensor
     uint64_t tiles = (static_cast<uint64_t>(it.total_tiles) << 32) | it.tiles;
     uint64_t div = (static_cast<uint64_t>(it.by_tiles.s) << 32) | it.by_tiles.m;
@@ -2439,19 +2439,19 @@ static int quantize_groups_per_wave(int dtype, int noise_bits, int hdr)
     return quantize_by_runs(dtype, noise_bits, hdr) ? kQpGroupsF16 : kTileGroups;
 }
 
+// Fills the table but for its first tile; `most` receives the tiles of the largest tensor.
 template <int CAPACITY>
 static int make_multi_table(const char* who, const actq_tensor* tensors, int32_t count, int64_t N, int64_t first_sample,
-                            MultiTable<CAPACITY>* t, dim3* grid, int groups_per_wave, int waves_per_block, int run)
+                            MultiTable<CAPACITY>* t, int groups_per_wave, uint64_t* most)
 {
-    t->count = static_cast<uint32_t>(count);
     t->first_sample = static_cast<uint32_t>(first_sample);
-    uint64_t most = 0;
+    *most = 0;
     for (int32_t i = 0; i < count; ++i) {
         const int64_t ng = (tensors[i].D + kGroup - 1) / kGroup;
         const uint64_t per_sample = static_cast<uint64_t>((ng + groups_per_wave - 1) / groups_per_wave);
         const uint64_t tiles = per_sample * static_cast<uint64_t>(N);
         if (tiles >= (uint64_t(1) << 31)) return fail(ACTQ_EINVAL, "%s: tensor %d has too many tiles for one launch", who, i);
-        if (tiles > most) most = tiles;
+        if (tiles > *most) *most = tiles;
         MultiItem& it = t->item[i];
         it.x = tensors[i].x;
         it.out = tensors[i].out;
@@ -2465,10 +2465,25 @@ static int make_multi_table(const char* who, const actq_tensor* tensors, int32_t
         it.tiles = static_cast<uint32_t>(per_sample);
         it.total_tiles = static_cast<uint32_t>(tiles);
     }
+    return ACTQ_OK;
+}
+
+// A launch has fewer than 2^32 lanes along x, that is 2^26 tiles; kLaunchTiles are whole runs in every order.
+constexpr uint64_t kLaunchTiles = uint64_t(1) << 25;
+
+// launch(grid, first tile) for as many launches as `most` tiles need.
+template <typename F>
+static int each_launch(const char* who, uint64_t most, int32_t count, int waves_per_block, int run, F launch)
+{
     // whole runs of 8 * run blocks (`run` blocks per XCD): every order of wave_unit covers a run exactly
     const uint64_t blocks_per_run = 8u * static_cast<uint64_t>(run);
     const uint64_t per_run = blocks_per_run * static_cast<uint64_t>(waves_per_block);
-    *grid = dim3(static_cast<unsigned>((most + per_run - 1) / per_run * blocks_per_run), static_cast<unsigned>(count));
+    for (uint64_t first = 0; first < most; first += kLaunchTiles) {
+        const uint64_t tiles = most - first < kLaunchTiles ? most - first : kLaunchTiles;
+        launch(dim3(static_cast<unsigned>((tiles + per_run - 1) / per_run * blocks_per_run), static_cast<unsigned>(count)),
+               static_cast<uint32_t>(first));
+        if (int rc = check_launch(who)) return rc;
+    }
     return ACTQ_OK;
 }
 
@@ -2477,18 +2492,20 @@ template <int CAPACITY>
 static int group_stats_launch(const char* who, const actq_tensor* tensors, int32_t count, int dtype, int64_t N, bool ragged, hipStream_t s)
 {
     MultiTable<CAPACITY> t;
-    dim3 grid;
-    if (int rc = make_multi_table(who, tensors, count, N, 0, &t, &grid, kTileGroups, kGsBlock / kWave, kGsRun)) return rc;
-    if constexpr (CAPACITY == 1) {
-        if (ragged) {
-            if (dtype == ACTQ_F32) group_stats_multi_kernel<float, true, 1><<<grid, kGsBlock, 0, s>>>(t);
-            else group_stats_multi_kernel<_Float16, true, 1><<<grid, kGsBlock, 0, s>>>(t);
-            return check_launch(who);
+    uint64_t most;
+    if (int rc = make_multi_table(who, tensors, count, N, 0, &t, kTileGroups, &most)) return rc;
+    return each_launch(who, most, count, kGsBlock / kWave, kGsRun, [&](dim3 grid, uint32_t first) {
+        t.first_tile = first;
+        if constexpr (CAPACITY == 1) {
+            if (ragged) {
+                if (dtype == ACTQ_F32) group_stats_multi_kernel<float, true, 1><<<grid, kGsBlock, 0, s>>>(t);
+                else group_stats_multi_kernel<_Float16, true, 1><<<grid, kGsBlock, 0, s>>>(t);
+                return;
+            }
         }
-    }
-    if (dtype == ACTQ_F32) group_stats_multi_kernel<float, false, CAPACITY><<<grid, kGsBlock, 0, s>>>(t);
-    else group_stats_multi_kernel<_Float16, false, CAPACITY><<<grid, kGsBlock, 0, s>>>(t);
-    return check_launch(who);
+        if (dtype == ACTQ_F32) group_stats_multi_kernel<float, false, CAPACITY><<<grid, kGsBlock, 0, s>>>(t);
+        else group_stats_multi_kernel<_Float16, false, CAPACITY><<<grid, kGsBlock, 0, s>>>(t);
+    });
 }
 
 struct QuantizeCall {
@@ -2529,29 +2546,30 @@ static int quantize_launch(const char* who, const actq_tensor* tensors, int32_t 
                            bool ragged, const QuantizeCall& c, hipStream_t s)
 {
     MultiTable<CAPACITY> t;
-    dim3 grid;
-    const int per_wave = quantize_groups_per_wave(dtype, c.noise_bits, c.hdr);
-    if (int rc = make_multi_table(who, tensors, count, N, first_sample, &t, &grid, per_wave, kWavesPerBlock, kQpRun)) return rc;
-    if (dtype == ACTQ_F32) {
-        if (c.noise_bits == 16) {
-            if (c.hdr == ACTQ_HDR_F32) quantize_tile_launch<float, 16, 0>(ragged, t, grid, c, s);
-            else if (c.hdr == ACTQ_HDR_BF16) quantize_tile_launch<float, 16, 1>(ragged, t, grid, c, s);
-            else quantize_tile_launch<float, 16, 2>(ragged, t, grid, c, s);
+    uint64_t most;
+    if (int rc = make_multi_table(who, tensors, count, N, first_sample, &t, quantize_groups_per_wave(dtype, c.noise_bits, c.hdr), &most)) return rc;
+    return each_launch(who, most, count, kWavesPerBlock, kQpRun, [&](dim3 grid, uint32_t first) {
+        t.first_tile = first;
+        if (dtype == ACTQ_F32) {
+            if (c.noise_bits == 16) {
+                if (c.hdr == ACTQ_HDR_F32) quantize_tile_launch<float, 16, 0>(ragged, t, grid, c, s);
+                else if (c.hdr == ACTQ_HDR_BF16) quantize_tile_launch<float, 16, 1>(ragged, t, grid, c, s);
+                else quantize_tile_launch<float, 16, 2>(ragged, t, grid, c, s);
+            } else {
+                if (c.hdr == ACTQ_HDR_F32) quantize_tile_launch<float, 24, 0>(ragged, t, grid, c, s);
+                else if (c.hdr == ACTQ_HDR_BF16) quantize_tile_launch<float, 24, 1>(ragged, t, grid, c, s);
+                else quantize_tile_launch<float, 24, 2>(ragged, t, grid, c, s);
+            }
+        } else if (c.noise_bits == 16) {
+            if (c.hdr == ACTQ_HDR_F32) quantize_run_launch<0>(ragged, t, grid, c, s);
+            else if (c.hdr == ACTQ_HDR_BF16) quantize_run_launch<1>(ragged, t, grid, c, s);
+            else quantize_tile_launch<_Float16, 16, 2>(ragged, t, grid, c, s);
         } else {
-            if (c.hdr == ACTQ_HDR_F32) quantize_tile_launch<float, 24, 0>(ragged, t, grid, c, s);
-            else if (c.hdr == ACTQ_HDR_BF16) quantize_tile_launch<float, 24, 1>(ragged, t, grid, c, s);
-            else quantize_tile_launch<float, 24, 2>(ragged, t, grid, c, s);
+            if (c.hdr == ACTQ_HDR_F32) quantize_tile_launch<_Float16, 24, 0>(ragged, t, grid, c, s);
+            else if (c.hdr == ACTQ_HDR_BF16) quantize_tile_launch<_Float16, 24, 1>(ragged, t, grid, c, s);
+            else quantize_tile_launch<_Float16, 24, 2>(ragged, t, grid, c, s);
         }
-    } else if (c.noise_bits == 16) {
-        if (c.hdr == ACTQ_HDR_F32) quantize_run_launch<0>(ragged, t, grid, c, s);
-        else if (c.hdr == ACTQ_HDR_BF16) quantize_run_launch<1>(ragged, t, grid, c, s);
-        else quantize_tile_launch<_Float16, 16, 2>(ragged, t, grid, c, s);
-    } else {
-        if (c.hdr == ACTQ_HDR_F32) quantize_tile_launch<_Float16, 24, 0>(ragged, t, grid, c, s);
-        else if (c.hdr == ACTQ_HDR_BF16) quantize_tile_launch<_Float16, 24, 1>(ragged, t, grid, c, s);
-        else quantize_tile_launch<_Float16, 24, 2>(ragged, t, grid, c, s);
-    }
-    return check_launch(who);
+    });
 }
 
 template <typename T, int NG, int HDR, int CAPACITY>
@@ -2575,18 +2593,19 @@ static int dequantize_launch(const char* who, const actq_tensor* tensors, int32_
                              int64_t N, int layout, hipStream_t s)
 {
     MultiTable<CAPACITY> t;
-    dim3 grid;
-    const int run = layout == kWholeGroups ? 1 : kDqRaggedRun;
-    if (int rc = make_multi_table(who, tensors, count, N, 0, &t, &grid, NG, kDqBlock / kWave, run)) return rc;
+    uint64_t most;
+    if (int rc = make_multi_table(who, tensors, count, N, 0, &t, NG, &most)) return rc;
     const uint8_t* pk = static_cast<const uint8_t*>(packed);
-    if (hdr == ACTQ_HDR_F32) dequantize_typed_launch<T, NG, 0>(layout, t, grid, pk, capacity, s);
-    else if (hdr == ACTQ_HDR_BF16) dequantize_typed_launch<T, NG, 1>(layout, t, grid, pk, capacity, s);
-    else dequantize_typed_launch<T, NG, 2>(layout, t, grid, pk, capacity, s);
-    return check_launch(who);
+    return each_launch(who, most, count, kDqBlock / kWave, layout == kWholeGroups ? 1 : kDqRaggedRun, [&](dim3 grid, uint32_t first) {
+        t.first_tile = first;
+        if (hdr == ACTQ_HDR_F32) dequantize_typed_launch<T, NG, 0>(layout, t, grid, pk, capacity, s);
+        else if (hdr == ACTQ_HDR_BF16) dequantize_typed_launch<T, NG, 1>(layout, t, grid, pk, capacity, s);
+        else dequantize_typed_launch<T, NG, 2>(layout, t, grid, pk, capacity, s);
+    });
 }
 
-// A single tensor is a table of one.  A launch holds fewer than 2^31 tiles: a tensor with more (2^31
-// samples of a group each, say) goes sample range by sample range.  f(first sample, samples) launches one.
+// A single tensor is a table of one.  A table counts fewer than 2^31 tiles per tensor: a tensor with more
+// (2^31 samples of a group each, say) goes sample range by sample range.  f(first sample, samples) is one.
 template <typename F>
 static int by_sample_ranges(int64_t N, int64_t D, int groups_per_wave, F f)
 {

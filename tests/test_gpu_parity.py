@@ -436,6 +436,28 @@ def test_ragged_samples_in_every_mode(N, D, dtype, noise_bits, hf):
             assert np.array_equal(run.dequantize(dt).view(np.uint8), want.view(np.uint8))
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+def test_more_tiles_than_one_launch_holds(dtype):
+    """2^26 + 5 samples of two elements: a tile each, 2^32 lanes, in several launches.  Values 0 and r are grid
+    points, so codes, headers and results are known whatever the noise."""
+    N = (1 << 26) + 5
+    r = 1 + (torch.arange(N, device="cuda:0") % 7).to(dtype)
+    x = torch.stack([torch.zeros_like(r), r], dim=1)
+    gmin, grange = B.group_stats(x)
+    assert not gmin.any() and torch.equal(grange.view(-1), r.float())
+    del gmin, grange
+    bits = torch.ones(N, dtype=torch.uint8, device="cuda:0")
+    offsets = torch.arange(N, device="cuda:0") * 32
+    packed = torch.full((N * 32,), 0xA5, dtype=torch.uint8, device="cuda:0")
+    header = torch.full((N * 2,), float("nan"), device="cuda:0")
+    B.quantize_pack(x, bits, offsets, packed, header, seed=3, noise_bits=16)
+    assert (packed.view(N, 32)[:, 0] == 2).all() and not packed.view(N, 32)[:, 1:].any()
+    assert not header.view(N, 2)[:, 0].any() and torch.equal(header.view(N, 2)[:, 1], r.float())
+    out = torch.full_like(x, float("nan"))
+    B.unpack_dequantize(packed, header, bits, offsets, out)
+    assert torch.equal(out, x)
+
+
 @pytest.mark.parametrize("b", [2, 3, 4, 5, 6, 7, 8])
 def test_binary16_overshoot_with_the_bfloat16_header(b):
     """A group range that bfloat16 holds exactly and whose scaled maximum lies one ulp above B, on the elements
