@@ -7,10 +7,9 @@
 //     position of the maximum inside its window.  Backward gathers, for every input
 //     location, the output gradients whose stored position points at it.
 //
-// Both are pure streaming kernels bound by HBM.  ReLU uses the same decomposition as the
-// quantizer: one wavefront per tile of four 128-bit loads per lane; the comparison masks
+// Both are pure streaming kernels bound by HBM.  In ReLU the comparison masks
 // come out of v_cmp as 64-bit wavefront masks, and a few lanes interleave them into the
-// LSB-first stream, so the bits leave as one coalesced store per tile without LDS.
+// LSB-first stream, so the bits leave as one coalesced store per wavefront without LDS.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -24,7 +23,6 @@ namespace {
 constexpr int kWave = 64;
 constexpr int kWavesPerBlock = 4;
 constexpr int kBlock = kWave * kWavesPerBlock;
-constexpr int kLoadsPerTile = 4;
 
 int launched(const char* who)
 {
@@ -34,9 +32,12 @@ int launched(const char* who)
 }
 
 // ------------------------------------------------------------------------------------
-// ReLU.  A lane owns E consecutive elements per load (E = 4 binary32 or 8 binary16 values:
-// 128 bits); a load of the wavefront covers 64*E elements = 2*E words of the bit stream.
-
+// ReLU.  A lane owns E consecutive elements (E = 4 binary32 or 8 binary16 values: 128 bits); a wavefront
+// covers 64*E elements = 2*E words of the bit stream, with one load and one store per lane.  What bounds it
+// is the mixed stream of reads and writes (6.4 TB/s of the stem's 1.67 GB); short wavefronts and a bit stream
+// that is written and read through the L2 serve it best: with four loads per lane and a non-temporal bit stream
+// ReLU and 3x3 pooling, forward and backward, took 145 instead of 139 us on binary16 [64, 64, 113, 113]
+// and 908 instead of 892 us on binary32 [256, 64, 112, 112] (one load 141 / 896, two 143 / 914).
 template <typename T>
 struct Lanes;
 
@@ -76,66 +77,43 @@ __global__ __launch_bounds__(kBlock) void relu_forward_kernel(const T* x, int64_
 {
     constexpr int E = Lanes<T>::E;
     typedef typename Lanes<T>::vec vec;
-    constexpr int kWordsPerLoad = 2 * E;           // 64 * E bits
+    constexpr int kWords = 2 * E;                  // 64 * E bits
     constexpr int kLanesPerWord = 32 / E;          // lanes whose bits share one word
-    constexpr int64_t kTileElems = int64_t(kLoadsPerTile) * kWave * E;
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t tile = static_cast<int64_t>(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6);
-    const int64_t first = tile * kTileElems;
+    const int64_t tile = (static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6);
+    const int64_t first = tile * (kWave * E), mine = first + lane * E;
     if (first >= n) return;
-    const bool full = first + kTileElems <= n;
+    const bool full = first + kWave * E <= n;
 
-    vec v[kLoadsPerTile];
+    vec v;
     if (full) {
-#pragma unroll
-        for (int u = 0; u < kLoadsPerTile; ++u)
-            v[u] = __builtin_nontemporal_load(reinterpret_cast<const vec*>(x + first + (u * kWave + lane) * E));
+        v = __builtin_nontemporal_load(reinterpret_cast<const vec*>(x + mine));
     } else {
 #pragma unroll
-        for (int u = 0; u < kLoadsPerTile; ++u)
-#pragma unroll
-            for (int k = 0; k < E; ++k) {
-                const int64_t i = first + (u * kWave + lane) * E + k;
-                v[u][k] = i < n ? x[i] : static_cast<T>(0.0f);  // past the end: bit 0, nothing stored
-            }
+        for (int k = 0; k < E; ++k) v[k] = mine + k < n ? x[mine + k] : static_cast<T>(0.0f);  // past the end: bit 0, nothing stored
     }
-
-    // m[u][k]: lane l's bit says whether element k of lane l in load u is positive
-    uint64_t m[kLoadsPerTile][E];
-#pragma unroll
-    for (int u = 0; u < kLoadsPerTile; ++u) {
-        vec out;
-#pragma unroll
-        for (int k = 0; k < E; ++k) {
-            const bool positive = static_cast<float>(v[u][k]) > 0.0f;
-            m[u][k] = __ballot(positive);
-            out[k] = positive ? v[u][k] : static_cast<T>(0.0f);
-        }
-        if (full) {
-            __builtin_nontemporal_store(out, reinterpret_cast<vec*>(y + first + (u * kWave + lane) * E));
-        } else {
-#pragma unroll
-            for (int k = 0; k < E; ++k) {
-                const int64_t i = first + (u * kWave + lane) * E + k;
-                if (i < n) y[i] = out[k];
-            }
-        }
-    }
-
-    // Word j of the tile's stream (j = lane) holds the bits of kLanesPerWord lanes of load
-    // u = j / kWordsPerLoad: stream bit E*l + k is bit l of m[u][k].
-    const int u_sel = lane / kWordsPerLoad;
-    const int first_lane = (lane % kWordsPerLoad) * kLanesPerWord;
-    uint32_t word = 0;
+    uint64_t m[E];   // lane l's bit says whether element k of lane l is positive
+    vec out;
 #pragma unroll
     for (int k = 0; k < E; ++k) {
-        uint64_t mk = m[0][k];
-#pragma unroll
-        for (int u = 1; u < kLoadsPerTile; ++u) mk = u_sel == u ? m[u][k] : mk;
-        word |= spread<E>(static_cast<uint32_t>(mk >> first_lane)) << k;
+        const bool positive = static_cast<float>(v[k]) > 0.0f;
+        m[k] = __ballot(positive);
+        out[k] = positive ? v[k] : static_cast<T>(0.0f);
     }
-    const int64_t w = tile * (kLoadsPerTile * kWordsPerLoad) + lane;
-    if (lane < kLoadsPerTile * kWordsPerLoad && w < mask_words) __builtin_nontemporal_store(word, mask + w);
+    if (full) {
+        __builtin_nontemporal_store(out, reinterpret_cast<vec*>(y + mine));
+    } else {
+#pragma unroll
+        for (int k = 0; k < E; ++k)
+            if (mine + k < n) y[mine + k] = out[k];
+    }
+
+    // Word j of the tile's stream (j = lane) holds the bits of kLanesPerWord lanes: stream bit E*l + k is bit l of m[k].
+    uint32_t word = 0;
+#pragma unroll
+    for (int k = 0; k < E; ++k) word |= spread<E>(static_cast<uint32_t>(m[k] >> (lane % kWords * kLanesPerWord))) << k;
+    const int64_t w = tile * kWords + lane;
+    if (lane < kWords && w < mask_words) mask[w] = word;
 }
 
 template <typename T>
@@ -144,47 +122,32 @@ __global__ __launch_bounds__(kBlock) void relu_backward_kernel(const uint32_t* _
 {
     constexpr int E = Lanes<T>::E;
     typedef typename Lanes<T>::vec vec;
-    constexpr int kWordsPerLoad = 2 * E;
-    constexpr int64_t kTileElems = int64_t(kLoadsPerTile) * kWave * E;
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t tile = static_cast<int64_t>(blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6);
-    const int64_t first = tile * kTileElems;
+    const int64_t tile = (static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x) * kWavesPerBlock + (threadIdx.x >> 6);
+    const int64_t first = tile * (kWave * E), mine = first + lane * E;
     if (first >= n) return;
-    const bool full = first + kTileElems <= n;
+    const bool full = first + kWave * E <= n;
 
-    vec g[kLoadsPerTile];
-    uint32_t word[kLoadsPerTile];
+    // the lane's E bits start at bit E*lane of the tile's 64*E-bit stretch
+    const int64_t w = tile * (2 * E) + (lane * E >> 5);
+    const uint32_t word = mask[w < mask_words ? w : mask_words - 1];  // past the end: any word, its elements are not stored
+    vec g;
+    if (full) {
+        g = __builtin_nontemporal_load(reinterpret_cast<const vec*>(grad_y + mine));
+    } else {
 #pragma unroll
-    for (int u = 0; u < kLoadsPerTile; ++u) {
-        // the lane's E bits start at bit E*lane of the load's 64*E-bit stretch
-        int64_t w = tile * (kLoadsPerTile * kWordsPerLoad) + u * kWordsPerLoad + (lane * E >> 5);
-        w = w < mask_words ? w : mask_words - 1;  // past the end: any word, its elements are not stored
-        word[u] = __builtin_nontemporal_load(mask + w);
-        if (full) {
-            g[u] = __builtin_nontemporal_load(reinterpret_cast<const vec*>(grad_y + first + (u * kWave + lane) * E));
-        } else {
-#pragma unroll
-            for (int k = 0; k < E; ++k) {
-                const int64_t i = first + (u * kWave + lane) * E + k;
-                g[u][k] = i < n ? grad_y[i] : static_cast<T>(0.0f);
-            }
-        }
+        for (int k = 0; k < E; ++k) g[k] = mine + k < n ? grad_y[mine + k] : static_cast<T>(0.0f);
     }
+    const uint32_t bits = word >> ((lane * E) & 31);
+    vec out;
 #pragma unroll
-    for (int u = 0; u < kLoadsPerTile; ++u) {
-        const uint32_t mine = word[u] >> ((lane * E) & 31);
-        vec out;
+    for (int k = 0; k < E; ++k) out[k] = (bits >> k) & 1u ? g[k] : static_cast<T>(0.0f);
+    if (full) {
+        __builtin_nontemporal_store(out, reinterpret_cast<vec*>(grad_x + mine));
+    } else {
 #pragma unroll
-        for (int k = 0; k < E; ++k) out[k] = (mine >> k) & 1u ? g[u][k] : static_cast<T>(0.0f);
-        if (full) {
-            __builtin_nontemporal_store(out, reinterpret_cast<vec*>(grad_x + first + (u * kWave + lane) * E));
-        } else {
-#pragma unroll
-            for (int k = 0; k < E; ++k) {
-                const int64_t i = first + (u * kWave + lane) * E + k;
-                if (i < n) grad_x[i] = out[k];
-            }
-        }
+        for (int k = 0; k < E; ++k)
+            if (mine + k < n) grad_x[mine + k] = out[k];
     }
 }
 
@@ -834,17 +797,24 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_backward_rows_kernel(const u
 
 }  // namespace
 
+// Blocks of kWavesPerBlock wavefronts that each take 64 lanes of 16 bytes, along x and then y (a grid has
+// fewer than 2^32 lanes along x).
+static dim3 relu_blocks(int64_t n, int64_t element_bytes)
+{
+    const int64_t per_block = int64_t(kBlock) * 16 / element_bytes, blocks = (n + per_block - 1) / per_block;
+    const int64_t along_x = blocks < (int64_t(1) << 22) ? blocks : int64_t(1) << 22;
+    return dim3(static_cast<unsigned>(along_x), static_cast<unsigned>((blocks + along_x - 1) / along_x));
+}
+
 int launch_relu_forward(const void* x, int dtype, int64_t n, void* y, uint8_t* mask, void* stream)
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t mask_words = (n + 255) / 256 * 8;
     if (dtype == ACTQ_F32) {
-        const int64_t tiles = (n + 1023) / 1024;
-        relu_forward_kernel<float><<<static_cast<unsigned>((tiles + kWavesPerBlock - 1) / kWavesPerBlock), kBlock, 0, s>>>(
+        relu_forward_kernel<float><<<relu_blocks(n, 4), kBlock, 0, s>>>(
             static_cast<const float*>(x), n, mask_words, static_cast<float*>(y), reinterpret_cast<uint32_t*>(mask));
     } else {
-        const int64_t tiles = (n + 2047) / 2048;
-        relu_forward_kernel<_Float16><<<static_cast<unsigned>((tiles + kWavesPerBlock - 1) / kWavesPerBlock), kBlock, 0, s>>>(
+        relu_forward_kernel<_Float16><<<relu_blocks(n, 2), kBlock, 0, s>>>(
             static_cast<const _Float16*>(x), n, mask_words, static_cast<_Float16*>(y), reinterpret_cast<uint32_t*>(mask));
     }
     return launched("actq_relu_forward");
@@ -855,12 +825,10 @@ int launch_relu_backward(const uint8_t* mask, const void* grad_y, int dtype, int
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t mask_words = (n + 255) / 256 * 8;
     if (dtype == ACTQ_F32) {
-        const int64_t tiles = (n + 1023) / 1024;
-        relu_backward_kernel<float><<<static_cast<unsigned>((tiles + kWavesPerBlock - 1) / kWavesPerBlock), kBlock, 0, s>>>(
+        relu_backward_kernel<float><<<relu_blocks(n, 4), kBlock, 0, s>>>(
             reinterpret_cast<const uint32_t*>(mask), mask_words, static_cast<const float*>(grad_y), n, static_cast<float*>(grad_x));
     } else {
-        const int64_t tiles = (n + 2047) / 2048;
-        relu_backward_kernel<_Float16><<<static_cast<unsigned>((tiles + kWavesPerBlock - 1) / kWavesPerBlock), kBlock, 0, s>>>(
+        relu_backward_kernel<_Float16><<<relu_blocks(n, 2), kBlock, 0, s>>>(
             reinterpret_cast<const uint32_t*>(mask), mask_words, static_cast<const _Float16*>(grad_y), n, static_cast<_Float16*>(grad_x));
     }
     return launched("actq_relu_backward");
