@@ -589,7 +589,8 @@ struct Carrier<_Float16, 2> {
 // clamped).  A copy to the right of or below its original never wins, because only a larger value
 // replaces the running maximum; one to the left or above wins in its original's place, and the
 // position moves to the original (which is the first of the equal values inside the image).
-template <typename T, int K, int P, int S>
+// NT: non-temporal stores.
+template <typename T, int K, int P, int S, bool NT>
 __global__ __launch_bounds__(kBlock) void maxpool2d_forward_rows_kernel(const T* __restrict__ x, Pool g, RowPool q,
                                                                         T* __restrict__ y, uint8_t* __restrict__ argmax)
 {
@@ -673,7 +674,7 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_forward_rows_kernel(const T*
     if (!live || left <= 0) return;
     const int64_t o = static_cast<int64_t>(strip) * g.OW + j0;
     if (left >= NO) {
-        if (sizeof(T) == 4) {   // non-temporal: 50 -> 46 us on [4096, 111, 120]; binary16 is 2 % slower with it
+        if (NT) {
             __builtin_nontemporal_store(out, reinterpret_cast<vec_out*>(yr + o));
             __builtin_nontemporal_store(static_cast<vec_codes>(codes), reinterpret_cast<vec_codes*>(argmax + o));
         } else {
@@ -764,6 +765,7 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_backward_rows_kernel(const u
         for (int t = 0; t < NO; ++t) code[u][1 + t] = row_ok[u] && j0 + t < g.OW ? code[u][1 + t] : kNone;
     }
     const int left = g.W - E * static_cast<int32_t>(c);   // input columns from the lane's first on, > 0
+    vec_in rows[S];   // all of them before the first store: two rows share lines, which meet if their stores are close
 #pragma unroll
     for (int rr = 0; rr < S; ++rr) {
         vec_in out;
@@ -783,6 +785,12 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_backward_rows_kernel(const u
             }
             out[e] = static_cast<T>(acc);
         }
+        if (S > 1) asm volatile("" : "+v"(out));
+        rows[rr] = out;
+    }
+#pragma unroll
+    for (int rr = 0; rr < S; ++rr) {
+        const vec_in out = rows[rr];
         const int32_t r = S * stretch + rr;
         if (!live || r >= g.H) continue;
         T* dst = grad_x + (static_cast<int64_t>(plane) * g.H + r) * g.W + static_cast<int64_t>(E) * c;
@@ -793,6 +801,60 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_backward_rows_kernel(const u
             store_first<E>(dst, out, left);
         }
     }
+}
+
+// Backward of 2x2 windows without overlap: an input lies in one window, so a lane produces 16 bytes of ONE
+// input row and a wavefront 1 KiB without gaps.  (Two rows per lane, as above, read every gradient once instead
+// of twice but write every other row of the wavefront's stretch per instruction.)
+template <typename T>
+__global__ __launch_bounds__(kBlock) void maxpool2d_backward_2x2_kernel(const uint8_t* __restrict__ argmax,
+                                                                        const T* __restrict__ grad_y, Pool g, RowPool q,
+                                                                        T* __restrict__ grad_x)
+{
+    typedef typename RowVec<T, 2>::in vec_in;
+    typedef typename RowVec<T, 2>::out vec_out;
+    typedef typename RowVec<T, 2>::codes vec_codes;
+    constexpr int E = 16 / sizeof(T), NO = E / 2;
+    constexpr uint32_t kNone = 0x100;                          // no window position
+    const uint32_t idx = blockIdx.x * kBlock + threadIdx.x;
+    if (idx >= q.total) return;
+    const uint32_t strip = fastdiv(idx, q.by_chunks);          // input row over all planes
+    const uint32_t c = idx - strip * q.chunks;
+    const uint32_t plane = fastdiv(strip, q.by_rows);
+    const int32_t r = static_cast<int32_t>(strip - plane * q.rows), i = r >> 1;
+    const int32_t j0 = NO * static_cast<int32_t>(c);
+    const int64_t at = (static_cast<int64_t>(plane) * g.OH + min(i, g.OH - 1)) * g.OW + j0;
+    float gy[NO];
+    uint32_t code[NO];
+    if (at + NO > q.elems) {
+#pragma unroll
+        for (int t = 0; t < NO; ++t) {
+            const int64_t o = min(at + t, q.elems - 1);
+            gy[t] = static_cast<float>(grad_y[o]);
+            code[t] = argmax[o];
+        }
+    } else {
+        const vec_out w = *reinterpret_cast<const vec_out*>(grad_y + at);
+        const uint64_t cw = *reinterpret_cast<const vec_codes*>(argmax + at);
+#pragma unroll
+        for (int t = 0; t < NO; ++t) {
+            gy[t] = static_cast<float>(w[t]);
+            code[t] = static_cast<uint32_t>(cw >> (8 * t)) & 0xffu;
+        }
+    }
+    const uint32_t first = 2 * (static_cast<uint32_t>(r) & 1u);   // position of the row's even columns
+    vec_in out;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const uint32_t k = i < g.OH && j0 + e / 2 < g.OW ? code[e / 2] : kNone;
+        float acc = 0.0f;
+        acc += k == first + e % 2 ? gy[e / 2] : 0.0f;
+        out[e] = static_cast<T>(acc);
+    }
+    T* dst = grad_x + static_cast<int64_t>(strip) * g.W + static_cast<int64_t>(E) * c;
+    const int left = g.W - E * static_cast<int32_t>(c);
+    if (left >= E) __builtin_nontemporal_store(out, reinterpret_cast<vec_in*>(dst));   // 24 against 35 us on binary16 [4096, 112, 112]
+    else store_first<E>(dst, out, left);
 }
 
 }  // namespace
@@ -855,10 +917,9 @@ static Pool make_pool(const PoolShape& p, int64_t planes, int64_t per_plane, dim
 
 constexpr int kPoolBwdBlock = 256;   // threads per block of the streaming backward kernel [128 .. 1024 alike]
 
-// Backward path of its own for binary32 on even extents (3x3 / stride 2 / padding 1 and 2x2 / stride 2 /
-// padding 0, H = 2 OH and W = 2 OW, rows a multiple of 16 bytes long): planes and rows flatten into one
-// index without any row or column being special but at the ends of a plane, and every load and store is
-// aligned.
+// Backward path of its own for even extents (3x3 / stride 2 / padding 1 and 2x2 / stride 2 / padding 0, H = 2 OH
+// and W = 2 OW, rows a multiple of 32 bytes long): planes and rows flatten into one index without any row or
+// column being special but at the ends of a plane, and every load and store is aligned.
 struct StreamPool {
     uint32_t chunks_per_row;   // W / E
     FastDiv by_chunks, by_rows;  // by_rows: division by OH
@@ -879,7 +940,7 @@ __device__ __forceinline__ uint32_t from_right_lane(uint32_t v)
     return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), kWaveShiftLeft1, 0xf, 0xf, false));
 }
 
-template <typename T, int K, int P>
+template <typename T, int K, int P, bool JOIN>
 __global__ __launch_bounds__(kPoolBwdBlock) void maxpool2d_backward_stream_kernel(const uint8_t* __restrict__ argmax,
                                                                            const T* __restrict__ grad_y, Pool g,
                                                                            StreamPool q, T* __restrict__ grad_x)
@@ -943,6 +1004,8 @@ __global__ __launch_bounds__(kPoolBwdBlock) void maxpool2d_backward_stream_kerne
             code[u][NO] = lane == kWave - 1 ? edge_c : code[u][NO];
         }
     }
+    vec_in rows[2];
+    T* dst = grad_x + 2 * static_cast<int64_t>(strip) * g.W + static_cast<int64_t>(E) * ch;
 #pragma unroll
     for (int rr = 0; rr < 2; ++rr) {
         vec_in out;
@@ -963,9 +1026,13 @@ __global__ __launch_bounds__(kPoolBwdBlock) void maxpool2d_backward_stream_kerne
             }
             out[e] = static_cast<T>(acc);
         }
-        if (!live) continue;
-        T* dst = grad_x + (2 * static_cast<int64_t>(strip) + rr) * g.W + static_cast<int64_t>(E) * ch;
-        __builtin_nontemporal_store(out, reinterpret_cast<vec_in*>(dst));
+        if (JOIN) asm volatile("" : "+v"(out));
+        rows[rr] = out;
+        if (!JOIN && live) __builtin_nontemporal_store(out, reinterpret_cast<vec_in*>(dst + rr * g.W));
+    }
+    if (JOIN && live) {
+        __builtin_nontemporal_store(rows[0], reinterpret_cast<vec_in*>(dst));
+        __builtin_nontemporal_store(rows[1], reinterpret_cast<vec_in*>(dst + g.W));
     }
 }
 
@@ -1008,10 +1075,19 @@ static void maxpool_forward_typed(const T* x, int64_t planes, const PoolShape& p
         dim3 unused;
         const Pool g = make_pool(p, planes, 1, &unused);
         const unsigned blocks = (rows.total + kBlock - 1) / kBlock;
-        if (p.sh == 1) maxpool2d_forward_rows_kernel<T, 3, 1, 1><<<blocks, kBlock, 0, s>>>(x, g, rows, y, argmax);
-        else if (p.kh == 2) maxpool2d_forward_rows_kernel<T, 2, 0, 2><<<blocks, kBlock, 0, s>>>(x, g, rows, y, argmax);
-        else if (p.ph == 1) maxpool2d_forward_rows_kernel<T, 3, 1, 2><<<blocks, kBlock, 0, s>>>(x, g, rows, y, argmax);
-        else maxpool2d_forward_rows_kernel<T, 3, 0, 2><<<blocks, kBlock, 0, s>>>(x, g, rows, y, argmax);
+        // Non-temporal stores: binary32 50 -> 46 us on [4096, 111, 120], binary16 2x2/2 27.9 -> 25.8 us on [4096, 112, 112], 3x3/2
+        // 54.9 -> 52.8 us on [4096, 160, 160]; binary16 rows of other lengths are up to 5 % slower with them (3x3/1 on [65536, 28, 28]
+        // 74 -> 78 us).
+#define ACTQ_POOL_ROWS(K, P, S)                                                                                       \
+    do {                                                                                                             \
+        if (sizeof(T) == 4 || p.W % 8 == 0) maxpool2d_forward_rows_kernel<T, K, P, S, true><<<blocks, kBlock, 0, s>>>(x, g, rows, y, argmax);  \
+        else maxpool2d_forward_rows_kernel<T, K, P, S, sizeof(T) == 4><<<blocks, kBlock, 0, s>>>(x, g, rows, y, argmax);  \
+    } while (0)
+        if (p.sh == 1) ACTQ_POOL_ROWS(3, 1, 1);
+        else if (p.kh == 2) ACTQ_POOL_ROWS(2, 0, 2);
+        else if (p.ph == 1) ACTQ_POOL_ROWS(3, 1, 2);
+        else ACTQ_POOL_ROWS(3, 0, 2);
+#undef ACTQ_POOL_ROWS
         return;
     }
     const Pool g = make_pool(p, planes, static_cast<int64_t>(p.OH) * p.OW, &grid);
@@ -1026,7 +1102,16 @@ static void maxpool_backward_typed(const uint8_t* argmax, const T* grad_y, int64
 {
     dim3 grid;
     constexpr int kE = 16 / static_cast<int>(sizeof(T));
-    const bool stream_geometry = sizeof(T) == 4 && row_geometry(p) && p.sh == 2 && 2 * p.OH == p.H && 2 * p.OW == p.W && p.W % 8 == 0 &&
+    const int64_t bytes = planes * p.H * p.W * static_cast<int64_t>(sizeof(T));   // of the result
+    const int64_t row_bytes = p.W * static_cast<int64_t>(sizeof(T));
+    // Even extents, rows of whole 32-byte sectors.  Binary16: 3x3 results beyond 64 MiB (smaller ones leave
+    // the row kernel's cached stores faster: 13 against 16 us on [65536, 16, 16]).  2x2: binary32 only, and only
+    // what the kernel of one row per lane below loses: results beyond 256 MiB (63 against 80 us on [8192, 96, 96], 198
+    // against 210 on [16384, 112, 112]), or beyond 128 with rows of whole 64 bytes (40 against 43 us on [1024, 224, 224]; on
+    // rows of 224 bytes, [16384, 56, 56], 60 against 43).
+    const bool stream_window = p.kh == 3 ? p.ph == 1 && (sizeof(T) == 4 || bytes > (int64_t(64) << 20))
+                                         : sizeof(T) == 4 && bytes > (int64_t(row_bytes % 64 == 0 ? 128 : 256) << 20);
+    const bool stream_geometry = row_geometry(p) && p.sh == 2 && stream_window && 2 * p.OH == p.H && 2 * p.OW == p.W && row_bytes % 32 == 0 &&
                                  aligned_to(grad_x, 16) && aligned_to(grad_y, 16) && aligned_to(argmax, 4) &&
                                  planes * p.OH * (p.W / kE) < (int64_t(1) << 31);
     if (stream_geometry) {
@@ -1039,28 +1124,44 @@ static void maxpool_backward_typed(const uint8_t* argmax, const T* grad_y, int64
         dim3 unused;
         const Pool g = make_pool(p, planes, 1, &unused);
         const unsigned blocks = (q.total + kPoolBwdBlock - 1) / kPoolBwdBlock;
-        if (p.kh == 3) maxpool2d_backward_stream_kernel<T, 3, 1><<<blocks, kPoolBwdBlock, 0, s>>>(argmax, grad_y, g, q, grad_x);
-        else maxpool2d_backward_stream_kernel<T, 2, 0><<<blocks, kPoolBwdBlock, 0, s>>>(argmax, grad_y, g, q, grad_x);
+        // Rows that end inside 64 bytes share them with the next row: both rows are computed before either is stored, so
+        // that the shared pieces meet (3x3, binary32 [16384, 56, 56] 65 -> 56 us, binary16 [4096, 112, 112] 33 -> 27 us; without
+        // shared pieces it costs: binary16 [65536, 32, 32] 39 -> 41 us).
+        if (p.kh == 2) {
+            if constexpr (sizeof(T) == 4) maxpool2d_backward_stream_kernel<T, 2, 0, false><<<blocks, kPoolBwdBlock, 0, s>>>(argmax, grad_y, g, q, grad_x);
+        } else if (row_bytes % 64 != 0) {
+            maxpool2d_backward_stream_kernel<T, 3, 1, true><<<blocks, kPoolBwdBlock, 0, s>>>(argmax, grad_y, g, q, grad_x);
+        } else {
+            maxpool2d_backward_stream_kernel<T, 3, 1, false><<<blocks, kPoolBwdBlock, 0, s>>>(argmax, grad_y, g, q, grad_x);
+        }
         return;
     }
-    // Binary32, no overlap between the windows, aligned rows, planes that fill the blocks of a grid over planes: four
-    // inputs of one row per lane stay faster (44 against 49 us on [4096, 112, 116]; small planes: 73 against 53 us on
-    // [65536, 28, 28]).
-    const bool quad_rows = sizeof(T) == 4 && p.kh == 2 && p.sh == 2 && p.W % 4 == 0 && aligned_to(grad_x, 16) &&
-                           static_cast<int64_t>(p.H) * p.W >= 8192;
     RowPool rows;
-    if (row_geometry(p) && !quad_rows && row_pool(planes, (static_cast<int64_t>(p.H) + p.sh - 1) / p.sh, p.W, kE, planes * p.OH * p.OW, &rows)) {
+    // 2x2 windows on rows of whole groups of four: a lane owns one input row (two rows of it: binary32 [4096, 112, 120]
+    // 57 -> 46 us, [65536, 28, 28] 60 -> 43, binary16 [4096, 112, 112] 31 -> 24, [16384, 56, 56] 34 -> 24).  Results beyond the
+    // Infinity Cache (binary16 [16384, 112, 112] 105 -> 122 us) and rows of other lengths (binary16 [4096, 113, 113] 39 -> 41 us,
+    // binary32 57 -> 62) stay with two.
+    const bool single_rows = p.kh == 2 && p.W % 4 == 0 && bytes <= (int64_t(256) << 20);
+    const int64_t rows_per_lane = single_rows ? 1 : p.sh;
+    if (row_geometry(p) && row_pool(planes, (static_cast<int64_t>(p.H) + rows_per_lane - 1) / rows_per_lane, p.W, kE, planes * p.OH * p.OW, &rows)) {
         dim3 unused;
         const Pool g = make_pool(p, planes, 1, &unused);
         const unsigned blocks = (rows.total + kBlock - 1) / kBlock;
-        // Binary32 rows of odd alignment and a result that outgrows the caches (128 MiB of the 256): non-temporal stores
-        // (61 -> 48 us on [4096, 113, 113], 72 -> 54 us on [16384, 57, 57]; smaller results and aligned rows lose by them: 24
-        // against 28 us on [8192, 57, 57], 60 against 100 us on [65536, 28, 28]; binary16 loses 2 to 10 %).
-        const bool nt = sizeof(T) == 4 && p.W % 4 != 0 && planes * p.H * p.W >= (int64_t(128) << 18);
+        if (single_rows) {
+            maxpool2d_backward_2x2_kernel<T><<<blocks, kBlock, 0, s>>>(argmax, grad_y, g, rows, grad_x);
+            return;
+        }
+        // Non-temporal stores for rows of whole 32-byte sectors and a result that does not stay in the caches (binary16
+        // 3x3/2, padding 0: 42 -> 29 us on [16384, 64, 64], 64 -> 47 us on [4096, 160, 160]; binary32 63 -> 51 us on
+        // [16384, 64, 64]; rows of 112 bytes 60 -> 100 us on [65536, 28, 28], 33 MB of 16 x 16 planes 13 -> 20 us), and for
+        // binary32 rows of odd alignment from 128 MiB on (61 -> 48 us on [4096, 113, 113], 72 -> 54 us on
+        // [16384, 57, 57]; 24 -> 28 us on [8192, 57, 57]; binary16 loses 2 to 10 %).
+        const bool nt = (row_bytes % 32 == 0 && bytes > (int64_t(64) << 20)) ||
+                        (sizeof(T) == 4 && p.W % 4 != 0 && bytes >= (int64_t(128) << 20));
 #define ACTQ_POOL_ROWS(K, P, S)                                                                                              \
     do {                                                                                                                    \
-        if (nt) maxpool2d_backward_rows_kernel<T, K, P, S, sizeof(T) == 4><<<blocks, kBlock, 0, s>>>(argmax, grad_y, g, rows, grad_x);  \
-        else maxpool2d_backward_rows_kernel<T, K, P, S, false><<<blocks, kBlock, 0, s>>>(argmax, grad_y, g, rows, grad_x);   \
+        if (nt) maxpool2d_backward_rows_kernel<T, K, P, S, true><<<blocks, kBlock, 0, s>>>(argmax, grad_y, g, rows, grad_x);    \
+        else maxpool2d_backward_rows_kernel<T, K, P, S, false><<<blocks, kBlock, 0, s>>>(argmax, grad_y, g, rows, grad_x);      \
     } while (0)
         if (p.sh == 1) ACTQ_POOL_ROWS(3, 1, 1);
         else if (p.kh == 2) ACTQ_POOL_ROWS(2, 0, 2);

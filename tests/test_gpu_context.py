@@ -156,6 +156,35 @@ def test_maxpool_rows_of_any_extent(shape, k, s, p, dtype):
     _pool_round_trip(x, g, H, W, (k, k), (s, s), (p, p), (1, 1))
 
 
+# rows of whole groups of four and of eight, whole 32 and 64 bytes, over even and odd heights
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+@pytest.mark.parametrize("k,s,p", [(3, 2, 1), (3, 2, 0), (2, 2, 0), (3, 1, 1)])
+@pytest.mark.parametrize("shape", [((5,), 8, 8), ((3,), 16, 24), ((3,), 9, 12), ((2,), 7, 20), ((7,), 4, 16), ((3,), 5, 32), ((2,), 6, 56)])
+def test_maxpool_aligned_rows(shape, k, s, p, dtype):
+    test_maxpool_rows_of_any_extent(shape, k, s, p, dtype)
+
+
+@pytest.mark.parametrize("dtype,planes,H,W,k,s,p", [
+    (torch.float16, 2752, 112, 112, 3, 2, 1), (torch.float16, 8256, 64, 64, 3, 2, 1), (torch.float16, 8400, 63, 64, 3, 2, 1),
+    (torch.float16, 8256, 64, 64, 3, 2, 0), (torch.float16, 8256, 64, 64, 3, 1, 1), (torch.float16, 2752, 112, 112, 2, 2, 0),
+    (torch.float16, 10752, 112, 112, 2, 2, 0), (torch.float32, 10560, 40, 40, 3, 2, 0), (torch.float32, 10560, 41, 40, 3, 2, 1),
+    (torch.float32, 8208, 64, 64, 2, 2, 0), (torch.float32, 21440, 56, 56, 2, 2, 0), (torch.float32, 21504, 57, 56, 2, 2, 0)])
+def test_large_maxpool_gradients_equal_those_of_their_parts(dtype, planes, H, W, k, s, p):
+    """The stores depend on the size of the result; parts of 16 planes are the sizes that the oracle checks."""
+    x = torch.randn((planes, H, W), device="cuda:0").to(dtype).mul_(4).round_()     # many ties
+    y, arg = B.maxpool2d_forward(x, (k, k), (s, s), (p, p))
+    g = torch.randn(y.shape, device="cuda:0").to(dtype)
+    gx = B.maxpool2d_backward(arg, g, H, W, (k, k), (s, s), (p, p))
+    for at in (0, planes // 2 & -16, planes - 16):
+        part = slice(at, at + 16)
+        assert torch.equal(B.maxpool2d_backward(arg[part].clone(), g[part].clone(), H, W, (k, k), (s, s), (p, p)), gx[part])
+        y1, a1 = B.maxpool2d_forward(x[part].clone(), (k, k), (s, s), (p, p))
+        assert torch.equal(y1, y[part]) and torch.equal(a1, arg[part])
+    # every gradient went to exactly one input where windows do not overlap
+    if k == s:
+        assert torch.equal((gx != 0).sum(), (g != 0).sum())
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
 @pytest.mark.parametrize("shape,k,s,p", [((2, 57, 57), 3, 2, 1), ((3, 30, 31), 3, 2, 0), ((2, 28, 27), 2, 2, 0), ((2, 19, 21), 3, 1, 1),
                                          ((2, 16, 16), 3, 2, 1), ((2, 16, 24), 2, 2, 0)])
