@@ -589,18 +589,19 @@ struct Carrier<_Float16, 2> {
 // clamped).  A copy to the right of or below its original never wins, because only a larger value
 // replaces the running maximum; one to the left or above wins in its original's place, and the
 // position moves to the original (which is the first of the equal values inside the image).
-// NT: non-temporal stores.
-template <typename T, int K, int P, int S, bool NT>
+// PH, PW: padding of the rows and of the columns.  NT: non-temporal stores.
+template <typename T, int K, int PH, int PW, int S, bool NT>
 __global__ __launch_bounds__(kBlock) void maxpool2d_forward_rows_kernel(const T* __restrict__ x, Pool g, RowPool q,
                                                                         T* __restrict__ y, uint8_t* __restrict__ argmax)
 {
+    static_assert(K == 3 || PW == 0, "a padded column is the first or the last of three");
     typedef Carrier<T, S> C;
     typedef typename C::raw raw;
     typedef raw vec_in __attribute__((ext_vector_type(16 / sizeof(T)), aligned(sizeof(T))));
     typedef raw vec_out __attribute__((ext_vector_type(16 / sizeof(T) / S), aligned(sizeof(T))));
     typedef typename RowVec<T, S>::codes vec_codes;
     constexpr int E = 16 / sizeof(T), NO = E / S;
-    constexpr bool kLeft = P == 1, kRight = K == 3 && (P == 0 || S == 1);   // columns needed from the neighbours
+    constexpr bool kLeft = PW == 1, kRight = K == 3 && (PW == 0 || S == 1);   // columns needed from the neighbours
     const uint32_t idx = blockIdx.x * kBlock + threadIdx.x;
     const bool live = idx < q.total;
     const uint32_t id = live ? idx : q.total - 1;   // every lane takes part in the shift
@@ -611,7 +612,7 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_forward_rows_kernel(const T*
     int64_t at[K];   // the lane's first element of every window row
 #pragma unroll
     for (int a = 0; a < K; ++a) {
-        const int32_t r = min(max(S * i - P + a, 0), g.H - 1);
+        const int32_t r = min(max(S * i - PH + a, 0), g.H - 1);
         at[a] = (static_cast<int64_t>(plane) * g.H + r) * g.W + static_cast<int64_t>(E) * c;
     }
     const raw* xr = reinterpret_cast<const raw*>(x);
@@ -647,9 +648,9 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_forward_rows_kernel(const T*
     uint64_t codes = 0;
 #pragma unroll
     for (int e = 0; e < NO; ++e) {
-        // column S (j0 + e) - P + b = E c - 1 + slot
-        constexpr int kFirst = 1 - P;
-        const bool past = P == 1 && S * (j0 + e) + 1 >= g.W;   // the window's last column is padding
+        // column S (j0 + e) - PW + b = E c - 1 + slot
+        constexpr int kFirst = 1 - PW;
+        const bool past = PW == 1 && S * (j0 + e) + 1 >= g.W;   // the window's last column is padding
         typename C::type best = v[0][S * e + kFirst];
         uint32_t best_k = 0;
 #pragma unroll
@@ -658,15 +659,13 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_forward_rows_kernel(const T*
             for (int b = 0; b < K; ++b) {
                 if (a == 0 && b == 0) continue;
                 typename C::type val = v[a][S * e + b + kFirst];
-                if (P == 1 && b == K - 1) val = past ? v[a][S * e + b - 1 + kFirst] : val;
+                if (PW == 1 && b == K - 1) val = past ? v[a][S * e + b - 1 + kFirst] : val;
                 const bool take = C::value(val) > C::value(best);
                 best = take ? val : best;
                 best_k = take ? static_cast<uint32_t>(a * K + b) : best_k;
             }
-        if (P == 1) {
-            if (e == 0) best_k += c == 0 && (best_k == 0 || best_k == 3 || best_k == 6) ? 1u : 0u;
-            best_k += i == 0 && best_k < K ? K : 0u;
-        }
+        if (PW == 1 && e == 0) best_k += c == 0 && (best_k == 0 || best_k == 3 || best_k == 6) ? 1u : 0u;
+        if (PH == 1) best_k += i == 0 && best_k < K ? K : 0u;
         out[e] = C::back(best);
         codes |= static_cast<uint64_t>(best_k) << (8 * e);
     }
@@ -1063,6 +1062,15 @@ static bool row_geometry(const PoolShape& p)
     return p.sh == 2 ? (p.kh == 3 && p.ph <= 1) || (p.kh == 2 && p.ph == 0) : p.sh == 1 && p.kh == 3 && p.ph == 1;
 }
 
+// Windows that are padded along one axis only, stride 2: 3x3 beside the rows' ends, 2x2 above and below.
+// Forward, the rows are only clamped, so these take the same kernel (against one output per lane, [4096, 112, 112]:
+// binary32 85 -> 50 and 55 -> 48 us, binary16 77 -> 27 and 49 -> 25 us).
+static bool one_sided_row_geometry(const PoolShape& p)
+{
+    if (p.kh != p.kw || p.sh != 2 || p.sw != 2 || p.dh != 1 || p.dw != 1) return false;
+    return (p.kh == 3 && p.ph == 0 && p.pw == 1) || (p.kh == 2 && p.ph == 1 && p.pw == 0);
+}
+
 template <typename T>
 static void maxpool_forward_typed(const T* x, int64_t planes, const PoolShape& p, T* y, uint8_t* argmax, hipStream_t s)
 {
@@ -1070,23 +1078,26 @@ static void maxpool_forward_typed(const T* x, int64_t planes, const PoolShape& p
     constexpr int kE = 16 / static_cast<int>(sizeof(T));
     RowPool rows;
     // the columns that lanes must hold: those over the outputs, and with K = 3 and no padding one more
-    const int64_t columns = static_cast<int64_t>(p.sw) * p.OW + (p.kh == 3 && p.ph == 0 ? 1 : 0);
-    if (row_geometry(p) && row_pool(planes, p.OH, columns, kE, planes * p.H * p.W, &rows)) {
+    const int64_t columns = static_cast<int64_t>(p.sw) * p.OW + (p.kh == 3 && p.pw == 0 ? 1 : 0);
+    if ((row_geometry(p) || one_sided_row_geometry(p)) && row_pool(planes, p.OH, columns, kE, planes * p.H * p.W, &rows)) {
         dim3 unused;
         const Pool g = make_pool(p, planes, 1, &unused);
         const unsigned blocks = (rows.total + kBlock - 1) / kBlock;
         // Non-temporal stores: binary32 50 -> 46 us on [4096, 111, 120], binary16 2x2/2 27.9 -> 25.8 us on [4096, 112, 112], 3x3/2
         // 54.9 -> 52.8 us on [4096, 160, 160]; binary16 rows of other lengths are up to 5 % slower with them (3x3/1 on [65536, 28, 28]
         // 74 -> 78 us).
-#define ACTQ_POOL_ROWS(K, P, S)                                                                                       \
-    do {                                                                                                             \
-        if (sizeof(T) == 4 || p.W % 8 == 0) maxpool2d_forward_rows_kernel<T, K, P, S, true><<<blocks, kBlock, 0, s>>>(x, g, rows, y, argmax);  \
-        else maxpool2d_forward_rows_kernel<T, K, P, S, sizeof(T) == 4><<<blocks, kBlock, 0, s>>>(x, g, rows, y, argmax);  \
+        const bool nt = sizeof(T) == 4 || p.W % 8 == 0;
+#define ACTQ_POOL_ROWS(K, PH, PW, S)                                                                                                         \
+    do {                                                                                                                                     \
+        if (nt) maxpool2d_forward_rows_kernel<T, K, PH, PW, S, true><<<blocks, kBlock, 0, s>>>(x, g, rows, y, argmax);                       \
+        else if constexpr (sizeof(T) == 2) maxpool2d_forward_rows_kernel<T, K, PH, PW, S, false><<<blocks, kBlock, 0, s>>>(x, g, rows, y, argmax); \
     } while (0)
-        if (p.sh == 1) ACTQ_POOL_ROWS(3, 1, 1);
-        else if (p.kh == 2) ACTQ_POOL_ROWS(2, 0, 2);
-        else if (p.ph == 1) ACTQ_POOL_ROWS(3, 1, 2);
-        else ACTQ_POOL_ROWS(3, 0, 2);
+        if (p.sh == 1) ACTQ_POOL_ROWS(3, 1, 1, 1);
+        else if (p.kh == 2 && p.ph == 0) ACTQ_POOL_ROWS(2, 0, 0, 2);
+        else if (p.kh == 2) ACTQ_POOL_ROWS(2, 1, 0, 2);
+        else if (p.pw == 0) ACTQ_POOL_ROWS(3, 0, 0, 2);
+        else if (p.ph == 0) ACTQ_POOL_ROWS(3, 0, 1, 2);
+        else ACTQ_POOL_ROWS(3, 1, 1, 2);
 #undef ACTQ_POOL_ROWS
         return;
     }
