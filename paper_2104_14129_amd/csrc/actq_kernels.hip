@@ -1703,7 +1703,7 @@ constexpr int kSelectBins = 256;
 struct SelectLds {
     uint64_t hist[2][kSelectBins];   // both cleared by the caller, as is `count`
     uint64_t key[kWave], amount[kWave];
-    uint32_t count[2];
+    uint64_t count[2];               // moves: up to 7 * 2^31
 };
 
 // `each(f)` calls f(price, bits freed) for the thread's candidates.  All candidates of the workgroup:
@@ -1753,7 +1753,7 @@ __device__ Threshold select_price(const Each& each, uint64_t n, uint64_t lo, uin
         // what is left, counted, and listed if it is little
         each([&](uint64_t key, uint64_t freed) {
             if (key >= lo && key <= hi) {
-                const uint32_t at = __hip_atomic_fetch_add(&s.count[turn], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                const uint64_t at = __hip_atomic_fetch_add(&s.count[turn], uint64_t(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 if (at < kWave) {
                     s.key[at] = key;
                     s.amount[at] = freed;
@@ -1977,7 +1977,8 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
     __shared__ SelectLds sel;
     __shared__ uint64_t wave_a[kAllocWavesMax], wave_b[kAllocWavesMax], wave_c[kAllocWavesMax], wave_d[kAllocWavesMax];
     __shared__ uint64_t wave_round[2][kAllocWavesMax], wave_bytes[kAllocQuads * kAllocWavesMax];
-    __shared__ uint32_t list_count, bracket_lo, bracket_hi;
+    __shared__ uint64_t list_count;   // moves: up to 7 * 2^31
+    __shared__ uint32_t bracket_lo, bracket_hi;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int waves = kAllocWavesMax;
@@ -2213,7 +2214,7 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
         const auto walk = [&](auto f) { walk_items(f, [](int64_t, int, int) {}); };
         uint64_t lo = ~uint64_t(0), hi = 0;
         walk_items([&](uint64_t key, uint64_t freed) {
-            const uint32_t at = __hip_atomic_fetch_add(&list_count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            const uint64_t at = __hip_atomic_fetch_add(&list_count, uint64_t(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             if (at < kAllocList) {
                 list_key[at] = key;
                 list_amount[at] = freed;

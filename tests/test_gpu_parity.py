@@ -564,6 +564,20 @@ def test_device_allocator_at_the_limits_of_its_kernels(M, widths, law):
         assert np.array_equal(offs, np.concatenate([[0], np.cumsum(per)[:-1]])) and total == int(per.sum())
 
 
+def test_device_allocator_with_more_than_2_to_the_32_equal_moves():
+    """2^30 items of sensitivity 0 with four steps each: 2^32 undecided moves, all at the price of the threshold.  The
+    first items go down to one bit until the budget holds, the others keep eight."""
+    M = 1 << 30
+    w = torch.zeros(M, device="cuda:0")
+    bits, offs, res = B.allocate_bits_device(w, 1, 2 * M, 0x11E)
+    k, rest = divmod(6 * M, 7)                       # an item frees seven bits; the last one goes 8 -> 4 -> 3 -> 2 -> 1
+    assert 0 < rest <= 4 + 1 + 1
+    last = 4 if rest <= 4 else (3 if rest <= 5 else 2)
+    assert (bits[:k] == 1).all() and int(bits[k]) == last and (bits[k + 1:] == 8).all()
+    assert int(res[1]) == 0 and int(res[0]) == 32 * (k + last + 8 * (M - k - 1))
+    assert int(offs[0]) == 0 and int(offs[k]) == 32 * k and int(offs[M - 1]) == int(res[0]) - 256
+
+
 def test_device_allocator_writes_widths_at_any_byte_address():
     M = 5003
     w = synth.lognormal_sensitivities(M, seed=3)
