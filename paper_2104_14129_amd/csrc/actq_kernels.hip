@@ -1703,6 +1703,7 @@ constexpr int kSelectBins = 256;
 struct SelectLds {
     uint64_t hist[2][kSelectBins];   // both cleared by the caller, as is `count`
     uint64_t key[kWave], amount[kWave];
+    uint64_t least[kAllocWavesMax], most[kAllocWavesMax];   // per wavefront
     uint64_t count[2];               // moves: up to 7 * 2^31
 };
 
@@ -1766,6 +1767,24 @@ __device__ Threshold select_price(const Each& each, uint64_t n, uint64_t lo, uin
         __syncthreads();
         n = s.count[turn];
         if (n <= kWave) break;
+        // Many moves in one bin: the bracket shrinks to their prices.  Equal ones (items of the same size and sensitivity)
+        // are told apart from nearly equal ones here and not bit by bit (256 items of sensitivity 1, all widths: 20.2 -> 12.1 us).
+        uint64_t least = ~uint64_t(0), most = 0;
+        each([&](uint64_t key, uint64_t) {
+            if (key >= lo && key <= hi) {
+                least = key < least ? key : least;
+                most = key > most ? key : most;
+            }
+        });
+        least = wave_reduce(least, Min());
+        most = wave_reduce(most, Max());
+        if (lane == 0) {
+            s.least[tid >> 6] = least;
+            s.most[tid >> 6] = most;
+        }
+        __syncthreads();
+        lo = combine_waves(s.least, blockDim.x >> 6, ~uint64_t(0), Min());
+        hi = combine_waves(s.most, blockDim.x >> 6, 0, Max());
     }
     // at most one move per lane: sums over the cheaper and over the not dearer ones of the list
     const bool live = lane < static_cast<int>(n);

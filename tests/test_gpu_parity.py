@@ -539,6 +539,8 @@ def _spread(rng, M, law):
         return np.exp(rng.uniform(np.log(1e-30), np.log(1e30), M)).astype(np.float32)
     if law == "close":         # more undecided moves than the kernel lists, all prices different
         return (1.0 + np.arange(M) * 2.0 ** -22).astype(np.float32)
+    if law == "groups":        # ninety equal ones each, the groups close together: more than a wavefront of equal prices
+        return (1.0 + (np.arange(M) // 90) * 2.0 ** -22).astype(np.float32)
     if law == "few":           # a handful of values: many ties at the threshold, and some free items
         return rng.choice(np.array([0.0, 1e-45, 1.0, 1.0000001, 3.0], dtype=np.float32), M)
     return np.full(M, {"zero": 0.0, "one": 1.0}[law], dtype=np.float32)
@@ -546,13 +548,13 @@ def _spread(rng, M, law):
 
 # items around the limits of the two kernels: 2048 moves and 1024 items (one workgroup of single
 # moves), rounds of 4096 items, 16,384 items in registers; remainders of the quadruples
-@pytest.mark.parametrize("law", ["wide", "close", "few", "zero", "one"])
-@pytest.mark.parametrize("M,widths", [(292, 0x1FE), (293, 0x1FE), (682, 0x116), (683, 0x116), (1024, 0x102), (1025, 0x102), (4096, 0x116),
+@pytest.mark.parametrize("law", ["wide", "close", "groups", "few", "zero", "one"])
+@pytest.mark.parametrize("M,widths", [(65, 0x102), (128, 0x1FE), (292, 0x1FE), (293, 0x1FE), (682, 0x116), (683, 0x116), (1024, 0x102), (1025, 0x102), (4096, 0x116),
                                       (4097, 0x1FE), (4099, 0x106), (16384, 0x116), (16385, 0x116), (16390, 0x1FE)])
 def test_device_allocator_at_the_limits_of_its_kernels(M, widths, law):
     rng = np.random.default_rng(M)
     w = _spread(rng, M, law)
-    D = np.full(M, 25088, dtype=np.int64) if law == "close" else rng.choice([1, 256, 25088, 802816, 2 ** 34 - 1], M).astype(np.int64)
+    D = np.full(M, 25088, dtype=np.int64) if law in ("close", "groups") else rng.choice([1, 256, 25088, 802816, 2 ** 34 - 1], M).astype(np.int64)
     lo = min(b for b in range(1, 9) if widths >> b & 1)
     # the host allocator (a heap, checked against the oracle elsewhere) is the reference at these sizes
     for mean in (lo + 0.003, 2.0, 6.7):
