@@ -1564,7 +1564,10 @@ __global__ __launch_bounds__(kSensMaxBlock) void sample_sensitivity_kernel(const
 constexpr int kAllocBlock = 1024;
 constexpr int kAllocWavesMax = kAllocBlock / kWave;
 constexpr int kMaxSteps = 7;
-constexpr int kSmallMoves = 2048;     // the small kernel: moves, at most two per thread
+// Moves of the small kernel.  Where it ends: 1024 items with all widths 18 against 26 us with the large kernel, 2048 items
+// with {1, 2, 4, 8} 20 against 24 us; what lies beyond (1300 items with all widths, 25 us) is as fast in the large one.
+constexpr int kSmallMoves = 2048;                          // at most two per thread
+constexpr int kMostSmallMoves = kAllocBlock * kMaxSteps;   // at most seven per thread
 constexpr int kAllocBins = 4096;      // bins of the large kernel's table over w / D
 constexpr int kAllocList = 1024;      // exactly priced moves the large kernel keeps in LDS
 constexpr int kAllocQuads = 4;        // quadruples of consecutive items per thread kept in registers: 16,384 items in all
@@ -1843,22 +1846,29 @@ __device__ __forceinline__ double ladder_price(const Ladder& lad, int k)
     return v;
 }
 
-// M <= 1024 and M * steps <= kSmallMoves: every price in LDS, at most two per thread, an item per thread.
+// At most MOVES moves and ITEMS items per thread: every price in LDS (2048 moves: 37 of the 160 KB; 7168: 119).
+template <int MOVES, int ITEMS>
 __global__ __launch_bounds__(kAllocBlock) void allocate_bits_small_kernel(const float* __restrict__ w, AllocArgs a,
                                                                           uint8_t* __restrict__ bits,
                                                                           uint64_t* __restrict__ offsets,
                                                                           int64_t* __restrict__ result)
 {
-    __shared__ uint64_t key[kSmallMoves], amount[kSmallMoves];   // move r * M + i
+    __shared__ uint64_t key[MOVES], amount[MOVES];   // move r * M + i
     __shared__ SelectLds sel;
     __shared__ uint64_t wave_elems[kAllocWavesMax], wave_lo[kAllocWavesMax], wave_hi[kAllocWavesMax], wave_bad[kAllocWavesMax];
     __shared__ uint64_t wave_ties[kAllocWavesMax], wave_bytes[kAllocWavesMax];
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
     const int threads = blockDim.x, waves = threads >> 6;
     const int M = static_cast<int>(a.M), steps = a.lad.count - 1, moves = M * steps;
-    const bool live = tid < M;
-    const float wi = live ? w[tid] : 0.0f;
-    int64_t Di = live ? (a.D_items ? a.D_items[tid] : a.D) : 0;
+    const int first = tid * ITEMS;   // the thread's items, consecutive ones
+    float wi[ITEMS];
+    int64_t Di[ITEMS];
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) {
+        const bool live = first + q < M;
+        wi[q] = live ? w[first + q] : 0.0f;
+        Di[q] = live ? (a.D_items ? a.D_items[first + q] : a.D) : 0;
+    }
     uint64_t lo = ~uint64_t(0), hi = 0;
     for (int e = tid; e < moves; e += threads) {
         const int r = static_cast<int>(static_cast<uint32_t>(e) / static_cast<uint32_t>(M)), i = e - r * M;
@@ -1873,11 +1883,18 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_small_kernel(const 
     }
     for (int k = tid; k < 2 * kSelectBins; k += threads) (&sel.hist[0][0])[k] = 0;
     if (tid < 2) sel.count[tid] = 0;
-    const bool ok = live && valid_item(wi, Di);
-    const uint64_t e64 = wave_reduce(ok ? static_cast<uint64_t>(Di) : uint64_t(0), Add());
+    uint64_t my_elems = 0;
+    bool my_bad = false;
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) {
+        const bool live = first + q < M, ok = live && valid_item(wi[q], Di[q]);
+        my_elems += ok ? static_cast<uint64_t>(Di[q]) : uint64_t(0);
+        my_bad = my_bad || (live && !ok);
+    }
+    const uint64_t e64 = wave_reduce(my_elems, Add());
     lo = wave_reduce(lo, Min());
     hi = wave_reduce(hi, Max());
-    const uint64_t bad = __ballot(live && !ok);
+    const uint64_t bad = __ballot(my_bad);
     if (lane == 0) {
         wave_elems[wave] = e64;
         wave_lo[wave] = lo;
@@ -1896,33 +1913,57 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_small_kernel(const 
         t = select_price(each, static_cast<uint64_t>(moves), combine_waves(wave_lo, waves, ~uint64_t(0), Min()),
                          combine_waves(wave_hi, waves, 0, Max()), v.need, 0, sel);
     }
-    if (Di <= 0 || Di >= (int64_t(1) << 34)) Di = live ? 1 : 0;   // invalid input: stay memory-safe
-    int rung = v.loose ? 0 : steps, ties = 0;
-    if (v.search && live) {
-        rung = 0;
-        for (int r = 0; r < steps; ++r) {
-            const uint64_t k = key[r * M + tid];
-            rung += k < t.price ? 1 : 0;
-            ties += k == t.price ? 1 : 0;
+    int rung[ITEMS], ties[ITEMS];
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) {
+        const bool live = first + q < M;
+        if (Di[q] <= 0 || Di[q] >= (int64_t(1) << 34)) Di[q] = live ? 1 : 0;   // invalid input: stay memory-safe
+        rung[q] = v.loose ? 0 : steps;
+        ties[q] = 0;
+        if (v.search && live) {
+            rung[q] = 0;
+            for (int r = 0; r < steps; ++r) {
+                const uint64_t k = key[r * M + first + q];
+                rung[q] += k < t.price ? 1 : 0;
+                ties[q] += k == t.price ? 1 : 0;
+            }
         }
     }
     if (t.ties > 1) {
         // the moves at the threshold in (item, step) order, until the budget holds
         const uint64_t rest = v.need - t.below;
-        uint64_t unused;
-        uint64_t freed = block_exclusive_scan(static_cast<uint64_t>(Di) * static_cast<uint64_t>(ladder_width(a, rung) - ladder_width(a, rung + ties)),
-                                              wave_ties, unused);
-        for (; ties > 0 && freed < rest; --ties, ++rung)
-            freed += static_cast<uint64_t>(Di) * static_cast<uint64_t>(ladder_width(a, rung) - ladder_width(a, rung + 1));
+        const auto tie_bits = [&](int q) {
+            return static_cast<uint64_t>(Di[q]) * static_cast<uint64_t>(ladder_width(a, rung[q]) - ladder_width(a, rung[q] + ties[q]));
+        };
+        uint64_t sum = 0, unused;
+#pragma unroll
+        for (int q = 0; q < ITEMS; ++q) sum += tie_bits(q);
+        uint64_t before = block_exclusive_scan(sum, wave_ties, unused);
+#pragma unroll
+        for (int q = 0; q < ITEMS; ++q) {
+            uint64_t freed = before;
+            before += tie_bits(q);
+            for (; ties[q] > 0 && freed < rest; --ties[q], ++rung[q])
+                freed += static_cast<uint64_t>(Di[q]) * static_cast<uint64_t>(ladder_width(a, rung[q]) - ladder_width(a, rung[q] + 1));
+        }
     } else {
-        rung += ties;   // the one move at the threshold is applied
+#pragma unroll
+        for (int q = 0; q < ITEMS; ++q) rung[q] += ties[q];   // the one move at the threshold is applied
     }
-    const int b = ladder_width(a, rung);
-    uint64_t total;
-    const uint64_t off = block_exclusive_scan(live ? stream_bytes(Di, b) : 0, wave_bytes, total);
-    if (live) {
-        bits[tid] = static_cast<uint8_t>(b);
-        offsets[tid] = off;
+    uint64_t bytes[ITEMS], sum = 0, total;
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) {
+        bytes[q] = first + q < M ? stream_bytes(Di[q], ladder_width(a, rung[q])) : 0;
+        sum += bytes[q];
+    }
+    uint64_t off = block_exclusive_scan(sum, wave_bytes, total);
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) {
+        if (first + q < M) {
+            bits[first + q] = static_cast<uint8_t>(ladder_width(a, rung[q]));
+            offsets[first + q] = off;
+        }
+        off += bytes[q];
     }
     if (tid == 0) {
         result[0] = static_cast<int64_t>(total);
@@ -1982,7 +2023,7 @@ typedef int64_t i64x2_a8 __attribute__((ext_vector_type(2), aligned(8)));
 
 // Any M.  A thread's items come in quadruples of consecutive ones, 4096 items per round; the
 // bins (ratios, before there are bins) and element counts of the first kAllocQuads rounds stay in registers.
-// M >= 4: the small kernel takes everything up to kSmallMoves / 7 items.
+// M >= 4: the small kernel takes everything up to 1024 items.
 __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float* __restrict__ w, AllocArgs a,
                                                                     uint8_t* __restrict__ bits,
                                                                     uint64_t* __restrict__ offsets,
@@ -2758,11 +2799,14 @@ int launch_allocate_bits(const float* w, const int64_t* D_items, int64_t D, int6
     for (int k = 0; k < lad.count; ++k) a.width_nibbles |= static_cast<uint32_t>(lad.width[k]) << (4 * k);
     const int64_t moves = M * (lad.count - 1);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (M <= kAllocBlock && moves <= kSmallMoves) {
+    if (M <= 2 * kAllocBlock && moves <= kMostSmallMoves) {
         // a thread per move up to the largest workgroup: the (binary64) division of a move is most of its cost
         const int64_t most = moves > M ? moves : M;
         const int64_t lanes = (most + kWave - 1) / kWave * kWave;
-        allocate_bits_small_kernel<<<1, static_cast<unsigned>(lanes < kAllocBlock ? lanes : kAllocBlock), 0, s>>>(w, a, bits, offsets, result);
+        const unsigned block = static_cast<unsigned>(lanes < kAllocBlock ? lanes : kAllocBlock);
+        if (M > kAllocBlock) allocate_bits_small_kernel<kMostSmallMoves, 2><<<1, block, 0, s>>>(w, a, bits, offsets, result);
+        else if (moves > kSmallMoves) allocate_bits_small_kernel<kMostSmallMoves, 1><<<1, block, 0, s>>>(w, a, bits, offsets, result);
+        else allocate_bits_small_kernel<kSmallMoves, 1><<<1, block, 0, s>>>(w, a, bits, offsets, result);
     } else {
         allocate_bits_kernel<<<1, kAllocBlock, 0, s>>>(w, a, bits, offsets, result);
     }

@@ -546,10 +546,11 @@ def _spread(rng, M, law):
     return np.full(M, {"zero": 0.0, "one": 1.0}[law], dtype=np.float32)
 
 
-# items around the limits of the two kernels: 2048 moves and 1024 items (one workgroup of single
-# moves), rounds of 4096 items, 16,384 items in registers; remainders of the quadruples
+# items around the limits of the two kernels: 2048 and 7168 moves, 1024 and 2048 items (one or two per thread of the
+# small kernel), rounds of 4096 items, 16,384 items in registers; remainders of the quadruples
 @pytest.mark.parametrize("law", ["wide", "close", "groups", "few", "zero", "one"])
-@pytest.mark.parametrize("M,widths", [(65, 0x102), (128, 0x1FE), (292, 0x1FE), (293, 0x1FE), (682, 0x116), (683, 0x116), (1024, 0x102), (1025, 0x102), (4096, 0x116),
+@pytest.mark.parametrize("M,widths", [(65, 0x102), (128, 0x1FE), (292, 0x1FE), (293, 0x1FE), (682, 0x116), (683, 0x116), (1024, 0x102), (1024, 0x1FE), (1025, 0x102), (1025, 0x1FE), (1337, 0x116),
+                                      (1792, 0x11E), (1793, 0x11E), (2047, 0x116), (2048, 0x116), (2049, 0x116), (4096, 0x116),
                                       (4097, 0x1FE), (4099, 0x106), (16384, 0x116), (16385, 0x116), (16390, 0x1FE)])
 def test_device_allocator_at_the_limits_of_its_kernels(M, widths, law):
     rng = np.random.default_rng(M)
