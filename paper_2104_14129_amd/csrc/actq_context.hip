@@ -802,9 +802,10 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_backward_rows_kernel(const u
     }
 }
 
-// Backward of 2x2 windows without overlap: an input lies in one window, so a lane produces 16 bytes of ONE
-// input row and a wavefront 1 KiB without gaps.  (Two rows per lane, as above, read every gradient once instead
-// of twice but write every other row of the wavefront's stretch per instruction.)
+// Backward of 2x2 windows without overlap for small results: an input lies in one window, so a lane produces 16 bytes
+// of ONE input row.  Twice the wavefronts of the kernel above with half the chain each, which is what counts as long as the
+// result takes no longer than they do (10 MiB: 9.0 against 10.5 us binary32, 9.9 against 11.4 binary16); beyond it, reading
+// every gradient twice does (20 MiB alike, 60 MiB up to 50 % behind).
 template <typename T>
 __global__ __launch_bounds__(kBlock) void maxpool2d_backward_2x2_kernel(const uint8_t* __restrict__ argmax,
                                                                         const T* __restrict__ grad_y, Pool g, RowPool q,
@@ -852,7 +853,7 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_backward_2x2_kernel(const ui
     }
     T* dst = grad_x + static_cast<int64_t>(strip) * g.W + static_cast<int64_t>(E) * c;
     const int left = g.W - E * static_cast<int32_t>(c);
-    if (left >= E) __builtin_nontemporal_store(out, reinterpret_cast<vec_in*>(dst));   // 24 against 35 us on binary16 [4096, 112, 112]
+    if (left >= E) __builtin_nontemporal_store(out, reinterpret_cast<vec_in*>(dst));
     else store_first<E>(dst, out, left);
 }
 
@@ -1062,6 +1063,45 @@ static bool row_geometry(const PoolShape& p)
     return p.sh == 2 ? (p.kh == 3 && p.ph <= 1) || (p.kh == 2 && p.ph == 0) : p.sh == 1 && p.kh == 3 && p.ph == 1;
 }
 
+// Which backward kernel a row geometry takes.  The times are those of a call as a training step makes it: the gradient has
+// just been written, the positions and the result's old lines are not in the caches (1 GiB has gone through them).  (Over a few tensors in
+// turn part of the result stays in the 256 MiB Infinity Cache and other kernels win.)  What decides is how the stores meet the
+// 128-byte lines of the result: a line whose pieces leave in two instructions far apart, or in two XCDs, is written twice.
+struct BackwardRule {
+    bool single;   // 2x2: a lane owns one input row
+    bool stream;   // otherwise: the kernel for even extents and aligned rows, or the row kernel
+    bool join;     // the stream kernel computes both rows of a lane before it stores either
+    bool nt;       // the row kernel's stores are non-temporal
+};
+
+static BackwardRule backward_rule(int64_t planes, const PoolShape& p, int64_t element_bytes)
+{
+    BackwardRule r = {false, false, false, false};
+    if (!row_geometry(p)) return r;
+    const int64_t row = p.W * element_bytes, mib = planes * p.H * row >> 20;   // of the result
+    const bool even = p.sh == 2 && 2 * p.OH == p.H && 2 * p.OW == p.W && p.W % 8 == 0;
+    if (p.kh == 3) {
+        // 3x3 / 2 / 1: the stream kernel but for the shortest rows, which lie many to a line (binary16, 100 to 300 MiB: rows of 32 bytes are 7 to 20 %
+        // faster with the row kernel, of 48 bytes 5 to 9 % slower, of 112 bytes 13 % at 100 MiB, of 256 bytes 15 % at 60).
+        r.stream = even && p.ph == 1 && row >= (element_bytes == 2 ? 48 : 32);
+        // Rows that end inside a line share it with the next row, and the two pieces meet (binary16, 100 MiB: rows of 80 bytes 47 %, of
+        // 112 bytes 40 %, of 224 bytes 5 %; binary32 rows of 64 and 96 bytes 15 and 35 %; whole lines lose up to 6 %).
+        r.join = row % 128 != 0;
+    } else if (p.W % 4 == 0 && mib < 20) {
+        r.single = true;
+    } else {
+        // 2x2: always on whole 64 bytes (against the row kernel with the better stores, binary16 at 100 MiB: rows of 64 bytes 14 %, of 128 11 %, of
+        // 192 21 %, binary32 14 to 21 %).  Rows with other ends lose more the larger the result, the short ones first (binary16, rows of 112 bytes:
+        // 40 MiB 7 % ahead, 60 alike, 100 11 % behind, 300 40 %; of 224 bytes: 60 MiB 3 % ahead, 150 2 % behind, 200 9 %).
+        r.stream = even && (row % 64 == 0 || mib < (row < 128 ? 48 : 160));
+    }
+    // Long rows and rows of whole sectors (2x2 from 192 bytes on, where rows of 96 bytes lose 15 to 50 %): binary16, 100 MiB, 2x2 rows of 450 bytes
+    // 12 %, of 600 12 %, 3x3 / 2 / 1 of 600 18 %, 3x3 / 2 / 0 of 2000 21 %; binary32 2x2 rows of 900 bytes 12 %.  Shorter rows lose: binary32 2x2 rows of
+    // 112 bytes 46 %, of 240 bytes 10 %.
+    r.nt = row >= 256 || row % 128 == 0 || (row % 32 == 0 && row >= (p.kh == 3 ? 96 : 192));
+    return r;
+}
+
 // Windows that are padded along one axis only, stride 2: 3x3 beside the rows' ends, 2x2 above and below.
 // Forward, the rows are only clamped, so these take the same kernel (against one output per lane, [4096, 112, 112]:
 // binary32 85 -> 50 and 55 -> 48 us, binary16 77 -> 27 and 49 -> 25 us).
@@ -1113,17 +1153,8 @@ static void maxpool_backward_typed(const uint8_t* argmax, const T* grad_y, int64
 {
     dim3 grid;
     constexpr int kE = 16 / static_cast<int>(sizeof(T));
-    const int64_t bytes = planes * p.H * p.W * static_cast<int64_t>(sizeof(T));   // of the result
-    const int64_t row_bytes = p.W * static_cast<int64_t>(sizeof(T));
-    // Even extents, rows of whole 32-byte sectors.  Binary16: 3x3 results beyond 64 MiB (smaller ones leave
-    // the row kernel's cached stores faster: 13 against 16 us on [65536, 16, 16]).  2x2: binary32 only, and only
-    // what the kernel of one row per lane below loses: results beyond 256 MiB (63 against 80 us on [8192, 96, 96], 198
-    // against 210 on [16384, 112, 112]), or beyond 128 with rows of whole 64 bytes (40 against 43 us on [1024, 224, 224]; on
-    // rows of 224 bytes, [16384, 56, 56], 60 against 43).
-    const bool stream_window = p.kh == 3 ? p.ph == 1 && (sizeof(T) == 4 || bytes > (int64_t(64) << 20))
-                                         : sizeof(T) == 4 && bytes > (int64_t(row_bytes % 64 == 0 ? 128 : 256) << 20);
-    const bool stream_geometry = row_geometry(p) && p.sh == 2 && stream_window && 2 * p.OH == p.H && 2 * p.OW == p.W && row_bytes % 32 == 0 &&
-                                 aligned_to(grad_x, 16) && aligned_to(grad_y, 16) && aligned_to(argmax, 4) &&
+    const BackwardRule rule = backward_rule(planes, p, sizeof(T));
+    const bool stream_geometry = rule.stream && aligned_to(grad_x, 16) && aligned_to(grad_y, 16) && aligned_to(argmax, 4) &&
                                  planes * p.OH * (p.W / kE) < (int64_t(1) << 31);
     if (stream_geometry) {
         StreamPool q;
@@ -1135,43 +1166,24 @@ static void maxpool_backward_typed(const uint8_t* argmax, const T* grad_y, int64
         dim3 unused;
         const Pool g = make_pool(p, planes, 1, &unused);
         const unsigned blocks = (q.total + kPoolBwdBlock - 1) / kPoolBwdBlock;
-        // Rows that end inside 64 bytes share them with the next row: both rows are computed before either is stored, so
-        // that the shared pieces meet (3x3, binary32 [16384, 56, 56] 65 -> 56 us, binary16 [4096, 112, 112] 33 -> 27 us; without
-        // shared pieces it costs: binary16 [65536, 32, 32] 39 -> 41 us).
-        if (p.kh == 2) {
-            if constexpr (sizeof(T) == 4) maxpool2d_backward_stream_kernel<T, 2, 0, false><<<blocks, kPoolBwdBlock, 0, s>>>(argmax, grad_y, g, q, grad_x);
-        } else if (row_bytes % 64 != 0) {
-            maxpool2d_backward_stream_kernel<T, 3, 1, true><<<blocks, kPoolBwdBlock, 0, s>>>(argmax, grad_y, g, q, grad_x);
-        } else {
-            maxpool2d_backward_stream_kernel<T, 3, 1, false><<<blocks, kPoolBwdBlock, 0, s>>>(argmax, grad_y, g, q, grad_x);
-        }
+        if (p.kh == 2) maxpool2d_backward_stream_kernel<T, 2, 0, false><<<blocks, kPoolBwdBlock, 0, s>>>(argmax, grad_y, g, q, grad_x);
+        else if (rule.join) maxpool2d_backward_stream_kernel<T, 3, 1, true><<<blocks, kPoolBwdBlock, 0, s>>>(argmax, grad_y, g, q, grad_x);
+        else maxpool2d_backward_stream_kernel<T, 3, 1, false><<<blocks, kPoolBwdBlock, 0, s>>>(argmax, grad_y, g, q, grad_x);
         return;
     }
     RowPool rows;
-    // 2x2 windows on rows of whole groups of four: a lane owns one input row (two rows of it: binary32 [4096, 112, 120]
-    // 57 -> 46 us, [65536, 28, 28] 60 -> 43, binary16 [4096, 112, 112] 31 -> 24, [16384, 56, 56] 34 -> 24).  Results beyond the
-    // Infinity Cache (binary16 [16384, 112, 112] 105 -> 122 us) and rows of other lengths (binary16 [4096, 113, 113] 39 -> 41 us,
-    // binary32 57 -> 62) stay with two.
-    const bool single_rows = p.kh == 2 && p.W % 4 == 0 && bytes <= (int64_t(256) << 20);
-    const int64_t rows_per_lane = single_rows ? 1 : p.sh;
+    const int64_t rows_per_lane = rule.single ? 1 : p.sh;
     if (row_geometry(p) && row_pool(planes, (static_cast<int64_t>(p.H) + rows_per_lane - 1) / rows_per_lane, p.W, kE, planes * p.OH * p.OW, &rows)) {
         dim3 unused;
         const Pool g = make_pool(p, planes, 1, &unused);
         const unsigned blocks = (rows.total + kBlock - 1) / kBlock;
-        if (single_rows) {
+        if (rule.single) {
             maxpool2d_backward_2x2_kernel<T><<<blocks, kBlock, 0, s>>>(argmax, grad_y, g, rows, grad_x);
             return;
         }
-        // Non-temporal stores for rows of whole 32-byte sectors and a result that does not stay in the caches (binary16
-        // 3x3/2, padding 0: 42 -> 29 us on [16384, 64, 64], 64 -> 47 us on [4096, 160, 160]; binary32 63 -> 51 us on
-        // [16384, 64, 64]; rows of 112 bytes 60 -> 100 us on [65536, 28, 28], 33 MB of 16 x 16 planes 13 -> 20 us), and for
-        // binary32 rows of odd alignment from 128 MiB on (61 -> 48 us on [4096, 113, 113], 72 -> 54 us on
-        // [16384, 57, 57]; 24 -> 28 us on [8192, 57, 57]; binary16 loses 2 to 10 %).
-        const bool nt = (row_bytes % 32 == 0 && bytes > (int64_t(64) << 20)) ||
-                        (sizeof(T) == 4 && p.W % 4 != 0 && bytes >= (int64_t(128) << 20));
 #define ACTQ_POOL_ROWS(K, P, S)                                                                                              \
     do {                                                                                                                    \
-        if (nt) maxpool2d_backward_rows_kernel<T, K, P, S, true><<<blocks, kBlock, 0, s>>>(argmax, grad_y, g, rows, grad_x);    \
+        if (rule.nt) maxpool2d_backward_rows_kernel<T, K, P, S, true><<<blocks, kBlock, 0, s>>>(argmax, grad_y, g, rows, grad_x);    \
         else maxpool2d_backward_rows_kernel<T, K, P, S, false><<<blocks, kBlock, 0, s>>>(argmax, grad_y, g, rows, grad_x);      \
     } while (0)
         if (p.sh == 1) ACTQ_POOL_ROWS(3, 1, 1);

@@ -199,22 +199,30 @@ def test_maxpool_aligned_rows(shape, k, s, p, dtype):
     test_maxpool_rows_of_any_extent(shape, k, s, p, dtype)
 
 
+# The backward kernels and their stores depend on the size of the result and on the length and alignment of a row.
 @pytest.mark.parametrize("dtype,planes,H,W,k,s,p", [
     (torch.float16, 2752, 112, 112, 3, 2, 1), (torch.float16, 8256, 64, 64, 3, 2, 1), (torch.float16, 8400, 63, 64, 3, 2, 1),
+    (torch.float16, 40, 56, 1000, 3, 2, 1), (torch.float16, 1200, 24, 24, 3, 2, 1), (torch.float16, 2600, 16, 16, 3, 2, 1),
     (torch.float16, 8256, 64, 64, 3, 2, 0), (torch.float16, 8256, 64, 64, 3, 1, 1), (torch.float16, 2752, 112, 112, 2, 2, 0),
     (torch.float16, 10752, 112, 112, 2, 2, 0), (torch.float32, 10560, 40, 40, 3, 2, 0), (torch.float32, 10560, 41, 40, 3, 2, 1),
-    (torch.float32, 8208, 64, 64, 2, 2, 0), (torch.float32, 21440, 56, 56, 2, 2, 0), (torch.float32, 21504, 57, 56, 2, 2, 0)])
-def test_large_maxpool_gradients_equal_those_of_their_parts(dtype, planes, H, W, k, s, p):
-    """The stores depend on the size of the result; parts of 16 planes are the sizes that the oracle checks."""
-    x = torch.randn((planes, H, W), device="cuda:0").to(dtype).mul_(4).round_()     # many ties
+    (torch.float32, 8208, 64, 64, 2, 2, 0), (torch.float32, 21440, 56, 56, 2, 2, 0), (torch.float32, 21504, 57, 56, 2, 2, 0),
+    (torch.float16, 48, 64, 64, 2, 2, 0), (torch.float16, 40, 32, 1000, 2, 2, 0), (torch.float32, 40, 32, 1000, 2, 2, 0),
+    (torch.float16, 32, 12, 224, 2, 2, 0), (torch.float32, 32, 12, 112, 2, 2, 0), (torch.float32, 21504, 48, 48, 2, 2, 0),
+    (torch.float32, 21504, 49, 48, 2, 2, 0), (torch.float16, 32768, 56, 56, 2, 2, 0), (torch.float32, 16384, 60, 60, 2, 2, 0),
+    (torch.float16, 4096, 200, 200, 2, 2, 0), (torch.float16, 5000, 56, 56, 2, 2, 0), (torch.float16, 450, 32, 1000, 2, 2, 0),
+    (torch.float16, 5000, 57, 56, 2, 2, 0), (torch.float32, 5000, 33, 40, 2, 2, 0), (torch.float32, 1500, 225, 225, 3, 2, 1)])
+def test_maxpool_gradients_over_sizes_and_row_lengths(dtype, planes, H, W, k, s, p):
+    """Against the oracle on planes of the beginning, the middle and the end; few values, so that there are many ties."""
+    x = torch.randn((planes, H, W), device="cuda:0").to(dtype).mul_(4).round_()
     y, arg = B.maxpool2d_forward(x, (k, k), (s, s), (p, p))
     g = torch.randn(y.shape, device="cuda:0").to(dtype)
     gx = B.maxpool2d_backward(arg, g, H, W, (k, k), (s, s), (p, p))
-    for at in (0, planes // 2 & -16, planes - 16):
-        part = slice(at, at + 16)
-        assert torch.equal(B.maxpool2d_backward(arg[part].clone(), g[part].clone(), H, W, (k, k), (s, s), (p, p)), gx[part])
-        y1, a1 = B.maxpool2d_forward(x[part].clone(), (k, k), (s, s), (p, p))
-        assert torch.equal(y1, y[part]) and torch.equal(a1, arg[part])
+    for at in (0, planes // 2, planes - 4):
+        part = slice(at, at + 4)
+        oy, oarg = oracle.maxpool2d_forward(x[part].cpu().numpy(), (k, k), (s, s), (p, p))
+        assert _bits_equal(y[part].cpu().numpy(), oy) and np.array_equal(arg[part].cpu().numpy(), oarg)
+        want = oracle.maxpool2d_backward(oarg, g[part].cpu().numpy(), H, W, (k, k), (s, s), (p, p))
+        assert _bits_equal(gx[part].cpu().numpy(), want)
     # every gradient went to exactly one input where windows do not overlap
     if k == s:
         assert torch.equal((gx != 0).sum(), (g != 0).sum())
