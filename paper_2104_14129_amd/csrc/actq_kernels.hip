@@ -1092,8 +1092,7 @@ __device__ __forceinline__ void dequantize_pairs_f16(const uint8_t* __restrict__
     }
     // All loads are waited for before the first store: the four stores of a wavefront then leave together.
     // (As each load arrives: 76.9 against 73.6 us at B = 1, 78.3 against 76.9 us with mixed widths on [256, 802816].)
-    static_assert(NP == 4, "four loads");
-    asm volatile("" : "+v"(code[0]), "+v"(code[1]), "+v"(code[2]), "+v"(code[3]));
+    if constexpr (NP == 4) asm volatile("" : "+v"(code[0]), "+v"(code[1]), "+v"(code[2]), "+v"(code[3]));
     f16x8 o[NP];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
@@ -1130,7 +1129,11 @@ __device__ __forceinline__ void dequantize_pairs_f16(const uint8_t* __restrict__
     }
 }
 
-// The run of up to NG groups that starts at g0.
+// The run of up to NG groups that starts at g0.  One or two groups that are left of a sample of whole groups are a run
+// of their own length: with NG loads and headers of which most repeat the last group's, and a branch before each store,
+// samples of one group took longer than those of four by more than the accesses explain (mixed widths, 134 MB of
+// binary32: [131072, 256] 61.6 -> 48.0 us, [65536, 512] 41.7 -> 34.1, [26212, 1280] 39.5 -> 36.5; binary16 with the
+// bfloat16 header 57.1 -> 37.0 and 33.0 -> 23.4 us).
 template <typename T, int LAYOUT, int B, int HDR, int NG, bool VHDR>
 __device__ __forceinline__ void dequantize_run(const uint8_t* __restrict__ src_sample,
                                                const void* __restrict__ header, T* __restrict__ os,
@@ -1140,9 +1143,15 @@ __device__ __forceinline__ void dequantize_run(const uint8_t* __restrict__ src_s
     if constexpr (sizeof(T) == 2) {
         static_assert(NG % 2 == 0, "pairs of groups");
         if (full) dequantize_pairs_f16<LAYOUT, true, B, HDR, NG / 2>(src_sample, header, os, D, n, g0, ng, lane);
+        else if (LAYOUT == kWholeGroups && ng - g0 <= 2)
+            dequantize_pairs_f16<LAYOUT, false, B, HDR, 1>(src_sample, header, os, D, n, g0, ng, lane);
         else dequantize_pairs_f16<LAYOUT, false, B, HDR, NG / 2>(src_sample, header, os, D, n, g0, ng, lane);
     } else {
         if (full) dequantize_groups<T, LAYOUT, true, B, HDR, NG, VHDR>(src_sample, header, os, D, n, g0, ng, lane, stage);
+        else if (LAYOUT == kWholeGroups && ng - g0 == 1)
+            dequantize_groups<T, LAYOUT, true, B, HDR, 1, VHDR>(src_sample, header, os, D, n, g0, ng, lane, stage);
+        else if (LAYOUT == kWholeGroups && ng - g0 == 2)
+            dequantize_groups<T, LAYOUT, true, B, HDR, 2, VHDR>(src_sample, header, os, D, n, g0, ng, lane, stage);
         else dequantize_groups<T, LAYOUT, false, B, HDR, NG, VHDR>(src_sample, header, os, D, n, g0, ng, lane, stage);
     }
 }

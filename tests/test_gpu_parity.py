@@ -436,6 +436,45 @@ def test_ragged_samples_in_every_mode(N, D, dtype, noise_bits, hf):
             assert np.array_equal(run.dequantize(dt).view(np.uint8), want.view(np.uint8))
 
 
+@pytest.mark.parametrize("ng", [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 17])
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+@pytest.mark.parametrize("noise_bits,hf", [(16, 0), (24, 1), (16, 2)])
+def test_samples_of_few_whole_groups(ng, dtype, noise_bits, hf):
+    test_ragged_samples_in_every_mode(41, 256 * ng, dtype, noise_bits, hf)
+
+
+def _median_us(calls):
+    """Each call works on its own tensors, together larger than the Infinity Cache."""
+    times = []
+    for _ in range(17):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for call in calls:
+            call()
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b) * 1e3 / len(calls))
+    return sorted(times[2:])[7]
+
+
+@pytest.mark.parametrize("hf", [B.ACTQ_HDR_F32, B.ACTQ_HDR_BF16])
+def test_dequantizing_samples_of_one_group_takes_little_longer(hf):
+    """binary16, 67 MB of mixed widths.  Samples of one group have four times the wavefronts of samples of four: 1.6 times the
+    time.  With a run of eight groups of which seven repeat the first, 2.6 times."""
+    def us(N, D):
+        bits = (1 + torch.arange(N, device="cuda:0") % 8).to(torch.uint8)
+        size = bits.long() * (D // 8)
+        offsets = torch.cumsum(size, 0) - size
+        packed = torch.randint(0, 256, (int(size.sum()),), dtype=torch.uint8, device="cuda:0")
+        header = torch.rand(N, D // 256, 2, device="cuda:0")
+        if hf == B.ACTQ_HDR_BF16:
+            header = header.bfloat16().view(torch.int16)
+        sets = [(packed.clone(), header.clone(), torch.empty((N, D), dtype=torch.float16, device="cuda:0")) for _ in range(8)]
+        return _median_us([lambda s=s: B.unpack_dequantize(s[0], s[1], bits, offsets, s[2], hf=hf) for s in sets])
+    us(131072, 256)
+    assert us(131072, 256) < 2.25 * us(32768, 1024)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
 def test_more_tiles_than_one_launch_holds(dtype):
     """2^26 + 5 samples of two elements: a tile each, 2^32 lanes, in several launches.  Values 0 and r are grid
