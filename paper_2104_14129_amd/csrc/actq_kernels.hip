@@ -632,12 +632,14 @@ __device__ __forceinline__ void quantize_run_f16(const _Float16* __restrict__ xs
     const bool valid = g < ng;
     g = valid ? g : ng - 1;
     const uint32_t chunk = (g << 3) + (static_cast<uint32_t>(lane) & 7u);   // 64-byte piece of the sample, four noise counters
-    // A full run arrives in the order of the addresses (load p takes kilobyte p, lane l its bytes
+    // A run arrives in the order of the addresses (load p takes kilobyte p, lane l its bytes
     // 16 l .. 16 l + 15) and is dealt to the lanes through the LDS further down; loading a lane's own
     // 64 bytes directly costs a third of the kernel's time (121 against 78 us on the ResNet-50 stem
-    // tensor: four loads whose lanes are 64 bytes apart touch 32 cache lines each).  Only the last,
-    // shorter run of a sample of whole groups is loaded that way.
-    const bool full = RAGGED ? (static_cast<uint64_t>(g0 + kQpGroupsF16) << 8) <= D : g0 + kQpGroupsF16 <= ng;   // the same for the whole wavefront
+    // tensor: four loads whose lanes are 64 bytes apart touch 32 cache lines each).  Past the end of a
+    // sample of whole groups its last piece is repeated, for lanes that store nothing (until then the
+    // shorter run was loaded lane by lane: [26212, 1280] 26.8 -> 20.6 us, and in tiles of four groups,
+    // binary32 [43688, 768] 45.1 -> 26.7 us).
+    const bool full = !RAGGED || (static_cast<uint64_t>(g0 + kQpGroupsF16) << 8) <= D;   // the same for the whole wavefront
     u32x4 x[4];
     if (RAGGED) {
         const _Float16* run = xs + (static_cast<int64_t>(g0) << 8);
@@ -650,11 +652,10 @@ __device__ __forceinline__ void quantize_run_f16(const _Float16* __restrict__ xs
             for (int p = 0; p < 4; ++p) x[p] = guarded_piece(run, static_cast<uint32_t>(8 * (64 * p + lane)), last);
         }
     } else {
-        const uint32_t first = full ? (g0 << 5) + static_cast<uint32_t>(lane) : 4u * chunk;   // in 16-byte pieces of the sample
-        const uint32_t step = full ? 64u : 1u;
-        const u32x4* src = reinterpret_cast<const u32x4*>(xs);
+        const u32x4* src = reinterpret_cast<const u32x4*>(xs) + (static_cast<int64_t>(g0) << 5);
+        const uint32_t last = ((ng - g0) << 5) - 1u;   // the sample's last 16-byte piece
 #pragma unroll
-        for (int p = 0; p < 4; ++p) x[p] = __builtin_nontemporal_load(src + (static_cast<int64_t>(first) + p * step));
+        for (int p = 0; p < 4; ++p) x[p] = __builtin_nontemporal_load(src + min(static_cast<uint32_t>(64 * p + lane), last));
     }
     uint32_t width_word = load_readonly(reinterpret_cast<const uint32_t*>(a.bits) + (n >> 2));
     uint64_t off = load_readonly(a.offsets + n);
@@ -671,15 +672,13 @@ __device__ __forceinline__ void quantize_run_f16(const _Float16* __restrict__ xs
         asm volatile("" : "+v"(rnd[4 * p]), "+v"(rnd[4 * p + 1]), "+v"(rnd[4 * p + 2]), "+v"(rnd[4 * p + 3]));
         __builtin_amdgcn_sched_barrier(0);
     }
-    if (RAGGED || full) {
-        // 16-byte piece i of the run sits at slot i + i / 16: one spare slot per 256 bytes, so that the
-        // sixteen lanes the LDS serves at a time hit every bank once on the way in and on the way out
+    // 16-byte piece i of the run sits at slot i + i / 16: one spare slot per 256 bytes, so that the
+    // sixteen lanes the LDS serves at a time hit every bank once on the way in and on the way out
 #pragma unroll
-        for (int p = 0; p < 4; ++p) stage[68 * p + lane + (lane >> 4)] = x[p];
-        wave_lds_handover();
+    for (int p = 0; p < 4; ++p) stage[68 * p + lane + (lane >> 4)] = x[p];
+    wave_lds_handover();
 #pragma unroll
-        for (int p = 0; p < 4; ++p) x[p] = stage[4 * lane + p + (lane >> 2)];
-    }
+    for (int p = 0; p < 4; ++p) x[p] = stage[4 * lane + p + (lane >> 2)];
     uint32_t xw[16];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
@@ -827,7 +826,7 @@ __device__ __forceinline__ void quantize_tile(const T* __restrict__ xs, uint32_t
     const bool valid = g < ng;
     g = valid ? g : ng - 1;
     const uint32_t chunk = (g << 4) + (static_cast<uint32_t>(lane) & 15u);   // sixteen elements of the sample
-    const bool full = RAGGED ? (static_cast<uint64_t>(g0 + kTileGroups) << 8) <= D : g0 + kTileGroups <= ng;   // the same for the whole wavefront
+    const bool full = !RAGGED || (static_cast<uint64_t>(g0 + kTileGroups) << 8) <= D;   // the same for the whole wavefront
     u32x4 x[kP];
     if (RAGGED) {
         const T* tile = xs + (static_cast<int64_t>(g0) << 8);
@@ -840,11 +839,10 @@ __device__ __forceinline__ void quantize_tile(const T* __restrict__ xs, uint32_t
             for (int p = 0; p < kP; ++p) x[p] = guarded_piece(tile, static_cast<uint32_t>(kE * (64 * p + lane)), last);
         }
     } else {
-        const uint32_t first = full ? g0 * (16 * kP) + static_cast<uint32_t>(lane) : kP * chunk;   // in 16-byte pieces of the sample
-        const uint32_t step = full ? 64u : 1u;
-        const u32x4* src = reinterpret_cast<const u32x4*>(xs);
+        const u32x4* src = reinterpret_cast<const u32x4*>(xs) + static_cast<int64_t>(g0) * (16 * kP);
+        const uint32_t last = (ng - g0) * (16 * kP) - 1u;   // the sample's last 16-byte piece
 #pragma unroll
-        for (int p = 0; p < kP; ++p) x[p] = __builtin_nontemporal_load(src + (static_cast<int64_t>(first) + p * step));
+        for (int p = 0; p < kP; ++p) x[p] = __builtin_nontemporal_load(src + min(static_cast<uint32_t>(64 * p + lane), last));
     }
     uint32_t width_word = load_readonly(reinterpret_cast<const uint32_t*>(a.bits) + (n >> 2));
     uint64_t off = load_readonly(a.offsets + n);
@@ -861,14 +859,12 @@ __device__ __forceinline__ void quantize_tile(const T* __restrict__ xs, uint32_t
         asm volatile("" : "+v"(rnd[4 * p]), "+v"(rnd[4 * p + 1]), "+v"(rnd[4 * p + 2]), "+v"(rnd[4 * p + 3]));
         __builtin_amdgcn_sched_barrier(0);
     }
-    if (RAGGED || full) {
-        // piece i of the tile at slot i + i / 16 (see quantize_run_f16)
+    // piece i of the tile at slot i + i / 16 (see quantize_run_f16)
 #pragma unroll
-        for (int p = 0; p < kP; ++p) stage[68 * p + lane + (lane >> 4)] = x[p];
-        wave_lds_handover();
+    for (int p = 0; p < kP; ++p) stage[68 * p + lane + (lane >> 4)] = x[p];
+    wave_lds_handover();
 #pragma unroll
-        for (int p = 0; p < kP; ++p) x[p] = stage[kP * lane + p + lane * kP / 16];
-    }
+    for (int p = 0; p < kP; ++p) x[p] = stage[kP * lane + p + lane * kP / 16];
     float v[16];
 #pragma unroll
     for (int p = 0; p < kP; ++p)

@@ -475,6 +475,22 @@ def test_dequantizing_samples_of_one_group_takes_little_longer(hf):
     assert us(131072, 256) < 2.25 * us(32768, 1024)
 
 
+@pytest.mark.parametrize("hf", [B.ACTQ_HDR_F32, B.ACTQ_HDR_BF16])
+def test_quantizing_samples_of_three_groups_takes_no_longer(hf):
+    """binary32, 134 MB of mixed widths.  A tile holds four groups: with the same number of wavefronts 0.75 of the work and the same
+    time as samples of four.  With loads 64 bytes apart in the shorter tile, 1.7 times."""
+    def us(N, D):
+        bits = (1 + torch.arange(N, device="cuda:0") % 8).to(torch.uint8)
+        size = bits.long() * (D // 8)
+        offsets = torch.cumsum(size, 0) - size
+        sets = [(torch.randn((N, D), device="cuda:0"), torch.empty(int(size.sum()), dtype=torch.uint8, device="cuda:0"),
+                 torch.empty(N * (D // 256) * 2, dtype=torch.int16 if hf == B.ACTQ_HDR_BF16 else torch.float32, device="cuda:0"))
+                for _ in range(6)]
+        return _median_us([lambda s=s: B.quantize_pack(s[0], bits, offsets, s[1], s[2], 1, 2, 16, hf=hf) for s in sets])
+    us(43688, 768)
+    assert us(43688, 768) < 1.35 * us(32768, 1024)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
 def test_more_tiles_than_one_launch_holds(dtype):
     """2^26 + 5 samples of two elements: a tile each, 2^32 lanes, in several launches.  Values 0 and r are grid
