@@ -1218,12 +1218,35 @@ static void maxpool_backward_typed(const uint8_t* argmax, const T* grad_y, int64
     else maxpool2d_backward_kernel<T, 0><<<grid, kBlock, 0, s>>>(argmax, grad_y, planes, g, grad_x);
 }
 
+// The row kernels number their lanes in 31 bits; larger tensors (34 GB and more) take several launches over ranges of planes
+// (3x3 / 1 / 1 on binary16 [1369572, 112, 112] with a lane per element: forward 64 ms, backward 78; in two launches 19.7 and 25.0).
+// `each` gets the first plane and the number of planes.
+template <typename T, typename Each>
+static void over_planes(int64_t planes, const PoolShape& p, const Each& each)
+{
+    constexpr int64_t kE = 16 / static_cast<int64_t>(sizeof(T));
+    const int64_t height = p.H > p.OH ? p.H : p.OH, width = p.W > p.sw * static_cast<int64_t>(p.OW) ? p.W : p.sw * static_cast<int64_t>(p.OW);
+    const int64_t most = ((int64_t(1) << 31) - 1) / (height * ((width + 1 + kE - 1) / kE));   // a bound on the lanes of either direction
+    int64_t step = planes;
+    if (most >= 1 && (row_geometry(p) || one_sided_row_geometry(p))) {
+        const int64_t launches = (planes + most - 1) / most;
+        step = (planes + launches - 1) / launches;
+    }
+    for (int64_t at = 0; at < planes; at += step) each(at, planes - at < step ? planes - at : step);
+}
+
 int launch_maxpool2d_forward(const void* x, int dtype, int64_t planes, const PoolShape& p, void* y,
                              uint8_t* argmax, void* stream)
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (dtype == ACTQ_F32) maxpool_forward_typed(static_cast<const float*>(x), planes, p, static_cast<float*>(y), argmax, s);
-    else maxpool_forward_typed(static_cast<const _Float16*>(x), planes, p, static_cast<_Float16*>(y), argmax, s);
+    const int64_t in = static_cast<int64_t>(p.H) * p.W, out = static_cast<int64_t>(p.OH) * p.OW;
+    const auto typed = [&](const auto* from, auto* to) {
+        over_planes<std::remove_pointer_t<decltype(to)>>(planes, p, [&](int64_t at, int64_t count) {
+            maxpool_forward_typed(from + at * in, count, p, to + at * out, argmax + at * out, s);
+        });
+    };
+    if (dtype == ACTQ_F32) typed(static_cast<const float*>(x), static_cast<float*>(y));
+    else typed(static_cast<const _Float16*>(x), static_cast<_Float16*>(y));
     return launched("actq_maxpool2d_forward");
 }
 
@@ -1231,10 +1254,14 @@ int launch_maxpool2d_backward(const uint8_t* argmax, const void* grad_y, int dty
                               const PoolShape& p, void* grad_x, void* stream)
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (dtype == ACTQ_F32)
-        maxpool_backward_typed(argmax, static_cast<const float*>(grad_y), planes, p, static_cast<float*>(grad_x), s);
-    else
-        maxpool_backward_typed(argmax, static_cast<const _Float16*>(grad_y), planes, p, static_cast<_Float16*>(grad_x), s);
+    const int64_t in = static_cast<int64_t>(p.H) * p.W, out = static_cast<int64_t>(p.OH) * p.OW;
+    const auto typed = [&](const auto* from, auto* to) {
+        over_planes<std::remove_pointer_t<decltype(to)>>(planes, p, [&](int64_t at, int64_t count) {
+            maxpool_backward_typed(argmax + at * out, from + at * out, count, p, to + at * in, s);
+        });
+    };
+    if (dtype == ACTQ_F32) typed(static_cast<const float*>(grad_y), static_cast<float*>(grad_x));
+    else typed(static_cast<const _Float16*>(grad_y), static_cast<_Float16*>(grad_x));
     return launched("actq_maxpool2d_backward");
 }
 

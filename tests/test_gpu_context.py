@@ -191,6 +191,47 @@ def test_maxpool_padded_along_one_axis_takes_no_longer(k, p, like):
     assert us(p) < 1.4 * us(like)
 
 
+def test_maxpool_with_more_planes_than_a_launch_has_lanes():
+    """2^31 + 5 planes of one element: each is its own maximum, at the centre of its window."""
+    n = (1 << 31) + 5
+    x = torch.arange(-97, 98, device="cuda:0").half().repeat(n // 195 + 1)[:n].view(n, 1, 1)
+    y, arg = B.maxpool2d_forward(x, (3, 3), (2, 2), (1, 1))
+    assert torch.equal(y, x) and int(arg.min()) == 4 and int(arg.max()) == 4
+    y.fill_(float("nan"))
+    assert torch.equal(B.maxpool2d_backward(arg, x, 1, 1, (3, 3), (2, 2), (1, 1), grad_x=y), x)
+
+
+def test_maxpool_beyond_2_to_the_31_lanes_takes_no_longer():
+    """binary16, 34 GB: twice the traffic of half the planes.  With a lane per element it takes six times as long."""
+    planes, some = (1 << 31) // (112 * 14) + 3, 1024
+    part = torch.randn((some, 112, 112), device="cuda:0").half()
+    x = part.repeat((planes + some - 1) // some, 1, 1)[:planes]
+    window = (3, 3), (1, 1), (1, 1)
+    y, arg = torch.empty_like(x), torch.empty(x.shape, dtype=torch.uint8, device="cuda:0")
+    def ms(call):
+        times = []
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            call()
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times)
+    forward = lambda n: ms(lambda: B.maxpool2d_forward(x[:n], *window, (1, 1), y[:n], arg[:n]))
+    half, whole = forward(planes // 2), forward(planes)
+    want, codes = B.maxpool2d_forward(part, *window)
+    places = [(0, some)] + [(k * some, some) for k in (planes // 2 // some, planes // 2 // some + 1)] + [(planes // some * some, planes % some)]
+    for at, count in places:
+        assert torch.equal(y[at:at + count], want[:count]) and torch.equal(arg[at:at + count], codes[:count])
+    backward = lambda n: ms(lambda: B.maxpool2d_backward(arg[:n], x[:n], 112, 112, *window, grad_x=y[:n]))
+    half_back, whole_back = backward(planes // 2), backward(planes)
+    want = B.maxpool2d_backward(codes, part, 112, 112, *window)
+    for at, count in places:
+        assert torch.equal(y[at:at + count], want[:count])
+    assert whole < 2.6 * half and whole_back < 2.6 * half_back, (half, whole, half_back, whole_back)
+
+
 # rows of whole groups of four and of eight, whole 32 and 64 bytes, over even and odd heights
 @pytest.mark.parametrize("dtype", [np.float32, np.float16])
 @pytest.mark.parametrize("k,s,p", [(3, 2, 1), (3, 2, 0), (2, 2, 0), (3, 1, 1)])
