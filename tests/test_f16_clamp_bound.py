@@ -2,8 +2,10 @@
 below 8 bits.  That is sound if, for every range r a binary16 group can have, the largest scaled
 value fl32(r * fl32(B / r)) plus the largest noise (1 - 2^-16), rounded to binary32, stays below
 B + 1 (Sec. 4.1 scaling; every other element of the group scales to no more than the maximum does,
-by monotonicity of rounding).  Checked here on every range with Z = 0 (all positive binary16
-numbers) and on a million random (Z, maximum) pairs; for 8 bits the same computation must find
+by monotonicity of rounding).  With the bfloat16 header r is the stored range, rounded up, which a
+difference of the group never passes; the largest is that of 65504 above a Z rounded down from -65504.
+Checked here on every range with Z = 0 (all positive binary16 numbers), on a million random
+(Z, maximum) pairs and on every bfloat16 range in [2^-24, 2^18]; for 8 bits the same computation must find
 ranges that do reach 256, or the kernel's remaining clamp would be dead code."""
 import numpy as np
 import pytest
@@ -27,7 +29,9 @@ def _ranges() -> np.ndarray:
     fa = (a | sa).view(np.float16).astype(np.float32)
     fc = (c | sc).view(np.float16).astype(np.float32)
     diff = (np.maximum(fa, fc) - np.minimum(fa, fc)).astype(np.float32)
-    return np.concatenate([pos, diff[diff > 0]])
+    low, high = (np.array([v], dtype=np.float32).view(np.uint32)[0] >> 16 for v in (2.0 ** -24, 2.0 ** 18))
+    bf16 = (np.arange(low, high + 1, dtype=np.uint32) << 16).view(np.float32)
+    return np.concatenate([pos, diff[diff > 0], bf16])
 
 
 @pytest.mark.parametrize("b", [1, 2, 3, 4, 5, 6, 7])

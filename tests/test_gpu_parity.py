@@ -602,11 +602,12 @@ def _spread(rng, M, law):
 
 
 # items around the limits of the two kernels: 2048 and 7168 moves, 1024 and 2048 items (one or two per thread of the
-# small kernel), rounds of 4096 items, 16,384 items in registers; remainders of the quadruples
+# small kernel), rounds of 4096 items, 16,384 items in registers, one, two and six further rounds; remainders of the quadruples
 @pytest.mark.parametrize("law", ["wide", "close", "groups", "few", "zero", "one"])
 @pytest.mark.parametrize("M,widths", [(65, 0x102), (128, 0x1FE), (292, 0x1FE), (293, 0x1FE), (682, 0x116), (683, 0x116), (1024, 0x102), (1024, 0x1FE), (1025, 0x102), (1025, 0x1FE), (1337, 0x116),
                                       (1792, 0x11E), (1793, 0x11E), (2047, 0x116), (2048, 0x116), (2049, 0x116), (4096, 0x116),
-                                      (4097, 0x1FE), (4099, 0x106), (16384, 0x116), (16385, 0x116), (16390, 0x1FE)])
+                                      (4097, 0x1FE), (4099, 0x106), (16384, 0x116), (16385, 0x116), (16390, 0x1FE),
+                                      (20480, 0x116), (20481, 0x1FE), (24577, 0x116), (40960, 0x1FE)])
 def test_device_allocator_at_the_limits_of_its_kernels(M, widths, law):
     rng = np.random.default_rng(M)
     w = _spread(rng, M, law)
@@ -672,6 +673,38 @@ def test_device_allocator_edges():
     D2[3] = 0
     got, offs, total, status = _device_alloc(w, D2, 2 * M * 512, P, False)
     assert status == B.ACTQ_EINVAL and np.all(got == 1)
+
+
+# more moves than the small kernel takes; the last items lie in the second round beyond the registers
+@pytest.mark.parametrize("M", [5003, 20481])
+@pytest.mark.parametrize("uniform", [True, False])
+def test_large_device_allocator_edges(M, uniform):
+    rng = np.random.default_rng(M)
+    w = rng.lognormal(0, 2, M).astype(np.float32)
+    D = np.full(M, 512, dtype=np.int64)
+    P = B.ACTQ_WIDTHS_POW2
+    _check_alloc(w, D, 8 * M * 512, P, uniform)            # exactly loose
+    _check_alloc(w, D, 8 * M * 512 - 1, P, uniform)        # one move
+    _check_alloc(w, D, M * 512, P, uniform)                # exactly everything at one bit
+    _check_alloc(w, D, M * 512 - 1, P, uniform)            # infeasible
+    _check_alloc(w, D, 0, P, uniform)
+    _check_alloc(w, D, 3 * M * 512, 1 << 3, uniform)       # a single allowed width
+    _check_alloc(w, D, 3 * M * 512 - 1, 1 << 3, uniform)
+    w[[5, M - 2]] = -0.0                                    # negative zero is a valid, free item
+    _check_alloc(w, D, 2 * M * 512, B.ACTQ_WIDTHS_ALL, uniform)
+    per = np.arange(M) * 64
+    for at in (17, M // 2, M - 4098 if M > 16384 else M - 5, M - 1):   # a register round, the first and the second further one
+        for bad in (np.nan, np.inf, -1.0):
+            w2 = w.copy()
+            w2[at] = bad
+            got, offs, total, status = _device_alloc(w2, D, 2 * M * 512, P, uniform)
+            assert status == B.ACTQ_EINVAL and np.all(got == 1) and np.array_equal(offs, per) and total == M * 64
+        if not uniform:
+            for size in (0, -7):
+                D2 = D.copy()
+                D2[at] = size
+                got, offs, total, status = _device_alloc(w, D2, 2 * M * 512, P, False)
+                assert status == B.ACTQ_EINVAL and np.all(got == 1) and np.array_equal(offs[:at + 1], per[:at + 1])
 
 
 def test_device_allocator_feeds_the_quantizer_without_a_host_hop():
