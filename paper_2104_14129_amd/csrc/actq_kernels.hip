@@ -914,9 +914,9 @@ __device__ __forceinline__ void quantize_tile(const T* __restrict__ xs, uint32_t
 // ------------------------------------------------------------------------------------
 // Sec. 4.1: h^ = code * scale + Z.
 
-// At eight bits, where a quarter (binary16: half) of the traffic are codes that come in, the last store of a
-// wavefront goes out when the others have been acknowledged: binary32 [128, 802816] 85 -> 82 us, binary16 51.9 -> 51.4.
-// At two bits the same wait costs 9 %.
+// binary32 at eight bits, where a fifth of the traffic are codes that come in: the last store of a wavefront
+// goes out when the others have been acknowledged ([128, 802816] 85 -> 82 us).  At two bits the same wait
+// costs 9 %; binary16 is paced by its loads instead (dequantize_pairs_f16).
 __device__ __forceinline__ void wait_for_stores()
 {
     constexpr int kVmcnt0 = 0x0F70;   // vmcnt(0), the other counters as they are
@@ -1085,10 +1085,14 @@ __device__ __forceinline__ void dequantize_pairs_f16(const uint8_t* __restrict__
         const f32x2 hd_odd = load_header<HDR>(header, hdr0 + (FULL ? odd : min(odd, last)), static_cast<float>(code_mask));
         hd[p].x = half ? hd_odd.x : hd_even.x;
         hd[p].y = half ? hd_odd.y : hd_even.y;
+        // At eight bits, where a third of the traffic are codes, a pair's loads stay one behind the other and its
+        // store leaves when they are there (all loads first, all waited for: [256, 802816] 98.5 against 96.3 us with
+        // the binary32 header, 98.0 against 95.9 with the bfloat16 header; [128, 802816] 51.7 against 50.5).
+        if (FULL && B == 8) __builtin_amdgcn_sched_barrier(0);
     }
-    // All loads are waited for before the first store: the four stores of a wavefront then leave together.
+    // Otherwise all loads are waited for before the first store: the four stores of a wavefront then leave together.
     // (As each load arrives: 76.9 against 73.6 us at B = 1, 78.3 against 76.9 us with mixed widths on [256, 802816].)
-    if constexpr (NP == 4) asm volatile("" : "+v"(code[0]), "+v"(code[1]), "+v"(code[2]), "+v"(code[3]));
+    if constexpr (NP == 4 && B != 8) asm volatile("" : "+v"(code[0]), "+v"(code[1]), "+v"(code[2]), "+v"(code[3]));
     f16x8 o[NP];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
@@ -1098,7 +1102,6 @@ __device__ __forceinline__ void dequantize_pairs_f16(const uint8_t* __restrict__
             const uint32_t q = static_cast<uint32_t>(mine >> (k * B)) & code_mask;
             o[p][k] = Io<_Float16>::narrow(__builtin_fmaf(static_cast<float>(q), hd[p].y, hd[p].x));
         }
-        if (FULL && B == 8 && p == NP - 1) wait_for_stores();
         if (FULL) store(run_out + p * 512, o[p]);
     }
     if (FULL) {
