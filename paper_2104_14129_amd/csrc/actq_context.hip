@@ -1123,14 +1123,17 @@ static void maxpool_forward_typed(const T* x, int64_t planes, const PoolShape& p
         dim3 unused;
         const Pool g = make_pool(p, planes, 1, &unused);
         const unsigned blocks = (rows.total + kBlock - 1) / kBlock;
-        // Non-temporal stores: binary32 50 -> 46 us on [4096, 111, 120], binary16 2x2/2 27.9 -> 25.8 us on [4096, 112, 112], 3x3/2
-        // 54.9 -> 52.8 us on [4096, 160, 160]; binary16 rows of other lengths are up to 5 % slower with them (3x3/1 on [65536, 28, 28]
-        // 74 -> 78 us).
-        const bool nt = sizeof(T) == 4 || p.W % 8 == 0;
+        // Non-temporal stores of y and the positions but on rows of other lengths than whole 16 bytes (binary16 3x3/1 on [65536, 28, 28] 74 -> 78 us
+        // with them; binary32 2x2 as in a step, where x has just been written and the layer behind reads y: [6158, 113, 113] alone 88 -> 96 us,
+        // [2052, 113, 113] with a pass over y 33 -> 39).  binary32 3x3 keeps them there too: over a few tensors in turn [4096, 111, 120]
+        // 50 -> 46 us and 3x3/1 on [1026, 113, 113] 35 -> 29, in a step alike alone and 5 to 10 % behind with the pass over y.  On whole 16 bytes,
+        // over a few tensors in turn: binary16 2x2/2 27.9 -> 25.8 us on [4096, 112, 112], 3x3/2 54.9 -> 52.8 us on [4096, 160, 160]; with the pass
+        // over y, results that would have stayed in the Infinity Cache cost 10 to 20 % more.
+        const bool nt = sizeof(T) == 4 ? p.kh == 3 || p.W % 4 == 0 : p.W % 8 == 0;
 #define ACTQ_POOL_ROWS(K, PH, PW, S)                                                                                                         \
     do {                                                                                                                                     \
         if (nt) maxpool2d_forward_rows_kernel<T, K, PH, PW, S, true><<<blocks, kBlock, 0, s>>>(x, g, rows, y, argmax);                       \
-        else if constexpr (sizeof(T) == 2) maxpool2d_forward_rows_kernel<T, K, PH, PW, S, false><<<blocks, kBlock, 0, s>>>(x, g, rows, y, argmax); \
+        else if constexpr (sizeof(T) == 2 || K == 2) maxpool2d_forward_rows_kernel<T, K, PH, PW, S, false><<<blocks, kBlock, 0, s>>>(x, g, rows, y, argmax); \
     } while (0)
         if (p.sh == 1) ACTQ_POOL_ROWS(3, 1, 1, 1);
         else if (p.kh == 2 && p.ph == 0) ACTQ_POOL_ROWS(2, 0, 0, 2);

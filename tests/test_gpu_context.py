@@ -251,7 +251,8 @@ def test_maxpool_aligned_rows(shape, k, s, p, dtype):
     (torch.float16, 32, 12, 224, 2, 2, 0), (torch.float32, 32, 12, 112, 2, 2, 0), (torch.float32, 21504, 48, 48, 2, 2, 0),
     (torch.float32, 21504, 49, 48, 2, 2, 0), (torch.float16, 32768, 56, 56, 2, 2, 0), (torch.float32, 16384, 60, 60, 2, 2, 0),
     (torch.float16, 4096, 200, 200, 2, 2, 0), (torch.float16, 5000, 56, 56, 2, 2, 0), (torch.float16, 450, 32, 1000, 2, 2, 0),
-    (torch.float16, 5000, 57, 56, 2, 2, 0), (torch.float32, 5000, 33, 40, 2, 2, 0), (torch.float32, 1500, 225, 225, 3, 2, 1)])
+    (torch.float16, 5000, 57, 56, 2, 2, 0), (torch.float32, 5000, 33, 40, 2, 2, 0), (torch.float32, 1500, 225, 225, 3, 2, 1),
+    (torch.float32, 6158, 113, 113, 2, 2, 0), (torch.float32, 500, 114, 114, 2, 2, 0), (torch.float16, 12000, 113, 113, 2, 2, 0)])
 def test_maxpool_gradients_over_sizes_and_row_lengths(dtype, planes, H, W, k, s, p):
     """Against the oracle on planes of the beginning, the middle and the end; few values, so that there are many ties."""
     x = torch.randn((planes, H, W), device="cuda:0").to(dtype).mul_(4).round_()
