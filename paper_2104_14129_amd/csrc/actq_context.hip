@@ -293,8 +293,8 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_backward_kernel(const uint8_
 }
 
 // ------------------------------------------------------------------------------------
-// Backward path for square windows K in {2, 3}, stride S in {1, 2}, dilation 1, any legal padding, where the
-// row kernels further down do not apply or lose.  With one element per lane the kernel above is bound by
+// Backward path for square windows K in {2, 3}, stride S in {1, 2}, dilation 1 with the paddings that the row kernels
+// further down do not serve (2x2 / 1, 2x2 / 2 with padding, 3x3 / 1 without, padding along one axis).  With one element per lane the kernel above is bound by
 // instruction issue, not by HBM (a wavefront that produces 256 bytes can afford only about two
 // dozen vector instructions), so here a lane produces four consecutive elements of a row: the
 // index arithmetic, the row checks and the loads of the neighbouring outputs are shared, and
@@ -393,8 +393,8 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_backward_quad_kernel(const u
 // from there comes by a wavefront shift; the wavefront's edge lane takes it through the scalar data path.
 // Columns past the end of a row are read (they belong to the next row) and ignored; the wavefront that
 // would read past the tensor's end goes element by element.
-// Against one output (forward) and four inputs (backward) per lane: 3x3 / 2 / 1 on binary16 [4096, 113, 113]
-// 74 -> 29 us forward and 122 -> 31 us backward, binary32 87 -> 47 and 150 -> 49 us.
+// Against one output (forward) and four inputs (backward) per lane, over a few tensors in turn: 3x3 / 2 / 1 on binary16
+// [4096, 113, 113] 74 -> 29 us forward and 122 -> 31 us backward, binary32 87 -> 47 and 150 -> 49 us.
 struct RowPool {
     uint32_t chunks;              // lanes per row
     FastDiv by_chunks, by_rows;   // by_rows: division by the rows (forward: output rows; backward: stretches of S input rows) of a plane

@@ -54,13 +54,12 @@ constexpr int kBlock = kWave * kWavesPerBlock;
 constexpr int kTileGroups = 4;
 constexpr int kMaxMulti = ACTQ_MAX_TENSORS_PER_CALL;  // tensors of one multi-tensor launch
 
-// Launch shapes of the multi-tensor kernels (which also serve single binary32 tensors of full
-// groups).  Each value was chosen by A/B runs on the 53-tensor ResNet-50 sweep at batch 256,
+// Launch shapes of the statistics, quantizer and dequantizer kernels, for one tensor as for several.
+// Each value was chosen by A/B runs on the 53-tensor ResNet-50 sweep at batch 256,
 // alternatives in brackets.
 constexpr int kDqGroupsF32 = 4;         // dequantizer: groups per wavefront, binary32 output [2, 1: slower]
 constexpr int kDqGroupsF16 = 8;         //              binary16 output: the same 4 KiB per wavefront
 constexpr int kDqBlock = 256;           //              threads per block [512 alike; 1024, 128, 64 slower]
-constexpr bool kDqVectorHeader = true;  //              group headers by lane-uniform vector loads [scalar loads: 10 % slower on cold data]
 constexpr int kDqXcdMap = 1;            //              tiles dealt to the XCDs modulo 8 [plain order: 13 % slower]
 constexpr int kDqRaggedRun = 16;        //              ragged samples: consecutive workgroups' tiles per XCD
 constexpr int kGsBlock = 256;           // statistics: threads per block [64 .. 1024: alike or slower]
@@ -264,10 +263,6 @@ __device__ __forceinline__ uint32_t bf16_ceil_bits(float f)
     return (u >> 16) + (((u & 0xffffu) != 0 && (u >> 31) == 0) ? 1u : 0u);
 }
 
-// (Z, scale = R / B) of group `index` from either header format.
-// Header of group `index` as (Z, step R / B).  HDR: 0 = stored as such in binary32; 1 = (Z, R) in
-// bfloat16; 2 = one (Z, R) pair in binary32 for the whole tensor, the step being 0 when R is 0
-// or B / R overflows (the degenerate rule of the quantizer).
 // A zero the compiler cannot see through, in a vector register: added to a wavefront-uniform
 // index it keeps the load on the vector memory path.
 __device__ __forceinline__ uint32_t vector_zero()
@@ -277,7 +272,11 @@ __device__ __forceinline__ uint32_t vector_zero()
     return z;
 }
 
-// The same header through the vector memory path: every lane loads the same address.
+// Header of group `index` as (Z, step R / B).  HDR: 0 = stored as such in binary32; 1 = (Z, R) in
+// bfloat16; 2 = one (Z, R) pair in binary32 for the whole tensor, the step being 0 when R is 0
+// or B / R overflows (the degenerate rule of the quantizer).
+// This one through the vector memory path: every lane loads the same address (binary32 output;
+// scalar loads are 10 % slower there on cold data).
 template <int HDR>
 __device__ __forceinline__ f32x2 load_header_vector(const void* __restrict__ header, int64_t index, float kB, uint32_t vzero)
 {
@@ -298,6 +297,7 @@ __device__ __forceinline__ f32x2 load_header_vector(const void* __restrict__ hea
     return static_cast<const f32x2*>(header)[index + vzero];
 }
 
+// The same header through the scalar data path, `index` being uniform (binary16 output).
 template <int HDR>
 __device__ __forceinline__ f32x2 load_header(const void* __restrict__ header, int64_t index, float kB)
 {
@@ -412,7 +412,7 @@ __device__ __forceinline__ uint32_t valid_bits(int count, int k)
 //   * a lane works on 32 consecutive elements, so a group is eight lanes and a wavefront
 //     takes a run of EIGHT groups: what is paid once per group and lane (the reduction across
 //     lanes, the two IEEE divisions, addresses, the header) is spread over twice the elements
-//     of the general path's tile.  32 elements are exactly what four Philox calls serve with
+//     of a tile of four groups (quantize_tile).  32 elements are exactly what four Philox calls serve with
 //     16-bit noise: a lane uses all words of its own calls and nothing is traded between
 //     lanes.  The run's four kilobytes are loaded in address order and dealt to the lanes
 //     through the LDS (LDS instructions do not take vector-ALU issue slots);
@@ -939,7 +939,7 @@ __device__ __forceinline__ void end_of_width()
 // the stores of a wavefront would go out one at a time.)  Otherwise (the last run of a sample)
 // groups past the end repeat the loads of the sample's last group, all values are computed, and
 // then what exists is stored.
-template <typename T, int LAYOUT, bool FULL, int B, int HDR, int NG, bool VHDR>
+template <typename T, int LAYOUT, bool FULL, int B, int HDR, int NG>
 __device__ __forceinline__ void dequantize_groups(const uint8_t* __restrict__ src_sample,
                                                   const void* __restrict__ header, T* __restrict__ os,
                                                   int64_t D, uint32_t n, uint32_t g0, uint32_t ng, int lane, uint32_t* stage)
@@ -958,8 +958,7 @@ __device__ __forceinline__ void dequantize_groups(const uint8_t* __restrict__ sr
     const uint32_t shift = first_bit - 8u * byte;
     uint32_t word[NG];
     f32x2 hd[NG];
-    uint32_t vzero = 0;
-    if (VHDR) vzero = vector_zero();
+    const uint32_t vzero = vector_zero();
     // bases of the run: the groups are constant offsets from them (address arithmetic per group cost 2 %)
     const uint8_t* run_src = src_sample + static_cast<uint64_t>(g0) * (32 * B);
     const int64_t hdr0 = static_cast<int64_t>(n) * ng + g0;
@@ -974,8 +973,7 @@ __device__ __forceinline__ void dequantize_groups(const uint8_t* __restrict__ sr
         else if constexpr (kAligned) word[u] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(src));
         else word[u] = __builtin_nontemporal_load(reinterpret_cast<const word_a1*>(src));
         const int64_t index = hdr0 + at;
-        hd[u] = VHDR ? load_header_vector<HDR>(header, index, static_cast<float>(code_mask), vzero)
-                     : load_header<HDR>(header, index, static_cast<float>(code_mask));
+        hd[u] = load_header_vector<HDR>(header, index, static_cast<float>(code_mask), vzero);
     }
     if constexpr (kStaged) {
         constexpr int kWords = NG * 8 * B;
@@ -1133,7 +1131,7 @@ __device__ __forceinline__ void dequantize_pairs_f16(const uint8_t* __restrict__
 // samples of one group took longer than those of four by more than the accesses explain (mixed widths, 134 MB of
 // binary32: [131072, 256] 61.6 -> 48.0 us, [65536, 512] 41.7 -> 34.1, [26212, 1280] 39.5 -> 36.5; binary16 with the
 // bfloat16 header 57.1 -> 37.0 and 33.0 -> 23.4 us).
-template <typename T, int LAYOUT, int B, int HDR, int NG, bool VHDR>
+template <typename T, int LAYOUT, int B, int HDR, int NG>
 __device__ __forceinline__ void dequantize_run(const uint8_t* __restrict__ src_sample,
                                                const void* __restrict__ header, T* __restrict__ os,
                                                int64_t D, uint32_t n, uint32_t g0, uint32_t ng, int lane, uint32_t* stage)
@@ -1146,12 +1144,12 @@ __device__ __forceinline__ void dequantize_run(const uint8_t* __restrict__ src_s
             dequantize_pairs_f16<LAYOUT, false, B, HDR, 1>(src_sample, header, os, D, n, g0, ng, lane);
         else dequantize_pairs_f16<LAYOUT, false, B, HDR, NG / 2>(src_sample, header, os, D, n, g0, ng, lane);
     } else {
-        if (full) dequantize_groups<T, LAYOUT, true, B, HDR, NG, VHDR>(src_sample, header, os, D, n, g0, ng, lane, stage);
+        if (full) dequantize_groups<T, LAYOUT, true, B, HDR, NG>(src_sample, header, os, D, n, g0, ng, lane, stage);
         else if (LAYOUT == kWholeGroups && ng - g0 == 1)
-            dequantize_groups<T, LAYOUT, true, B, HDR, 1, VHDR>(src_sample, header, os, D, n, g0, ng, lane, stage);
+            dequantize_groups<T, LAYOUT, true, B, HDR, 1>(src_sample, header, os, D, n, g0, ng, lane, stage);
         else if (LAYOUT == kWholeGroups && ng - g0 == 2)
-            dequantize_groups<T, LAYOUT, true, B, HDR, 2, VHDR>(src_sample, header, os, D, n, g0, ng, lane, stage);
-        else dequantize_groups<T, LAYOUT, false, B, HDR, NG, VHDR>(src_sample, header, os, D, n, g0, ng, lane, stage);
+            dequantize_groups<T, LAYOUT, true, B, HDR, 2>(src_sample, header, os, D, n, g0, ng, lane, stage);
+        else dequantize_groups<T, LAYOUT, false, B, HDR, NG>(src_sample, header, os, D, n, g0, ng, lane, stage);
     }
 }
 
@@ -1392,16 +1390,15 @@ __global__ __launch_bounds__(kDqBlock) void unpack_dequantize_multi_kernel(Multi
     if (!range_ok(off, static_cast<uint64_t>(ng) * 32u * b, capacity)) return;
     const uint8_t* src = packed + off;
     const uint32_t g0 = c.tile * NG;
-    constexpr bool V = kDqVectorHeader;
     switch (b) {
-        case 1: dequantize_run<T, LAYOUT, 1, HDR, NG, V>(src, header, os, D, n, g0, ng, lane, stage); break;
-        case 2: dequantize_run<T, LAYOUT, 2, HDR, NG, V>(src, header, os, D, n, g0, ng, lane, stage); break;
-        case 3: dequantize_run<T, LAYOUT, 3, HDR, NG, V>(src, header, os, D, n, g0, ng, lane, stage); break;
-        case 4: dequantize_run<T, LAYOUT, 4, HDR, NG, V>(src, header, os, D, n, g0, ng, lane, stage); break;
-        case 5: dequantize_run<T, LAYOUT, 5, HDR, NG, V>(src, header, os, D, n, g0, ng, lane, stage); break;
-        case 6: dequantize_run<T, LAYOUT, 6, HDR, NG, V>(src, header, os, D, n, g0, ng, lane, stage); break;
-        case 7: dequantize_run<T, LAYOUT, 7, HDR, NG, V>(src, header, os, D, n, g0, ng, lane, stage); break;
-        case 8: dequantize_run<T, LAYOUT, 8, HDR, NG, V>(src, header, os, D, n, g0, ng, lane, stage); break;
+        case 1: dequantize_run<T, LAYOUT, 1, HDR, NG>(src, header, os, D, n, g0, ng, lane, stage); break;
+        case 2: dequantize_run<T, LAYOUT, 2, HDR, NG>(src, header, os, D, n, g0, ng, lane, stage); break;
+        case 3: dequantize_run<T, LAYOUT, 3, HDR, NG>(src, header, os, D, n, g0, ng, lane, stage); break;
+        case 4: dequantize_run<T, LAYOUT, 4, HDR, NG>(src, header, os, D, n, g0, ng, lane, stage); break;
+        case 5: dequantize_run<T, LAYOUT, 5, HDR, NG>(src, header, os, D, n, g0, ng, lane, stage); break;
+        case 6: dequantize_run<T, LAYOUT, 6, HDR, NG>(src, header, os, D, n, g0, ng, lane, stage); break;
+        case 7: dequantize_run<T, LAYOUT, 7, HDR, NG>(src, header, os, D, n, g0, ng, lane, stage); break;
+        case 8: dequantize_run<T, LAYOUT, 8, HDR, NG>(src, header, os, D, n, g0, ng, lane, stage); break;
         default: return;
     }
 }
@@ -1556,7 +1553,7 @@ __global__ __launch_bounds__(kSensMaxBlock) void sample_sensitivity_kernel(const
 //   * select_price narrows a bracket [lo, hi] of price patterns, starting from the smallest and
 //     the largest candidate instead of from 64 free bits, and stops as soon as at most 64
 //     candidates are left: mostly one histogram instead of eight;
-//   * a small problem (allocate_bits_small_kernel) has one move per thread and every price in LDS;
+//   * a small problem (allocate_bits_small_kernel: up to 2048 items and 7168 moves) has every price in LDS;
 //   * a large one (allocate_bits_kernel) does not price its moves at all at first.  A price is
 //     (w / D) * c_r to within a few units in the last place, so a histogram of the ITEMS over
 //     w / D gives bounds of the bits freed below any price t: sum_r dw_r * (elements of the items
@@ -2031,7 +2028,10 @@ typedef int64_t i64x2_a8 __attribute__((ext_vector_type(2), aligned(8)));
 
 // Any M.  A thread's items come in quadruples of consecutive ones, 4096 items per round; the
 // bins (ratios, before there are bins) and element counts of the first kAllocQuads rounds stay in registers.
-// M >= 4: the small kernel takes everything up to 1024 items.
+// M >= 4: the small kernel takes everything up to 1024 items, which is at most 7168 moves.
+// More than kAllocList undecided moves are priced again in every turn of select_price, which the ties end:
+// 13,568 items {1, 2, 4, 8} take 28.5 us with log-normal sensitivities, 30.7 with prices a unit apart, 69 if all
+// are one and 89 if all are zero (eight widths: 30.3, 32.4, 71 and 130).
 __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float* __restrict__ w, AllocArgs a,
                                                                     uint8_t* __restrict__ bits,
                                                                     uint64_t* __restrict__ offsets,
