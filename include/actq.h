@@ -275,7 +275,9 @@ int actq_allocate_bits_device(const float* w, const int64_t* D_items, int64_t D,
  *
  * The descriptor array lives in HOST memory and is copied into the launch; the
  * pointers inside are device pointers with the alignment rules of the
- * single-tensor calls.  Fields a call does not use may be NULL.
+ * single-tensor calls (so where several tensors' widths lie one behind the other
+ * in one array, N must be a multiple of four: `bits` is 4-byte aligned).  Fields
+ * a call does not use may be NULL.
  */
 #define ACTQ_MAX_TENSORS_PER_CALL 40
 typedef struct actq_tensor {

@@ -39,6 +39,8 @@ def size_classes(Ds, max_per_call: int = B.MAX_TENSORS_PER_CALL, small: int = 0)
 
 class TensorSetPlan:
     """Buffers, tables and launches for tensors x[l] of shape [N, Ds[l]] (one dtype, full groups).
+    N must be a multiple of four if there are several tensors: their widths lie one behind the other and each
+    tensor's must start at an aligned word, otherwise `quantize_pack` and `unpack_dequantize` are refused.
 
     All items (tensor l, sample n) share one bit stream `packed`; item l*N + n has its width in
     `bits` and its byte offset in `offsets`, both written by the device-side allocator
