@@ -1553,20 +1553,19 @@ __global__ __launch_bounds__(kSensMaxBlock) void sample_sensitivity_kernel(const
 // (i, r) order until the budget holds.  One workgroup finds the threshold and works out of LDS;
 // a prefix sum then turns the widths into byte offsets.
 //
-// What bounds it: one workgroup has one compute unit, so the number of (binary64) divisions, LDS
-// atomics and barriers is the time.  A radix selection over the 64-bit patterns of all prices
-// (eight passes of eight bits) took 154 us for 13,568 items with all eight widths, 101 us with
-// {1, 2, 4, 8}, and 10 us for 128 items.  Hence:
-//   * select_price narrows a bracket [lo, hi] of price patterns, starting from the smallest and
-//     the largest candidate instead of from 64 free bits, and stops as soon as at most 64
-//     candidates are left: mostly one histogram instead of eight;
-//   * a small problem (allocate_bits_small_kernel: up to 2048 items and 7168 moves) has every price in LDS;
+// What bounds it: one workgroup has one compute unit, and most phases are chains of dependent instructions, LDS round trips
+// and barriers.  A radix selection over the 64-bit patterns of all prices (eight passes of eight bits) took 154 us for 13,568
+// items with all eight widths, 101 us with {1, 2, 4, 8}, and 10 us for 128 items.  Hence:
+//   * a small problem (allocate_bits_small_kernel: up to 1024 items, 2048 of one size) has every price in registers and takes one
+//     histogram over the range of the prices: the bin that holds the threshold has a handful of moves, which are ranked;
 //   * a large one (allocate_bits_kernel) does not price its moves at all at first.  A price is
 //     (w / D) * c_r to within a few units in the last place, so a histogram of the ITEMS over
 //     w / D gives bounds of the bits freed below any price t: sum_r dw_r * (elements of the items
 //     with w / D < t / c_r).  A search over t on that table leaves a bracket that holds the
-//     threshold and, typically, one or two hundred of the 95,000 moves; only those are priced
-//     exactly, and the widths of all other items follow from comparing w / D with t / c_r.
+//     threshold and, typically, one or two hundred of the 95,000 moves; only the items of those are priced
+//     exactly, and the widths of all other items follow from comparing w / D with t / c_r;
+//   * many (nearly) equal prices are left to select_price, which narrows a bracket [lo, hi] of price patterns until at most
+//     64 candidates are left.
 // The order of w / D is taken from the upper 32 bits of its binary64 pattern (20 bits of mantissa),
 // computed to within one unit.  Every comparison on it leaves a margin of two units: what passes is
 // cheaper (dearer) by one unit at least, 2^-21, and the rounding errors of t / c_r and of the price
@@ -1576,19 +1575,24 @@ __global__ __launch_bounds__(kSensMaxBlock) void sample_sensitivity_kernel(const
 constexpr int kAllocBlock = 1024;
 constexpr int kAllocWavesMax = kAllocBlock / kWave;
 constexpr int kMaxSteps = 7;
-// Moves of the small kernel.  Where it ends: 1024 items with all widths 18 against 26 us with the large kernel, 2048 items
-// with {1, 2, 4, 8} 20 against 24 us; what lies beyond (1300 items with all widths, 25 us) is as fast in the large one.
-constexpr int kSmallMoves = 2048;                          // at most two per thread
-constexpr int kMostSmallMoves = kAllocBlock * kMaxSteps;   // at most seven per thread
+// Items per thread of the small kernel from 1025 items on, if they are of one size (2048 with all widths 12.5 against 14.4 us with the
+// large kernel, with {1, 2, 4, 8} 9.7 against 13.2).  With sizes of their own it ends at 1024 (12.0 us; 2048 18.5 against 14.4 us).
+constexpr int kSmallItems = 2;
 constexpr int kAllocBins = 4096;      // bins of the large kernel's table over w / D
-constexpr int kAllocList = 1024;      // exactly priced moves the large kernel keeps in LDS
+constexpr int kAllocList = 1024;      // items with undecided steps the large kernel lists: one per thread
 constexpr int kAllocQuads = 4;        // quadruples of consecutive items per thread kept in registers: 16,384 items in all
+
+// What the budget is compared with.
+struct AllocBudget {
+    uint64_t bits;
+    uint32_t widest, narrowest;   // allowed widths
+};
 
 struct AllocArgs {
     int64_t M;
     int64_t D;               // element count of every item when D_items is null
     const int64_t* D_items;  // per-item element counts, or null
-    int64_t budget_bits;
+    AllocBudget total;
     Ladder lad;
     double inverse[kMaxSteps];   // 1 / lad.price[r]
     uint32_t width_nibbles;      // lad.width[k] in bits 4 k .. 4 k + 3
@@ -1618,7 +1622,21 @@ __device__ __forceinline__ uint64_t read_lane(uint64_t v, int src)
     return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
+__device__ __forceinline__ uint32_t read_lane(uint32_t v, int src)
+{
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), src));
+}
+
 // Inclusive prefix sum inside each row of sixteen lanes.
+__device__ __forceinline__ uint32_t row_inclusive_scan(uint32_t v)
+{
+    v += dpp_u32<0x111>(v);   // row_shr:1, 2, 4, 8 with zero fill
+    v += dpp_u32<0x112>(v);
+    v += dpp_u32<0x114>(v);
+    v += dpp_u32<0x118>(v);
+    return v;
+}
+
 __device__ __forceinline__ uint64_t row_inclusive_scan(uint64_t v)
 {
     v += row_shift_right<1>(v);
@@ -1642,9 +1660,18 @@ __device__ __forceinline__ uint64_t wave_inclusive_scan(uint64_t v, int lane)
     return v + before;
 }
 
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v, int)
+{
+    v = row_inclusive_scan(v);
+    v += static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x142, 0xa, 0xf, false));   // row_bcast:15 to rows 1 and 3
+    v += static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x143, 0xc, 0xf, false));   // row_bcast:31 to rows 2 and 3
+    return v;
+}
+
 struct Add { template <typename V> __device__ V operator()(V a, V b) const { return a + b; } };
 struct Min { template <typename V> __device__ V operator()(V a, V b) const { return a < b ? a : b; } };
 struct Max { template <typename V> __device__ V operator()(V a, V b) const { return a > b ? a : b; } };
+struct Or { template <typename V> __device__ V operator()(V a, V b) const { return a | b; } };
 
 // Reduction over each row of sixteen lanes, in every lane of it.
 template <typename Op>
@@ -1675,6 +1702,17 @@ __device__ __forceinline__ uint64_t wave_reduce(uint64_t v, Op op)
     return op(op(read_lane(v, 0), read_lane(v, 16)), op(read_lane(v, 32), read_lane(v, 48)));
 }
 
+// Reduction over each row of sixteen lanes of 32-bit values, read from its first lane.
+template <typename Op>
+__device__ __forceinline__ uint32_t row_result(uint32_t v, Op op)
+{
+    v = op(v, dpp_u32<kDppXor1>(v));
+    v = op(v, dpp_u32<kDppXor2>(v));
+    v = op(v, dpp_u32<kDppHalfMirror>(v));
+    v = op(v, dpp_u32<kDppXor8>(v));
+    return read_lane(v, 0);
+}
+
 // Second half of a reduction over the workgroup, behind a barrier: the wavefronts' results.
 template <typename Op>
 __device__ __forceinline__ uint64_t combine_waves(const uint64_t* of_wave, int waves, uint64_t identity, Op op)
@@ -1685,17 +1723,18 @@ __device__ __forceinline__ uint64_t combine_waves(const uint64_t* of_wave, int w
 
 // Exclusive prefix sum over the workgroup in thread order; `total` receives the sum.  One barrier;
 // `of_wave` (one entry per wavefront) must not be in use by anything else until the next barrier.
-__device__ __forceinline__ uint64_t block_exclusive_scan(uint64_t v, uint64_t* of_wave, uint64_t& total)
+template <typename V>
+__device__ __forceinline__ V block_exclusive_scan(V v, V* of_wave, V& total)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int waves = blockDim.x >> 6;
-    const uint64_t incl = wave_inclusive_scan(v, lane);
+    const V incl = wave_inclusive_scan(v, lane);
     if (lane == kWave - 1) of_wave[wave] = incl;
     __syncthreads();
     const int k = lane & 15;
-    const uint64_t own = k < waves ? of_wave[k] : 0;
-    const uint64_t upto = row_inclusive_scan(own);
+    const V own = k < waves ? of_wave[k] : V(0);
+    const V upto = row_inclusive_scan(own);
     total = read_lane(upto, 15);
     return read_lane(upto, wave) - read_lane(own, wave) + incl - v;
 }
@@ -1816,9 +1855,12 @@ __device__ Threshold select_price(const Each& each, uint64_t n, uint64_t lo, uin
     return Threshold{read_lane(key, src), below + read_lane(cheaper, src), read_lane(ties, src)};
 }
 
+// The sensitivity finite and not negative (see valid_sensitivity_bits), 0 < D < 2^34.
 __device__ __forceinline__ bool valid_item(float w, int64_t D)
 {
-    return valid_sensitivity_bits(__float_as_uint(w)) && D > 0 && D < (int64_t(1) << 34);
+    constexpr int kZeroOrPositive = 0x1E0;   // either zero, positive subnormal, positive normal
+    const uint32_t low = static_cast<uint32_t>(D), high = static_cast<uint32_t>(static_cast<uint64_t>(D) >> 32);
+    return __builtin_amdgcn_classf(w, kZeroOrPositive) & (high < 4u) & ((low | high) != 0u);
 }
 
 __device__ __forceinline__ uint64_t stream_bytes(int64_t D, int width)
@@ -1833,15 +1875,13 @@ struct AllocVerdict {
     int64_t status;
 };
 
-__device__ __forceinline__ AllocVerdict alloc_verdict(uint64_t elems, bool invalid, const AllocArgs& a)
+__host__ __device__ inline AllocVerdict alloc_verdict(uint64_t elems, bool invalid, const AllocBudget& b)
 {
-    const uint64_t budget = static_cast<uint64_t>(a.budget_bits);
-    const uint64_t widest = static_cast<uint64_t>(a.lad.width[0]), narrowest = static_cast<uint64_t>(a.lad.width[a.lad.count - 1]);
     AllocVerdict v;
-    v.loose = !invalid && elems * widest <= budget;
-    const bool infeasible = !invalid && elems * narrowest > budget;
+    v.loose = !invalid && elems * b.widest <= b.bits;
+    const bool infeasible = !invalid && elems * b.narrowest > b.bits;
     v.search = !invalid && !v.loose && !infeasible;
-    v.need = elems * widest - budget;
+    v.need = elems * b.widest - b.bits;
     v.status = invalid ? ACTQ_EINVAL : (infeasible ? ACTQ_EINFEASIBLE : ACTQ_OK);
     return v;
 }
@@ -1858,128 +1898,320 @@ __device__ __forceinline__ double ladder_price(const Ladder& lad, int k)
     return v;
 }
 
-// At most MOVES moves and ITEMS items per thread: every price in LDS (2048 moves: 37 of the 160 KB; 7168: 119).
-template <int MOVES, int ITEMS>
-__global__ __launch_bounds__(kAllocBlock) void allocate_bits_small_kernel(const float* __restrict__ w, AllocArgs a,
+constexpr int kSmallBins = 512;
+
+// The bin of `hist` in which the running sum of freed bits, from `start` on, reaches `need`; `below`: the sum before it.  Every
+// wavefront for itself; exactly one lane holds the bin.
+template <typename Amount>
+__device__ __forceinline__ uint32_t winning_bin(const Amount* hist, Amount need, Amount start, int lane, Amount& below)
+{
+    constexpr int kPer = kSmallBins / kWave;
+    Amount hb[kPer], mine = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) { hb[k] = hist[kPer * lane + k]; mine += hb[k]; }
+    Amount run = start + wave_inclusive_scan(mine, lane) - mine;
+    const uint64_t vote = __ballot(run < need && run + mine >= need);
+    uint32_t digit = static_cast<uint32_t>(kPer * lane);
+    bool found = false;
+#pragma unroll
+    for (int k = 0; k + 1 < kPer; ++k) {
+        found = found || run + hb[k] >= need;
+        run += found ? Amount(0) : hb[k];
+        digit += found ? 0u : 1u;
+    }
+    const int src = vote ? __builtin_ctzll(vote) : 0;
+    below = read_lane(run, src);
+    return read_lane(digit, src);
+}
+
+// The threshold among n <= 64 moves, one per lane, ranked from registers: its price, the bits freed by the cheaper moves and
+// the number of moves of this price.  Every wavefront for itself.
+template <typename Amount>
+__device__ __forceinline__ void rank_moves(const uint64_t* keys, const Amount* amounts, int n, Amount need, Amount start, int lane,
+                                           uint64_t& price, Amount& below, uint64_t& count)
+{
+    const bool listed = lane < n;
+    const uint64_t own = listed ? keys[lane] : ~uint64_t(0);
+    const Amount frees = listed ? amounts[lane] : Amount(0);
+    Amount cheaper = 0, upto = 0;
+    uint32_t ties = 0;
+    for (int k = 0; k < n; ++k) {
+        const uint64_t other = read_lane(own, k);
+        const Amount freed = read_lane(frees, k);
+        cheaper += other < own ? freed : Amount(0);
+        upto += other <= own ? freed : Amount(0);
+        ties += other == own ? 1u : 0u;
+    }
+    const uint64_t vote = __ballot(listed && start + cheaper < need && start + upto >= need);
+    const int src = vote ? __builtin_ctzll(vote) : 0;
+    price = read_lane(own, src);
+    below = start + read_lane(cheaper, src);
+    count = read_lane(ties, src);
+}
+
+// The threshold among n moves, which `each(f)` enumerates, with many (nearly) equal prices: the bracket starts at the smallest and the
+// largest of them, and equal ones need no more than that.  Called by the whole workgroup.
+template <typename Each>
+__device__ __forceinline__ Threshold select_among(const Each& each, uint64_t n, uint64_t need, uint64_t below, SelectLds& s)
+{
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), waves = blockDim.x >> 6;
+    uint64_t least = ~uint64_t(0), most = 0;
+    each([&](uint64_t key, uint64_t) {
+        least = key < least ? key : least;
+        most = key > most ? key : most;
+    });
+    least = wave_reduce(least, Min());
+    most = wave_reduce(most, Max());
+    for (int k = tid; k < 2 * kSelectBins; k += blockDim.x) (&s.hist[0][0])[k] = 0;
+    if (tid < 2) s.count[tid] = 0;
+    if (lane == 0) {
+        s.least[tid >> 6] = least;
+        s.most[tid >> 6] = most;
+    }
+    __syncthreads();
+    return select_price(each, n, combine_waves(s.least, waves, ~uint64_t(0), Min()), combine_waves(s.most, waves, 0, Max()), need, below, s);
+}
+
+// What the small kernel is told.  Items of one size: the totals are known on the host, and with them what they decide and how
+// much is to be freed, in units of D bits.
+struct SmallAllocArgs {
+    int32_t M, steps;
+    uint32_t width_nibbles;      // lad.width[k] in bits 4 k .. 4 k + 3
+    uint32_t need;               // items of one size: units to free
+    int32_t status;              // items of one size: ACTQ_OK or ACTQ_EINFEASIBLE
+    uint32_t search, loose;
+    uint64_t unit_bytes;         // items of one size: stream bytes per bit of width
+    int64_t D;                   // element count of every item when D_items is null
+    double reciprocal;           // 1 / D
+    const int64_t* D_items;      // per-item element counts, or null
+    AllocBudget total;           // per-item sizes
+    double price[kMaxSteps];     // of step r, for a unit of w / D; ascending
+};
+
+// (w c) / d as one IEEE division gives it, from y = 1 / d rounded to nearest (d an integer below 2^34, w c between 2^-165 and
+// 2^128 or zero: nothing over- or underflows).  The first correction makes the quotient one of the two binary64 numbers around
+// the true one, the second picks the nearer (Markstein's theorem on quotients by a correctly rounded reciprocal).
+__device__ __forceinline__ uint64_t quotient_bits(double a, double d, double y)
+{
+    double q = a * y;
+    q = __builtin_fma(__builtin_fma(-q, d, a), y, q);
+    q = __builtin_fma(__builtin_fma(-q, d, a), y, q);
+    return static_cast<uint64_t>(__double_as_longlong(q + 0.0));   // -0.0 becomes +0.0
+}
+
+// ITEMS consecutive items per thread, all their prices in registers.  UNIFORM: items of one size.
+// A problem of this size is one chain of dependent instructions in a few wavefronts, so what counts is their number: prices by a
+// reciprocal instead of a division each, minimum and maximum of the prices from the upper halves of their patterns, freed bits as
+// 32-bit multiples of the common size, one histogram that leaves a handful of moves, and those ranked from registers.  Many (nearly)
+// equal prices go on to select_among.  Kernel durations with a thread per move and the prices in LDS, and so, items of one size:
+// 4 with {1, 2, 4, 8} 4.8 -> 3.6 us, 128 5.3 -> 3.7, 256 with all widths 7.7 -> 4.4, 1024 16.1 -> 7.6, 2048 23.0 -> 12.5;
+// per-item sizes: 300 with all widths 8.8 -> 5.6, 1024 17.2 -> 12.0.
+template <bool UNIFORM, int ITEMS>
+__global__ __launch_bounds__(kAllocBlock) void allocate_bits_small_kernel(const float* __restrict__ w, SmallAllocArgs a,
                                                                           uint8_t* __restrict__ bits,
                                                                           uint64_t* __restrict__ offsets,
                                                                           int64_t* __restrict__ result)
 {
-    __shared__ uint64_t key[MOVES], amount[MOVES];   // move r * M + i
+    typedef typename std::conditional<UNIFORM, uint32_t, uint64_t>::type Amount;   // freed bits: units of D, or bits
+    __shared__ Amount hist[kSmallBins];
+    __shared__ uint64_t list_key[kWave];
+    __shared__ Amount list_amount[kWave];
+    __shared__ uint32_t list_count;
+    __shared__ uint32_t wave_lo[kAllocWavesMax], wave_hi[kAllocWavesMax];
+    __shared__ uint64_t wave_elems[kAllocWavesMax], wave_ties[kAllocWavesMax];
+    __shared__ Amount wave_sum[kAllocWavesMax];
     __shared__ SelectLds sel;
-    __shared__ uint64_t wave_elems[kAllocWavesMax], wave_lo[kAllocWavesMax], wave_hi[kAllocWavesMax], wave_bad[kAllocWavesMax];
-    __shared__ uint64_t wave_ties[kAllocWavesMax], wave_bytes[kAllocWavesMax];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
-    const int threads = blockDim.x, waves = threads >> 6;
-    const int M = static_cast<int>(a.M), steps = a.lad.count - 1, moves = M * steps;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), threads = blockDim.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = threads >> 6;
+    const int M = a.M, steps = a.steps;
     const int first = tid * ITEMS;   // the thread's items, consecutive ones
+    const auto width_of = [&](int k) { return static_cast<int>((a.width_nibbles >> (4 * k)) & 15u); };
     float wi[ITEMS];
     int64_t Di[ITEMS];
 #pragma unroll
     for (int q = 0; q < ITEMS; ++q) {
-        const bool live = first + q < M;
-        wi[q] = live ? w[first + q] : 0.0f;
-        Di[q] = live ? (a.D_items ? a.D_items[first + q] : a.D) : 0;
+        const int i = first + q < M ? first + q : M - 1;
+        wi[q] = w[i];
+        Di[q] = UNIFORM ? a.D : a.D_items[i];
     }
-    uint64_t lo = ~uint64_t(0), hi = 0;
-    for (int e = tid; e < moves; e += threads) {
-        const int r = static_cast<int>(static_cast<uint32_t>(e) / static_cast<uint32_t>(M)), i = e - r * M;
-        const float wm = w[i];
-        int64_t Dm = a.D_items ? a.D_items[i] : a.D;
-        if (!valid_item(wm, Dm)) Dm = 1;   // the whole problem is invalid then, and nothing is searched
-        const uint64_t k = price_bits(wm, Dm, ladder_price(a.lad, r));
-        key[e] = k;
-        amount[e] = static_cast<uint64_t>(Dm) * static_cast<uint64_t>(ladder_width(a, r) - ladder_width(a, r + 1));
-        lo = k < lo ? k : lo;
-        hi = k > hi ? k : hi;
-    }
-    for (int k = tid; k < 2 * kSelectBins; k += threads) (&sel.hist[0][0])[k] = 0;
-    if (tid < 2) sel.count[tid] = 0;
-    uint64_t my_elems = 0;
-    bool my_bad = false;
+    for (int k = tid; k < kSmallBins; k += threads) hist[k] = 0;
+    if (tid == 0) list_count = 0;
+    uint64_t key[ITEMS][kMaxSteps];   // steps that do not exist: no price
+    uint32_t lo = ~0u, hi = 0;        // upper halves of the prices; invalid items: bit 31 of hi
+    uint64_t elems = 0;
 #pragma unroll
     for (int q = 0; q < ITEMS; ++q) {
-        const bool live = first + q < M, ok = live && valid_item(wi[q], Di[q]);
-        my_elems += ok ? static_cast<uint64_t>(Di[q]) : uint64_t(0);
-        my_bad = my_bad || (live && !ok);
+        const bool live = first + q < M;
+        const bool ok = UNIFORM ? valid_sensitivity_bits(__float_as_uint(wi[q])) : valid_item(wi[q], Di[q]);
+        if (!UNIFORM) {
+            elems += live && ok ? static_cast<uint64_t>(Di[q]) : uint64_t(0);
+            if (Di[q] <= 0 || Di[q] >= (int64_t(1) << 34)) Di[q] = 1;   // invalid input: stay memory-safe
+        }
+        const double d = static_cast<double>(Di[q]), y = UNIFORM ? a.reciprocal : 1.0 / d, weight = static_cast<double>(wi[q]);
+        uint32_t top = 0;
+#pragma unroll
+        for (int r = 0; r < kMaxSteps; ++r) {
+            key[q][r] = ~uint64_t(0);
+            if (r < steps) {
+                const uint64_t k = quotient_bits(weight * a.price[r], d, y);
+                key[q][r] = live ? k : ~uint64_t(0);
+                top = static_cast<uint32_t>(k >> 32);   // the last step is the dearest
+            }
+        }
+        const uint32_t least = static_cast<uint32_t>(key[q][0] >> 32);
+        lo = least < lo ? least : lo;
+        top = ok ? top : 0x80000000u;
+        hi = live && top > hi ? top : hi;
     }
-    const uint64_t e64 = wave_reduce(my_elems, Add());
     lo = wave_reduce(lo, Min());
     hi = wave_reduce(hi, Max());
-    const uint64_t bad = __ballot(my_bad);
-    if (lane == 0) {
-        wave_elems[wave] = e64;
-        wave_lo[wave] = lo;
-        wave_hi[wave] = hi;
-        wave_bad[wave] = bad;
+    if (!UNIFORM) elems = wave_reduce(elems, Add());
+    if (waves > 1) {
+        if (lane == 0) {
+            wave_lo[wave] = lo;
+            wave_hi[wave] = hi;
+            if (!UNIFORM) wave_elems[wave] = elems;
+        }
+        __syncthreads();
+        const int k = lane & 15, at = k < waves ? k : 0;
+        lo = row_result(wave_lo[at], Min());
+        hi = row_result(wave_hi[at], Max());
+        if (!UNIFORM) elems = combine_waves(wave_elems, waves, 0, Add());
+    } else {
+        __syncthreads();   // the histogram is cleared
     }
-    __syncthreads();
-    const uint64_t elems = combine_waves(wave_elems, waves, 0, Add());
-    const bool invalid = combine_waves(wave_bad, waves, 0, Max()) != 0;
-    const AllocVerdict v = alloc_verdict(elems, invalid, a);
-    Threshold t = {0, 0, 0};
-    if (v.search) {
-        const auto each = [&](auto f) {
-            for (int e = tid; e < moves; e += threads) f(key[e], amount[e]);
-        };
-        t = select_price(each, static_cast<uint64_t>(moves), combine_waves(wave_lo, waves, ~uint64_t(0), Min()),
-                         combine_waves(wave_hi, waves, 0, Max()), v.need, 0, sel);
+    const bool invalid = (hi >> 31) != 0;
+    bool search = a.search != 0, loose = a.loose != 0;
+    int64_t status = a.status;
+    Amount need = static_cast<Amount>(a.need);
+    if (!UNIFORM) {
+        const AllocVerdict v = alloc_verdict(elems, false, a.total);
+        search = v.search;
+        loose = v.loose;
+        status = v.status;
+        need = static_cast<Amount>(v.need);
+    }
+    if (invalid) {
+        search = loose = false;
+        status = ACTQ_EINVAL;
+    }
+    const auto freed_by = [&](int q, int from, int to) {   // by going from rung `from` to rung `to`
+        return static_cast<Amount>(UNIFORM ? 1 : Di[q]) * static_cast<Amount>(width_of(from) - width_of(to));
+    };
+
+    uint64_t threshold = 0;    // the price of the last move,
+    Amount below = 0;          // the bits freed by all cheaper ones,
+    uint64_t at_threshold = 0; // and how many moves have exactly this price
+    if (search) {
+        // the bin in which the running sum of freed bits reaches `need`
+        const uint32_t span = hi - lo;
+        int shift = 23 - __builtin_clz(span | 1u);   // (span >> shift) < 512
+        shift = shift > 0 ? shift : 0;
+        const auto bin_of = [&](uint64_t k) { return (static_cast<uint32_t>(k >> 32) - lo) >> shift; };
+        uint32_t digit = 0, here = 0;
+        int n = M * steps;
+        if (span != 0) {
+#pragma unroll
+            for (int q = 0; q < ITEMS; ++q)
+#pragma unroll
+                for (int r = 0; r < kMaxSteps; ++r)
+                    if (r < steps && first + q < M)
+                        __hip_atomic_fetch_add(&hist[bin_of(key[q][r])], freed_by(q, r, r + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            __syncthreads();
+            digit = winning_bin(hist, need, Amount(0), lane, below);
+        }
+        // its moves
+#pragma unroll
+        for (int q = 0; q < ITEMS; ++q)
+#pragma unroll
+            for (int r = 0; r < kMaxSteps; ++r)
+                if (r < steps) here |= first + q < M && bin_of(key[q][r]) == digit ? 1u << (q * kMaxSteps + r) : 0u;
+        if (span != 0) {
+            if (here != 0) {
+                uint32_t at = __hip_atomic_fetch_add(&list_count, static_cast<uint32_t>(__builtin_popcount(here)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+                for (int q = 0; q < ITEMS; ++q)
+#pragma unroll
+                    for (int r = 0; r < kMaxSteps; ++r)
+                        if (here >> (q * kMaxSteps + r) & 1u) {
+                            if (at < kWave) {
+                                list_key[at] = key[q][r];
+                                list_amount[at] = freed_by(q, r, r + 1);
+                            }
+                            ++at;
+                        }
+            }
+            __syncthreads();
+            n = __builtin_amdgcn_readfirstlane(static_cast<int>(list_count));
+        }
+        if (span != 0 && n <= kWave) {
+            rank_moves(list_key, list_amount, n, need, below, lane, threshold, below, at_threshold);
+        } else {
+            const auto each = [&](auto f) {
+#pragma unroll
+                for (int q = 0; q < ITEMS; ++q)
+#pragma unroll
+                    for (int r = 0; r < kMaxSteps; ++r)
+                        if (here >> (q * kMaxSteps + r) & 1u) f(key[q][r], static_cast<uint64_t>(freed_by(q, r, r + 1)));
+            };
+            const Threshold t = select_among(each, static_cast<uint64_t>(n), static_cast<uint64_t>(need), static_cast<uint64_t>(below), sel);
+            threshold = t.price;
+            below = static_cast<Amount>(t.below);
+            at_threshold = t.ties;
+        }
     }
     int rung[ITEMS], ties[ITEMS];
 #pragma unroll
     for (int q = 0; q < ITEMS; ++q) {
-        const bool live = first + q < M;
-        if (Di[q] <= 0 || Di[q] >= (int64_t(1) << 34)) Di[q] = live ? 1 : 0;   // invalid input: stay memory-safe
-        rung[q] = v.loose ? 0 : steps;
+        rung[q] = loose ? 0 : steps;
         ties[q] = 0;
-        if (v.search && live) {
+        if (search) {
             rung[q] = 0;
-            for (int r = 0; r < steps; ++r) {
-                const uint64_t k = key[r * M + first + q];
-                rung[q] += k < t.price ? 1 : 0;
-                ties[q] += k == t.price ? 1 : 0;
+#pragma unroll
+            for (int r = 0; r < kMaxSteps; ++r) {
+                rung[q] += key[q][r] < threshold ? 1 : 0;
+                ties[q] += key[q][r] == threshold ? 1 : 0;
             }
         }
     }
-    if (t.ties > 1) {
+    if (at_threshold > 1) {
         // the moves at the threshold in (item, step) order, until the budget holds
-        const uint64_t rest = v.need - t.below;
-        const auto tie_bits = [&](int q) {
-            return static_cast<uint64_t>(Di[q]) * static_cast<uint64_t>(ladder_width(a, rung[q]) - ladder_width(a, rung[q] + ties[q]));
-        };
+        const uint64_t rest = static_cast<uint64_t>(need - below);
         uint64_t sum = 0, unused;
 #pragma unroll
-        for (int q = 0; q < ITEMS; ++q) sum += tie_bits(q);
+        for (int q = 0; q < ITEMS; ++q) sum += static_cast<uint64_t>(freed_by(q, rung[q], rung[q] + ties[q]));
         uint64_t before = block_exclusive_scan(sum, wave_ties, unused);
 #pragma unroll
         for (int q = 0; q < ITEMS; ++q) {
             uint64_t freed = before;
-            before += tie_bits(q);
-            for (; ties[q] > 0 && freed < rest; --ties[q], ++rung[q])
-                freed += static_cast<uint64_t>(Di[q]) * static_cast<uint64_t>(ladder_width(a, rung[q]) - ladder_width(a, rung[q] + 1));
+            before += static_cast<uint64_t>(freed_by(q, rung[q], rung[q] + ties[q]));
+            for (; ties[q] > 0 && freed < rest; --ties[q], ++rung[q]) freed += static_cast<uint64_t>(freed_by(q, rung[q], rung[q] + 1));
         }
     } else {
 #pragma unroll
         for (int q = 0; q < ITEMS; ++q) rung[q] += ties[q];   // the one move at the threshold is applied
     }
-    uint64_t bytes[ITEMS], sum = 0, total;
+    // offsets: widths (items of one size) or bytes, summed in item order
+    Amount size[ITEMS], sum = 0, total;
 #pragma unroll
     for (int q = 0; q < ITEMS; ++q) {
-        bytes[q] = first + q < M ? stream_bytes(Di[q], ladder_width(a, rung[q])) : 0;
-        sum += bytes[q];
+        const int width = width_of(rung[q]);
+        size[q] = first + q < M ? static_cast<Amount>(UNIFORM ? static_cast<uint64_t>(width) : stream_bytes(Di[q], width)) : Amount(0);
+        sum += size[q];
     }
-    uint64_t off = block_exclusive_scan(sum, wave_bytes, total);
+    Amount before = block_exclusive_scan(sum, wave_sum, total);
+    const uint64_t unit = UNIFORM ? a.unit_bytes : 1;
 #pragma unroll
     for (int q = 0; q < ITEMS; ++q) {
         if (first + q < M) {
-            bits[first + q] = static_cast<uint8_t>(ladder_width(a, rung[q]));
-            offsets[first + q] = off;
+            bits[first + q] = static_cast<uint8_t>(width_of(rung[q]));
+            offsets[first + q] = static_cast<uint64_t>(before) * unit;
         }
-        off += bytes[q];
+        before += size[q];
     }
     if (tid == 0) {
-        result[0] = static_cast<int64_t>(total);
-        result[1] = v.status;
+        result[0] = static_cast<int64_t>(static_cast<uint64_t>(total) * unit);
+        result[1] = status;
     }
 }
 
@@ -1988,7 +2220,9 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_small_kernel(const 
 // tenth of a binary64 division.  A valid sensitivity is not negative; -0.0 counts as 0.
 __device__ __forceinline__ uint32_t ratio_of(float w, int64_t D)
 {
-    const float d = __builtin_fmaf(static_cast<float>(static_cast<uint32_t>(D >> 32)), 4294967296.0f, static_cast<float>(static_cast<uint32_t>(D)));
+    uint32_t low = static_cast<uint32_t>(D), high = static_cast<uint32_t>(static_cast<uint64_t>(D) >> 32);
+    asm("" : "+v"(low), "+v"(high));   // two words to the compiler, which makes one long conversion of the 64 bits
+    const float d = __builtin_fmaf(static_cast<float>(high), 4294967296.0f, static_cast<float>(low));
     const double q = static_cast<double>(w) * static_cast<double>(__builtin_amdgcn_rcpf(d));
     return static_cast<uint32_t>(static_cast<uint64_t>(__double_as_longlong(q)) >> 32) & 0x7fffffffu;
 }
@@ -2006,39 +2240,52 @@ struct RatioBracket {
     uint32_t below[kMaxSteps], above[kMaxSteps];
 };
 
-__device__ __forceinline__ void make_bracket(uint64_t lo, uint64_t hi, const AllocArgs& a, RatioBracket& b)
-{
-#pragma unroll
-    for (int r = 0; r < kMaxSteps; ++r) {
-        const bool step = r + 1 < a.lad.count;
-        // a ladder with fewer steps: the unused ones are never cheaper (`above` is not looked at)
-        b.below[r] = step ? static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(ratio_at(lo, a.inverse[r])))) : 0u;
-        b.above[r] = step ? static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(ratio_at(hi, a.inverse[r])))) + 2u : 0u;
-    }
-}
+// The bins [0, below[r]) hold only items whose step r is certainly cheaper than the bracket, the bins from above[r] on
+// only items whose step is certainly not; both fall with r.
+struct BinBracket {
+    uint32_t below[kMaxSteps], above[kMaxSteps];
+};
 
-// For items with ratios in [least, most]: the steps before `first` are cheaper than the bracket for all
-// of them, steps [first, last) are undecided.
-__device__ __forceinline__ void bracket_steps(const RatioBracket& b, int steps, uint32_t least, uint32_t most, int& first, int& last)
+// For items with ratio u: the steps before `first` are cheaper than the bracket, steps [first, last) are undecided.
+__device__ __forceinline__ void bracket_steps(const RatioBracket& b, int steps, uint32_t u, int& first, int& last)
 {
     first = 0;
     last = 0;
 #pragma unroll
     for (int r = 0; r < kMaxSteps; ++r) {
-        first += most + 2u < b.below[r] ? 1 : 0;
-        last += r < steps && least <= b.above[r] ? 1 : 0;
+        first += u + 2u < b.below[r] ? 1 : 0;
+        last += r < steps && u <= b.above[r] ? 1 : 0;
+    }
+}
+
+// The rung of an item near the threshold, and its moves of exactly that price.
+__device__ __forceinline__ void settle_item(float wi, int64_t Di, const AllocArgs& a, const RatioBracket& br, int steps, uint64_t price, int& rung, int& ties)
+{
+    int first, last;
+    bracket_steps(br, steps, ratio_of(wi, Di), first, last);
+    rung = first;
+    ties = 0;
+    for (int r = first; r < last; ++r) {
+        const uint64_t key = price_bits(wi, Di, ladder_price(a.lad, r));
+        rung += key < price ? 1 : 0;
+        ties += key == price ? 1 : 0;
     }
 }
 
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef int64_t i64x2_a8 __attribute__((ext_vector_type(2), aligned(8)));
+typedef int64_t i64x4 __attribute__((ext_vector_type(4)));
+typedef int64_t i64x4_a8 __attribute__((ext_vector_type(4), aligned(8)));
 
-// Any M.  A thread's items come in quadruples of consecutive ones, 4096 items per round; the
-// bins (ratios, before there are bins) and element counts of the first kAllocQuads rounds stay in registers.
-// M >= 4: the small kernel takes everything up to 1024 items, which is at most 7168 moves.
-// More than kAllocList undecided moves are priced again in every turn of select_price, which the ties end:
-// 13,568 items {1, 2, 4, 8} take 28.5 us with log-normal sensitivities, 30.7 with prices a unit apart, 69 if all
-// are one and 89 if all are zero (eight widths: 30.3, 32.4, 71 and 130).
+// Any M.  A thread's items come in quadruples of consecutive ones, 4096 items per round; the bins (ratios, before there are
+// bins) and group counts of the first kAllocQuads rounds stay in registers.  M >= 4: the small kernel takes fewer.
+// The items in a bin with undecided steps are listed, one per thread, and from there on they are the small kernel's problem:
+// exact prices in registers, a histogram over the bracket, the bin that holds the threshold, its few moves ranked.  More of
+// them than the list holds are priced again in every turn of select_price, which the ties end.
+// 2049 items of the ResNet-50's sizes with all widths 23.1 -> 14.4 us, 13,568 29.5 -> 19.8 ({1, 2, 4, 8}: 27.1 -> 19.1), 40,960
+// 82.2 -> 57.9; 13,568 of sensitivity one 43.7 -> 42.8, of zero 126 -> 119.  Before: the undecided moves walked and priced by the
+// threads that hold their items, minima, maxima and three barriers more around a histogram of theirs, the table in 64 bits
+// (an LDS addition of 64 bits takes twice as long), the bins classified a second time, every round's work done for M items or 16,384.
 __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float* __restrict__ w, AllocArgs a,
                                                                     uint8_t* __restrict__ bits,
                                                                     uint64_t* __restrict__ offsets,
@@ -2046,13 +2293,19 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
 {
     constexpr int kQ = 4, kCached = kAllocQuads * kQ;
     constexpr int64_t kRound = int64_t(kAllocBlock) * kQ;
-    __shared__ uint64_t table[kAllocBins + 1];   // elements of the items per bin of w / D, then their prefix sums
-    __shared__ uint32_t step_class[kAllocBins / 4];   // per bin, a byte: bracket_steps' `first`, and 8 if any step is undecided
-    __shared__ uint64_t list_key[kAllocList], list_amount[kAllocList];
+    // elements of the items per bin of w / D, then their prefix sums: 32-bit multiples of 2^scale if they are that small
+    __shared__ uint64_t table[kAllocBins + 2];
+    __shared__ uint32_t step_class[kAllocBins / 4];   // per bin, a byte: steps certainly cheaper than the bracket, and 8 if any step is undecided
+    __shared__ uint32_t list_item[kAllocList];        // items with undecided steps
+    __shared__ uint8_t list_rung[kAllocList];         // their rungs, and their moves at the threshold in the upper half
+    __shared__ uint64_t hist[kSmallBins];             // bits freed by the undecided moves per bin of the bracket
+    __shared__ uint64_t rank_key[kWave], rank_amount[kWave];
     __shared__ SelectLds sel;
-    __shared__ uint64_t wave_a[kAllocWavesMax], wave_b[kAllocWavesMax], wave_c[kAllocWavesMax], wave_d[kAllocWavesMax];
+    __shared__ uint64_t wave_a[kAllocWavesMax], wave_b[kAllocWavesMax], wave_c[kAllocWavesMax];
+    __shared__ uint32_t wave_lo[kAllocWavesMax], wave_hi[kAllocWavesMax], wave_or[kAllocWavesMax], wave_scan[kAllocWavesMax];
     __shared__ uint64_t wave_round[2][kAllocWavesMax], wave_bytes[kAllocQuads * kAllocWavesMax];
-    __shared__ uint64_t list_count;   // moves: up to 7 * 2^31
+    __shared__ uint32_t list_count, rank_count;       // items: fewer than 2^31
+    __shared__ uint64_t move_count;                   // moves: up to 7 * 2^31
     __shared__ uint32_t bracket_lo, bracket_hi;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2062,104 +2315,126 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
     const auto item = [&](int j) { return (j / kQ) * kRound + tid * kQ + j % kQ; };
     const auto elements = [&](int64_t i) { return a.D_items ? a.D_items[i] : a.D; };
 
-    for (int k = tid; k <= kAllocBins; k += kAllocBlock) table[k] = 0;
-    for (int k = tid; k < 2 * kSelectBins; k += kAllocBlock) (&sel.hist[0][0])[k] = 0;
-    if (tid < 2) sel.count[tid] = 0;
-    if (tid == 0) list_count = 0;
-
     // Ratios, totals and validation.  An empty slot has D = 0 and the largest ratio.
     constexpr uint32_t kNone = 0x7fffffffu;
     uint32_t ratio[kCached];
     int64_t size[kCached];
     uint64_t my_elems = 0;
-    uint32_t lo_ratio = kNone, hi_ratio = 0;   // over the positive ratios
-    bool bad = false;
+    uint32_t lo_less1 = kNone - 1u, hi_ratio = 0;   // over the positive ratios, the smallest less 1; bit 31 of hi_ratio: an invalid item
+    uint32_t all_sizes = 0;                    // lower words, or-ed
     float weight[kCached];
     // Whole quadruples per load (a load instruction costs its 64 addresses, not its bytes); one that
     // reaches past the end is taken from the last four items and shifted into place below.
+    f32x4 weight4[kAllocQuads];
+    i64x4 size4[kAllocQuads];
 #pragma unroll
     for (int k = 0; k < kAllocQuads; ++k) {
         const int64_t i0 = item(k * kQ), at = i0 < M - kQ ? i0 : M - kQ;
-        const f32x4_a4 x = *reinterpret_cast<const f32x4_a4*>(w + at);
-#pragma unroll
-        for (int q = 0; q < kQ; ++q) weight[k * kQ + q] = x[q];
+        weight4[k] = *reinterpret_cast<const f32x4_a4*>(w + at);
+        if (a.D_items) size4[k] = *reinterpret_cast<const i64x4_a8*>(a.D_items + at);
+        else size4[k] = i64x4{a.D, a.D, a.D, a.D};
     }
-    if (a.D_items) {
-#pragma unroll
-        for (int k = 0; k < kAllocQuads; ++k) {
-            const int64_t i0 = item(k * kQ), at = i0 < M - kQ ? i0 : M - kQ;
-            const i64x2_a8 x = *reinterpret_cast<const i64x2_a8*>(a.D_items + at), y = *reinterpret_cast<const i64x2_a8*>(a.D_items + at + 2);
-            size[k * kQ] = x[0];
-            size[k * kQ + 1] = x[1];
-            size[k * kQ + 2] = y[0];
-            size[k * kQ + 3] = y[1];
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < kCached; ++j) size[j] = a.D;
+    for (int k = tid; k < kAllocBins + 2; k += kAllocBlock) table[k] = 0;
+    if (tid < kSmallBins) hist[tid] = 0;
+    if (tid == 0) {
+        list_count = 0;
+        rank_count = 0;
+        move_count = 0;
     }
 #pragma unroll
     for (int k = 0; k < kAllocQuads; ++k) {
+        // all loads before the first use of one: left alone, the compiler moves each under the branch of its round, one latency behind the other
+        asm volatile("" : "+v"(weight4[k]), "+v"(size4[k][0]), "+v"(size4[k][1]), "+v"(size4[k][2]), "+v"(size4[k][3]));
         if ((k + 1) * kRound > M) {
             const int64_t past = item(k * kQ) - (M - kQ);   // 1, 2, 3: the quadruple is shifted by that much; from 4 on it is empty
+            const bool one = past > 0 && (past & 1) != 0, two = past > 0 && (past & 2) != 0;
+            weight4[k] = one ? __builtin_shufflevector(weight4[k], weight4[k], 1, 2, 3, 3) : weight4[k];
+            weight4[k] = two ? __builtin_shufflevector(weight4[k], weight4[k], 2, 3, 3, 3) : weight4[k];
+            size4[k] = one ? __builtin_shufflevector(size4[k], size4[k], 1, 2, 3, 3) : size4[k];
+            size4[k] = two ? __builtin_shufflevector(size4[k], size4[k], 2, 3, 3, 3) : size4[k];
+        }
 #pragma unroll
-            for (int q = 0; q < kQ; ++q) {
-                const int j = k * kQ + q;
-#pragma unroll
-                for (int p = 1; p + q < kQ; ++p) {
-                    weight[j] = past == p ? weight[j + p] : weight[j];
-                    size[j] = past == p ? size[j + p] : size[j];
-                }
-            }
+        for (int q = 0; q < kQ; ++q) {
+            weight[k * kQ + q] = weight4[k][q];
+            size[k * kQ + q] = size4[k][q];
         }
     }
+    // The ratio of an item; straight-line code, every item of a wavefront takes it.
+    const auto count_item = [&](bool live, float wi, int64_t& Di) {
+        const bool ok = live & valid_item(wi, Di);
+        const uint32_t u = ratio_of(wi, Di), counted = ok ? u : kNone, less1 = counted - 1u;   // 0 becomes the largest
+        lo_less1 = less1 < lo_less1 ? less1 : lo_less1;
+        const uint32_t top = ok ? u : (live ? 0x80000000u : 0u);
+        hi_ratio = top > hi_ratio ? top : hi_ratio;
+        Di = ok ? Di : 0;
+        my_elems += static_cast<uint64_t>(Di);
+        all_sizes |= static_cast<uint32_t>(Di);
+        return counted;
+    };
+    // rounds in which this wavefront has items: the others cost it nothing
+    const auto in_round = [&](int k) { return k * kRound + wave * (kWave * kQ) < M; };
 #pragma unroll
-    for (int j = 0; j < kCached; ++j) {
-        const bool live = item(j) < M;
-        const bool ok = live && valid_item(weight[j], size[j]);
-        bad = bad || (live && !ok);
-        ratio[j] = ok ? ratio_of(weight[j], size[j]) : kNone;
-        size[j] = ok ? size[j] : 0;
-        my_elems += static_cast<uint64_t>(size[j]);
-        if (ok && ratio[j] != 0) {
-            lo_ratio = ratio[j] < lo_ratio ? ratio[j] : lo_ratio;
-            hi_ratio = ratio[j] > hi_ratio ? ratio[j] : hi_ratio;
+    for (int k = 0; k < kAllocQuads; ++k) {
+        if (!in_round(k)) {
+#pragma unroll
+            for (int j = k * kQ; j < (k + 1) * kQ; ++j) {
+                ratio[j] = kNone;
+                size[j] = 0;
+            }
+            continue;
         }
-        if (j % kQ == kQ - 1) __builtin_amdgcn_sched_barrier(0);   // a quadruple at a time: the temporaries stay in registers
+#pragma unroll
+        for (int j = k * kQ; j < (k + 1) * kQ; ++j) {
+            const int32_t left = static_cast<int32_t>(M < (int64_t(1) << 30) ? M : int64_t(1) << 30) - (j / kQ) * static_cast<int32_t>(kRound);
+            ratio[j] = count_item(tid * kQ + j % kQ < left, weight[j], size[j]);
+        }
+        __builtin_amdgcn_sched_barrier(0);   // a quadruple at a time: the temporaries stay in registers
     }
     // items beyond the registers: recomputed in every pass
-    const auto further = [&](auto f) {
-        for (int64_t base = kAllocQuads * kRound; base < M; base += kRound)
-            for (int q = 0; q < kQ; ++q) {
-                const int64_t i = base + tid * kQ + q;
-                if (i < M) f(i, w[i], elements(i));
-            }
+    const auto further_quads = [&](auto f) {   // f(first item, first of them that counts, sensitivities, sizes)
+        for (int64_t i0 = kAllocQuads * kRound + tid * kQ; i0 < M; i0 += kRound) {
+            const int64_t at = i0 < M - kQ ? i0 : M - kQ;
+            const f32x4 x = *reinterpret_cast<const f32x4_a4*>(w + at);
+            i64x4 y = {a.D, a.D, a.D, a.D};
+            if (a.D_items) y = *reinterpret_cast<const i64x4_a8*>(a.D_items + at);
+            f(at, static_cast<int>(i0 - at), x, y);
+        }
     };
-    further([&](int64_t, float wi, int64_t Di) {
-        if (!valid_item(wi, Di)) { bad = true; return; }
-        my_elems += static_cast<uint64_t>(Di);
-        const uint32_t u = ratio_of(wi, Di);
-        if (u != 0) {
-            lo_ratio = u < lo_ratio ? u : lo_ratio;
-            hi_ratio = u > hi_ratio ? u : hi_ratio;
+    const auto further = [&](auto f) {
+        further_quads([&](int64_t at, int from, f32x4 x, i64x4 y) {
+#pragma unroll
+            for (int q = 0; q < kQ; ++q)
+                if (q >= from) f(at + q, x[q], y[q]);
+        });
+    };
+    further_quads([&](int64_t, int from, f32x4 x, i64x4 y) {
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) {
+            int64_t Di = y[q];
+            (void)count_item(q >= from, x[q], Di);
         }
     });
     {
-        const uint64_t e = wave_reduce(my_elems, Add()), l = wave_reduce(lo_ratio, Min()), h = wave_reduce(hi_ratio, Max());
-        const uint64_t any_bad = __ballot(bad);
+        const uint64_t e = wave_reduce(my_elems, Add());
+        const uint32_t l = wave_reduce(lo_less1, Min()), h = wave_reduce(hi_ratio, Max()), o = wave_reduce(all_sizes, Or());
         if (lane == 0) {
             wave_a[wave] = e;
-            wave_b[wave] = l;
-            wave_c[wave] = h;
-            wave_d[wave] = any_bad;
+            wave_lo[wave] = l;
+            wave_hi[wave] = h;
+            wave_or[wave] = o;
         }
     }
     __syncthreads();
     const uint64_t elems = combine_waves(wave_a, waves, 0, Add());
-    const uint32_t first_ratio = static_cast<uint32_t>(combine_waves(wave_b, waves, kNone, Min()));
-    const uint32_t last_ratio = static_cast<uint32_t>(combine_waves(wave_c, waves, 0, Max()));   // 0: every price is 0
-    const bool invalid = combine_waves(wave_d, waves, 0, Max()) != 0;
-    const AllocVerdict v = alloc_verdict(elems, invalid, a);
+    const uint32_t first_ratio = row_result(wave_lo[lane & 15], Min()) + 1u;
+    const uint32_t last_ratio = row_result(wave_hi[lane & 15], Max());   // 0: every price is 0
+    const uint32_t sizes = row_result(wave_or[lane & 15], Or());
+    const bool invalid = (last_ratio >> 31) != 0;
+    const AllocVerdict v = alloc_verdict(elems, invalid, a.total);
+    // 2^scale divides every size
+    const int scale = sizes ? __builtin_ctz(sizes) : 31;
+    const bool narrow = (elems >> scale) >> 32 == 0;
+    uint32_t* const table32 = reinterpret_cast<uint32_t*>(table);
 
     Threshold t = {0, 0, 0};
     RatioBracket br;
@@ -2172,46 +2447,42 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
         const uint32_t bin = u == 0 ? 0u : 1u + ((u - first_ratio) >> shift);
         return bin < static_cast<uint32_t>(kAllocBins) ? bin : static_cast<uint32_t>(kAllocBins - 1);
     };
-    uint64_t hb[4] = {0, 0, 0, 0};   // elements of the items in bins 4 tid .. 4 tid + 3
-    // step_class of the thread's four bins for the bracket `br`; returns the bits freed by the steps that are cheaper than it
-    const auto classify = [&]() {
-        uint32_t classes = 0;
-        uint64_t freed = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const uint32_t bin = static_cast<uint32_t>(4 * tid + k);
-            const uint32_t least = bin == 0 ? 0u : first_ratio + ((bin - 1u) << shift);
-            const uint32_t most = bin == 0 ? 0u : least + ((1u << shift) - 1u);
-            int first, last;
-            bracket_steps(br, steps, least, most, first, last);
-            classes |= static_cast<uint32_t>(first | (first < last ? 8 : 0)) << (8 * k);
-            freed += hb[k] * static_cast<uint64_t>(a.lad.width[0] - ladder_width(a, first));
-        }
-        step_class[tid] = classes;
-        return freed;
-    };
     const auto class_of = [&](uint32_t bin) { return static_cast<uint32_t>(reinterpret_cast<const uint8_t*>(step_class)[bin]); };
+    uint32_t price_lo = 0, price_hi = 0;    // the bracket: upper halves of price patterns
+    // rungs and tied moves of the items in registers, four bits each
+    uint64_t rungs = 0, tied = 0;
     if (v.search) {
         const auto add_item = [&](uint32_t bin, int64_t D) {
-            __hip_atomic_fetch_add(&table[bin], static_cast<uint64_t>(D), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (narrow) __hip_atomic_fetch_add(&table32[bin], static_cast<uint32_t>(static_cast<uint64_t>(D) >> scale), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            else __hip_atomic_fetch_add(&table[bin], static_cast<uint64_t>(D), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         };
 #pragma unroll
-        for (int j = 0; j < kCached; ++j) {
-            ratio[j] = bin_of(ratio[j]);   // bins from here on
-            if (size[j] != 0) add_item(ratio[j], size[j]);
+        for (int k = 0; k < kAllocQuads; ++k) {
+            if (!in_round(k)) continue;
+#pragma unroll
+            for (int j = k * kQ; j < (k + 1) * kQ; ++j) {
+                ratio[j] = bin_of(ratio[j]);   // bins from here on
+                if (size[j] != 0) add_item(ratio[j], size[j]);
+            }
         }
         further([&](int64_t, float wi, int64_t Di) { add_item(bin_of(ratio_of(wi, Di)), Di); });
         __syncthreads();
-        uint64_t mine = 0, total;
+        // elements of the items in the bins before a bin
+        const auto to_prefix = [&](auto* entry, auto* of_wave) {
+            typedef typename std::remove_reference<decltype(*entry)>::type V;
+            V own[4], mine = 0, total;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) { hb[k] = table[4 * tid + k]; mine += hb[k]; }
-        uint64_t run = block_exclusive_scan(mine, wave_round[0], total);
+            for (int k = 0; k < 4; ++k) { own[k] = entry[4 * tid + k]; mine += own[k]; }
+            V run = block_exclusive_scan(mine, of_wave, total);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            table[4 * tid + k] = run;   // elements of the items in the bins before this one
-            run += hb[k];
-        }
-        if (tid == kAllocBlock - 1) table[kAllocBins] = run;
+            for (int k = 0; k < 4; ++k) {
+                entry[4 * tid + k] = run;
+                run += own[k];
+            }
+            if (tid == kAllocBlock - 1) entry[kAllocBins] = run;
+        };
+        if (narrow) to_prefix(table32, wave_scan);
+        else to_prefix(table, wave_round[0]);
         __syncthreads();
 
         // ---- the bracket: wavefront 0 evaluates both bounds of the bits freed below 64 prices at a time
@@ -2226,21 +2497,44 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
                 const uint32_t width = right - left;
                 const uint32_t p = left + static_cast<uint32_t>(static_cast<uint64_t>(width) * static_cast<uint32_t>(lane) / 63u);
                 uint64_t most = 0, least = 0;   // bits freed by the moves cheaper than p: upper and lower bound
+                const auto add_steps = [&](auto from, auto to) {   // the look-ups of all these steps are in flight together
+                    uint32_t b_least[kMaxSteps], b_most[kMaxSteps];
 #pragma unroll
-                for (int r = 0; r < kMaxSteps; ++r) {
-                    if (r >= steps) continue;
-                    const uint32_t u = ratio_at(static_cast<uint64_t>(p) << 32, a.inverse[r]);
-                    const uint64_t dw = static_cast<uint64_t>(a.lad.width[r] - a.lad.width[r + 1]);
-                    // items of ratio < u - 2 only: whole bins before the one that holds it
-                    const uint32_t x = u > 2u ? u - 2u : 0u;
-                    uint32_t b_least = x <= first_ratio ? 1u : 1u + ((x - first_ratio) >> shift);
-                    b_least = x == 0 ? 0u : (b_least < static_cast<uint32_t>(kAllocBins) ? b_least : static_cast<uint32_t>(kAllocBins));
-                    // every item of ratio <= u + 2: whole bins up to the one that holds it
-                    const uint32_t y = u + 2u;
-                    uint32_t b_most = y < first_ratio ? 1u : 2u + ((y - first_ratio) >> shift);
-                    b_most = b_most < static_cast<uint32_t>(kAllocBins) ? b_most : static_cast<uint32_t>(kAllocBins);
-                    least += dw * table[b_least];
-                    most += dw * table[b_most];
+                    for (int r = from; r < to; ++r) {
+                        const uint32_t u = ratio_at(static_cast<uint64_t>(p) << 32, a.inverse[r]);   // 0 for a step that does not exist
+                        // items of ratio < u - 2 only: whole bins before the one that holds it
+                        const uint32_t x = u > 2u ? u - 2u : 0u;
+                        const uint32_t bl = x <= first_ratio ? 1u : 1u + ((x - first_ratio) >> shift);
+                        b_least[r] = x == 0 ? 0u : (bl < static_cast<uint32_t>(kAllocBins) ? bl : static_cast<uint32_t>(kAllocBins));
+                        // every item of ratio <= u + 2: whole bins up to the one that holds it
+                        const uint32_t y = u + 2u;
+                        const uint32_t bm = y < first_ratio ? 1u : 2u + ((y - first_ratio) >> shift);
+                        b_most[r] = bm < static_cast<uint32_t>(kAllocBins) ? bm : static_cast<uint32_t>(kAllocBins);
+                    }
+                    const auto look_up = [&](const auto* entry) {
+                        typedef typename std::remove_const<typename std::remove_reference<decltype(*entry)>::type>::type V;
+                        V e_least[kMaxSteps], e_most[kMaxSteps];
+#pragma unroll
+                        for (int r = from; r < to; ++r) {
+                            e_least[r] = entry[b_least[r]];
+                            e_most[r] = entry[b_most[r]];
+                        }
+#pragma unroll
+                        for (int r = from; r < to; ++r) {
+                            const uint32_t dw = static_cast<uint32_t>(a.lad.width[r] - a.lad.width[r + 1]);
+                            const uint32_t counted = r < steps ? dw : 0u;
+                            least += static_cast<uint64_t>(counted) * e_least[r];
+                            most += static_cast<uint64_t>(counted) * e_most[r];
+                        }
+                    };
+                    if (narrow) look_up(table32);
+                    else look_up(table);
+                };
+                add_steps(std::integral_constant<int, 0>(), std::integral_constant<int, 3>());
+                if (steps > 3) add_steps(std::integral_constant<int, 3>(), std::integral_constant<int, kMaxSteps>());
+                if (narrow) {
+                    least <<= scale;
+                    most <<= scale;
                 }
                 const uint64_t not_yet = __ballot(most < v.need), enough = __ballot(least >= v.need);
                 if (not_yet) lo = left + static_cast<uint32_t>(static_cast<uint64_t>(width) * static_cast<uint32_t>(63 - __builtin_clzll(not_yet)) / 63u);
@@ -2257,114 +2551,236 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
         }
         __syncthreads();
 
-        // ---- the undecided moves, priced exactly
-        make_bracket(static_cast<uint64_t>(bracket_lo) << 32, static_cast<uint64_t>(bracket_hi) << 32, a, br);
-        uint64_t my_below = classify();
-        __syncthreads();
-        uint32_t undecided = 0;   // of the items in registers: those in a bin with undecided steps
-#pragma unroll
-        for (int j = 0; j < kCached; ++j) undecided |= size[j] != 0 && (class_of(ratio[j]) & 8u) ? 1u << j : 0u;
-        // every undecided move of this thread: f(price, bits freed); before(D, class) once per item that is looked at
-        const auto walk_items = [&](auto f, auto before) {
-            const auto moves_of = [&](float wi, int64_t Di, uint32_t cls, uint32_t u) {
-                int first, last;
-                bracket_steps(br, steps, u, u, first, last);
-                before(Di, static_cast<int>(cls & 7u), first);
-                for (int r = first; r < last; ++r)
-                    f(price_bits(wi, Di, ladder_price(a.lad, r)),
-                      static_cast<uint64_t>(Di) * static_cast<uint64_t>(ladder_width(a, r) - ladder_width(a, r + 1)));
-            };
-            for (uint32_t m = undecided; m != 0; m &= m - 1) {
-                const int64_t i = item(__builtin_ctz(m));
-                const float wi = w[i];
-                const int64_t Di = elements(i);
-                const uint32_t u = ratio_of(wi, Di);
-                moves_of(wi, Di, class_of(bin_of(u)), u);
-            }
-            further([&](int64_t, float wi, int64_t Di) {
-                const uint32_t u = ratio_of(wi, Di), cls = class_of(bin_of(u));
-                if (cls & 8u) moves_of(wi, Di, cls, u);
-            });
-        };
-        const auto walk = [&](auto f) { walk_items(f, [](int64_t, int, int) {}); };
-        uint64_t lo = ~uint64_t(0), hi = 0;
-        walk_items([&](uint64_t key, uint64_t freed) {
-            const uint64_t at = __hip_atomic_fetch_add(&list_count, uint64_t(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (at < kAllocList) {
-                list_key[at] = key;
-                list_amount[at] = freed;
-            }
-            lo = key < lo ? key : lo;
-            hi = key > hi ? key : hi;
-        }, [&](int64_t Di, int of_bin, int of_item) {   // cheaper steps of the item beyond those counted with its bin
-            my_below += static_cast<uint64_t>(Di) * static_cast<uint64_t>(ladder_width(a, of_bin) - ladder_width(a, of_item));
-        });
+        // ---- what the bracket decides, per bin
+        price_lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(bracket_lo)));
+        price_hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(bracket_hi)));
+        BinBracket bins;
+        uint64_t my_below = 0;   // bits freed by moves that are cheaper than the bracket
         {
+            // lane r: step r
+            double inverse = 0.0;
+            uint32_t dw = 0;
+#pragma unroll
+            for (int r = 0; r < kMaxSteps; ++r) {
+                inverse = lane == r ? a.inverse[r] : inverse;
+                dw = lane == r && r < steps ? static_cast<uint32_t>(a.lad.width[r] - a.lad.width[r + 1]) : dw;
+            }
+            const bool step = lane < steps;
+            // a ladder with fewer steps: the unused ones are never cheaper (`above` is not looked at)
+            const uint32_t below = step ? ratio_at(static_cast<uint64_t>(price_lo) << 32, inverse) : 0u;
+            const uint32_t above = step ? ratio_at(static_cast<uint64_t>(price_hi) << 32, inverse) + 2u : 0u;
+            // bin b > 0 holds the ratios first_ratio + ((b - 1) << shift) .. first_ratio + (b << shift) - 1
+            uint32_t bin_below = below > first_ratio + 2u ? 1u + ((below - first_ratio - 2u) >> shift) : 1u;
+            bin_below = below > 2u ? bin_below : 0u;
+            uint32_t bin_above = above >= first_ratio ? 2u + ((above - first_ratio) >> shift) : 1u;
+            bin_below = bin_below < static_cast<uint32_t>(kAllocBins) ? bin_below : static_cast<uint32_t>(kAllocBins);
+            bin_above = step ? bin_above : 0u;
+#pragma unroll
+            for (int r = 0; r < kMaxSteps; ++r) {
+                br.below[r] = read_lane(below, r);
+                br.above[r] = read_lane(above, r);
+                bins.below[r] = read_lane(bin_below, r);
+                bins.above[r] = read_lane(bin_above, r);
+            }
+            if (wave == 0 && step)
+                my_below = static_cast<uint64_t>(dw) * (narrow ? static_cast<uint64_t>(table32[bin_below]) << scale : table[bin_below]);
+        }
+        {
+            uint32_t classes = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t bin = static_cast<uint32_t>(4 * tid + k);
+                uint32_t first = 0, last = 0;
+#pragma unroll
+                for (int r = 0; r < kMaxSteps; ++r) {
+                    first += bin < bins.below[r] ? 1u : 0u;
+                    last += bin < bins.above[r] ? 1u : 0u;
+                }
+                classes |= (first | (first < last ? 8u : 0u)) << (8 * k);
+            }
+            step_class[tid] = classes;
+        }
+        __syncthreads();
+
+        // ---- the items in a bin with undecided steps, listed
+        uint32_t undecided = 0, listed_at = 0;
+#pragma unroll
+        for (int k = 0; k < kAllocQuads; ++k) {
+            if (!in_round(k)) continue;
+#pragma unroll
+            for (int j = k * kQ; j < (k + 1) * kQ; ++j) {
+                const uint32_t cls = class_of(ratio[j]);
+                undecided |= size[j] != 0 && (cls & 8u) ? 1u << j : 0u;
+                rungs |= static_cast<uint64_t>(cls & 7u) << (4 * j);
+            }
+        }
+        if (undecided != 0) {
+            listed_at = __hip_atomic_fetch_add(&list_count, static_cast<uint32_t>(__builtin_popcount(undecided)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            uint32_t at = listed_at;
+            for (uint32_t m = undecided; m != 0; m &= m - 1, ++at)
+                if (at < static_cast<uint32_t>(kAllocList)) list_item[at] = static_cast<uint32_t>(item(__builtin_ctz(m)));
+        }
+        further([&](int64_t i, float wi, int64_t Di) {
+            if (!(class_of(bin_of(ratio_of(wi, Di))) & 8u)) return;
+            const uint32_t at = __hip_atomic_fetch_add(&list_count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (at < static_cast<uint32_t>(kAllocList)) list_item[at] = static_cast<uint32_t>(i);
+        });
+        __syncthreads();
+        const uint32_t listed = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(list_count)));
+        if (listed <= static_cast<uint32_t>(kAllocList)) {
+            // a thread per item: its undecided moves, priced exactly, into the bins of the bracket
+            uint64_t key[kMaxSteps];   // upper half below price_lo: cheaper, from price_hi on: dearer than the threshold
+            uint32_t here = 0;
+            const bool mine = static_cast<uint32_t>(tid) < listed;
+            const uint32_t spread = price_hi - price_lo - 1u;   // price_lo < price_hi
+            int fine = 23 - __builtin_clz(spread | 1u);         // (spread >> fine) < 512
+            fine = fine > 0 ? fine : 0;
+            int64_t Di = 0;
+            if (mine) {
+                const int64_t i = list_item[tid];
+                const float wi = w[i];
+                Di = elements(i);
+                const uint32_t cls = class_of(bin_of(ratio_of(wi, Di)));
+                const double d = static_cast<double>(Di), y = 1.0 / d, of_item = static_cast<double>(wi);
+#pragma unroll
+                for (int r = 0; r < kMaxSteps; ++r) {
+                    key[r] = r < steps ? quotient_bits(of_item * a.lad.price[r], d, y) : ~uint64_t(0);
+                    const uint32_t top = static_cast<uint32_t>(key[r] >> 32);
+                    const uint64_t freed = static_cast<uint64_t>(Di) * static_cast<uint64_t>(a.lad.width[r] - (r + 1 < 8 ? a.lad.width[r + 1] : 0));
+                    // cheaper steps of the item beyond those counted with its bin
+                    if (top < price_lo && static_cast<uint32_t>(r) >= (cls & 7u)) my_below += freed;
+                    if (top >= price_lo && top < price_hi) {
+                        here |= 1u << r;
+                        __hip_atomic_fetch_add(&hist[(top - price_lo) >> fine], freed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                }
+            }
+            {
+                const uint64_t b = wave_reduce(my_below, Add());
+                if (lane == 0) wave_a[wave] = b;
+            }
+            __syncthreads();
+            const uint64_t cheaper_than_all = combine_waves(wave_a, waves, 0, Add());
+            uint64_t below;
+            const uint32_t digit = winning_bin(hist, v.need, cheaper_than_all, lane, below);
+            // the moves in the bin that holds the threshold
+            uint32_t chosen = 0;
+#pragma unroll
+            for (int r = 0; r < kMaxSteps; ++r)
+                chosen |= (here >> r & 1u) && ((static_cast<uint32_t>(key[r] >> 32) - price_lo) >> fine) == digit ? 1u << r : 0u;
+            if (chosen != 0) {
+                uint32_t at = __hip_atomic_fetch_add(&rank_count, static_cast<uint32_t>(__builtin_popcount(chosen)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+                for (int r = 0; r < kMaxSteps; ++r)
+                    if (chosen >> r & 1u) {
+                        if (at < static_cast<uint32_t>(kWave)) {
+                            rank_key[at] = key[r];
+                            rank_amount[at] = static_cast<uint64_t>(Di) * static_cast<uint64_t>(a.lad.width[r] - a.lad.width[r + 1]);
+                        }
+                        ++at;
+                    }
+            }
+            __syncthreads();
+            const int n = __builtin_amdgcn_readfirstlane(static_cast<int>(rank_count));
+            if (n <= kWave) {
+                rank_moves(rank_key, rank_amount, n, v.need, below, lane, t.price, t.below, t.ties);
+            } else {
+                const auto each = [&](auto f) {
+#pragma unroll
+                    for (int r = 0; r < kMaxSteps; ++r)
+                        if (chosen >> r & 1u) f(key[r], static_cast<uint64_t>(Di) * static_cast<uint64_t>(a.lad.width[r] - a.lad.width[r + 1]));
+                };
+                t = select_among(each, static_cast<uint64_t>(n), v.need, below, sel);
+            }
+            if (mine) {
+                uint32_t rung = 0, ties = 0;
+#pragma unroll
+                for (int r = 0; r < kMaxSteps; ++r) {
+                    rung += key[r] < t.price ? 1u : 0u;
+                    ties += key[r] == t.price ? 1u : 0u;
+                }
+                if (t.ties == 1) { rung += ties; ties = 0; }   // the one move at the threshold is applied
+                list_rung[tid] = static_cast<uint8_t>(rung | ties << 4);
+            }
+            __syncthreads();
+            for (uint32_t m = undecided; m != 0; m &= m - 1, ++listed_at) {
+                const int j = __builtin_ctz(m);
+                const uint32_t state = list_rung[listed_at];
+                rungs = (rungs & ~(uint64_t(15) << (4 * j))) | (static_cast<uint64_t>(state & 15u) << (4 * j));
+                tied |= static_cast<uint64_t>(state >> 4) << (4 * j);
+            }
+        } else {
+            // many (nearly) equal prices: the undecided moves, priced again in every turn; before(D, class) once per item that is looked at
+            const auto walk_items = [&](auto f, auto before) {
+                const auto moves_of = [&](float wi, int64_t Di, uint32_t cls, uint32_t u) {
+                    int first, last;
+                    bracket_steps(br, steps, u, first, last);
+                    before(Di, static_cast<int>(cls & 7u), first);
+                    for (int r = first; r < last; ++r)
+                        f(price_bits(wi, Di, ladder_price(a.lad, r)),
+                          static_cast<uint64_t>(Di) * static_cast<uint64_t>(ladder_width(a, r) - ladder_width(a, r + 1)));
+                };
+                for (uint32_t m = undecided; m != 0; m &= m - 1) {
+                    const int64_t i = item(__builtin_ctz(m));
+                    const float wi = w[i];
+                    const int64_t Di = elements(i);
+                    const uint32_t u = ratio_of(wi, Di);
+                    moves_of(wi, Di, class_of(bin_of(u)), u);
+                }
+                further_quads([&](int64_t, int from, f32x4 x, i64x4 y) {
+#pragma unroll 1
+                    for (int q = 0; q < kQ; ++q) {   // rolled: this is inlined five times
+                        const float wi = x[0];
+                        const int64_t Di = y[0];
+                        x = __builtin_shufflevector(x, x, 1, 2, 3, 3);
+                        y = __builtin_shufflevector(y, y, 1, 2, 3, 3);
+                        if (q < from) continue;
+                        const uint32_t u = ratio_of(wi, Di), cls = class_of(bin_of(u));
+                        if (cls & 8u) moves_of(wi, Di, cls, u);
+                    }
+                });
+            };
+            const auto walk = [&](auto f) { walk_items(f, [](int64_t, int, int) {}); };
+            for (int k = tid; k < 2 * kSelectBins; k += kAllocBlock) (&sel.hist[0][0])[k] = 0;
+            if (tid < 2) sel.count[tid] = 0;
+            uint64_t lo = ~uint64_t(0), hi = 0, moves = 0;
+            walk_items([&](uint64_t key, uint64_t) {
+                ++moves;
+                lo = key < lo ? key : lo;
+                hi = key > hi ? key : hi;
+            }, [&](int64_t Di, int of_bin, int of_item) {   // cheaper steps of the item beyond those counted with its bin
+                my_below += static_cast<uint64_t>(Di) * static_cast<uint64_t>(ladder_width(a, of_bin) - ladder_width(a, of_item));
+            });
             const uint64_t b = wave_reduce(my_below, Add());
             lo = wave_reduce(lo, Min());
             hi = wave_reduce(hi, Max());
+            moves = wave_reduce(moves, Add());
             if (lane == 0) {
                 wave_a[wave] = b;
                 wave_b[wave] = lo;
                 wave_c[wave] = hi;
+                if (moves != 0) __hip_atomic_fetch_add(&move_count, moves, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
-        }
-        __syncthreads();
-        const uint64_t below = combine_waves(wave_a, waves, 0, Add());
-        lo = combine_waves(wave_b, waves, ~uint64_t(0), Min());
-        hi = combine_waves(wave_c, waves, 0, Max());
-        const uint64_t n = list_count;
-        if (n <= kAllocList) {
-            const auto each = [&](auto f) {
-                for (int e = tid; e < static_cast<int>(n); e += kAllocBlock) f(list_key[e], list_amount[e]);
-            };
-            t = select_price(each, n, lo, hi, v.need, below, sel);
-        } else {
-            t = select_price(walk, n, lo, hi, v.need, below, sel);   // many (nearly) equal prices
-        }
-        make_bracket(t.price, t.price, a, br);
-        __syncthreads();   // step_class has been read by everyone
-        classify();
-        __syncthreads();
-    }
-
-    // ---- widths, then offsets, in item order
-    const auto settle = [&](float wi, int64_t Di, int& rung, int& ties) {   // an item near the threshold
-        int first, last;
-        const uint32_t u = ratio_of(wi, Di);
-        bracket_steps(br, steps, u, u, first, last);
-        rung = first;
-        ties = 0;
-        for (int r = first; r < last; ++r) {
-            const uint64_t key = price_bits(wi, Di, ladder_price(a.lad, r));
-            rung += key < t.price ? 1 : 0;
-            ties += key == t.price ? 1 : 0;
-        }
-    };
-    const uint64_t rest = v.need - t.below;   // bits still to free among the moves priced exactly at the threshold
-    uint64_t tie_carry = 0, byte_carry = 0;
-    // rungs and tied moves of the items in registers, four bits each
-    uint64_t rungs = 0, tied = 0;
-    if (v.search) {
-        uint32_t near = 0;
-#pragma unroll
-        for (int j = 0; j < kCached; ++j) {
-            const uint32_t cls = class_of(ratio[j]);
-            near |= size[j] != 0 && (cls & 8u) ? 1u << j : 0u;
-            rungs |= static_cast<uint64_t>(cls & 7u) << (4 * j);
-        }
-        for (uint32_t m = near; m != 0; m &= m - 1) {
-            const int j = __builtin_ctz(m);
-            const int64_t i = item(j);
-            int rung, ties;
-            settle(w[i], elements(i), rung, ties);
-            if (t.ties == 1) { rung += ties; ties = 0; }   // the one move at the threshold is applied
-            rungs = (rungs & ~(uint64_t(15) << (4 * j))) | (static_cast<uint64_t>(rung) << (4 * j));
-            tied |= static_cast<uint64_t>(ties) << (4 * j);
+            __syncthreads();
+            t = select_price(walk, move_count, combine_waves(wave_b, waves, ~uint64_t(0), Min()), combine_waves(wave_c, waves, 0, Max()),
+                             v.need, combine_waves(wave_a, waves, 0, Add()), sel);
+            for (uint32_t m = undecided; m != 0; m &= m - 1) {
+                const int j = __builtin_ctz(m);
+                const int64_t i = item(j);
+                int rung, ties;
+                settle_item(w[i], elements(i), a, br, steps, t.price, rung, ties);
+                if (t.ties == 1) { rung += ties; ties = 0; }
+                rungs = (rungs & ~(uint64_t(15) << (4 * j))) | (static_cast<uint64_t>(rung) << (4 * j));
+                tied |= static_cast<uint64_t>(ties) << (4 * j);
+            }
         }
     } else if (!v.loose) {
         rungs = 0x1111111111111111ull * static_cast<uint64_t>(steps);
     }
+
+    // ---- offsets, in item order
+    const uint64_t rest = v.need - t.below;   // bits still to free among the moves priced exactly at the threshold
+    uint64_t tie_carry = 0, byte_carry = 0;
     const auto apply_ties = [&](int64_t Di, int& rung, int ties, uint64_t freed) {
         for (; ties > 0 && freed < rest; --ties, ++rung)
             freed += static_cast<uint64_t>(Di) * static_cast<uint64_t>(ladder_width(a, rung) - ladder_width(a, rung + 1));
@@ -2396,7 +2812,14 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
         }
     }
     const bool word_stores = (reinterpret_cast<uintptr_t>(bits) & 3u) == 0;
-    const auto store_quad = [&](int64_t i0, uint32_t widths, const uint64_t (&at)[kQ]) {
+    // widths and offsets of the quadruple from i0 on; units: 32 bytes of the stream per item
+    const auto store_quad = [&](int64_t i0, uint32_t widths, const uint32_t (&units)[kQ], uint64_t off) {
+        uint64_t at[kQ];
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) {
+            at[q] = off;
+            off += static_cast<uint64_t>(units[q]) * 32u;
+        }
         if (i0 + kQ <= M && word_stores) {
             *reinterpret_cast<uint32_t*>(bits + i0) = widths;
             i64x2_a8 x, y;
@@ -2415,25 +2838,34 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
                 offsets[i0 + q] = at[q];
             }
     };
+    // groups of an item: below 2^26, so that a quadruple's units stay below 2^31
+    const auto groups_of = [](int64_t D) { return static_cast<uint32_t>((static_cast<uint64_t>(D) + (kGroup - 1)) >> 8); };
     // the byte sums of all rounds in registers go through one barrier
     {
-        uint64_t upto[kAllocQuads], own[kAllocQuads];
+        uint64_t upto[kAllocQuads];
+        uint32_t units[kCached], own[kAllocQuads], widths[kAllocQuads];
 #pragma unroll
         for (int k = 0; k < kAllocQuads; ++k) {
             own[k] = 0;
+            widths[k] = 0;
+            upto[k] = 0;
+            if (in_round(k)) {
 #pragma unroll
-            for (int q = 0; q < kQ; ++q) {
-                const int j = k * kQ + q;
-                int64_t Di = size[j];
-                if (invalid) {   // invalid input: stay memory-safe, with the sizes as they are where they can be
-                    const int64_t i = item(j);
-                    Di = i < M ? elements(i) : 0;
-                    if (Di <= 0 || Di >= (int64_t(1) << 34)) Di = i < M ? 1 : 0;
-                    size[j] = Di;
+                for (int q = 0; q < kQ; ++q) {
+                    const int j = k * kQ + q;
+                    if (invalid) {   // invalid input: stay memory-safe, with the sizes as they are where they can be
+                        const int64_t i = item(j);
+                        int64_t Di = i < M ? elements(i) : 0;
+                        if (Di <= 0 || Di >= (int64_t(1) << 34)) Di = i < M ? 1 : 0;
+                        size[j] = Di;
+                    }
+                    const uint32_t b = static_cast<uint32_t>(ladder_width(a, static_cast<int>(rungs >> (4 * j)) & 15));
+                    units[j] = groups_of(size[j]) * b;
+                    own[k] += units[j];
+                    widths[k] |= b << (8 * q);
                 }
-                own[k] += stream_bytes(Di, ladder_width(a, static_cast<int>(rungs >> (4 * j)) & 15));
+                upto[k] = wave_inclusive_scan(static_cast<uint64_t>(own[k]), lane);
             }
-            upto[k] = wave_inclusive_scan(own[k], lane);
             if (lane == kWave - 1) wave_bytes[k * kAllocWavesMax + wave] = upto[k];
         }
         __syncthreads();
@@ -2441,19 +2873,11 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
         const uint64_t scan = row_inclusive_scan(of_wave);
 #pragma unroll
         for (int k = 0; k < kAllocQuads; ++k) {
-            uint64_t off = byte_carry + read_lane(scan, 16 * k + wave) - read_lane(of_wave, 16 * k + wave) + upto[k] - own[k];
-            byte_carry += read_lane(scan, 16 * k + 15);
-            uint64_t at[kQ];
-            uint32_t widths = 0;
-#pragma unroll
-            for (int q = 0; q < kQ; ++q) {
-                const int j = k * kQ + q;
-                const int b = ladder_width(a, static_cast<int>(rungs >> (4 * j)) & 15);
-                widths |= static_cast<uint32_t>(b) << (8 * q);
-                at[q] = off;
-                off += stream_bytes(size[j], b);
-            }
-            store_quad(item(k * kQ), widths, at);
+            const uint64_t off = byte_carry + 32u * (read_lane(scan, 16 * k + wave) - read_lane(of_wave, 16 * k + wave) + upto[k] - own[k]);
+            byte_carry += 32u * read_lane(scan, 16 * k + 15);
+            if (!in_round(k)) continue;
+            const uint32_t quad[kQ] = {units[k * kQ], units[k * kQ + 1], units[k * kQ + 2], units[k * kQ + 3]};
+            store_quad(item(k * kQ), widths[k], quad, off);
         }
     }
     // items beyond the registers, round by round
@@ -2472,32 +2896,36 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
                 const float wi = w[i];
                 const uint32_t cls = class_of(bin_of(ratio_of(wi, D4[q])));
                 rung[q] = static_cast<int>(cls & 7u);
-                if (cls & 8u) settle(wi, D4[q], rung[q], ties[q]);
+                if (cls & 8u) settle_item(wi, D4[q], a, br, steps, t.price, rung[q], ties[q]);
             }
             tie4[q] = tie_bits(D4[q], rung[q], ties[q]);
             sum += tie4[q];
         }
-        uint64_t before = tie_carry + block_exclusive_scan(sum, wave_round[0], total);
-        tie_carry += total;
-        uint64_t bytes = 0;
+        if (t.ties > 1) {
+            uint64_t before = tie_carry + block_exclusive_scan(sum, wave_round[0], total);
+            tie_carry += total;
+#pragma unroll
+            for (int q = 0; q < kQ; ++q) {
+                apply_ties(D4[q], rung[q], ties[q], before);
+                before += tie4[q];
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < kQ; ++q) rung[q] += ties[q];   // the one move at the threshold is applied
+        }
+        uint32_t units[kQ], widths = 0;
+        uint64_t all = 0;
 #pragma unroll
         for (int q = 0; q < kQ; ++q) {
-            apply_ties(D4[q], rung[q], ties[q], before);
-            before += tie4[q];
-            bytes += stream_bytes(D4[q], ladder_width(a, rung[q]));
+            const uint32_t b = static_cast<uint32_t>(ladder_width(a, rung[q]));
+            units[q] = groups_of(D4[q]) * b;
+            all += units[q];
+            widths |= b << (8 * q);
         }
-        uint64_t off = byte_carry + block_exclusive_scan(bytes, wave_round[1], total);
-        byte_carry += total;
-        uint64_t at[kQ];
-        uint32_t widths = 0;
-#pragma unroll
-        for (int q = 0; q < kQ; ++q) {
-            const int b = ladder_width(a, rung[q]);
-            widths |= static_cast<uint32_t>(b) << (8 * q);
-            at[q] = off;
-            off += stream_bytes(D4[q], b);
-        }
-        store_quad(base + tid * kQ, widths, at);
+        const uint64_t off = byte_carry + 32u * block_exclusive_scan(all, wave_round[1], total);
+        byte_carry += 32u * total;
+        store_quad(base + tid * kQ, widths, units, off);
+        if (t.ties <= 1) __syncthreads();   // wave_round[1] has been read by everyone
     }
     if (tid == 0) {
         result[0] = static_cast<int64_t>(byte_carry);
@@ -2803,26 +3231,42 @@ int launch_unpack_dequantize_multi(const actq_tensor* tensors, int32_t count, co
 int launch_allocate_bits(const float* w, const int64_t* D_items, int64_t D, int64_t M, int64_t budget_bits,
                          const Ladder& lad, uint8_t* bits, uint64_t* offsets, int64_t* result, void* stream)
 {
-    AllocArgs a;
-    a.M = M;
-    a.D = D;
-    a.D_items = D_items;
-    a.budget_bits = budget_bits;
-    a.lad = lad;
-    for (int r = 0; r < kMaxSteps; ++r) a.inverse[r] = r + 1 < lad.count ? 1.0 / lad.price[r] : 0.0;
-    a.width_nibbles = 0;
-    for (int k = 0; k < lad.count; ++k) a.width_nibbles |= static_cast<uint32_t>(lad.width[k]) << (4 * k);
-    const int64_t moves = M * (lad.count - 1);
+    uint32_t width_nibbles = 0;
+    for (int k = 0; k < lad.count; ++k) width_nibbles |= static_cast<uint32_t>(lad.width[k]) << (4 * k);
+    const AllocBudget total = {static_cast<uint64_t>(budget_bits), static_cast<uint32_t>(lad.width[0]), static_cast<uint32_t>(lad.width[lad.count - 1])};
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (M <= 2 * kAllocBlock && moves <= kMostSmallMoves) {
-        // a thread per move up to the largest workgroup: the (binary64) division of a move is most of its cost
-        const int64_t most = moves > M ? moves : M;
-        const int64_t lanes = (most + kWave - 1) / kWave * kWave;
+    if (M <= (D_items ? 1 : kSmallItems) * kAllocBlock) {
+        SmallAllocArgs a = {};
+        a.M = static_cast<int32_t>(M);
+        a.steps = lad.count - 1;
+        a.width_nibbles = width_nibbles;
+        a.D = D;
+        a.D_items = D_items;
+        a.total = total;
+        for (int r = 0; r < kMaxSteps; ++r) a.price[r] = lad.price[r];
+        if (!D_items) {
+            const AllocVerdict v = alloc_verdict(static_cast<uint64_t>(M) * static_cast<uint64_t>(D), false, total);
+            a.search = v.search;
+            a.loose = v.loose;
+            a.status = static_cast<int32_t>(v.status);
+            a.need = v.search ? static_cast<uint32_t>((v.need + static_cast<uint64_t>(D) - 1) / static_cast<uint64_t>(D)) : 0u;
+            a.unit_bytes = static_cast<uint64_t>((D + kGroup - 1) / kGroup) * (kGroup / 8);
+            a.reciprocal = 1.0 / static_cast<double>(D);
+        }
+        const int64_t lanes = (M + kWave - 1) / kWave * kWave;
         const unsigned block = static_cast<unsigned>(lanes < kAllocBlock ? lanes : kAllocBlock);
-        if (M > kAllocBlock) allocate_bits_small_kernel<kMostSmallMoves, 2><<<1, block, 0, s>>>(w, a, bits, offsets, result);
-        else if (moves > kSmallMoves) allocate_bits_small_kernel<kMostSmallMoves, 1><<<1, block, 0, s>>>(w, a, bits, offsets, result);
-        else allocate_bits_small_kernel<kSmallMoves, 1><<<1, block, 0, s>>>(w, a, bits, offsets, result);
+        if (D_items) allocate_bits_small_kernel<false, 1><<<1, block, 0, s>>>(w, a, bits, offsets, result);
+        else if (M > kAllocBlock) allocate_bits_small_kernel<true, kSmallItems><<<1, block, 0, s>>>(w, a, bits, offsets, result);
+        else allocate_bits_small_kernel<true, 1><<<1, block, 0, s>>>(w, a, bits, offsets, result);
     } else {
+        AllocArgs a;
+        a.M = M;
+        a.D = D;
+        a.D_items = D_items;
+        a.total = total;
+        a.lad = lad;
+        for (int r = 0; r < kMaxSteps; ++r) a.inverse[r] = r + 1 < lad.count ? 1.0 / lad.price[r] : 0.0;
+        a.width_nibbles = width_nibbles;
         allocate_bits_kernel<<<1, kAllocBlock, 0, s>>>(w, a, bits, offsets, result);
     }
     return check_launch("actq_allocate_bits_device");

@@ -623,6 +623,26 @@ def test_device_allocator_at_the_limits_of_its_kernels(M, widths, law):
         assert np.array_equal(offs, np.concatenate([[0], np.cumsum(per)[:-1]])) and total == int(per.sum())
 
 
+# items of one size, where the small kernel counts in units of that size: one and two items per thread, the first item beyond
+# it, one wavefront and a partial second one; sizes whose reciprocal is exact, is not, and the largest
+@pytest.mark.parametrize("law", ["wide", "close", "groups", "few", "zero", "one"])
+@pytest.mark.parametrize("M,widths", [(1, 0x1FE), (4, 0x116), (64, 0x1FE), (65, 0x116), (512, 0x102), (1024, 0x1FE), (1025, 0x116),
+                                      (2047, 0x1FE), (2048, 0x11E), (2049, 0x1FE)])
+def test_device_allocator_of_items_of_one_size(M, widths, law):
+    rng = np.random.default_rng(100 + M)
+    w = _spread(rng, M, law)
+    lo = min(b for b in range(1, 9) if widths >> b & 1)
+    for size in (1, 256, 25089, 2 ** 34 - 1):
+        D = np.full(M, size, dtype=np.int64)
+        for mean in (lo + 0.003, 2.0, 6.7):
+            budget = int(mean * M * size)
+            want = B.allocate_bits(w, D, max(budget, lo * M * size), widths)   # the host's heap, checked against the oracle elsewhere
+            got, offs, total, status = _device_alloc(w, D, max(budget, lo * M * size), widths, True)
+            assert status == 0 and np.array_equal(got, want), (size, mean, np.flatnonzero(got != want)[:6])
+            per = ((D + 255) // 256) * 32 * want.astype(np.int64)
+            assert np.array_equal(offs, np.concatenate([[0], np.cumsum(per)[:-1]])) and total == int(per.sum())
+
+
 def test_device_allocator_with_more_than_2_to_the_32_equal_moves():
     """2^30 items of sensitivity 0 with four steps each: 2^32 undecided moves, all at the price of the threshold.  The
     first items go down to one bit until the budget holds, the others keep eight."""
