@@ -1,8 +1,10 @@
-"""ctypes binding of libactq's C ABI (include/actq.h): argument marshalling only.
+"""Binding of libactq's C ABI (include/actq.h): argument marshalling only.
 
 Every function takes torch tensors (device memory and streams are PyTorch's) or numpy
-arrays for the host-side calls, checks dtypes / contiguity, and forwards raw pointers.
-There is no CPU fallback: if the HIP library cannot be loaded the import of the symbols
+arrays for the host-side calls, checks dtypes / contiguity, and forwards raw pointers: through ctypes
+the calls of the host and those for several tensors, through the native module actq_torch
+(csrc/actq_torch.cpp) the device calls, where the host's time counts.
+There is no CPU fallback: if the HIP library or the module cannot be loaded the first call
 fails with an error.
 """
 from __future__ import annotations
@@ -14,6 +16,7 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libactq.so")
+HOST_PATH = os.path.join(_HERE, "actq_torch.so")
 
 ACTQ_OK, ACTQ_EINVAL, ACTQ_EINFEASIBLE, ACTQ_EHIP = 0, -1, -2, -3
 ACTQ_F32, ACTQ_F16 = 0, 1
@@ -134,6 +137,39 @@ def lib() -> ctypes.CDLL:
     return L
 
 
+_host = None
+# the library's entry points that the native module calls, in the order in which it takes their addresses
+_ATTACHED = ("actq_last_error", "actq_group_stats", "actq_sample_sensitivity", "actq_allocate_bits_device", "actq_quantize_pack",
+             "actq_unpack_dequantize", "actq_relu_mask_bytes", "actq_relu_forward", "actq_relu_backward", "actq_pool2d_output_size",
+             "actq_maxpool2d_forward", "actq_maxpool2d_backward")
+
+
+def host():
+    """The native module, built from the source beside it (as the library is) and told where the library's entry points are."""
+    global _host
+    if _host is None:
+        import importlib.machinery
+        import importlib.util
+        import torch  # noqa: F401  (brings the libraries the module needs)
+        from . import build as _build
+        L = lib()
+        want, have = _build.host_source_hash(), _digest_in_file(HOST_PATH)
+        if have != want:
+            try:
+                _build.build_host()
+            except Exception as exc:
+                raise RuntimeError(f"{HOST_PATH} was built from another source or for another torch (digest {have}, expected {want}) "
+                                   f"and cannot be rebuilt here: {exc}") from exc
+        loader = importlib.machinery.ExtensionFileLoader("actq_torch", HOST_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("actq_torch", loader))
+        loader.exec_module(module)
+        if module.source_hash != want:
+            raise RuntimeError(f"{HOST_PATH} reports source digest {module.source_hash}, expected {want}")
+        module.attach(ActqError, tuple(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _ATTACHED))
+        _host = module
+    return _host
+
+
 def _check(rc: int) -> None:
     if rc != ACTQ_OK:
         raise ActqError(rc, lib().actq_last_error().decode())
@@ -209,19 +245,7 @@ def packed_bytes(N: int, D: int, bits_host, G: int = G_DEFAULT):
 
 def group_stats(x, gmin=None, grange=None, G: int = G_DEFAULT, stream=None):
     """Device: per-group (min, range) of x viewed as [N, D]; returns float32 [N, ng] tensors."""
-    torch = _torch()
-    N, D = _view2d(x)
-    ng = (D + G - 1) // G
-    if gmin is None:
-        gmin = torch.empty((N, ng), dtype=torch.float32, device=x.device)
-    if grange is None:
-        grange = torch.empty((N, ng), dtype=torch.float32, device=x.device)
-    if gmin.numel() != N * ng or grange.numel() != N * ng:
-        raise ValueError("gmin / grange must hold N*ng floats")
-    _check(lib().actq_group_stats(_dev(x, name="x"), _dtype_code(x), N, D, G,
-                                  _dev(gmin, torch.float32, "gmin"), _dev(grange, torch.float32, "grange"),
-                                  _stream(stream)))
-    return gmin, grange
+    return (_host or host()).group_stats(x, gmin, grange, G, stream)
 
 
 def header_bytes(N: int, D: int, hf: int = ACTQ_HDR_F32, G: int = G_DEFAULT) -> int:
@@ -230,63 +254,23 @@ def header_bytes(N: int, D: int, hf: int = ACTQ_HDR_F32, G: int = G_DEFAULT) -> 
     return int(out.value)
 
 
-def _header_ptr(header, N, ng, hf):
-    torch = _torch()
-    want = torch.int16 if hf == ACTQ_HDR_BF16 else torch.float32
-    if header.dtype != want:
-        raise TypeError(f"header must be {want} for this header format, got {header.dtype}")
-    if header.numel() != (2 if hf == ACTQ_HDR_TENSOR else N * ng * 2):
-        raise ValueError("header must hold N*ng*2 entries (2 for ACTQ_HDR_TENSOR)")
-    return _dev(header, want, "header")
-
-
 def quantize_pack(x, bits, offsets, packed, header, seed: int, tag: int = 0, noise_bits: int = 24,
                   G: int = G_DEFAULT, stream=None, hf: int = ACTQ_HDR_F32):
     """Device: writes the bit stream into `packed` (uint8) and the group headers into `header`
     (float32 [N*ng*2] for ACTQ_HDR_F32, int16 [N*ng*2] bfloat16 bit patterns for ACTQ_HDR_BF16).
     With ACTQ_HDR_TENSOR `header` is the float32 [2] pair from tensor_stats and is only read."""
-    torch = _torch()
-    N, D = _view2d(x)
-    ng = (D + G - 1) // G
-    if bits.numel() != N or offsets.numel() != N:
-        raise ValueError("bits and offsets must have N entries")
-    _check(lib().actq_quantize_pack(_dev(x, name="x"), _dtype_code(x), N, D, G,
-                                    _dev(bits, torch.uint8, "bits"), _dev(offsets, torch.int64, "offsets"),
-                                    seed & (2 ** 64 - 1), tag & (2 ** 64 - 1), noise_bits,
-                                    _dev(packed, torch.uint8, "packed"), packed.numel(),
-                                    _header_ptr(header, N, ng, hf), hf, _stream(stream)))
-    return packed, header
+    return (_host or host()).quantize_pack(x, bits, offsets, packed, header, seed, tag, noise_bits, G, stream, hf)
 
 
 def unpack_dequantize(packed, header, bits, offsets, out, G: int = G_DEFAULT, stream=None,
                       hf: int = ACTQ_HDR_F32):
     """Device: reconstructs `out` ([N, ...] float32 or float16) from the bit stream."""
-    torch = _torch()
-    N, D = _view2d(out)
-    ng = (D + G - 1) // G
-    if bits.numel() != N or offsets.numel() != N:
-        raise ValueError("bits and offsets must have N entries")
-    _check(lib().actq_unpack_dequantize(_dev(packed, torch.uint8, "packed"), packed.numel(),
-                                        _header_ptr(header, N, ng, hf), hf,
-                                        _dev(bits, torch.uint8, "bits"), _dev(offsets, torch.int64, "offsets"),
-                                        N, D, G, _dev(out, name="out"), _dtype_code(out), _stream(stream)))
-    return out
+    return (_host or host()).unpack_dequantize(packed, header, bits, offsets, out, G, stream, hf)
 
 
 def sample_sensitivity(grange, grad2=None, w=None, G: int = G_DEFAULT, stream=None):
     """Device: w[n] = (G/6) * grad2[n] * sum_g grange[n, g]^2 (grad2 = None means 1)."""
-    torch = _torch()
-    if grange.dim() != 2:
-        raise ValueError("grange must be [N, ng]")
-    N, ng = int(grange.shape[0]), int(grange.shape[1])
-    if w is None:
-        w = torch.empty(N, dtype=torch.float32, device=grange.device)
-    if w.numel() != N or (grad2 is not None and grad2.numel() != N):
-        raise ValueError("w and grad2 must have N entries")
-    g2 = None if grad2 is None else _dev(grad2, torch.float32, "grad2")
-    _check(lib().actq_sample_sensitivity(_dev(grange, torch.float32, "grange"), N, ng, G, g2,
-                                         _dev(w, torch.float32, "w"), _stream(stream)))
-    return w
+    return (_host or host()).sample_sensitivity(grange, grad2, w, G, stream)
 
 
 def allocate_bits(w_host, D_host, budget_bits: int, widths: int = ACTQ_WIDTHS_POW2) -> np.ndarray:
@@ -312,58 +296,15 @@ def allocate_bits_device(w, D, budget_bits: int, widths: int = ACTQ_WIDTHS_POW2,
     tensor [M]; `D` is an int (every item has D elements) or an int64 device tensor [M].
     Returns (bits uint8 [M], offsets int64 [M], result int64 [2] = total bytes, status); nothing
     is synchronised, so the status is the caller's to read when convenient."""
-    torch = _torch()
-    M = int(w.numel())
-    if bits is None:
-        bits = torch.empty(M, dtype=torch.uint8, device=w.device)
-    if offsets is None:
-        offsets = torch.empty(M, dtype=torch.int64, device=w.device)
-    if result is None:
-        result = torch.empty(2, dtype=torch.int64, device=w.device)
-    if bits.numel() != M or offsets.numel() != M or result.numel() != 2:
-        raise ValueError("bits and offsets must have M entries, result 2")
-    if isinstance(D, int):
-        d_items, d_uniform = None, D
-    else:
-        if D.numel() != M:
-            raise ValueError("D must have M entries")
-        d_items, d_uniform = _dev(D, torch.int64, "D"), 0
-    _check(lib().actq_allocate_bits_device(_dev(w, torch.float32, "w"), d_items, d_uniform, M, G,
-                                           int(budget_bits), int(widths), _dev(bits, torch.uint8, "bits"),
-                                           _dev(offsets, torch.int64, "offsets"),
-                                           _dev(result, torch.int64, "result"), _stream(stream)))
-    return bits, offsets, result
+    return (_host or host()).allocate_bits_device(w, D, int(budget_bits), int(widths), bits, offsets, result, G, stream)
 
 
 def compress_mixed(x, grad2, budget_bits: int, widths: int, packed_capacity: int, seed: int, tag: int, noise_bits: int,
                    hf: int = ACTQ_HDR_F32):
     """Device: the forward pass of one activation, x viewed as [N, D], on the current stream: group
-    statistics, sensitivities, bit allocation, quantize + pack -- the same four calls with one
-    marshalling and one scratch tensor.  Returns (bits, offsets, packed, header)."""
-    torch = _torch()
-    N, D = _view2d(x)
-    ng = (D + G_DEFAULT - 1) // G_DEFAULT
-    xp, dt, dev = _dev(x, name="x"), _dtype_code(x), x.device
-    if grad2 is not None and grad2.numel() != N:
-        raise ValueError("grad2 must have N entries")
-    g2 = None if grad2 is None else _dev(grad2, torch.float32, "grad2")
-    L, stream, groups = lib(), _stream(None), N * ng
-    # int64: the allocator's result; then float32: minima, ranges, sensitivities
-    scratch = torch.empty(2 + (2 * groups + N + 1) // 2, dtype=torch.int64, device=dev)
-    result = scratch.data_ptr()
-    gmin = result + 16
-    grange, w = gmin + 4 * groups, gmin + 8 * groups
-    bits = torch.empty(N, dtype=torch.uint8, device=dev)
-    offsets = torch.empty(N, dtype=torch.int64, device=dev)
-    packed = torch.empty(packed_capacity, dtype=torch.uint8, device=dev)
-    header = torch.empty(groups * 2, dtype=torch.int16 if hf == ACTQ_HDR_BF16 else torch.float32, device=dev)
-    bp, op = bits.data_ptr(), offsets.data_ptr()
-    _check(L.actq_group_stats(xp, dt, N, D, G_DEFAULT, gmin, grange, stream))
-    _check(L.actq_sample_sensitivity(grange, N, ng, G_DEFAULT, g2, w, stream))
-    _check(L.actq_allocate_bits_device(w, None, D, N, G_DEFAULT, int(budget_bits), int(widths), bp, op, result, stream))
-    _check(L.actq_quantize_pack(xp, dt, N, D, G_DEFAULT, bp, op, seed & (2 ** 64 - 1), tag & (2 ** 64 - 1), noise_bits,
-                                packed.data_ptr(), packed_capacity, header.data_ptr(), hf, stream))
-    return bits, offsets, packed, header
+    statistics, sensitivities, bit allocation, quantize + pack with one marshalling and one scratch
+    tensor.  Returns (bits, offsets, packed, header)."""
+    return (_host or host()).compress_mixed(x, grad2, int(budget_bits), int(widths), packed_capacity, seed, tag, noise_bits, hf)
 
 
 # ----------------------------------------------------------------------------- exact layer contexts
@@ -376,30 +317,12 @@ def relu_mask_bytes(n: int) -> int:
 
 def relu_forward(x, y=None, mask=None, stream=None):
     """Device: y = max(x, 0) and the 1-bit context.  Returns (y, mask uint8)."""
-    torch = _torch()
-    n = int(x.numel())
-    if y is None:
-        y = torch.empty_like(x)
-    if mask is None:
-        mask = torch.empty(relu_mask_bytes(n), dtype=torch.uint8, device=x.device)
-    if y.numel() != n or y.dtype != x.dtype or mask.numel() != relu_mask_bytes(n):
-        raise ValueError("y must match x and mask must have relu_mask_bytes(n) bytes")
-    _check(lib().actq_relu_forward(_dev(x, None, "x"), _dtype_code(x), n, _dev(y, None, "y"),
-                                   _dev(mask, torch.uint8, "mask"), _stream(stream)))
-    return y, mask
+    return (_host or host()).relu_forward(x, y, mask, stream)
 
 
 def relu_backward(mask, grad_y, grad_x=None, stream=None):
     """Device: grad_x = grad_y where the stored bit is set, +0 elsewhere."""
-    torch = _torch()
-    n = int(grad_y.numel())
-    if grad_x is None:
-        grad_x = torch.empty_like(grad_y)
-    if grad_x.numel() != n or grad_x.dtype != grad_y.dtype or mask.numel() != relu_mask_bytes(n):
-        raise ValueError("grad_x must match grad_y and mask must have relu_mask_bytes(n) bytes")
-    _check(lib().actq_relu_backward(_dev(mask, torch.uint8, "mask"), _dev(grad_y, None, "grad_y"), _dtype_code(grad_y),
-                                    n, _dev(grad_x, None, "grad_x"), _stream(stream)))
-    return grad_x
+    return (_host or host()).relu_backward(mask, grad_y, grad_x, stream)
 
 
 def pool2d_output_size(H, W, kernel, stride, padding=(0, 0), dilation=(1, 1)):
@@ -411,39 +334,13 @@ def pool2d_output_size(H, W, kernel, stride, padding=(0, 0), dilation=(1, 1)):
 
 def maxpool2d_forward(x, kernel, stride, padding=(0, 0), dilation=(1, 1), y=None, argmax=None, stream=None):
     """Device: x [..., H, W] -> (y [..., OH, OW], argmax uint8 [..., OH, OW])."""
-    torch = _torch()
-    H, W = int(x.shape[-2]), int(x.shape[-1])
-    planes = int(x.numel() // (H * W))
-    OH, OW = pool2d_output_size(H, W, kernel, stride, padding, dilation)
-    shape = tuple(x.shape[:-2]) + (OH, OW)
-    if y is None:
-        y = torch.empty(shape, dtype=x.dtype, device=x.device)
-    if argmax is None:
-        argmax = torch.empty(shape, dtype=torch.uint8, device=x.device)
-    if y.numel() != planes * OH * OW or argmax.numel() != planes * OH * OW or y.dtype != x.dtype:
-        raise ValueError("y and argmax must have planes*OH*OW elements")
-    _check(lib().actq_maxpool2d_forward(_dev(x, None, "x"), _dtype_code(x), planes, H, W, *kernel, *stride, *padding,
-                                        *dilation, _dev(y, None, "y"), _dev(argmax, torch.uint8, "argmax"),
-                                        _stream(stream)))
-    return y, argmax
+    return (_host or host()).maxpool2d_forward(x, kernel, stride, padding, dilation, y, argmax, stream)
 
 
 def maxpool2d_backward(argmax, grad_y, H, W, kernel, stride, padding=(0, 0), dilation=(1, 1), grad_x=None,
                        stream=None):
     """Device: gradient of the input from the stored window positions."""
-    torch = _torch()
-    OH, OW = pool2d_output_size(H, W, kernel, stride, padding, dilation)
-    if tuple(grad_y.shape[-2:]) != (OH, OW) or argmax.numel() != grad_y.numel():
-        raise ValueError("grad_y and argmax must be [..., OH, OW]")
-    planes = int(grad_y.numel() // (OH * OW))
-    if grad_x is None:
-        grad_x = torch.empty(tuple(grad_y.shape[:-2]) + (H, W), dtype=grad_y.dtype, device=grad_y.device)
-    if grad_x.numel() != planes * H * W or grad_x.dtype != grad_y.dtype:
-        raise ValueError("grad_x must have planes*H*W elements")
-    _check(lib().actq_maxpool2d_backward(_dev(argmax, torch.uint8, "argmax"), _dev(grad_y, None, "grad_y"),
-                                         _dtype_code(grad_y), planes, H, W, *kernel, *stride, *padding, *dilation,
-                                         _dev(grad_x, None, "grad_x"), _stream(stream)))
-    return grad_x
+    return (_host or host()).maxpool2d_backward(argmax, grad_y, H, W, kernel, stride, padding, dilation, grad_x, stream)
 
 
 def tensor_stats(x, zr=None, stream=None):

@@ -1,4 +1,5 @@
-"""Builds libactq.so in-tree with hipcc for gfx950 (cross-compiles without a GPU)."""
+"""Builds libactq.so in-tree with hipcc for gfx950 (cross-compiles without a GPU), and actq_torch.so, the
+binding's native half, with the host compiler against torch's headers."""
 from __future__ import annotations
 
 import os
@@ -27,19 +28,35 @@ HIPCC_FLAGS = [
 ]
 
 
-def source_hash() -> str:
-    """Digest of everything the binary depends on: the sources, the public and internal headers
-    and the compiler flags."""
+HOST_LIB = os.path.join(_HERE, "actq_torch.so")
+HOST_SOURCE = "actq_torch.cpp"
+HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+              "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM"]   # what torch's headers for this platform ask for
+
+
+def _digest(files, *texts) -> str:
     import hashlib
     h = hashlib.sha256()
-    files = [os.path.join(CSRC, f) for f in sorted(os.listdir(CSRC)) if f.endswith((".hip", ".cpp", ".h"))]
-    files.append(os.path.join(ROOT, "include", "actq.h"))
     for path in files:
         h.update(os.path.basename(path).encode())
         with open(path, "rb") as f:
             h.update(f.read())
-    h.update(" ".join(HIPCC_FLAGS).encode())
+    for text in texts:
+        h.update(text.encode())
     return h.hexdigest()[:16]
+
+
+def source_hash() -> str:
+    """Digest of everything the library depends on: the sources, the public and internal headers
+    and the compiler flags."""
+    files = [os.path.join(CSRC, f) for f in sorted(os.listdir(CSRC)) if f.endswith((".hip", ".cpp", ".h")) and f != HOST_SOURCE]
+    return _digest(files + [os.path.join(ROOT, "include", "actq.h")], " ".join(HIPCC_FLAGS))
+
+
+def host_source_hash() -> str:
+    """The same for the binding's native half, which depends on torch's version as well."""
+    import torch
+    return _digest([os.path.join(CSRC, HOST_SOURCE), os.path.join(ROOT, "include", "actq.h")], " ".join(HOST_FLAGS), torch.__version__)
 
 
 def hipcc() -> str:
@@ -69,5 +86,32 @@ def build(verbose: bool = False) -> str:
     return LIB
 
 
+def build_host(verbose: bool = False) -> str:
+    """Compile the binding's native half; always recompiles."""
+    import sysconfig
+    import torch
+    where = os.path.dirname(torch.__file__)
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if cxx is None:
+        raise RuntimeError("no C++ compiler: actq_torch cannot be built")
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc())))
+    tmp = HOST_LIB + f".{os.getpid()}.tmp"
+    cmd = [cxx, *HOST_FLAGS, f'-DACTQ_SOURCE_HASH="{host_source_hash()}"', f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    for path in (os.path.join(ROOT, "include"), os.path.join(where, "include"), os.path.join(where, "include", "torch", "csrc", "api", "include"),
+                 os.path.join(rocm, "include"), sysconfig.get_paths()["include"]):
+        cmd += ["-isystem" if path.startswith(where) else "-I", path]
+    cmd += [os.path.join(CSRC, HOST_SOURCE), "-o", tmp, "-L" + os.path.join(where, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{cxx} failed:\n{r.stderr}")
+    if verbose and r.stderr.strip():
+        print(r.stderr, file=sys.stderr)
+    os.replace(tmp, HOST_LIB)
+    return HOST_LIB
+
+
 if __name__ == "__main__":
     print(build(verbose=True))
+    print(build_host(verbose=True))

@@ -49,6 +49,7 @@ class QConfig:
 
 
 config = QConfig()
+_DTYPES = (torch.float32, torch.float16)
 _tags = itertools.count(1)
 _copy_stream = None
 
@@ -94,37 +95,48 @@ def _uniform_widths(N: int, D: int, b: int, device):
     return hit
 
 
+def _settings(N: int, D: int, device):
+    """What the compression of an [N, D] activation is told under `config`: budget in bits, allowed widths, capacity of the
+    stream in bytes, seed, tag, noise bits, header format; widths and offsets if they are fixed."""
+    ng = (D + B.G_DEFAULT - 1) // B.G_DEFAULT
+    if config.mixed:
+        allowed = config.widths & 0x1FE
+        if not allowed:
+            raise ValueError("no allowed width")
+        narrowest = (allowed & -allowed).bit_length() - 1
+        if config.bits < narrowest:
+            raise ValueError(f"an average of {config.bits} bits is below the narrowest allowed width {narrowest}")
+        budget = int(config.bits * N * D)
+        capacity = budget // 8 + N * (ng * B.G_DEFAULT - D) + 32   # the budget in bytes plus the padding of ragged last groups
+        return budget, config.widths, max(capacity, 32), config.seed, next(_tags), config.noise_bits, config.header, None, None
+    b = int(config.bits)
+    if b != config.bits or not 1 <= b <= 8:
+        raise ValueError("a fixed width must be an integer from 1 to 8")
+    bits, offsets, capacity = _uniform_widths(N, D, b, device)
+    return 0, config.widths, max(capacity, 32), config.seed, next(_tags), config.noise_bits, config.header, bits, offsets
+
+
 def compress(x: torch.Tensor, grad2: torch.Tensor | None = None) -> SavedContext:
     """Quantize and pack `x` ([N, ...]: the first dimension indexes the samples) under `config`.
     `grad2` are the squared gradient norms per sample of Eq. (8) (None = all ones)."""
     if not x.is_cuda:
         raise ValueError("activation compression runs on the GPU only")
-    if x.dtype not in (torch.float32, torch.float16):
+    if x.dtype not in _DTYPES:
         raise TypeError(f"unsupported activation dtype {x.dtype}")
     x = x.contiguous()
     N = int(x.shape[0])
     D = int(x.numel() // N)
-    G = B.G_DEFAULT
-    ng = (D + G - 1) // G
     c = SavedContext()
     c.shape, c.dtype, c.N, c.D, c.hf, c.host, c.ready = tuple(x.shape), x.dtype, N, D, config.header, None, None
     x2 = x.view(N, D)
-    if config.mixed:
-        narrowest = min(b for b in range(1, 9) if config.widths >> b & 1)
-        if config.bits < narrowest:
-            raise ValueError(f"an average of {config.bits} bits is below the narrowest allowed width {narrowest}")
-        budget = int(config.bits * N * D)
-        capacity = budget // 8 + N * (ng * G - D) + 32   # the budget in bytes plus the padding of ragged last groups
-        c.bits, c.offsets, c.packed, c.header = B.compress_mixed(x2, grad2, budget, config.widths, max(capacity, 32), config.seed,
-                                                                 next(_tags), config.noise_bits, c.hf)
+    budget, widths, capacity, seed, tag, noise_bits, _, c.bits, c.offsets = _settings(N, D, x.device)
+    if c.bits is None:
+        c.bits, c.offsets, c.packed, c.header = B.compress_mixed(x2, grad2, budget, widths, capacity, seed, tag, noise_bits, c.hf)
     else:
-        b = int(config.bits)
-        if b != config.bits or not 1 <= b <= 8:
-            raise ValueError("a fixed width must be an integer from 1 to 8")
-        c.bits, c.offsets, capacity = _uniform_widths(N, D, b, x.device)
-        c.packed = torch.empty(max(capacity, 32), dtype=torch.uint8, device=x.device)
+        ng = (D + B.G_DEFAULT - 1) // B.G_DEFAULT
+        c.packed = torch.empty(capacity, dtype=torch.uint8, device=x.device)
         c.header = torch.empty(N * ng * 2, dtype=torch.int16 if c.hf == B.ACTQ_HDR_BF16 else torch.float32, device=x.device)
-        B.quantize_pack(x2, c.bits, c.offsets, c.packed, c.header, config.seed, next(_tags), config.noise_bits, hf=c.hf)
+        B.quantize_pack(x2, c.bits, c.offsets, c.packed, c.header, seed, tag, noise_bits, hf=c.hf)
     if config.swap:
         _swap_out(c)
     return c
@@ -163,6 +175,16 @@ def decompress(c: SavedContext) -> torch.Tensor:
 
 
 # ----------------------------------------------------------------------------- functions
+#
+# Linear, ReLU and max pooling have their autograd functions in the native module (csrc/actq_torch.cpp): a small layer
+# is bound by the host, and a function in Python costs it several times what its launches do (forward and backward,
+# ReLU and pooling of a small tensor 131 -> 64 us, a linear layer of 128 x 2048 -> 1000 224 -> 152 us).  Those below serve
+# what a native function cannot: contexts in host memory, torch.compile, torch.jit tracing, functorch's transforms,
+# tensor subclasses, torch-function modes, forward-mode tangents.
+
+def _native(*tensors) -> bool:
+    return not torch.compiler.is_compiling() and (B._host or B.host()).plain(*tensors)
+
 
 def _keep(ctx, c: SavedContext, *tensors) -> None:
     """Hands the compressed context to autograd: its tensors are released when the graph is, so a
@@ -283,6 +305,9 @@ def _pair(v):
 class QLinear(nn.Linear):
     def forward(self, x):
         if torch.is_grad_enabled() and x.is_cuda:
+            if not config.swap and x.dtype in _DTYPES and _native(x, self.weight, self.bias):
+                N = x.shape[0]
+                return B._host.linear(x, self.weight, self.bias, *_settings(N, x.numel() // N, x.device))
             return _QLinearFn.apply(x, self.weight, self.bias)
         return super().forward(x)
 
@@ -307,18 +332,18 @@ class QBatchNorm2d(nn.BatchNorm2d):
 
 class QReLU(nn.Module):
     def forward(self, x):
-        if torch.is_grad_enabled() and x.is_cuda and x.dtype in (torch.float32, torch.float16):
-            return _QReLUFn.apply(x)
+        if torch.is_grad_enabled() and x.is_cuda and x.dtype in _DTYPES:
+            return B._host.relu(x) if _native(x) else _QReLUFn.apply(x)
         return F.relu(x)
 
 
 class QMaxPool2d(nn.MaxPool2d):
     def forward(self, x):
         if (torch.is_grad_enabled() and x.is_cuda and not self.ceil_mode and not self.return_indices
-                and x.dtype in (torch.float32, torch.float16)):
+                and x.dtype in _DTYPES):
             k = _pair(self.kernel_size)
-            s = _pair(self.stride if self.stride is not None else self.kernel_size)
-            return _QMaxPool2dFn.apply(x, k, s, _pair(self.padding), _pair(self.dilation))
+            window = k, _pair(self.stride if self.stride is not None else self.kernel_size), _pair(self.padding), _pair(self.dilation)
+            return B._host.maxpool2d(x, *window) if _native(x) else _QMaxPool2dFn.apply(x, *window)
         return super().forward(x)
 
 

@@ -292,3 +292,85 @@ def test_calls_go_to_the_current_stream():
             assert B._stream(None) == b.cuda_stream and B._stream(a) == a.cuda_stream
         assert B._stream(None) == a.cuda_stream
     assert B._stream(None) == torch.cuda.current_stream().cuda_stream
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("layer", ["linear", "linear without bias", "linear fixed width", "relu", "pool"])
+def test_native_functions_equal_those_in_python(layer, dtype, monkeypatch):
+    """The layers take the native module's autograd functions, or those in Python where something watches: the same
+    results to the last bit, with strided inputs and inputs that need no gradient among them."""
+    import itertools
+    torch.manual_seed(8)
+    L.config.mixed, L.config.bits, L.config.seed = layer != "linear fixed width", 2.0, 21
+    if layer.startswith("linear"):
+        m = L.QLinear(130, 24, bias=layer != "linear without bias", device=DEV, dtype=dtype)
+        inputs = [torch.randn(9, 130, device=DEV), torch.randn(130, 7, device=DEV).t(), torch.randn(3, 5, 130, device=DEV)]
+    else:
+        m = L.QReLU() if layer == "relu" else L.QMaxPool2d(3, 2, 1)
+        inputs = [torch.randn(2, 3, 17, 20, device=DEV), torch.randn(2, 17, 20, 3, device=DEV).permute(0, 3, 1, 2)]
+    for x in inputs:
+        for needs in (True, False):
+            if not needs and not layer.startswith("linear"):
+                continue
+            x = x.to(dtype).detach().requires_grad_(needs)
+            seen = []
+            for native in (True, False):
+                if not native:
+                    monkeypatch.setattr(L, "_native", lambda *t: False)
+                L._tags = itertools.count(30)
+                y = m(x)
+                assert ("FnBackward" in y.grad_fn.name()) == (not native), y.grad_fn.name()   # a function in Python is named after its class
+                g = torch.linspace(-1, 1, y.numel(), device=DEV).reshape(y.shape).to(dtype)
+                seen.append([y.detach(), *torch.autograd.grad(y, ([x] if needs else []) + list(m.parameters()), g)])
+                monkeypatch.undo()
+            for a, b in zip(*seen):
+                assert a.dtype == b.dtype and torch.equal(a, b)
+
+
+def test_native_functions_serve_saved_tensor_hooks_and_report_the_library_s_errors():
+    packed = []
+
+    def pack(t):
+        packed.append(t)
+        return t.cpu()
+
+    x = torch.randn(4, 3, 16, 16, device=DEV, requires_grad=True)
+    net = nn.Sequential(L.QReLU(), L.QMaxPool2d(2), nn.Flatten(), L.QLinear(192, 5, device=DEV))
+    with torch.autograd.graph.saved_tensors_hooks(pack, lambda t: t.to(DEV)):
+        loss = net(x).square().sum()
+    assert len(packed) >= 1 + 1 + 5     # mask, positions, context and weight
+    loss.backward()
+    assert torch.isfinite(x.grad).all() and x.grad.abs().sum() > 0
+    with pytest.raises(RuntimeError):   # the graph has been released
+        loss.backward()
+    with pytest.raises(B.ActqError) as err:
+        L.QReLU()(torch.empty(0, device=DEV, requires_grad=True))
+    assert err.value.code == B.ACTQ_EINVAL and "relu" in str(err.value)
+
+
+def test_the_binding_refuses_wrong_arguments():
+    x = torch.randn(4, 512, device=DEV)
+    bits, offs = torch.full((4,), 2, dtype=torch.uint8, device=DEV), torch.arange(4, device=DEV) * 128
+    packed, header = torch.zeros(512, dtype=torch.uint8, device=DEV), torch.zeros(16, device=DEV)
+    wrong = [
+        (ValueError, lambda: B.group_stats(x.t())),                                     # not contiguous
+        (ValueError, lambda: B.group_stats(x, torch.empty(7, device=DEV))),
+        (TypeError, lambda: B.group_stats(x.double())),
+        (TypeError, lambda: B.group_stats(x.cpu().numpy())),
+        (TypeError, lambda: B.quantize_pack(x, bits.int(), offs, packed, header, 1)),
+        (TypeError, lambda: B.quantize_pack(x, bits, offs, packed, header, 1, hf=B.ACTQ_HDR_BF16)),
+        (ValueError, lambda: B.quantize_pack(x, bits[:3], offs, packed, header, 1)),
+        (ValueError, lambda: B.unpack_dequantize(packed, header[:14], bits, offs, x)),
+        (B.ActqError, lambda: B.quantize_pack(x, bits, offs, packed, header, 1, noise_bits=12)),
+        (ValueError, lambda: B.sample_sensitivity(x[0])),
+        (ValueError, lambda: B.allocate_bits_device(x[0], x[0].long()[:3], 5000)),
+        (B.ActqError, lambda: B.allocate_bits_device(x[0], 512, -1)),
+        (ValueError, lambda: B.relu_forward(x, x.half())),
+        (ValueError, lambda: B.relu_backward(packed, x)),
+        (B.ActqError, lambda: B.maxpool2d_forward(x.view(4, 16, 32), (2, 2), (2, 2), (2, 2))),
+        (ValueError, lambda: B.maxpool2d_backward(packed, x, 9, 9, (2, 2), (2, 2))),
+        (ZeroDivisionError, lambda: B.group_stats(x[:0])),
+    ]
+    for kind, call in wrong:
+        with pytest.raises(kind):
+            call()

@@ -1,0 +1,59 @@
+"""The native module of the binding: built from the source beside it, and left alone where something watches or
+transforms Python-level autograd functions (nothing here touches a GPU)."""
+import pytest
+import torch
+import torch.autograd.forward_ad as forward_ad
+import torch.nn as nn
+
+from paper_2104_14129_amd import binding as B
+from paper_2104_14129_amd import build as lib_build
+from paper_2104_14129_amd import layers as L
+
+
+def test_the_native_module_was_built_from_the_source_beside_it():
+    assert B.host().source_hash == lib_build.host_source_hash() == B._digest_in_file(B.HOST_PATH)
+
+
+def test_plain_tensors_and_parameters_take_the_native_functions():
+    x = torch.randn(3, 4)
+    assert L._native(x) and L._native(x.requires_grad_(), nn.Parameter(x.detach()), None)
+    with torch.no_grad():
+        assert L._native(x)
+
+
+class _Watching(torch.overrides.TorchFunctionMode):
+    def __torch_function__(self, func, types, args=(), kwargs=None):
+        return func(*args, **(kwargs or {}))
+
+
+class _Sub(torch.Tensor):
+    pass
+
+
+@pytest.mark.parametrize("what", ["trace", "vmap", "grad", "jvp", "dual", "mode", "subclass", "no tensor"])
+def test_watched_tensors_take_the_functions_in_python(what):
+    x, seen = torch.randn(3, 4), []
+
+    def probe(t):
+        seen.append(L._native(t))
+        return (t * 1.0).sum()
+
+    if what == "trace":
+        torch.jit.trace(probe, x, check_trace=False)
+    elif what == "vmap":
+        torch.func.vmap(probe)(x)
+    elif what == "grad":
+        torch.func.grad(probe)(x)
+    elif what == "jvp":
+        torch.func.jvp(probe, (x,), (x,))
+    elif what == "dual":
+        with forward_ad.dual_level():
+            probe(forward_ad.make_dual(x, x))
+    elif what == "mode":
+        with _Watching():
+            seen.append(L._native(x))
+    elif what == "subclass":
+        seen.append(L._native(x.as_subclass(_Sub)))
+    else:
+        seen.append(L._native(x.numpy()))
+    assert seen == [False]
