@@ -1516,6 +1516,9 @@ __global__ __launch_bounds__(kSensMaxBlock) void sample_sensitivity_kernel(const
     if (n >= N) return;
     const float* r = grange + static_cast<int64_t>(n) * ng;
     const uint32_t threads = blockDim.x;
+    // asked for now, needed at the end
+    float norm2 = 1.0f;
+    if (grad2) norm2 = grad2[n];
     float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
     uint32_t g = threadIdx.x;
     for (; g + 3 * threads < ng; g += 4 * threads) {
@@ -1534,13 +1537,16 @@ __global__ __launch_bounds__(kSensMaxBlock) void sample_sensitivity_kernel(const
     acc += dpp_f32<kDppXor8>(acc);
     acc += __shfl_xor(acc, 16);
     acc += __shfl_xor(acc, 32);
-    if ((threadIdx.x & (kWave - 1)) == 0) partial[threadIdx.x >> 6] = acc;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float total = 0.0f;
-        for (uint32_t k = 0; k < threads / kWave; ++k) total += partial[k];
-        w[n] = coeff * total * (grad2 ? grad2[n] : 1.0f);
+    float total = 0.0f;
+    if (threads == kWave) {
+        total += acc;
+    } else {
+        if ((threadIdx.x & (kWave - 1)) == 0) partial[threadIdx.x >> 6] = acc;
+        __syncthreads();
+        if (threadIdx.x == 0)
+            for (uint32_t k = 0; k < threads / kWave; ++k) total += partial[k];
     }
+    if (threadIdx.x == 0) w[n] = coeff * total * norm2;
 }
 
 // ------------------------------------------------------------------------------------
