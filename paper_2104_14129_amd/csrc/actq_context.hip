@@ -873,10 +873,10 @@ int launch_relu_forward(const void* x, int dtype, int64_t n, void* y, uint8_t* m
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t mask_words = (n + 255) / 256 * 8;
     if (dtype == ACTQ_F32) {
-        relu_forward_kernel<float><<<relu_blocks(n, 4), kBlock, 0, s>>>(
+        launch(relu_forward_kernel<float>, relu_blocks(n, 4), kBlock, s, 
             static_cast<const float*>(x), n, mask_words, static_cast<float*>(y), reinterpret_cast<uint32_t*>(mask));
     } else {
-        relu_forward_kernel<_Float16><<<relu_blocks(n, 2), kBlock, 0, s>>>(
+        launch(relu_forward_kernel<_Float16>, relu_blocks(n, 2), kBlock, s, 
             static_cast<const _Float16*>(x), n, mask_words, static_cast<_Float16*>(y), reinterpret_cast<uint32_t*>(mask));
     }
     return launched("actq_relu_forward");
@@ -887,10 +887,10 @@ int launch_relu_backward(const uint8_t* mask, const void* grad_y, int dtype, int
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t mask_words = (n + 255) / 256 * 8;
     if (dtype == ACTQ_F32) {
-        relu_backward_kernel<float><<<relu_blocks(n, 4), kBlock, 0, s>>>(
+        launch(relu_backward_kernel<float>, relu_blocks(n, 4), kBlock, s, 
             reinterpret_cast<const uint32_t*>(mask), mask_words, static_cast<const float*>(grad_y), n, static_cast<float*>(grad_x));
     } else {
-        relu_backward_kernel<_Float16><<<relu_blocks(n, 2), kBlock, 0, s>>>(
+        launch(relu_backward_kernel<_Float16>, relu_blocks(n, 2), kBlock, s, 
             reinterpret_cast<const uint32_t*>(mask), mask_words, static_cast<const _Float16*>(grad_y), n, static_cast<_Float16*>(grad_x));
     }
     return launched("actq_relu_backward");
@@ -1132,8 +1132,8 @@ static void maxpool_forward_typed(const T* x, int64_t planes, const PoolShape& p
         const bool nt = sizeof(T) == 4 ? p.kh == 3 || p.W % 4 == 0 : p.W % 8 == 0;
 #define ACTQ_POOL_ROWS(K, PH, PW, S)                                                                                                         \
     do {                                                                                                                                     \
-        if (nt) maxpool2d_forward_rows_kernel<T, K, PH, PW, S, true><<<blocks, kBlock, 0, s>>>(x, g, rows, y, argmax);                       \
-        else if constexpr (sizeof(T) == 2 || K == 2) maxpool2d_forward_rows_kernel<T, K, PH, PW, S, false><<<blocks, kBlock, 0, s>>>(x, g, rows, y, argmax); \
+        if (nt) launch(maxpool2d_forward_rows_kernel<T, K, PH, PW, S, true>, blocks, kBlock, s, x, g, rows, y, argmax);                       \
+        else if constexpr (sizeof(T) == 2 || K == 2) launch(maxpool2d_forward_rows_kernel<T, K, PH, PW, S, false>, blocks, kBlock, s, x, g, rows, y, argmax); \
     } while (0)
         if (p.sh == 1) ACTQ_POOL_ROWS(3, 1, 1, 1);
         else if (p.kh == 2 && p.ph == 0) ACTQ_POOL_ROWS(2, 0, 0, 2);
@@ -1145,9 +1145,9 @@ static void maxpool_forward_typed(const T* x, int64_t planes, const PoolShape& p
         return;
     }
     const Pool g = make_pool(p, planes, static_cast<int64_t>(p.OH) * p.OW, &grid);
-    if (p.kh == 3 && p.kw == 3) maxpool2d_forward_kernel<T, 3, 3><<<grid, kBlock, 0, s>>>(x, planes, g, y, argmax);
-    else if (p.kh == 2 && p.kw == 2) maxpool2d_forward_kernel<T, 2, 2><<<grid, kBlock, 0, s>>>(x, planes, g, y, argmax);
-    else maxpool2d_forward_kernel<T, 0, 0><<<grid, kBlock, 0, s>>>(x, planes, g, y, argmax);
+    if (p.kh == 3 && p.kw == 3) launch(maxpool2d_forward_kernel<T, 3, 3>, grid, kBlock, s, x, planes, g, y, argmax);
+    else if (p.kh == 2 && p.kw == 2) launch(maxpool2d_forward_kernel<T, 2, 2>, grid, kBlock, s, x, planes, g, y, argmax);
+    else launch(maxpool2d_forward_kernel<T, 0, 0>, grid, kBlock, s, x, planes, g, y, argmax);
 }
 
 template <typename T>
@@ -1169,9 +1169,9 @@ static void maxpool_backward_typed(const uint8_t* argmax, const T* grad_y, int64
         dim3 unused;
         const Pool g = make_pool(p, planes, 1, &unused);
         const unsigned blocks = (q.total + kPoolBwdBlock - 1) / kPoolBwdBlock;
-        if (p.kh == 2) maxpool2d_backward_stream_kernel<T, 2, 0, false><<<blocks, kPoolBwdBlock, 0, s>>>(argmax, grad_y, g, q, grad_x);
-        else if (rule.join) maxpool2d_backward_stream_kernel<T, 3, 1, true><<<blocks, kPoolBwdBlock, 0, s>>>(argmax, grad_y, g, q, grad_x);
-        else maxpool2d_backward_stream_kernel<T, 3, 1, false><<<blocks, kPoolBwdBlock, 0, s>>>(argmax, grad_y, g, q, grad_x);
+        if (p.kh == 2) launch(maxpool2d_backward_stream_kernel<T, 2, 0, false>, blocks, kPoolBwdBlock, s, argmax, grad_y, g, q, grad_x);
+        else if (rule.join) launch(maxpool2d_backward_stream_kernel<T, 3, 1, true>, blocks, kPoolBwdBlock, s, argmax, grad_y, g, q, grad_x);
+        else launch(maxpool2d_backward_stream_kernel<T, 3, 1, false>, blocks, kPoolBwdBlock, s, argmax, grad_y, g, q, grad_x);
         return;
     }
     RowPool rows;
@@ -1181,13 +1181,13 @@ static void maxpool_backward_typed(const uint8_t* argmax, const T* grad_y, int64
         const Pool g = make_pool(p, planes, 1, &unused);
         const unsigned blocks = (rows.total + kBlock - 1) / kBlock;
         if (rule.single) {
-            maxpool2d_backward_2x2_kernel<T><<<blocks, kBlock, 0, s>>>(argmax, grad_y, g, rows, grad_x);
+            launch(maxpool2d_backward_2x2_kernel<T>, blocks, kBlock, s, argmax, grad_y, g, rows, grad_x);
             return;
         }
 #define ACTQ_POOL_ROWS(K, P, S)                                                                                              \
     do {                                                                                                                    \
-        if (rule.nt) maxpool2d_backward_rows_kernel<T, K, P, S, true><<<blocks, kBlock, 0, s>>>(argmax, grad_y, g, rows, grad_x);    \
-        else maxpool2d_backward_rows_kernel<T, K, P, S, false><<<blocks, kBlock, 0, s>>>(argmax, grad_y, g, rows, grad_x);      \
+        if (rule.nt) launch(maxpool2d_backward_rows_kernel<T, K, P, S, true>, blocks, kBlock, s, argmax, grad_y, g, rows, grad_x);    \
+        else launch(maxpool2d_backward_rows_kernel<T, K, P, S, false>, blocks, kBlock, s, argmax, grad_y, g, rows, grad_x);      \
     } while (0)
         if (p.sh == 1) ACTQ_POOL_ROWS(3, 1, 1);
         else if (p.kh == 2) ACTQ_POOL_ROWS(2, 0, 2);
@@ -1202,7 +1202,7 @@ static void maxpool_backward_typed(const uint8_t* argmax, const T* grad_y, int64
         q.by_quads = make_fastdiv(static_cast<uint32_t>(q.quads_per_row));
         q.vector_ok = p.W % 4 == 0 && aligned_to(grad_x, 4 * sizeof(T));
         const Pool g = make_pool(p, planes, static_cast<int64_t>(p.H) * q.quads_per_row, &grid);
-#define ACTQ_POOL_BWD(K, S) maxpool2d_backward_quad_kernel<T, K, S><<<grid, kBlock, 0, s>>>(argmax, grad_y, planes, g, q, grad_x)
+#define ACTQ_POOL_BWD(K, S) launch(maxpool2d_backward_quad_kernel<T, K, S>, grid, kBlock, s, argmax, grad_y, planes, g, q, grad_x)
         if (p.kh == 3 && p.sh == 2) ACTQ_POOL_BWD(3, 2);
         else if (p.kh == 3) ACTQ_POOL_BWD(3, 1);
         else if (p.sh == 2) ACTQ_POOL_BWD(2, 2);
@@ -1215,10 +1215,10 @@ static void maxpool_backward_typed(const uint8_t* argmax, const T* grad_y, int64
     const int64_t reach_h = (static_cast<int64_t>(p.dh) * (p.kh - 1) + p.sh) / p.sh;
     const int64_t reach_w = (static_cast<int64_t>(p.dw) * (p.kw - 1) + p.sw) / p.sw;
     const int64_t reach = reach_h > reach_w ? reach_h : reach_w;
-    if (reach <= 1) maxpool2d_backward_kernel<T, 1><<<grid, kBlock, 0, s>>>(argmax, grad_y, planes, g, grad_x);
-    else if (reach == 2) maxpool2d_backward_kernel<T, 2><<<grid, kBlock, 0, s>>>(argmax, grad_y, planes, g, grad_x);
-    else if (reach == 3) maxpool2d_backward_kernel<T, 3><<<grid, kBlock, 0, s>>>(argmax, grad_y, planes, g, grad_x);
-    else maxpool2d_backward_kernel<T, 0><<<grid, kBlock, 0, s>>>(argmax, grad_y, planes, g, grad_x);
+    if (reach <= 1) launch(maxpool2d_backward_kernel<T, 1>, grid, kBlock, s, argmax, grad_y, planes, g, grad_x);
+    else if (reach == 2) launch(maxpool2d_backward_kernel<T, 2>, grid, kBlock, s, argmax, grad_y, planes, g, grad_x);
+    else if (reach == 3) launch(maxpool2d_backward_kernel<T, 3>, grid, kBlock, s, argmax, grad_y, planes, g, grad_x);
+    else launch(maxpool2d_backward_kernel<T, 0>, grid, kBlock, s, argmax, grad_y, planes, g, grad_x);
 }
 
 // The row kernels number their lanes in 31 bits; larger tensors (34 GB and more) take several launches over ranges of planes

@@ -3019,13 +3019,13 @@ static int group_stats_launch(const char* who, const actq_tensor* tensors, int32
         t.first_tile = first;
         if constexpr (CAPACITY == 1) {
             if (ragged) {
-                if (dtype == ACTQ_F32) group_stats_multi_kernel<float, true, 1><<<grid, kGsBlock, 0, s>>>(t);
-                else group_stats_multi_kernel<_Float16, true, 1><<<grid, kGsBlock, 0, s>>>(t);
+                if (dtype == ACTQ_F32) launch(group_stats_multi_kernel<float, true, 1>, grid, kGsBlock, s, t);
+                else launch(group_stats_multi_kernel<_Float16, true, 1>, grid, kGsBlock, s, t);
                 return;
             }
         }
-        if (dtype == ACTQ_F32) group_stats_multi_kernel<float, false, CAPACITY><<<grid, kGsBlock, 0, s>>>(t);
-        else group_stats_multi_kernel<_Float16, false, CAPACITY><<<grid, kGsBlock, 0, s>>>(t);
+        if (dtype == ACTQ_F32) launch(group_stats_multi_kernel<float, false, CAPACITY>, grid, kGsBlock, s, t);
+        else launch(group_stats_multi_kernel<_Float16, false, CAPACITY>, grid, kGsBlock, s, t);
     });
 }
 
@@ -3042,11 +3042,11 @@ static void quantize_tile_launch(bool ragged, const MultiTable<CAPACITY>& t, dim
     const uint32_t k0 = static_cast<uint32_t>(c.seed), k1 = static_cast<uint32_t>(c.seed >> 32);
     if constexpr (CAPACITY == 1) {
         if (ragged) {
-            quantize_pack_tile_kernel<T, NOISE_BITS, HDR, true, 1><<<grid, kBlock, 0, s>>>(t, k0, k1, c.tag, c.packed, c.capacity);
+            launch(quantize_pack_tile_kernel<T, NOISE_BITS, HDR, true, 1>, grid, kBlock, s, t, k0, k1, c.tag, c.packed, c.capacity);
             return;
         }
     }
-    quantize_pack_tile_kernel<T, NOISE_BITS, HDR, false, CAPACITY><<<grid, kBlock, 0, s>>>(t, k0, k1, c.tag, c.packed, c.capacity);
+    launch(quantize_pack_tile_kernel<T, NOISE_BITS, HDR, false, CAPACITY>, grid, kBlock, s, t, k0, k1, c.tag, c.packed, c.capacity);
 }
 
 template <int HDR, int CAPACITY>
@@ -3055,11 +3055,11 @@ static void quantize_run_launch(bool ragged, const MultiTable<CAPACITY>& t, dim3
     const uint32_t k0 = static_cast<uint32_t>(c.seed), k1 = static_cast<uint32_t>(c.seed >> 32);
     if constexpr (CAPACITY == 1) {
         if (ragged) {
-            quantize_pack_run_kernel<HDR, true, 1><<<grid, kBlock, 0, s>>>(t, k0, k1, c.tag, c.packed, c.capacity);
+            launch(quantize_pack_run_kernel<HDR, true, 1>, grid, kBlock, s, t, k0, k1, c.tag, c.packed, c.capacity);
             return;
         }
     }
-    quantize_pack_run_kernel<HDR, false, CAPACITY><<<grid, kBlock, 0, s>>>(t, k0, k1, c.tag, c.packed, c.capacity);
+    launch(quantize_pack_run_kernel<HDR, false, CAPACITY>, grid, kBlock, s, t, k0, k1, c.tag, c.packed, c.capacity);
 }
 
 template <int CAPACITY>
@@ -3098,15 +3098,15 @@ static void dequantize_typed_launch(int layout, const MultiTable<CAPACITY>& t, d
 {
     if constexpr (CAPACITY == 1) {
         if (layout == kRaggedLines) {
-            unpack_dequantize_multi_kernel<T, HDR, NG, kRaggedLines, 1><<<grid, kDqBlock, 0, s>>>(t, pk, capacity);
+            launch(unpack_dequantize_multi_kernel<T, HDR, NG, kRaggedLines, 1>, grid, kDqBlock, s, t, pk, capacity);
             return;
         }
         if (layout == kRagged) {
-            unpack_dequantize_multi_kernel<T, HDR, NG, kRagged, 1><<<grid, kDqBlock, 0, s>>>(t, pk, capacity);
+            launch(unpack_dequantize_multi_kernel<T, HDR, NG, kRagged, 1>, grid, kDqBlock, s, t, pk, capacity);
             return;
         }
     }
-    unpack_dequantize_multi_kernel<T, HDR, NG, kWholeGroups, CAPACITY><<<grid, kDqBlock, 0, s>>>(t, pk, capacity);
+    launch(unpack_dequantize_multi_kernel<T, HDR, NG, kWholeGroups, CAPACITY>, grid, kDqBlock, s, t, pk, capacity);
 }
 
 template <typename T, int NG, int CAPACITY>
@@ -3261,9 +3261,9 @@ int launch_allocate_bits(const float* w, const int64_t* D_items, int64_t D, int6
         }
         const int64_t lanes = (M + kWave - 1) / kWave * kWave;
         const unsigned block = static_cast<unsigned>(lanes < kAllocBlock ? lanes : kAllocBlock);
-        if (D_items) allocate_bits_small_kernel<false, 1><<<1, block, 0, s>>>(w, a, bits, offsets, result);
-        else if (M > kAllocBlock) allocate_bits_small_kernel<true, kSmallItems><<<1, block, 0, s>>>(w, a, bits, offsets, result);
-        else allocate_bits_small_kernel<true, 1><<<1, block, 0, s>>>(w, a, bits, offsets, result);
+        if (D_items) launch(allocate_bits_small_kernel<false, 1>, 1, block, s, w, a, bits, offsets, result);
+        else if (M > kAllocBlock) launch(allocate_bits_small_kernel<true, kSmallItems>, 1, block, s, w, a, bits, offsets, result);
+        else launch(allocate_bits_small_kernel<true, 1>, 1, block, s, w, a, bits, offsets, result);
     } else {
         AllocArgs a;
         a.M = M;
@@ -3273,7 +3273,7 @@ int launch_allocate_bits(const float* w, const int64_t* D_items, int64_t D, int6
         a.lad = lad;
         for (int r = 0; r < kMaxSteps; ++r) a.inverse[r] = r + 1 < lad.count ? 1.0 / lad.price[r] : 0.0;
         a.width_nibbles = width_nibbles;
-        allocate_bits_kernel<<<1, kAllocBlock, 0, s>>>(w, a, bits, offsets, result);
+        launch(allocate_bits_kernel, 1, kAllocBlock, s, w, a, bits, offsets, result);
     }
     return check_launch("actq_allocate_bits_device");
 }
@@ -3286,12 +3286,12 @@ int launch_tensor_stats(const void* x, int dtype, int64_t n, float* zr, void* st
     int64_t blocks = (chunks + kBlock - 1) / kBlock;
     if (blocks < 1) blocks = 1;
     if (blocks > 2048) blocks = 2048;  // eight resident blocks per compute unit: 4096 atomics in all
-    tensor_stats_init_kernel<<<1, kWave, 0, s>>>(words);
+    launch(tensor_stats_init_kernel, 1, kWave, s, words);
     if (dtype == ACTQ_F32)
-        tensor_stats_reduce_kernel<float><<<static_cast<unsigned>(blocks), kBlock, 0, s>>>(static_cast<const float*>(x), n, words);
+        launch(tensor_stats_reduce_kernel<float>, static_cast<unsigned>(blocks), kBlock, s, static_cast<const float*>(x), n, words);
     else
-        tensor_stats_reduce_kernel<_Float16><<<static_cast<unsigned>(blocks), kBlock, 0, s>>>(static_cast<const _Float16*>(x), n, words);
-    tensor_stats_finish_kernel<<<1, kWave, 0, s>>>(words);
+        launch(tensor_stats_reduce_kernel<_Float16>, static_cast<unsigned>(blocks), kBlock, s, static_cast<const _Float16*>(x), n, words);
+    launch(tensor_stats_finish_kernel, 1, kWave, s, words);
     return check_launch("actq_tensor_stats");
 }
 
@@ -3304,7 +3304,7 @@ int launch_sample_sensitivity(const float* grange, int64_t N, int64_t ng, int32_
     // one lane per group up to 1024 lanes, whole wavefronts
     const int64_t lanes = (ng + kWave - 1) / kWave * kWave;
     const unsigned block = static_cast<unsigned>(lanes < kSensMaxBlock ? lanes : kSensMaxBlock);
-    sample_sensitivity_kernel<<<dim3(gx, gy), block, 0, static_cast<hipStream_t>(stream)>>>(
+    launch(sample_sensitivity_kernel, dim3(gx, gy), block, static_cast<hipStream_t>(stream), 
         grange, static_cast<uint32_t>(N), static_cast<uint32_t>(ng), gx, static_cast<float>(G) / 6.0f, grad2, w);
     return check_launch("actq_sample_sensitivity");
 }
