@@ -32,6 +32,18 @@ int launched(const char* who)
 }
 
 // ------------------------------------------------------------------------------------
+// Whether a result of this many bytes is stored through the caches.  The next layer reads it (and the call behind that one):
+// a result that fits the 256 MiB Infinity Cache together with what that layer reads and writes is found there, and HBM has
+// the other half of the traffic left.  ReLU and pooling, forward and backward, one behind the other, non-temporal stores -> these
+// (us; 112 x 112 images, 3x3 / 2 / 1, activations of the given size in binary32 / binary16): 24 MiB 36.5 -> 35.8 / 39.2 -> 38.1, 48 MiB
+// 67.2 -> 60.6 / 68.9 -> 61.9, 80 MiB 104.2 -> 91.2 / 106.3 -> 94.7, 128 MiB 159.8 -> 138.9 / 160.6 -> 143.6, 160 MiB 197.1 -> 170.5 / 197.4 ->
+// 189.7; 2x2 / 2 on 56 x 56 alike, 113 x 113 2 to 8 %, 3x3 / 1 / 1 on 57 x 57 1 to 6 % (binary16 from 128 MiB on 0.8 % behind).
+// Beyond, the lines written last push out those that are read first: at 192 MiB it depends on the image, at 320 MiB all are 2 to 8 % behind.
+// Below, everything stays in the L2 caches, and stores that go through at once are ahead (16 MiB 27.5 -> 30.3).  A few results written
+// in turn and not read are up to 14 % slower (ReLU alone on two tensors, 24 and 32 MiB; from 100 MiB on alike).
+bool store_through_caches(int64_t bytes) { return bytes >= int64_t(24) << 20 && bytes <= int64_t(160) << 20; }
+
+// ------------------------------------------------------------------------------------
 // ReLU.  A lane owns E consecutive elements (E = 4 binary32 or 8 binary16 values: 128 bits); a wavefront
 // covers 64*E elements = 2*E words of the bit stream, with one load and one store per lane.  What bounds it
 // is the mixed stream of reads and writes (6.4 TB/s of the stem's 1.67 GB); short wavefronts and a bit stream
@@ -71,7 +83,8 @@ __device__ __forceinline__ uint32_t spread(uint32_t piece)
     }
 }
 
-template <typename T>
+// NT: non-temporal stores of y.
+template <typename T, bool NT>
 __global__ __launch_bounds__(kBlock) void relu_forward_kernel(const T* x, int64_t n, int64_t mask_words,
                                                               T* y, uint32_t* __restrict__ mask)
 {
@@ -101,7 +114,8 @@ __global__ __launch_bounds__(kBlock) void relu_forward_kernel(const T* x, int64_
         out[k] = positive ? v[k] : static_cast<T>(0.0f);
     }
     if (full) {
-        __builtin_nontemporal_store(out, reinterpret_cast<vec*>(y + mine));
+        if (NT) __builtin_nontemporal_store(out, reinterpret_cast<vec*>(y + mine));
+        else *reinterpret_cast<vec*>(y + mine) = out;
     } else {
 #pragma unroll
         for (int k = 0; k < E; ++k)
@@ -872,13 +886,15 @@ int launch_relu_forward(const void* x, int dtype, int64_t n, void* y, uint8_t* m
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t mask_words = (n + 255) / 256 * 8;
-    if (dtype == ACTQ_F32) {
-        launch(relu_forward_kernel<float>, relu_blocks(n, 4), kBlock, s, 
-            static_cast<const float*>(x), n, mask_words, static_cast<float*>(y), reinterpret_cast<uint32_t*>(mask));
-    } else {
-        launch(relu_forward_kernel<_Float16>, relu_blocks(n, 2), kBlock, s, 
-            static_cast<const _Float16*>(x), n, mask_words, static_cast<_Float16*>(y), reinterpret_cast<uint32_t*>(mask));
-    }
+    uint32_t* words = reinterpret_cast<uint32_t*>(mask);
+    const auto typed = [&](const auto* from, auto* to) {
+        typedef std::remove_pointer_t<decltype(to)> T;
+        const dim3 blocks = relu_blocks(n, sizeof(T));
+        if (store_through_caches(n * static_cast<int64_t>(sizeof(T)))) launch(relu_forward_kernel<T, false>, blocks, kBlock, s, from, n, mask_words, to, words);
+        else launch(relu_forward_kernel<T, true>, blocks, kBlock, s, from, n, mask_words, to, words);
+    };
+    if (dtype == ACTQ_F32) typed(static_cast<const float*>(x), static_cast<float*>(y));
+    else typed(static_cast<const _Float16*>(x), static_cast<_Float16*>(y));
     return launched("actq_relu_forward");
 }
 
@@ -940,7 +956,8 @@ __device__ __forceinline__ uint32_t from_right_lane(uint32_t v)
     return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), kWaveShiftLeft1, 0xf, 0xf, false));
 }
 
-template <typename T, int K, int P, bool JOIN>
+// JOIN: both rows before either store.  NT: non-temporal stores.
+template <typename T, int K, int P, bool JOIN, bool NT>
 __global__ __launch_bounds__(kPoolBwdBlock) void maxpool2d_backward_stream_kernel(const uint8_t* __restrict__ argmax,
                                                                            const T* __restrict__ grad_y, Pool g,
                                                                            StreamPool q, T* __restrict__ grad_x)
@@ -1006,6 +1023,10 @@ __global__ __launch_bounds__(kPoolBwdBlock) void maxpool2d_backward_stream_kerne
     }
     vec_in rows[2];
     T* dst = grad_x + 2 * static_cast<int64_t>(strip) * g.W + static_cast<int64_t>(E) * ch;
+    const auto store = [&](vec_in v, T* to) {
+        if (NT) __builtin_nontemporal_store(v, reinterpret_cast<vec_in*>(to));
+        else *reinterpret_cast<vec_in*>(to) = v;
+    };
 #pragma unroll
     for (int rr = 0; rr < 2; ++rr) {
         vec_in out;
@@ -1028,11 +1049,11 @@ __global__ __launch_bounds__(kPoolBwdBlock) void maxpool2d_backward_stream_kerne
         }
         if (JOIN) asm volatile("" : "+v"(out));
         rows[rr] = out;
-        if (!JOIN && live) __builtin_nontemporal_store(out, reinterpret_cast<vec_in*>(dst + rr * g.W));
+        if (!JOIN && live) store(out, dst + rr * g.W);
     }
     if (JOIN && live) {
-        __builtin_nontemporal_store(rows[0], reinterpret_cast<vec_in*>(dst));
-        __builtin_nontemporal_store(rows[1], reinterpret_cast<vec_in*>(dst + g.W));
+        store(rows[0], dst);
+        store(rows[1], dst + g.W);
     }
 }
 
@@ -1071,12 +1092,13 @@ struct BackwardRule {
     bool single;   // 2x2: a lane owns one input row
     bool stream;   // otherwise: the kernel for even extents and aligned rows, or the row kernel
     bool join;     // the stream kernel computes both rows of a lane before it stores either
-    bool nt;       // the row kernel's stores are non-temporal
+    bool cached;   // the stores go through the caches for the reader's sake (see store_through_caches)
+    bool nt;       // otherwise: the row kernel's are non-temporal
 };
 
 static BackwardRule backward_rule(int64_t planes, const PoolShape& p, int64_t element_bytes)
 {
-    BackwardRule r = {false, false, false, false};
+    BackwardRule r = {false, false, false, false, false};
     if (!row_geometry(p)) return r;
     const int64_t row = p.W * element_bytes, mib = planes * p.H * row >> 20;   // of the result
     const bool even = p.sh == 2 && 2 * p.OH == p.H && 2 * p.OW == p.W && p.W % 8 == 0;
@@ -1098,6 +1120,7 @@ static BackwardRule backward_rule(int64_t planes, const PoolShape& p, int64_t el
     // Long rows and rows of whole sectors (2x2 from 192 bytes on, where rows of 96 bytes lose 15 to 50 %): binary16, 100 MiB, 2x2 rows of 450 bytes
     // 12 %, of 600 12 %, 3x3 / 2 / 1 of 600 18 %, 3x3 / 2 / 0 of 2000 21 %; binary32 2x2 rows of 900 bytes 12 %.  Shorter rows lose: binary32 2x2 rows of
     // 112 bytes 46 %, of 240 bytes 10 %.
+    r.cached = store_through_caches(planes * p.H * row);
     r.nt = row >= 256 || row % 128 == 0 || (row % 32 == 0 && row >= (p.kh == 3 ? 96 : 192));
     return r;
 }
@@ -1129,11 +1152,17 @@ static void maxpool_forward_typed(const T* x, int64_t planes, const PoolShape& p
         // 50 -> 46 us and 3x3/1 on [1026, 113, 113] 35 -> 29, in a step alike alone and 5 to 10 % behind with the pass over y.  On whole 16 bytes,
         // over a few tensors in turn: binary16 2x2/2 27.9 -> 25.8 us on [4096, 112, 112], 3x3/2 54.9 -> 52.8 us on [4096, 160, 160]; with the pass
         // over y, results that would have stayed in the Infinity Cache cost 10 to 20 % more.
-        const bool nt = sizeof(T) == 4 ? p.kh == 3 || p.W % 4 == 0 : p.W % 8 == 0;
+        // Where the image and the result together fit the Infinity Cache, y is stored for its reader, too: with only the other kernels' stores
+        // through the caches ReLU and pooling in both directions take, 112 x 112, 3x3 / 2 / 1, binary32 64 MiB 81.2 us and with these 76.7, 160 MiB
+        // 181.0 and 169.8, binary16 96 MiB 118.3 and 111.5.  A result as large as the image (3x3 / 1 / 1, 57 x 57): 64 MiB 111.2 and 109.9, but
+        // 96 MiB 164.4 and 167.4, 160 MiB 278 and 283.
+        const int64_t elements = planes * p.OH * p.OW, result = elements * (static_cast<int64_t>(sizeof(T)) + 1);
+        const bool cached = store_through_caches(planes * p.H * p.W * static_cast<int64_t>(sizeof(T))) && result <= int64_t(80) << 20;
+        const bool nt = !cached && (sizeof(T) == 4 ? p.kh == 3 || p.W % 4 == 0 : p.W % 8 == 0);
 #define ACTQ_POOL_ROWS(K, PH, PW, S)                                                                                                         \
     do {                                                                                                                                     \
         if (nt) launch(maxpool2d_forward_rows_kernel<T, K, PH, PW, S, true>, blocks, kBlock, s, x, g, rows, y, argmax);                       \
-        else if constexpr (sizeof(T) == 2 || K == 2) launch(maxpool2d_forward_rows_kernel<T, K, PH, PW, S, false>, blocks, kBlock, s, x, g, rows, y, argmax); \
+        else launch(maxpool2d_forward_rows_kernel<T, K, PH, PW, S, false>, blocks, kBlock, s, x, g, rows, y, argmax); \
     } while (0)
         if (p.sh == 1) ACTQ_POOL_ROWS(3, 1, 1, 1);
         else if (p.kh == 2 && p.ph == 0) ACTQ_POOL_ROWS(2, 0, 0, 2);
@@ -1169,9 +1198,14 @@ static void maxpool_backward_typed(const uint8_t* argmax, const T* grad_y, int64
         dim3 unused;
         const Pool g = make_pool(p, planes, 1, &unused);
         const unsigned blocks = (q.total + kPoolBwdBlock - 1) / kPoolBwdBlock;
-        if (p.kh == 2) launch(maxpool2d_backward_stream_kernel<T, 2, 0, false>, blocks, kPoolBwdBlock, s, argmax, grad_y, g, q, grad_x);
-        else if (rule.join) launch(maxpool2d_backward_stream_kernel<T, 3, 1, true>, blocks, kPoolBwdBlock, s, argmax, grad_y, g, q, grad_x);
-        else launch(maxpool2d_backward_stream_kernel<T, 3, 1, false>, blocks, kPoolBwdBlock, s, argmax, grad_y, g, q, grad_x);
+        const auto stream = [&](auto nt) {
+            constexpr bool kNt = decltype(nt)::value;
+            if (p.kh == 2) launch(maxpool2d_backward_stream_kernel<T, 2, 0, false, kNt>, blocks, kPoolBwdBlock, s, argmax, grad_y, g, q, grad_x);
+            else if (rule.join) launch(maxpool2d_backward_stream_kernel<T, 3, 1, true, kNt>, blocks, kPoolBwdBlock, s, argmax, grad_y, g, q, grad_x);
+            else launch(maxpool2d_backward_stream_kernel<T, 3, 1, false, kNt>, blocks, kPoolBwdBlock, s, argmax, grad_y, g, q, grad_x);
+        };
+        if (rule.cached) stream(std::false_type());
+        else stream(std::true_type());
         return;
     }
     RowPool rows;
@@ -1186,7 +1220,7 @@ static void maxpool_backward_typed(const uint8_t* argmax, const T* grad_y, int64
         }
 #define ACTQ_POOL_ROWS(K, P, S)                                                                                              \
     do {                                                                                                                    \
-        if (rule.nt) launch(maxpool2d_backward_rows_kernel<T, K, P, S, true>, blocks, kBlock, s, argmax, grad_y, g, rows, grad_x);    \
+        if (rule.nt && !rule.cached) launch(maxpool2d_backward_rows_kernel<T, K, P, S, true>, blocks, kBlock, s, argmax, grad_y, g, rows, grad_x);    \
         else launch(maxpool2d_backward_rows_kernel<T, K, P, S, false>, blocks, kBlock, s, argmax, grad_y, g, rows, grad_x);      \
     } while (0)
         if (p.sh == 1) ACTQ_POOL_ROWS(3, 1, 1);

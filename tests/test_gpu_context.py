@@ -358,3 +358,33 @@ def test_maxpool_sees_new_contents_of_the_same_buffers(dtype):
         assert np.array_equal(arg.cpu().numpy(), oarg), round_
         assert _bits_equal(y.cpu().numpy(), oy), round_
         assert _bits_equal(gx.cpu().numpy(), oracle.maxpool2d_backward(oarg, g_np, H, W, k, s, p)), round_
+
+
+# results of 24 to 160 MiB are stored through the caches: the same bits as from halves, which go past them; aligned rows (the
+# stream kernel with and without joined rows, 2x2), rows of odd length, a result too large beside its image, and the upper end
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("mib,H,W,k,s,p", [(25, 112, 112, 3, 2, 1), (25, 64, 128, 3, 2, 1), (25, 56, 64, 2, 2, 0), (26, 56, 56, 2, 2, 0), (25, 113, 113, 3, 2, 1),
+                                           (25, 31, 45, 3, 2, 0), (25, 57, 60, 3, 1, 1), (100, 56, 56, 3, 1, 1), (160, 16, 16, 2, 2, 0)])
+def test_results_stored_through_the_caches_equal_those_that_are_not(mib, H, W, k, s, p, dtype):
+    size = torch.finfo(dtype).bits // 8
+    planes = (mib << 20) // (size * H * W) // 2 * 2
+    if mib == 160:
+        planes += 8                     # one call above the limit, its halves inside
+    whole, half = planes * H * W * size, planes // 2 * H * W * size
+    inside = lambda n: 24 << 20 <= n <= 160 << 20
+    assert inside(whole) != inside(half) or mib == 100     # there only the pooling result changes its side
+    g = torch.Generator(device="cuda").manual_seed(H + W)
+    x = torch.randn((planes, H, W), generator=g, device="cuda").to(dtype)
+    y, mask = B.relu_forward(x)
+    z, arg = B.maxpool2d_forward(y, (k, k), (s, s), (p, p))
+    gz = torch.randn(z.shape, generator=g, device="cuda").to(dtype)
+    gy = B.maxpool2d_backward(arg, gz, H, W, (k, k), (s, s), (p, p))
+    assert torch.equal(y, torch.relu(x))
+    for part in (slice(0, planes // 2), slice(planes // 2, planes)):
+        y2, _ = B.relu_forward(x[part].clone())     # (an aligned address)
+        z2, arg2 = B.maxpool2d_forward(y2, (k, k), (s, s), (p, p))
+        gy2 = B.maxpool2d_backward(arg2, gz[part], H, W, (k, k), (s, s), (p, p))
+        assert torch.equal(y[part], y2) and torch.equal(z[part], z2) and torch.equal(arg[part], arg2) and torch.equal(gy[part], gy2)
+    n = x.numel() // 2 // 256 * 256      # whole words of the bit stream
+    _, mask2 = B.relu_forward(x.view(-1)[:n])
+    assert torch.equal(mask[:n // 8], mask2)
