@@ -196,12 +196,13 @@ struct Io<_Float16> {
     }
 };
 
-template <typename T, bool ALIGNED>
+template <typename T, bool ALIGNED, bool NT>
 __device__ __forceinline__ void load4(const T* p, float (&v)[4])
 {
+    typedef typename std::conditional<ALIGNED, typename Io<T>::quad, typename Io<T>::quad_unaligned>::type source;
     typename Io<T>::quad t;
-    if constexpr (ALIGNED) t = __builtin_nontemporal_load(reinterpret_cast<const typename Io<T>::quad*>(p));
-    else t = __builtin_nontemporal_load(reinterpret_cast<const typename Io<T>::quad_unaligned*>(p));
+    if constexpr (NT) t = __builtin_nontemporal_load(reinterpret_cast<const source*>(p));
+    else t = *reinterpret_cast<const source*>(p);
     v[0] = static_cast<float>(t.x); v[1] = static_cast<float>(t.y);
     v[2] = static_cast<float>(t.z); v[3] = static_cast<float>(t.w);
 }
@@ -1283,8 +1284,8 @@ __device__ __forceinline__ void sample_width_offset(const MultiCursor& c, uint32
 }
 
 
-// Sec. 4.1: Z = min, R = max - min per group; one tile of four groups per wavefront.
-template <typename T, bool RAGGED, int CAPACITY>
+// Sec. 4.1: Z = min, R = max - min per group; one tile of four groups per wavefront.  NT: non-temporal loads.
+template <typename T, bool RAGGED, bool NT, int CAPACITY>
 __global__ __launch_bounds__(kGsBlock) void group_stats_multi_kernel(MultiTable<CAPACITY> t)
 {
     const int lane = threadIdx.x & (kWave - 1);
@@ -1298,7 +1299,7 @@ __global__ __launch_bounds__(kGsBlock) void group_stats_multi_kernel(MultiTable<
     if (!RAGGED || (static_cast<uint64_t>(g0 + kTileGroups) << 8) <= c.D) {
 #pragma unroll
         for (int u = 0; u < kTileGroups; ++u)   // a group past the end of the sample re-reads the tile's first (its results are not stored)
-            load4<T, !RAGGED>(tile + ((RAGGED || g0 + u < ng ? u << 8 : 0) + lane * 4), v[u]);
+            load4<T, !RAGGED, NT>(tile + ((RAGGED || g0 + u < ng ? u << 8 : 0) + lane * 4), v[u]);
     } else {
         // the tile in which the sample ends: elements past the end are copies of its last one
         const uint32_t last = static_cast<uint32_t>(c.D - (static_cast<uint64_t>(g0) << 8)) - 1u;
@@ -3008,6 +3009,18 @@ static int each_launch(const char* who, uint64_t most, int32_t count, int waves_
     return ACTQ_OK;
 }
 
+// Whether the statistics leave a tensor of this many bytes in the 256 MiB Infinity Cache, where the quantizer finds (part of) it:
+// ordinary loads instead of non-temporal ones.  Time from the statistics to the packed codes with non-temporal loads (us) and how it
+// changes with ordinary ones, 64 samples; "made" has a pass that writes the tensor in front, which is in the time:
+//              24 MiB       80 MiB       144 MiB      208 MiB      256 MiB      400 MiB
+// f32          16.8 +1.5%   33.9 -1.2%   54.1 -1.0%   74.7 -1.6%   89.9 +0.8%   135.4 +2.8%
+// f32, made    27.5 -8.7%   61.7 -4.6%   100.0 -3.4%  138.2 -2.8%  168.8 -2.5%  258.8 +13.8%
+// f16          19.0 +1.1%   37.4 -2.1%   57.7 -1.6%   80.7 -3.0%   96.7 -2.0%   146.8 -2.2%
+// f16, made    28.5 -0.3%   63.4 -1.3%   102.8 -2.5%  141.2 -2.3%  171.4 -2.1%  263.9 +12.5%
+// Samples that end inside a group, 24 to 208 MiB: f32 +0.2 to -3.4%, made -5 to -12%; f16 +0.8 to -3.4%, made -1.5 to -7%.  Up to 16 MiB
+// from +2% to -4%, which is what runs of one side differ by there.  The limit is the largest size measured where no form loses more than that.
+static bool stays_cached(int64_t bytes) { return bytes <= int64_t(208) << 20; }
+
 // Launches with a table of CAPACITY items; ragged samples come as single tensors only.
 template <int CAPACITY>
 static int group_stats_launch(const char* who, const actq_tensor* tensors, int32_t count, int dtype, int64_t N, bool ragged, hipStream_t s)
@@ -3017,15 +3030,26 @@ static int group_stats_launch(const char* who, const actq_tensor* tensors, int32
     if (int rc = make_multi_table(who, tensors, count, N, 0, &t, kTileGroups, &most)) return rc;
     return each_launch(who, most, count, kGsBlock / kWave, kGsRun, [&](dim3 grid, uint32_t first) {
         t.first_tile = first;
+        const auto typed = [&](auto element, auto nt) {
+            typedef decltype(element) T;
+            constexpr bool kNt = decltype(nt)::value;
+            if constexpr (CAPACITY == 1) {
+                if (ragged) {
+                    launch(group_stats_multi_kernel<T, true, kNt, 1>, grid, kGsBlock, s, t);
+                    return;
+                }
+            }
+            launch(group_stats_multi_kernel<T, false, kNt, CAPACITY>, grid, kGsBlock, s, t);
+        };
         if constexpr (CAPACITY == 1) {
-            if (ragged) {
-                if (dtype == ACTQ_F32) launch(group_stats_multi_kernel<float, true, 1>, grid, kGsBlock, s, t);
-                else launch(group_stats_multi_kernel<_Float16, true, 1>, grid, kGsBlock, s, t);
+            if (stays_cached(N * tensors[0].D * (dtype == ACTQ_F32 ? 4 : 2))) {
+                if (dtype == ACTQ_F32) typed(float(), std::false_type());
+                else typed(_Float16(), std::false_type());
                 return;
             }
         }
-        if (dtype == ACTQ_F32) launch(group_stats_multi_kernel<float, false, CAPACITY>, grid, kGsBlock, s, t);
-        else launch(group_stats_multi_kernel<_Float16, false, CAPACITY>, grid, kGsBlock, s, t);
+        if (dtype == ACTQ_F32) typed(float(), std::true_type());
+        else typed(_Float16(), std::true_type());
     });
 }
 

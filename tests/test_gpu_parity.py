@@ -1102,3 +1102,21 @@ def test_arguments_exactly_at_their_limits_are_accepted():
     zr = B.tensor_stats(torch.full((16,), 2.5, device=dev)[:1].contiguous())
     torch.cuda.synchronize()
     assert zr.cpu().tolist() == [2.5, 0.0]
+
+
+# statistics of single tensors up to 208 MiB load through the caches, larger ones do not: both against the extremes themselves, whole
+# groups, one element in the last group, and rows that begin off the loads' alignment
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("tail", [0, 1, 255])
+@pytest.mark.parametrize("over", [False, True])
+def test_statistics_on_both_sides_of_the_cached_size(over, tail, dtype):
+    N, size = 8, torch.finfo(dtype).bits // 8
+    groups = (208 << 20) // (size * N * 256)
+    D = (groups + over) * 256 - (256 - tail if tail else 0)
+    assert (N * D * size > 208 << 20) == over
+    g = torch.Generator(device="cuda").manual_seed(tail + 2 * over)
+    x = torch.randn((N, D), generator=g, device="cuda").to(dtype)
+    gmin, grange = B.group_stats(x)
+    full = torch.cat([x, x[:, -1:].expand(N, -D % 256)], 1).view(N, -1, 256).float()    # the last group repeats its last element
+    low = full.amin(2)
+    assert torch.equal(gmin, low) and torch.equal(grange, full.amax(2) - low)
