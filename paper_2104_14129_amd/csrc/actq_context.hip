@@ -36,12 +36,13 @@ int launched(const char* who)
 // a result that fits the 256 MiB Infinity Cache together with what that layer reads and writes is found there, and HBM has
 // the other half of the traffic left.  ReLU and pooling, forward and backward, one behind the other, non-temporal stores -> these
 // (us; 112 x 112 images, 3x3 / 2 / 1, activations of the given size in binary32 / binary16): 24 MiB 36.5 -> 35.8 / 39.2 -> 38.1, 48 MiB
-// 67.2 -> 60.6 / 68.9 -> 61.9, 80 MiB 104.2 -> 91.2 / 106.3 -> 94.7, 128 MiB 159.8 -> 138.9 / 160.6 -> 143.6, 160 MiB 197.1 -> 170.5 / 197.4 ->
-// 189.7; 2x2 / 2 on 56 x 56 alike, 113 x 113 2 to 8 %, 3x3 / 1 / 1 on 57 x 57 1 to 6 % (binary16 from 128 MiB on 0.8 % behind).
-// Beyond, the lines written last push out those that are read first: at 192 MiB it depends on the image, at 320 MiB all are 2 to 8 % behind.
+// 67.2 -> 60.6 / 68.9 -> 61.9, 80 MiB 104.2 -> 91.2 / 106.3 -> 94.7, 128 MiB 159.8 -> 138.9 in binary32; 2x2 / 2 on 56 x 56 alike, 113 x 113 2
+// to 8 %, 3x3 / 1 / 1 on 57 x 57 1 to 6 %.  Binary16 (twice the positions per byte) has lower limits, see relu_through_caches and backward_rule.
+// Beyond, the lines written last push out those that are read first: binary32 3x3 / 1 / 1 at 160 MiB loses 1 % on rows of 56 bytes (271 -> 274)
+// while other images gain up to 12 %; at 192 MiB it depends on the image, at 320 MiB all are 2 to 8 % behind.
 // Below, everything stays in the L2 caches, and stores that go through at once are ahead (16 MiB 27.5 -> 30.3).  A few results written
 // in turn and not read are up to 14 % slower (ReLU alone on two tensors, 24 and 32 MiB; from 100 MiB on alike).
-bool store_through_caches(int64_t bytes) { return bytes >= int64_t(24) << 20 && bytes <= int64_t(160) << 20; }
+bool store_through_caches(int64_t bytes) { return bytes >= int64_t(24) << 20 && bytes <= int64_t(144) << 20; }
 
 // ------------------------------------------------------------------------------------
 // ReLU.  A lane owns E consecutive elements (E = 4 binary32 or 8 binary16 values: 128 bits); a wavefront
@@ -882,6 +883,14 @@ static dim3 relu_blocks(int64_t n, int64_t element_bytes)
     return dim3(static_cast<unsigned>(along_x), static_cast<unsigned>((blocks + along_x - 1) / along_x));
 }
 
+// Binary16 up to 104 MiB: with stores through the caches ReLU and 3x3 / 1 / 1 pooling, both directions, are from 112 MiB on 0.5 to 1 % behind
+// (57 x 57 254.4 -> 255.7 us, 55 x 245 at 128 MiB 281.6 -> 284.4) and at 100 MiB alike or ahead.
+static bool relu_through_caches(int64_t n, int64_t element_bytes)
+{
+    const int64_t bytes = n * element_bytes;
+    return store_through_caches(bytes) && (element_bytes == 4 || bytes <= int64_t(104) << 20);
+}
+
 int launch_relu_forward(const void* x, int dtype, int64_t n, void* y, uint8_t* mask, void* stream)
 {
     hipStream_t s = static_cast<hipStream_t>(stream);
@@ -890,7 +899,7 @@ int launch_relu_forward(const void* x, int dtype, int64_t n, void* y, uint8_t* m
     const auto typed = [&](const auto* from, auto* to) {
         typedef std::remove_pointer_t<decltype(to)> T;
         const dim3 blocks = relu_blocks(n, sizeof(T));
-        if (store_through_caches(n * static_cast<int64_t>(sizeof(T)))) launch(relu_forward_kernel<T, false>, blocks, kBlock, s, from, n, mask_words, to, words);
+        if (relu_through_caches(n, sizeof(T))) launch(relu_forward_kernel<T, false>, blocks, kBlock, s, from, n, mask_words, to, words);
         else launch(relu_forward_kernel<T, true>, blocks, kBlock, s, from, n, mask_words, to, words);
     };
     if (dtype == ACTQ_F32) typed(static_cast<const float*>(x), static_cast<float*>(y));
@@ -1120,7 +1129,9 @@ static BackwardRule backward_rule(int64_t planes, const PoolShape& p, int64_t el
     // Long rows and rows of whole sectors (2x2 from 192 bytes on, where rows of 96 bytes lose 15 to 50 %): binary16, 100 MiB, 2x2 rows of 450 bytes
     // 12 %, of 600 12 %, 3x3 / 2 / 1 of 600 18 %, 3x3 / 2 / 0 of 2000 21 %; binary32 2x2 rows of 900 bytes 12 %.  Shorter rows lose: binary32 2x2 rows of
     // 112 bytes 46 %, of 240 bytes 10 %.
-    r.cached = store_through_caches(planes * p.H * row);
+    // For the reader's sake at stride 2 only: with 3x3 / 1 / 1 binary16 rows of 490 bytes lose (ReLU and pooling, both directions, 136 MiB 302 -> 307 us)
+    // and others are alike.  Binary16 up to 128 MiB (55 x 245, 3x3 / 2 / 1: 157.9 -> 152.7, but 160 MiB 201.9 -> 214.6).
+    r.cached = p.sh == 2 && store_through_caches(planes * p.H * row) && (element_bytes == 4 || planes * p.H * row <= int64_t(128) << 20);
     r.nt = row >= 256 || row % 128 == 0 || (row % 32 == 0 && row >= (p.kh == 3 ? 96 : 192));
     return r;
 }
