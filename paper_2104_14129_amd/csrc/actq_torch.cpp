@@ -53,8 +53,15 @@ constexpr int32_t kG = 256;
 
 // ----------------------------------------------------------------------------- errors and arguments
 
-// A call of the library; its status becomes the binding's exception.  The interpreter's lock is released
-// for the call if this thread holds it.
+// Python exceptions are raised from threads with and without the interpreter's lock (the autograd functions run without
+// it, their backward halves on threads of their own): both of these take it, and the error travels in the C++ exception.
+[[noreturn]] void throw_pending()   // under the lock
+{
+    python_error error;
+    error.persist();
+    throw error;
+}
+
 [[noreturn]] void raise(int code)
 {
     const std::string message = api.last_error();   // of this thread
@@ -64,11 +71,18 @@ constexpr int32_t kG = 256;
         PyErr_SetObject(actq_error, e);
         Py_DECREF(e);
     }
-    python_error error;
-    error.persist();
-    throw error;
+    throw_pending();
 }
 
+[[noreturn]] void python_exception(PyObject* type, const char* message)
+{
+    pybind11::gil_scoped_acquire gil;
+    PyErr_SetString(type, message);
+    throw_pending();
+}
+
+// A call of the library; its status becomes the binding's exception.  The interpreter's lock is released
+// for the call if this thread holds it.
 template <typename... Params, typename... Args>
 void call(int (*f)(Params...), Args... args)
 {
@@ -80,12 +94,6 @@ void call(int (*f)(Params...), Args... args)
         code = f(args...);
     }
     if (code != ACTQ_OK) raise(code);
-}
-
-[[noreturn]] void python_exception(PyObject* type, const char* message)
-{
-    PyErr_SetString(type, message);
-    throw python_error();
 }
 
 const Tensor& tensor_of(PyObject* o, const char* name)

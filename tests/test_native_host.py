@@ -57,3 +57,20 @@ def test_watched_tensors_take_the_functions_in_python(what):
     else:
         seen.append(L._native(x.numpy()))
     assert seen == [False]
+
+
+@pytest.mark.parametrize("what,kind,call", [
+    ("one dimension", IndexError, lambda h: h.maxpool2d(torch.randn(5), (2, 2), (2, 2), (0, 0), (1, 1))),
+    ("no dimension", IndexError, lambda h: h.maxpool2d(torch.tensor(1.0), (2, 2), (2, 2), (0, 0), (1, 1))),
+    ("no rows", ZeroDivisionError, lambda h: h.maxpool2d(torch.randn(2, 0, 5), (2, 2), (2, 2), (0, 0), (1, 1))),
+    ("no columns", ZeroDivisionError, lambda h: h.maxpool2d(torch.randn(2, 5, 0), (2, 2), (2, 2), (0, 0), (1, 1))),
+    ("window too large", B.ActqError, lambda h: h.maxpool2d(torch.randn(2, 4, 4), (9, 9), (2, 2), (0, 0), (1, 1))),
+    ("no samples", ZeroDivisionError, lambda h: h.linear(torch.randn(0, 5), torch.randn(3, 5), None, 100, 0x116, 64, 1, 1, 16, 0, None, None)),
+])
+def test_errors_of_the_autograd_functions_are_python_exceptions(what, kind, call):
+    """The functions run without the interpreter's lock; what they refuse is raised with it, once and again."""
+    for _ in range(2):
+        with pytest.raises(kind):
+            call(B.host())
+    with pytest.raises(ValueError, match="GPU"):     # and the next call is served as usual
+        B.host().relu(torch.randn(3))
