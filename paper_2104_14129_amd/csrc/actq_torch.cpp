@@ -150,7 +150,15 @@ struct View {
     int64_t N, D, groups;   // groups of a sample
 };
 
-View view_of(const Tensor& x, int64_t G = kG)
+// The size of a group, as the sizes of the outputs are worked out with it and as the library is told: one number.
+int32_t group_size(int64_t G)
+{
+    if (G == 0) python_exception(PyExc_ZeroDivisionError, "G must not be 0");
+    TORCH_CHECK_VALUE(G > 0 && G <= INT32_MAX, "G must be positive and fit 32 bits, got ", G);
+    return static_cast<int32_t>(G);
+}
+
+View view_of(const Tensor& x, int32_t G = kG)
 {
     if (x.dim() == 0) python_exception(PyExc_IndexError, "a tensor without dimensions has no samples");
     if (x.size(0) == 0) python_exception(PyExc_ZeroDivisionError, "no samples");
@@ -229,7 +237,7 @@ PyObject* tuple_of(std::initializer_list<PyObject*> items)
 PyObject* group_stats_impl(PyObject* const* a)
 {
     const Tensor& x = tensor_of(a[0], "x");
-    const int64_t G = integer(a[3]);
+    const int32_t G = group_size(integer(a[3]));
     TORCH_CHECK_VALUE(x.is_cuda(), "x must live on the GPU");
     const View v = view_of(x, G);
     const Tensor gmin = a[1] == Py_None ? empty_on(x, {v.N, v.groups}, at::kFloat) : tensor_of(a[1], "gmin");
@@ -238,7 +246,7 @@ PyObject* group_stats_impl(PyObject* const* a)
     const Memory xp = on_gpu(x, "x");
     const actq_dtype dt = dtype_of(x);
     const Memory lo = on_gpu(gmin, at::kFloat, "gmin"), range = on_gpu(grange, at::kFloat, "grange");
-    call(api.group_stats, xp, dt, v.N, v.D, static_cast<int32_t>(G), lo, range, stream_of(a[4]));
+    call(api.group_stats, xp, dt, v.N, v.D, G, lo, range, stream_of(a[4]));
     return tuple_of({give(a[1], gmin), give(a[2], grange)});
 }
 ACTQ_ENTRY(group_stats, 5)
@@ -301,14 +309,15 @@ PyObject* quantize_pack_impl(PyObject* const* a)
 {
     const Tensor &x = tensor_of(a[0], "x"), &bits = tensor_of(a[1], "bits"), &offsets = tensor_of(a[2], "offsets");
     const Tensor &packed = tensor_of(a[3], "packed"), &header = tensor_of(a[4], "header");
-    const int64_t G = integer(a[8]), hf = integer(a[10]);
+    const int32_t G = group_size(integer(a[8]));
+    const int64_t hf = integer(a[10]);
     const View v = view_of(x, G);
     TORCH_CHECK_VALUE(bits.numel() == v.N && offsets.numel() == v.N, "bits and offsets must have N entries");
     const Memory xp = on_gpu(x, "x");
     const actq_dtype dt = dtype_of(x);
     const Memory bp = on_gpu(bits, at::kByte, "bits"), op = on_gpu(offsets, at::kLong, "offsets"), pp = on_gpu(packed, at::kByte, "packed");
     const Memory hp = header_pointer(header, v.N * v.groups, hf);
-    call(api.quantize_pack, xp, dt, v.N, v.D, static_cast<int32_t>(G), bp, op, word(a[5]), word(a[6]), static_cast<int32_t>(integer(a[7])), pp,
+    call(api.quantize_pack, xp, dt, v.N, v.D, G, bp, op, word(a[5]), word(a[6]), static_cast<int32_t>(integer(a[7])), pp,
          static_cast<uint64_t>(packed.numel()), hp, static_cast<actq_header_format>(hf), stream_of(a[9]));
     return tuple_of({give(a[3], packed), give(a[4], header)});
 }
@@ -330,10 +339,11 @@ PyObject* unpack_dequantize_impl(PyObject* const* a)
 {
     const Tensor &packed = tensor_of(a[0], "packed"), &header = tensor_of(a[1], "header"), &bits = tensor_of(a[2], "bits");
     const Tensor &offsets = tensor_of(a[3], "offsets"), &out = tensor_of(a[4], "out");
-    const int64_t G = integer(a[5]), hf = integer(a[7]);
+    const int32_t G = group_size(integer(a[5]));
+    const int64_t hf = integer(a[7]);
     const View v = view_of(out, G);
     TORCH_CHECK_VALUE(bits.numel() == v.N && offsets.numel() == v.N, "bits and offsets must have N entries");
-    decompress(packed, header, bits, offsets, out, v, static_cast<int32_t>(G), hf, a[6]);
+    decompress(packed, header, bits, offsets, out, v, G, hf, a[6]);
     return give(a[4], out);
 }
 ACTQ_ENTRY(unpack_dequantize, 8)

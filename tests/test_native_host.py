@@ -74,3 +74,14 @@ def test_errors_of_the_autograd_functions_are_python_exceptions(what, kind, call
             call(B.host())
     with pytest.raises(ValueError, match="GPU"):     # and the next call is served as usual
         B.host().relu(torch.randn(3))
+
+
+@pytest.mark.parametrize("G,kind", [(0, ZeroDivisionError), (-1, ValueError), (-256, ValueError), (2 ** 31, ValueError), (2 ** 32 + 256, ValueError)])
+def test_a_group_size_that_is_none_is_refused(G, kind):
+    """Before anything is divided by it, and before a size beyond 32 bits becomes another one on its way to the library."""
+    x, bits, offsets = torch.randn(4, 512), torch.full((4,), 2, dtype=torch.uint8), torch.arange(4) * 128
+    packed, header = torch.zeros(512, dtype=torch.uint8), torch.zeros(16)
+    for call in (lambda: B.group_stats(x, G=G), lambda: B.quantize_pack(x, bits, offsets, packed, header, 1, G=G),
+                 lambda: B.unpack_dequantize(packed, header, bits, offsets, x, G=G)):
+        with pytest.raises(kind, match="^G must"):
+            call()
