@@ -510,10 +510,18 @@ void output_size(int32_t H, int32_t W, const Window& w, int32_t& OH, int32_t& OW
     call(api.pool2d_output_size, H, W, w.k[0], w.k[1], w.s[0], w.s[1], w.p[0], w.p[1], w.d[0], w.d[1], &OH, &OW);
 }
 
+// Rows or columns as the library takes them.  Cut to 32 bits, a larger extent would be another image, and the number of planes
+// worked out from it would not be that of the outputs.
+int32_t extent(int64_t rows_or_columns)
+{
+    TORCH_CHECK_VALUE(rows_or_columns <= INT32_MAX && rows_or_columns >= INT32_MIN, "rows and columns must fit 32 bits, got ", rows_or_columns);
+    return static_cast<int32_t>(rows_or_columns);
+}
+
 int32_t extent(const Tensor& t, int64_t dim)
 {
     if (t.dim() < 2) python_exception(PyExc_IndexError, "pooling needs rows and columns");
-    return static_cast<int32_t>(t.size(dim));
+    return extent(t.size(dim));
 }
 
 std::vector<int64_t> with_extent(const Tensor& t, int64_t H, int64_t W)
@@ -581,8 +589,8 @@ PyObject* maxpool2d_backward_impl(PyObject* const* a)
     const Tensor &arg = tensor_of(a[0], "argmax"), &grad_y = tensor_of(a[1], "grad_y");
     const Window w = window_of(a + 4);
     Pooling p;
-    p.H = static_cast<int32_t>(integer(a[2]));
-    p.W = static_cast<int32_t>(integer(a[3]));
+    p.H = extent(integer(a[2]));
+    p.W = extent(integer(a[3]));
     output_size(p.H, p.W, w, p.OH, p.OW);
     TORCH_CHECK_VALUE(grad_y.dim() >= 2 && grad_y.size(-2) == p.OH && grad_y.size(-1) == p.OW && arg.numel() == grad_y.numel(),
                       "grad_y and argmax must be [..., OH, OW]");

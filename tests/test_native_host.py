@@ -85,3 +85,14 @@ def test_a_group_size_that_is_none_is_refused(G, kind):
                  lambda: B.unpack_dequantize(packed, header, bits, offsets, x, G=G)):
         with pytest.raises(kind, match="^G must"):
             call()
+
+
+@pytest.mark.parametrize("shape", [(1, 2 ** 32 + 4, 2), (1, 2, 2 ** 32 + 4), (2 ** 31, 1)])
+def test_pooling_extents_beyond_32_bits_are_refused(shape):
+    """2^32 + 4 rows are not 4, in the functions that allocate by the one and count planes by the other."""
+    x, window = torch.empty(shape, dtype=torch.float16, device="meta"), ((1, 1), (1, 1), (0, 0), (1, 1))
+    grad = torch.empty((1, 4, 4), dtype=torch.float16, device="meta")
+    for call in (lambda: B.host().maxpool2d(x, *window), lambda: B.maxpool2d_forward(x, *window),
+                 lambda: B.maxpool2d_backward(grad, grad, *shape[-2:], *window)):
+        with pytest.raises(ValueError, match="fit 32 bits"):
+            call()
