@@ -323,10 +323,13 @@ PyObject* quantize_pack_impl(PyObject* const* a)
 }
 ACTQ_ENTRY(quantize_pack, 11)
 
+// The second halves (decompress, relu_backward_call, maxpool_backward_call) check the sizes of what the first halves left for
+// both of their callers: in the autograd functions it comes from the saved tensors, and those from hooks that may return any tensor.
 // `stream`: None or a torch stream; null without the interpreter's lock, for the current one.
 void decompress(const Tensor& packed, const Tensor& header, const Tensor& bits, const Tensor& offsets, const Tensor& out, const View& v, int32_t G,
                 int64_t hf, PyObject* stream)
 {
+    TORCH_CHECK_VALUE(bits.numel() == v.N && offsets.numel() == v.N, "bits and offsets must have N entries");
     const Memory pp = on_gpu(packed, at::kByte, "packed"), hp = header_pointer(header, v.N * v.groups, hf);
     const Memory bp = on_gpu(bits, at::kByte, "bits"), op = on_gpu(offsets, at::kLong, "offsets"), xp = on_gpu(out, "out");
     const actq_dtype dt = dtype_of(out);
@@ -341,9 +344,7 @@ PyObject* unpack_dequantize_impl(PyObject* const* a)
     const Tensor &offsets = tensor_of(a[3], "offsets"), &out = tensor_of(a[4], "out");
     const int32_t G = group_size(integer(a[5]));
     const int64_t hf = integer(a[7]);
-    const View v = view_of(out, G);
-    TORCH_CHECK_VALUE(bits.numel() == v.N && offsets.numel() == v.N, "bits and offsets must have N entries");
-    decompress(packed, header, bits, offsets, out, v, G, hf, a[6]);
+    decompress(packed, header, bits, offsets, out, view_of(out, G), G, hf, a[6]);
     return give(a[4], out);
 }
 ACTQ_ENTRY(unpack_dequantize, 8)
@@ -444,6 +445,8 @@ void relu_forward_call(const Tensor& x, const Tensor& y, const Tensor& mask, PyO
 
 void relu_backward_call(const Tensor& mask, const Tensor& grad_y, const Tensor& grad_x, PyObject* stream)
 {
+    TORCH_CHECK_VALUE(grad_x.numel() == grad_y.numel() && grad_x.scalar_type() == grad_y.scalar_type() && mask.numel() == mask_bytes(grad_y.numel()),
+                      "grad_x must match grad_y and mask must have relu_mask_bytes(n) bytes");
     const Memory mp = on_gpu(mask, at::kByte, "mask"), gp = on_gpu(grad_y, "grad_y");
     const actq_dtype dt = dtype_of(grad_y);
     const Memory xp = on_gpu(grad_x, "grad_x");
@@ -469,8 +472,6 @@ PyObject* relu_backward_impl(PyObject* const* a)
 {
     const Tensor &mask = tensor_of(a[0], "mask"), &grad_y = tensor_of(a[1], "grad_y");
     const Tensor grad_x = a[2] == Py_None ? at::empty_like(grad_y) : tensor_of(a[2], "grad_x");
-    TORCH_CHECK_VALUE(grad_x.numel() == grad_y.numel() && grad_x.scalar_type() == grad_y.scalar_type() && mask.numel() == mask_bytes(grad_y.numel()),
-                      "grad_x must match grad_y and mask must have relu_mask_bytes(n) bytes");
     relu_backward_call(mask, grad_y, grad_x, a[3]);
     return give(a[2], grad_x);
 }
@@ -558,8 +559,22 @@ void maxpool_forward_call(const Tensor& x, const Pooling& p, const Window& w, co
          stream ? stream_of(stream) : current_stream());
 }
 
+// Shapes of a backward call for images of H x W.
+Pooling pooling_of_gradient(const Tensor& grad_y, int32_t H, int32_t W, const Window& w)
+{
+    Pooling p;
+    p.H = H;
+    p.W = W;
+    output_size(H, W, w, p.OH, p.OW);
+    TORCH_CHECK_VALUE(grad_y.dim() >= 2 && grad_y.size(-2) == p.OH && grad_y.size(-1) == p.OW, "grad_y and argmax must be [..., OH, OW]");
+    p.planes = grad_y.numel() / (static_cast<int64_t>(p.OH) * p.OW);
+    return p;
+}
+
 void maxpool_backward_call(const Tensor& arg, const Tensor& grad_y, const Pooling& p, const Window& w, const Tensor& grad_x, PyObject* stream)
 {
+    TORCH_CHECK_VALUE(arg.numel() == grad_y.numel(), "grad_y and argmax must be [..., OH, OW]");
+    TORCH_CHECK_VALUE(grad_x.numel() == p.planes * p.H * p.W && grad_x.scalar_type() == grad_y.scalar_type(), "grad_x must have planes*H*W elements");
     const Memory ap = on_gpu(arg, at::kByte, "argmax"), gp = on_gpu(grad_y, "grad_y");
     const actq_dtype dt = dtype_of(grad_y);
     const Memory xp = on_gpu(grad_x, "grad_x");
@@ -588,15 +603,9 @@ PyObject* maxpool2d_backward_impl(PyObject* const* a)
 {
     const Tensor &arg = tensor_of(a[0], "argmax"), &grad_y = tensor_of(a[1], "grad_y");
     const Window w = window_of(a + 4);
-    Pooling p;
-    p.H = extent(integer(a[2]));
-    p.W = extent(integer(a[3]));
-    output_size(p.H, p.W, w, p.OH, p.OW);
-    TORCH_CHECK_VALUE(grad_y.dim() >= 2 && grad_y.size(-2) == p.OH && grad_y.size(-1) == p.OW && arg.numel() == grad_y.numel(),
-                      "grad_y and argmax must be [..., OH, OW]");
-    p.planes = grad_y.numel() / (static_cast<int64_t>(p.OH) * p.OW);
+    const int32_t H = extent(integer(a[2])), W = extent(integer(a[3]));
+    const Pooling p = pooling_of_gradient(grad_y, H, W, w);
     const Tensor grad_x = a[8] == Py_None ? empty_on(grad_y, with_extent(grad_y, p.H, p.W), grad_y.scalar_type()) : tensor_of(a[8], "grad_x");
-    TORCH_CHECK_VALUE(grad_x.numel() == p.planes * p.H * p.W && grad_x.scalar_type() == grad_y.scalar_type(), "grad_x must have planes*H*W elements");
     maxpool_backward_call(arg, grad_y, p, w, grad_x, a[9]);
     return give(a[8], grad_x);
 }
@@ -689,12 +698,7 @@ struct MaxPoolFn : torch::autograd::Function<MaxPoolFn> {
             w.p[i] = static_cast<int32_t>(g[6 + i]);
             w.d[i] = static_cast<int32_t>(g[8 + i]);
         }
-        Pooling p;
-        p.H = static_cast<int32_t>(g[0]);
-        p.W = static_cast<int32_t>(g[1]);
-        p.OH = extent(grad_y, -2);
-        p.OW = extent(grad_y, -1);
-        p.planes = grad_y.numel() / (static_cast<int64_t>(p.OH) * p.OW);
+        const Pooling p = pooling_of_gradient(grad_y, static_cast<int32_t>(g[0]), static_cast<int32_t>(g[1]), w);
         const Tensor grad_x = empty_on(grad_y, with_extent(grad_y, p.H, p.W), grad_y.scalar_type());
         maxpool_backward_call(arg, grad_y, p, w, grad_x, nullptr);
         return {grad_x, Tensor()};

@@ -1,6 +1,8 @@
 """Activation-compressed layers (Sec. 3.2 Eq. (4), Sec. 5.1): the saved context equals the oracle's
 bit for bit, the gradients are the stock backward applied to the dequantized context, the
 activation-compressed gradient is unbiased, and a small network trains."""
+import itertools
+
 import numpy as np
 import pytest
 import torch
@@ -346,6 +348,24 @@ def test_native_functions_serve_saved_tensor_hooks_and_report_the_library_s_erro
     with pytest.raises(B.ActqError) as err:
         L.QReLU()(torch.empty(0, device=DEV, requires_grad=True))
     assert err.value.code == B.ACTQ_EINVAL and "relu" in str(err.value)
+
+
+@pytest.mark.parametrize("native", [True, False])
+@pytest.mark.parametrize("layer,which,cut", [
+    ("relu", 0, lambda t: t[:-32]), ("pool", 0, lambda t: t[:, :, :-1].contiguous()), ("pool", 0, lambda t: t[..., :-1].contiguous()),
+    ("linear", 0, lambda t: t[:-1]), ("linear", 1, lambda t: t[:-1]), ("linear", 3, lambda t: t[:-2])])
+def test_saved_tensors_of_the_wrong_size_are_refused(layer, which, cut, native, monkeypatch):
+    """What a saved-tensor hook gives back is checked before the device reads it: here it comes back shorter than it was saved."""
+    if not native:
+        monkeypatch.setattr(L, "_native", lambda *t: False)
+    m = {"relu": lambda: L.QReLU(), "pool": lambda: L.QMaxPool2d(2), "linear": lambda: L.QLinear(300, 5, device=DEV)}[layer]()
+    x = torch.randn((9, 300) if layer == "linear" else (2, 3, 16, 16), device=DEV, requires_grad=True)
+    given_back, saved = [], itertools.count()
+    with torch.autograd.graph.saved_tensors_hooks(lambda t: (next(saved), t), lambda p: given_back.append(p[0]) or (cut(p[1]) if p[0] == which else p[1])):
+        y = m(x)
+    with pytest.raises(ValueError):
+        y.sum().backward()
+    assert which in given_back
 
 
 def test_the_binding_refuses_wrong_arguments():
