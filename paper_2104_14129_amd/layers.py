@@ -305,10 +305,11 @@ def _pair(v):
 class QLinear(nn.Linear):
     def forward(self, x):
         if torch.is_grad_enabled() and x.is_cuda:
-            if not config.swap and x.dtype in _DTYPES and _native(x, self.weight, self.bias):
+            weight, bias = self.weight, self.bias   # read once: a parametrization computes them each time
+            if not config.swap and x.dtype in _DTYPES and _native(x, weight, bias):
                 N = x.shape[0]
-                return B._host.linear(x, self.weight, self.bias, *_settings(N, x.numel() // N, x.device))
-            return _QLinearFn.apply(x, self.weight, self.bias)
+                return B._host.linear(x, weight, bias, *_settings(N, x.numel() // N, x.device))
+            return _QLinearFn.apply(x, weight, bias)
         return super().forward(x)
 
 

@@ -96,3 +96,33 @@ def test_pooling_extents_beyond_32_bits_are_refused(shape):
                  lambda: B.maxpool2d_backward(grad, grad, *shape[-2:], *window)):
         with pytest.raises(ValueError, match="fit 32 bits"):
             call()
+
+
+@pytest.mark.parametrize("native", [True, False])
+def test_a_parametrized_weight_is_computed_once_per_forward_pass(native, monkeypatch):
+    """A parametrization may keep state (spectral normalization steps its power iteration in each evaluation)."""
+    class Counting(nn.Module):
+        evaluations = 0
+
+        def forward(self, w):
+            self.evaluations += 1
+            return w * 1.0
+
+    class OnGpu:     # as much of a tensor as the layer looks at before it hands it on
+        is_cuda, dtype, shape, device = True, torch.float32, torch.Size((3, 4)), torch.device("cpu")
+
+        def numel(self):
+            return 12
+
+    class Host:
+        def linear(self, x, weight, bias, *settings):
+            return weight, bias
+
+    m, counting, seen = L.QLinear(4, 2), Counting(), []
+    nn.utils.parametrize.register_parametrization(m, "weight", counting, unsafe=True)
+    counting.evaluations = 0
+    monkeypatch.setattr(L, "_native", lambda *t: seen.append(t[1]) or native)
+    monkeypatch.setattr(B, "_host", Host())
+    monkeypatch.setattr(L._QLinearFn, "apply", lambda x, weight, bias: (weight, bias))
+    weight, bias = m(OnGpu())
+    assert counting.evaluations == 1 and weight is seen[0] and bias is m.bias
