@@ -158,7 +158,7 @@ def host():
             try:
                 _build.build_host()
             except Exception as exc:
-                raise RuntimeError(f"{HOST_PATH} was built from another source or for another torch (digest {have}, expected {want}) "
+                raise RuntimeError(f"{HOST_PATH} was built from another source or for another torch or interpreter (digest {have}, expected {want}) "
                                    f"and cannot be rebuilt here: {exc}") from exc
         loader = importlib.machinery.ExtensionFileLoader("actq_torch", HOST_PATH)
         module = importlib.util.module_from_spec(importlib.util.spec_from_loader("actq_torch", loader))

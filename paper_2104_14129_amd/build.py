@@ -54,9 +54,17 @@ def source_hash() -> str:
 
 
 def host_source_hash() -> str:
-    """The same for the binding's native half, which depends on torch's version as well."""
+    """The same for the binding's native half, which depends on the interpreter's binary interface and on torch's as well."""
+    import sysconfig
     import torch
-    return _digest([os.path.join(CSRC, HOST_SOURCE), os.path.join(ROOT, "include", "actq.h")], " ".join(HOST_FLAGS), torch.__version__)
+    return _digest([os.path.join(CSRC, HOST_SOURCE), os.path.join(ROOT, "include", "actq.h")], " ".join(HOST_FLAGS),
+                   f"{sysconfig.get_config_var('SOABI')} torch {torch.__version__} {_abi_flag()}")
+
+
+def _abi_flag() -> str:
+    """The C++ library's interface that this torch was built with."""
+    import torch
+    return f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"
 
 
 def hipcc() -> str:
@@ -96,7 +104,7 @@ def build_host(verbose: bool = False) -> str:
         raise RuntimeError("no C++ compiler: actq_torch cannot be built")
     rocm = os.path.dirname(os.path.dirname(os.path.realpath(hipcc())))
     tmp = HOST_LIB + f".{os.getpid()}.tmp"
-    cmd = [cxx, *HOST_FLAGS, f'-DACTQ_SOURCE_HASH="{host_source_hash()}"', f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    cmd = [cxx, *HOST_FLAGS, f'-DACTQ_SOURCE_HASH="{host_source_hash()}"', _abi_flag()]
     for path in (os.path.join(ROOT, "include"), os.path.join(where, "include"), os.path.join(where, "include", "torch", "csrc", "api", "include"),
                  os.path.join(rocm, "include"), sysconfig.get_paths()["include"]):
         cmd += ["-isystem" if path.startswith(where) else "-I", path]

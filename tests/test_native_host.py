@@ -126,3 +126,16 @@ def test_a_parametrized_weight_is_computed_once_per_forward_pass(native, monkeyp
     monkeypatch.setattr(L._QLinearFn, "apply", lambda x, weight, bias: (weight, bias))
     weight, bias = m(OnGpu())
     assert counting.evaluations == 1 and weight is seen[0] and bias is m.bias
+
+
+@pytest.mark.parametrize("what", ["interpreter", "torch", "C++ library"])
+def test_the_digest_names_all_that_the_module_is_built_against(what, monkeypatch):
+    import sysconfig
+    before, stock = lib_build.host_source_hash(), sysconfig.get_config_var
+    if what == "interpreter":
+        monkeypatch.setattr(sysconfig, "get_config_var", lambda name: "cpython-399-x86_64-linux-gnu" if name == "SOABI" else stock(name))
+    elif what == "torch":
+        monkeypatch.setattr(torch, "__version__", "0.0.0")
+    else:
+        monkeypatch.setattr(torch._C, "_GLIBCXX_USE_CXX11_ABI", not torch._C._GLIBCXX_USE_CXX11_ABI)
+    assert lib_build.host_source_hash() != before
