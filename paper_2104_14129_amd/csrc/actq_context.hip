@@ -32,19 +32,6 @@ int launched(const char* who)
 }
 
 // ------------------------------------------------------------------------------------
-// Whether a result of this many bytes is stored through the caches.  The next layer reads it (and the call behind that one):
-// a result that fits the 256 MiB Infinity Cache together with what that layer reads and writes is found there, and HBM has
-// the other half of the traffic left.  ReLU and pooling, forward and backward, one behind the other, non-temporal stores -> these
-// (us; 112 x 112 images, 3x3 / 2 / 1, activations of the given size in binary32 / binary16): 24 MiB 36.5 -> 35.8 / 39.2 -> 38.1, 48 MiB
-// 67.2 -> 60.6 / 68.9 -> 61.9, 80 MiB 104.2 -> 91.2 / 106.3 -> 94.7, 128 MiB 159.8 -> 138.9 in binary32; 2x2 / 2 on 56 x 56 alike, 113 x 113 2
-// to 8 %, 3x3 / 1 / 1 on 57 x 57 1 to 6 %.  Binary16 (twice the positions per byte) has lower limits, see relu_through_caches and backward_rule.
-// Beyond, the lines written last push out those that are read first: binary32 3x3 / 1 / 1 at 160 MiB loses 1 % on rows of 56 bytes (271 -> 274)
-// while other images gain up to 12 %; at 192 MiB it depends on the image, at 320 MiB all are 2 to 8 % behind.
-// Below, everything stays in the L2 caches, and stores that go through at once are ahead (16 MiB 27.5 -> 30.3).  A few results written
-// in turn and not read are up to 14 % slower (ReLU alone on two tensors, 24 and 32 MiB; from 100 MiB on alike).
-bool store_through_caches(int64_t bytes) { return bytes >= int64_t(24) << 20 && bytes <= int64_t(144) << 20; }
-
-// ------------------------------------------------------------------------------------
 // ReLU.  A lane owns E consecutive elements (E = 4 binary32 or 8 binary16 values: 128 bits); a wavefront
 // covers 64*E elements = 2*E words of the bit stream, with one load and one store per lane.  What bounds it
 // is the mixed stream of reads and writes (6.4 TB/s of the stem's 1.67 GB); short wavefronts and a bit stream
@@ -883,13 +870,22 @@ static dim3 relu_blocks(int64_t n, int64_t element_bytes)
     return dim3(static_cast<unsigned>(along_x), static_cast<unsigned>((blocks + along_x - 1) / along_x));
 }
 
-// Binary16 up to 104 MiB: with stores through the caches ReLU and 3x3 / 1 / 1 pooling, both directions, are from 112 MiB on 0.5 to 1 % behind
-// (57 x 57 254.4 -> 255.7 us, 55 x 245 at 128 MiB 281.6 -> 284.4) and at 100 MiB alike or ahead.
-static bool relu_through_caches(int64_t n, int64_t element_bytes)
-{
-    const int64_t bytes = n * element_bytes;
-    return store_through_caches(bytes) && (element_bytes == 4 || bytes <= int64_t(104) << 20);
-}
+// Whether y is stored through the caches: the next layer reads it, and a result that fits the 256 MiB Infinity Cache beside what
+// that layer reads and writes is found there.  Non-temporal stores -> these, medians:
+//   ReLU, pooling of its result and a pass over that, in a step with 768 MiB of other traffic between its two directions (us)
+//                               24 MiB        48 MiB        64 MiB        80 MiB        96 MiB        112 MiB       128 MiB
+//     binary32 112 x 112 3/2/1  27.1 -> 27.1  41.2 -> 40.6  50.7 -> 49.9  62.2 -> 59.8  70.5 -> 67.8  80.0 -> 78.2  90.4 -> 86.6
+//     binary32  51 x  14 3/1/1  39.0 -> 39.0  63.6 -> 63.3  81.0 -> 80.0  97.5 -> 96.8 114.9 ->113.9 131.7 ->132.1 148.5 ->152.8
+//     binary16 113 x 113 3/2/1  29.7 -> 29.4  44.5 -> 43.9  54.4 -> 53.3  64.9 -> 64.0  74.2 -> 72.8  83.3 -> 82.2  93.4 -> 91.3
+//     binary16  57 x  57 3/1/1  46.7 -> 46.3  75.0 -> 75.2  95.6 -> 95.2 115.8 ->115.5 136.4 ->136.7 158.7 ->159.2 177.9 ->182.2
+//   (binary32 57 x 57 3/1/1 and 144 MiB 173.3 -> 170.2, 51 x 14 169.1 -> 175.9)
+//   six layers of a pass, ReLU and a pass over its result, per layer, both types: from 24 to 112 MiB -1.5 to -4.6 %, at 128 MiB -1 %; with a residual read as
+//   well -0.4 to -5 %, at 128 MiB binary32 +1 %; where the pass in front updates its tensor in place +0.4 to +3.3 %
+// A call whose result nothing reads, over one to four tensors in turn: 24 MiB 6 to 15 % behind, 32 MiB 4 to 19 %, 40 MiB 1 to 11 %, 48 MiB -1 to +6 %, 64 to 112 MiB
+// -2 to +4 %.  Hence from the size at which the reader gains about what such a call loses, to the largest at which no image loses more than its runs differ.
+// Pooling stores past the caches in both directions: forward, its reader gains 0 to 2 us and a call by itself loses 0 to 3 (64 to 144 MiB); backward, binary16
+// gains nothing, and binary32 2 to 5 % in a step at the cost of up to 44 % alone (80 MiB, four tensors in turn 18.3 -> 25.9 us).
+static bool relu_through_caches(int64_t bytes) { return bytes >= int64_t(48) << 20 && bytes <= int64_t(112) << 20; }
 
 int launch_relu_forward(const void* x, int dtype, int64_t n, void* y, uint8_t* mask, void* stream)
 {
@@ -899,7 +895,7 @@ int launch_relu_forward(const void* x, int dtype, int64_t n, void* y, uint8_t* m
     const auto typed = [&](const auto* from, auto* to) {
         typedef std::remove_pointer_t<decltype(to)> T;
         const dim3 blocks = relu_blocks(n, sizeof(T));
-        if (relu_through_caches(n, sizeof(T))) launch(relu_forward_kernel<T, false>, blocks, kBlock, s, from, n, mask_words, to, words);
+        if (relu_through_caches(n * static_cast<int64_t>(sizeof(T)))) launch(relu_forward_kernel<T, false>, blocks, kBlock, s, from, n, mask_words, to, words);
         else launch(relu_forward_kernel<T, true>, blocks, kBlock, s, from, n, mask_words, to, words);
     };
     if (dtype == ACTQ_F32) typed(static_cast<const float*>(x), static_cast<float*>(y));
@@ -912,10 +908,10 @@ int launch_relu_backward(const uint8_t* mask, const void* grad_y, int dtype, int
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t mask_words = (n + 255) / 256 * 8;
     if (dtype == ACTQ_F32) {
-        launch(relu_backward_kernel<float>, relu_blocks(n, 4), kBlock, s, 
+        launch(relu_backward_kernel<float>, relu_blocks(n, 4), kBlock, s,
             reinterpret_cast<const uint32_t*>(mask), mask_words, static_cast<const float*>(grad_y), n, static_cast<float*>(grad_x));
     } else {
-        launch(relu_backward_kernel<_Float16>, relu_blocks(n, 2), kBlock, s, 
+        launch(relu_backward_kernel<_Float16>, relu_blocks(n, 2), kBlock, s,
             reinterpret_cast<const uint32_t*>(mask), mask_words, static_cast<const _Float16*>(grad_y), n, static_cast<_Float16*>(grad_x));
     }
     return launched("actq_relu_backward");
@@ -965,8 +961,8 @@ __device__ __forceinline__ uint32_t from_right_lane(uint32_t v)
     return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), kWaveShiftLeft1, 0xf, 0xf, false));
 }
 
-// JOIN: both rows before either store.  NT: non-temporal stores.
-template <typename T, int K, int P, bool JOIN, bool NT>
+// JOIN: both rows before either store.
+template <typename T, int K, int P, bool JOIN>
 __global__ __launch_bounds__(kPoolBwdBlock) void maxpool2d_backward_stream_kernel(const uint8_t* __restrict__ argmax,
                                                                            const T* __restrict__ grad_y, Pool g,
                                                                            StreamPool q, T* __restrict__ grad_x)
@@ -1032,10 +1028,6 @@ __global__ __launch_bounds__(kPoolBwdBlock) void maxpool2d_backward_stream_kerne
     }
     vec_in rows[2];
     T* dst = grad_x + 2 * static_cast<int64_t>(strip) * g.W + static_cast<int64_t>(E) * ch;
-    const auto store = [&](vec_in v, T* to) {
-        if (NT) __builtin_nontemporal_store(v, reinterpret_cast<vec_in*>(to));
-        else *reinterpret_cast<vec_in*>(to) = v;
-    };
 #pragma unroll
     for (int rr = 0; rr < 2; ++rr) {
         vec_in out;
@@ -1058,11 +1050,11 @@ __global__ __launch_bounds__(kPoolBwdBlock) void maxpool2d_backward_stream_kerne
         }
         if (JOIN) asm volatile("" : "+v"(out));
         rows[rr] = out;
-        if (!JOIN && live) store(out, dst + rr * g.W);
+        if (!JOIN && live) __builtin_nontemporal_store(out, reinterpret_cast<vec_in*>(dst + rr * g.W));
     }
     if (JOIN && live) {
-        store(rows[0], dst);
-        store(rows[1], dst + g.W);
+        __builtin_nontemporal_store(rows[0], reinterpret_cast<vec_in*>(dst));
+        __builtin_nontemporal_store(rows[1], reinterpret_cast<vec_in*>(dst + g.W));
     }
 }
 
@@ -1101,13 +1093,12 @@ struct BackwardRule {
     bool single;   // 2x2: a lane owns one input row
     bool stream;   // otherwise: the kernel for even extents and aligned rows, or the row kernel
     bool join;     // the stream kernel computes both rows of a lane before it stores either
-    bool cached;   // the stores go through the caches for the reader's sake (see store_through_caches)
-    bool nt;       // otherwise: the row kernel's are non-temporal
+    bool nt;       // the row kernel's stores are non-temporal
 };
 
 static BackwardRule backward_rule(int64_t planes, const PoolShape& p, int64_t element_bytes)
 {
-    BackwardRule r = {false, false, false, false, false};
+    BackwardRule r = {false, false, false, false};
     if (!row_geometry(p)) return r;
     const int64_t row = p.W * element_bytes, mib = planes * p.H * row >> 20;   // of the result
     const bool even = p.sh == 2 && 2 * p.OH == p.H && 2 * p.OW == p.W && p.W % 8 == 0;
@@ -1129,9 +1120,6 @@ static BackwardRule backward_rule(int64_t planes, const PoolShape& p, int64_t el
     // Long rows and rows of whole sectors (2x2 from 192 bytes on, where rows of 96 bytes lose 15 to 50 %): binary16, 100 MiB, 2x2 rows of 450 bytes
     // 12 %, of 600 12 %, 3x3 / 2 / 1 of 600 18 %, 3x3 / 2 / 0 of 2000 21 %; binary32 2x2 rows of 900 bytes 12 %.  Shorter rows lose: binary32 2x2 rows of
     // 112 bytes 46 %, of 240 bytes 10 %.
-    // For the reader's sake at stride 2 only: with 3x3 / 1 / 1 binary16 rows of 490 bytes lose (ReLU and pooling, both directions, 136 MiB 302 -> 307 us)
-    // and others are alike.  Binary16 up to 128 MiB (55 x 245, 3x3 / 2 / 1: 157.9 -> 152.7, but 160 MiB 201.9 -> 214.6).
-    r.cached = p.sh == 2 && store_through_caches(planes * p.H * row) && (element_bytes == 4 || planes * p.H * row <= int64_t(128) << 20);
     r.nt = row >= 256 || row % 128 == 0 || (row % 32 == 0 && row >= (p.kh == 3 ? 96 : 192));
     return r;
 }
@@ -1163,17 +1151,11 @@ static void maxpool_forward_typed(const T* x, int64_t planes, const PoolShape& p
         // 50 -> 46 us and 3x3/1 on [1026, 113, 113] 35 -> 29, in a step alike alone and 5 to 10 % behind with the pass over y.  On whole 16 bytes,
         // over a few tensors in turn: binary16 2x2/2 27.9 -> 25.8 us on [4096, 112, 112], 3x3/2 54.9 -> 52.8 us on [4096, 160, 160]; with the pass
         // over y, results that would have stayed in the Infinity Cache cost 10 to 20 % more.
-        // Where the image and the result together fit the Infinity Cache, y is stored for its reader, too: with only the other kernels' stores
-        // through the caches ReLU and pooling in both directions take, 112 x 112, 3x3 / 2 / 1, binary32 64 MiB 81.2 us and with these 76.7, 160 MiB
-        // 181.0 and 169.8, binary16 96 MiB 118.3 and 111.5.  A result as large as the image (3x3 / 1 / 1, 57 x 57): 64 MiB 111.2 and 109.9, but
-        // 96 MiB 164.4 and 167.4, 160 MiB 278 and 283.
-        const int64_t elements = planes * p.OH * p.OW, result = elements * (static_cast<int64_t>(sizeof(T)) + 1);
-        const bool cached = store_through_caches(planes * p.H * p.W * static_cast<int64_t>(sizeof(T))) && result <= int64_t(80) << 20;
-        const bool nt = !cached && (sizeof(T) == 4 ? p.kh == 3 || p.W % 4 == 0 : p.W % 8 == 0);
+        const bool nt = sizeof(T) == 4 ? p.kh == 3 || p.W % 4 == 0 : p.W % 8 == 0;
 #define ACTQ_POOL_ROWS(K, PH, PW, S)                                                                                                         \
     do {                                                                                                                                     \
-        if (nt) launch(maxpool2d_forward_rows_kernel<T, K, PH, PW, S, true>, blocks, kBlock, s, x, g, rows, y, argmax);                       \
-        else launch(maxpool2d_forward_rows_kernel<T, K, PH, PW, S, false>, blocks, kBlock, s, x, g, rows, y, argmax); \
+        if (nt) launch(maxpool2d_forward_rows_kernel<T, K, PH, PW, S, true>, blocks, kBlock, s, x, g, rows, y, argmax);                              \
+        else if constexpr (sizeof(T) == 2 || K == 2) launch(maxpool2d_forward_rows_kernel<T, K, PH, PW, S, false>, blocks, kBlock, s, x, g, rows, y, argmax); \
     } while (0)
         if (p.sh == 1) ACTQ_POOL_ROWS(3, 1, 1, 1);
         else if (p.kh == 2 && p.ph == 0) ACTQ_POOL_ROWS(2, 0, 0, 2);
@@ -1209,14 +1191,9 @@ static void maxpool_backward_typed(const uint8_t* argmax, const T* grad_y, int64
         dim3 unused;
         const Pool g = make_pool(p, planes, 1, &unused);
         const unsigned blocks = (q.total + kPoolBwdBlock - 1) / kPoolBwdBlock;
-        const auto stream = [&](auto nt) {
-            constexpr bool kNt = decltype(nt)::value;
-            if (p.kh == 2) launch(maxpool2d_backward_stream_kernel<T, 2, 0, false, kNt>, blocks, kPoolBwdBlock, s, argmax, grad_y, g, q, grad_x);
-            else if (rule.join) launch(maxpool2d_backward_stream_kernel<T, 3, 1, true, kNt>, blocks, kPoolBwdBlock, s, argmax, grad_y, g, q, grad_x);
-            else launch(maxpool2d_backward_stream_kernel<T, 3, 1, false, kNt>, blocks, kPoolBwdBlock, s, argmax, grad_y, g, q, grad_x);
-        };
-        if (rule.cached) stream(std::false_type());
-        else stream(std::true_type());
+        if (p.kh == 2) launch(maxpool2d_backward_stream_kernel<T, 2, 0, false>, blocks, kPoolBwdBlock, s, argmax, grad_y, g, q, grad_x);
+        else if (rule.join) launch(maxpool2d_backward_stream_kernel<T, 3, 1, true>, blocks, kPoolBwdBlock, s, argmax, grad_y, g, q, grad_x);
+        else launch(maxpool2d_backward_stream_kernel<T, 3, 1, false>, blocks, kPoolBwdBlock, s, argmax, grad_y, g, q, grad_x);
         return;
     }
     RowPool rows;
@@ -1231,7 +1208,7 @@ static void maxpool_backward_typed(const uint8_t* argmax, const T* grad_y, int64
         }
 #define ACTQ_POOL_ROWS(K, P, S)                                                                                              \
     do {                                                                                                                    \
-        if (rule.nt && !rule.cached) launch(maxpool2d_backward_rows_kernel<T, K, P, S, true>, blocks, kBlock, s, argmax, grad_y, g, rows, grad_x);    \
+        if (rule.nt) launch(maxpool2d_backward_rows_kernel<T, K, P, S, true>, blocks, kBlock, s, argmax, grad_y, g, rows, grad_x);    \
         else launch(maxpool2d_backward_rows_kernel<T, K, P, S, false>, blocks, kBlock, s, argmax, grad_y, g, rows, grad_x);      \
     } while (0)
         if (p.sh == 1) ACTQ_POOL_ROWS(3, 1, 1);
