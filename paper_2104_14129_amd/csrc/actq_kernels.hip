@@ -1587,6 +1587,10 @@ constexpr int kMaxSteps = 7;
 constexpr int kSmallItems = 2;
 constexpr int kAllocBins = 4096;      // bins of the large kernel's table over w / D
 constexpr int kAllocList = 1024;      // items with undecided steps the large kernel lists: one per thread
+// Beyond this many items a bin holds so many that the list of all items in undecided bins overflows, and their moves are priced in every
+// turn: each item is tested by itself then.  Log-normal sensitivities, all listed -> tested (us): 150,000 with all widths 400 -> 248 where the
+// list overflows and 214 -> 230 where it does not, 200,000 490 -> 302, 400,000 with {1, 2, 4, 8} 965 -> 594.
+constexpr int64_t kAllocFilter = 131072;
 constexpr int kAllocQuads = 4;        // quadruples of consecutive items per thread kept in registers: 16,384 items in all
 
 // What the budget is compared with.
@@ -2609,8 +2613,9 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
         }
         __syncthreads();
 
-        // ---- the items in a bin with undecided steps, listed
+        // ---- the items in a bin with undecided steps, listed; beyond kAllocFilter, those with undecided steps of their own
         uint32_t undecided = 0, listed_at = 0;
+        const bool filter = M > kAllocFilter;
 #pragma unroll
         for (int k = 0; k < kAllocQuads; ++k) {
             if (!in_round(k)) continue;
@@ -2621,17 +2626,49 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
                 rungs |= static_cast<uint64_t>(cls & 7u) << (4 * j);
             }
         }
+        const auto steps_freed = [&](int64_t Di, int from, int to) {   // bits freed by going from rung `from` to rung `to`
+            return static_cast<uint64_t>(Di) * static_cast<uint64_t>(ladder_width(a, from) - ladder_width(a, to));
+        };
+        if (filter) {
+            for (uint32_t m = undecided; m != 0; m &= m - 1) {
+                const int j = __builtin_ctz(m);
+                const int64_t i = item(j), Di = elements(i);
+                int first, last;
+                bracket_steps(br, steps, ratio_of(w[i], Di), first, last);
+                if (first != last) continue;
+                undecided &= ~(1u << j);
+                my_below += steps_freed(Di, static_cast<int>(rungs >> (4 * j)) & 15, first);   // those before are counted with its bin
+                rungs = (rungs & ~(uint64_t(15) << (4 * j))) | (static_cast<uint64_t>(first) << (4 * j));
+            }
+        }
         if (undecided != 0) {
             listed_at = __hip_atomic_fetch_add(&list_count, static_cast<uint32_t>(__builtin_popcount(undecided)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             uint32_t at = listed_at;
             for (uint32_t m = undecided; m != 0; m &= m - 1, ++at)
                 if (at < static_cast<uint32_t>(kAllocList)) list_item[at] = static_cast<uint32_t>(item(__builtin_ctz(m)));
         }
-        further([&](int64_t i, float wi, int64_t Di) {
-            if (!(class_of(bin_of(ratio_of(wi, Di))) & 8u)) return;
-            const uint32_t at = __hip_atomic_fetch_add(&list_count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (at < static_cast<uint32_t>(kAllocList)) list_item[at] = static_cast<uint32_t>(i);
-        });
+        uint64_t decided = 0;   // the same of the items beyond the registers: only the list leaves them out
+        const auto list_further = [&](auto tested) {
+            bool full = false;   // this thread has seen the list past its end: it is not used
+            further([&](int64_t i, float wi, int64_t Di) {
+                if (tested && full) return;
+                const uint32_t u = ratio_of(wi, Di), cls = class_of(bin_of(u));
+                if (!(cls & 8u)) return;
+                if (tested) {
+                    int first, last;
+                    bracket_steps(br, steps, u, first, last);
+                    if (first == last) {
+                        decided += steps_freed(Di, static_cast<int>(cls & 7u), first);
+                        return;
+                    }
+                }
+                const uint32_t at = __hip_atomic_fetch_add(&list_count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                full = at >= static_cast<uint32_t>(kAllocList);
+                if (!full) list_item[at] = static_cast<uint32_t>(i);
+            });
+        };
+        if (filter) list_further(std::true_type());
+        else list_further(std::false_type());
         __syncthreads();
         const uint32_t listed = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(list_count)));
         if (listed <= static_cast<uint32_t>(kAllocList)) {
@@ -2643,6 +2680,7 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
             int fine = 23 - __builtin_clz(spread | 1u);         // (spread >> fine) < 512
             fine = fine > 0 ? fine : 0;
             int64_t Di = 0;
+            my_below += decided;
             if (mine) {
                 const int64_t i = list_item[tid];
                 const float wi = w[i];
@@ -2653,7 +2691,7 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
                 for (int r = 0; r < kMaxSteps; ++r) {
                     key[r] = r < steps ? quotient_bits(of_item * a.lad.price[r], d, y) : ~uint64_t(0);
                     const uint32_t top = static_cast<uint32_t>(key[r] >> 32);
-                    const uint64_t freed = static_cast<uint64_t>(Di) * static_cast<uint64_t>(a.lad.width[r] - (r + 1 < 8 ? a.lad.width[r + 1] : 0));
+                    const uint64_t freed = static_cast<uint64_t>(Di) * static_cast<uint64_t>(a.lad.width[r] - a.lad.width[r + 1]);
                     // cheaper steps of the item beyond those counted with its bin
                     if (top < price_lo && static_cast<uint32_t>(r) >= (cls & 7u)) my_below += freed;
                     if (top >= price_lo && top < price_hi) {

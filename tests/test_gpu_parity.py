@@ -623,6 +623,23 @@ def test_device_allocator_at_the_limits_of_its_kernels(M, widths, law):
         assert np.array_equal(offs, np.concatenate([[0], np.cumsum(per)[:-1]])) and total == int(per.sum())
 
 
+# items on both sides of the number from which on each is tested before it is listed; further rounds with a remainder; lists that hold
+# the undecided and lists that overflow
+@pytest.mark.parametrize("law", ["log-normal", "wide", "groups", "few"])
+@pytest.mark.parametrize("M,widths,uniform", [(131072, 0x1FE, False), (131073, 0x116, False), (131075, 0x1FE, True), (262146, 0x116, True), (400001, 0x1FE, False)])
+def test_device_allocator_with_many_items_per_bin(M, widths, uniform, law):
+    rng = np.random.default_rng(M)
+    w = rng.lognormal(0, 2, M).astype(np.float32) if law == "log-normal" else _spread(rng, M, law)
+    D = np.full(M, 25088, dtype=np.int64) if uniform else rng.choice([1, 256, 25088, 802816], M).astype(np.int64)
+    for mean in (1.3, 2.0, 6.7):
+        budget = int(mean * float(D.sum()))
+        want = B.allocate_bits(w, D, budget, widths)
+        got, offs, total, status = _device_alloc(w, D, budget, widths, uniform)
+        assert status == 0 and np.array_equal(got, want), (mean, np.flatnonzero(got != want)[:6])
+        per = ((D + 255) // 256) * 32 * want.astype(np.int64)
+        assert np.array_equal(offs, np.concatenate([[0], np.cumsum(per)[:-1]])) and total == int(per.sum())
+
+
 # items of one size, where the small kernel counts in units of that size: one and two items per thread, the first item beyond
 # it, one wavefront and a partial second one; sizes whose reciprocal is exact, is not, and the largest
 @pytest.mark.parametrize("law", ["wide", "close", "groups", "few", "zero", "one"])
