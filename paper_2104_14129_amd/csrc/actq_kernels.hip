@@ -1563,7 +1563,7 @@ __global__ __launch_bounds__(kSensMaxBlock) void sample_sensitivity_kernel(const
 // What bounds it: one workgroup has one compute unit, and most phases are chains of dependent instructions, LDS round trips
 // and barriers.  A radix selection over the 64-bit patterns of all prices (eight passes of eight bits) took 154 us for 13,568
 // items with all eight widths, 101 us with {1, 2, 4, 8}, and 10 us for 128 items.  Hence:
-//   * a small problem (allocate_bits_small_kernel: up to 1024 items, 2048 of one size) has every price in registers and takes one
+//   * a small problem (allocate_bits_small_kernel: up to 1024 items, 2048 of one size or of few moves) has every price in registers and takes one
 //     histogram over the range of the prices: the bin that holds the threshold has a handful of moves, which are ranked;
 //   * a large one (allocate_bits_kernel) does not price its moves at all at first.  A price is
 //     (w / D) * c_r to within a few units in the last place, so a histogram of the ITEMS over
@@ -1582,9 +1582,16 @@ __global__ __launch_bounds__(kSensMaxBlock) void sample_sensitivity_kernel(const
 constexpr int kAllocBlock = 1024;
 constexpr int kAllocWavesMax = kAllocBlock / kWave;
 constexpr int kMaxSteps = 7;
-// Items per thread of the small kernel from 1025 items on, if they are of one size (2048 with all widths 12.5 against 14.4 us with the
-// large kernel, with {1, 2, 4, 8} 9.7 against 13.2).  With sizes of their own it ends at 1024 (12.0 us; 2048 18.5 against 14.4 us).
+// Items per thread of the small kernel from 1025 items on.  Of one size: 2048 with all widths 12.5 against 14.4 us with the large kernel, with
+// {1, 2, 4, 8} 9.7 against 13.2.
 constexpr int kSmallItems = 2;
+// With sizes of their own only up to this many moves.  Large kernel -> small one (us), log-normal sensitivities / all equal / all zero / half of them zero:
+//   {1, 8}         1025 items 13.3 -> 8.5 / 19.0 -> 10.6 / 18.5 -> 8.4 / 13.2 -> 11.9    2048 items 13.4 -> 9.6 / 20.6 -> 12.2 / 20.6 -> 8.5 / 13.8 -> 13.8
+//   {1, 2, 4}      1025 items 13.6 -> 9.1 / 19.0 -> 11.4 / 20.1 -> 8.7 / 13.2 -> 12.5    2048 items 13.4 -> 10.3 / 20.6 -> 13.8 / 22.5 -> 8.8 / 13.8 -> 14.5
+//   {1, 2, 4, 8}   1025 items 13.3 -> 10.3 / 19.3 -> 12.1 / 21.9 -> 8.7 / 13.3 -> 13.5   1300 items 13.6 -> 10.1 / 20.0 -> 13.0 / 23.9 -> 9.0 / 13.6 -> 14.3
+// Beyond, the bin of the threshold may hold more moves than are ranked: 2048 items, {1, 2, 4, 8}, log-normal 13.5 -> 13.7 or 17.8 by the draw, 1500 with all
+// widths 14.2 -> 18.5.
+constexpr int64_t kSmallMoves = 4 * kAllocBlock;
 constexpr int kAllocBins = 4096;      // bins of the large kernel's table over w / D
 constexpr int kAllocList = 1024;      // items with undecided steps the large kernel lists: one per thread
 // Beyond this many items a bin holds so many that the list of all items in undecided bins overflows, and their moves are priced in every
@@ -3303,7 +3310,8 @@ int launch_allocate_bits(const float* w, const int64_t* D_items, int64_t D, int6
     for (int k = 0; k < lad.count; ++k) width_nibbles |= static_cast<uint32_t>(lad.width[k]) << (4 * k);
     const AllocBudget total = {static_cast<uint64_t>(budget_bits), static_cast<uint32_t>(lad.width[0]), static_cast<uint32_t>(lad.width[lad.count - 1])};
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (M <= (D_items ? 1 : kSmallItems) * kAllocBlock) {
+    const bool two = M > kAllocBlock;   // items per thread
+    if (!two || (M <= kSmallItems * kAllocBlock && (!D_items || M * (lad.count - 1) <= kSmallMoves))) {
         SmallAllocArgs a = {};
         a.M = static_cast<int32_t>(M);
         a.steps = lad.count - 1;
@@ -3323,8 +3331,9 @@ int launch_allocate_bits(const float* w, const int64_t* D_items, int64_t D, int6
         }
         const int64_t lanes = (M + kWave - 1) / kWave * kWave;
         const unsigned block = static_cast<unsigned>(lanes < kAllocBlock ? lanes : kAllocBlock);
-        if (D_items) launch(allocate_bits_small_kernel<false, 1>, 1, block, s, w, a, bits, offsets, result);
-        else if (M > kAllocBlock) launch(allocate_bits_small_kernel<true, kSmallItems>, 1, block, s, w, a, bits, offsets, result);
+        if (D_items && two) launch(allocate_bits_small_kernel<false, kSmallItems>, 1, block, s, w, a, bits, offsets, result);
+        else if (D_items) launch(allocate_bits_small_kernel<false, 1>, 1, block, s, w, a, bits, offsets, result);
+        else if (two) launch(allocate_bits_small_kernel<true, kSmallItems>, 1, block, s, w, a, bits, offsets, result);
         else launch(allocate_bits_small_kernel<true, 1>, 1, block, s, w, a, bits, offsets, result);
     } else {
         AllocArgs a;

@@ -601,8 +601,8 @@ def _spread(rng, M, law):
     return np.full(M, {"zero": 0.0, "one": 1.0}[law], dtype=np.float32)
 
 
-# items around the limits of the two kernels: 2048 and 7168 moves, 1024 and 2048 items (one or two per thread of the
-# small kernel), rounds of 4096 items, 16,384 items in registers, one, two and six further rounds; remainders of the quadruples
+# items around the limits of the two kernels: 1024 and 2048 items (one or two per thread of the small kernel, two up to 4096 moves),
+# rounds of 4096 items, 16,384 items in registers, one, two and six further rounds; remainders of the quadruples
 @pytest.mark.parametrize("law", ["wide", "close", "groups", "few", "zero", "one"])
 @pytest.mark.parametrize("M,widths", [(65, 0x102), (128, 0x1FE), (292, 0x1FE), (293, 0x1FE), (682, 0x116), (683, 0x116), (1024, 0x102), (1024, 0x1FE), (1025, 0x102), (1025, 0x1FE), (1337, 0x116),
                                       (1792, 0x11E), (1793, 0x11E), (2047, 0x116), (2048, 0x116), (2049, 0x116), (4096, 0x116),
@@ -638,6 +638,13 @@ def test_device_allocator_with_many_items_per_bin(M, widths, uniform, law):
         assert status == 0 and np.array_equal(got, want), (mean, np.flatnonzero(got != want)[:6])
         per = ((D + 255) // 256) * 32 * want.astype(np.int64)
         assert np.array_equal(offs, np.concatenate([[0], np.cumsum(per)[:-1]])) and total == int(per.sum())
+
+
+# sizes of their own beyond 1024 items: two items per thread of the small kernel up to 4096 moves and 2048 items, the large kernel from there
+@pytest.mark.parametrize("law", ["wide", "close", "groups", "few", "zero", "one"])
+@pytest.mark.parametrize("M,widths", [(1025, 0x11E), (1365, 0x116), (1366, 0x116), (2047, 0x016), (2048, 0x016), (2048, 0x102), (2049, 0x102)])
+def test_device_allocator_with_two_items_of_their_own_sizes_per_thread(M, widths, law):
+    test_device_allocator_at_the_limits_of_its_kernels(M, widths, law)
 
 
 # items of one size, where the small kernel counts in units of that size: one and two items per thread, the first item beyond
