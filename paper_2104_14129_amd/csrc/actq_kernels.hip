@@ -1951,9 +1951,19 @@ __device__ __forceinline__ void rank_moves(const uint64_t* keys, const Amount* a
     const bool listed = lane < n;
     const uint64_t own = listed ? keys[lane] : ~uint64_t(0);
     const Amount frees = listed ? amounts[lane] : Amount(0);
+    // moves of one price (items of one size and sensitivity) need no ranking: 64 items of sensitivity one with {1, 2, 4, 8} 9.6 -> 6.3 us, with all
+    // widths 10.1 -> 6.6 (call to call)
+    const uint64_t one = read_lane(own, 0);
+    if (__ballot(listed && own != one) == 0) {
+        price = one;
+        below = start;
+        count = static_cast<uint64_t>(n);
+        return;
+    }
     Amount cheaper = 0, upto = 0;
     uint32_t ties = 0;
-    for (int k = 0; k < n; ++k) {
+#pragma unroll 4
+    for (int k = 0; k < ((n + 3) & ~3); ++k) {   // lanes past the list free nothing and have no price
         const uint64_t other = read_lane(own, k);
         const Amount freed = read_lane(frees, k);
         cheaper += other < own ? freed : Amount(0);

@@ -647,6 +647,18 @@ def test_device_allocator_with_two_items_of_their_own_sizes_per_thread(M, widths
     test_device_allocator_at_the_limits_of_its_kernels(M, widths, law)
 
 
+# lists of 1 to 64 moves around the threshold, of one price, of several, all different; multiples of four and remainders
+@pytest.mark.parametrize("law", ["close", "one", "few", "groups"])
+@pytest.mark.parametrize("M", [2, 3, 5, 8, 21, 22, 61, 62, 63, 64, 70])
+def test_device_allocator_ranks_lists_of_any_length(M, law):
+    w = _spread(np.random.default_rng(M), M, law)
+    D = np.full(M, 4096, dtype=np.int64)
+    for widths in (0x102, 0x116, 0x1FE):
+        for mean in (1.3, 2.0, 3.5, 7.9):
+            _check_alloc(w, D, int(mean * M * 4096), widths, True)
+            _check_alloc(w, D, int(mean * M * 4096), widths, False)
+
+
 # items of one size, where the small kernel counts in units of that size: one and two items per thread, the first item beyond
 # it, one wavefront and a partial second one; sizes whose reciprocal is exact, is not, and the largest
 @pytest.mark.parametrize("law", ["wide", "close", "groups", "few", "zero", "one"])
