@@ -3065,16 +3065,18 @@ static int each_launch(const char* who, uint64_t most, int32_t count, int waves_
 }
 
 // Whether the statistics leave a tensor of this many bytes in the 256 MiB Infinity Cache, where the quantizer finds (part of) it:
-// ordinary loads instead of non-temporal ones.  Time from the statistics to the packed codes with non-temporal loads (us) and how it
-// changes with ordinary ones, 64 samples; "made" has a pass that writes the tensor in front, which is in the time:
-//              24 MiB       80 MiB       144 MiB      208 MiB      256 MiB      400 MiB
-// f32          16.8 +1.5%   33.9 -1.2%   54.1 -1.0%   74.7 -1.6%   89.9 +0.8%   135.4 +2.8%
-// f32, made    27.5 -8.7%   61.7 -4.6%   100.0 -3.4%  138.2 -2.8%  168.8 -2.5%  258.8 +13.8%
-// f16          19.0 +1.1%   37.4 -2.1%   57.7 -1.6%   80.7 -3.0%   96.7 -2.0%   146.8 -2.2%
-// f16, made    28.5 -0.3%   63.4 -1.3%   102.8 -2.5%  141.2 -2.3%  171.4 -2.1%  263.9 +12.5%
-// Samples that end inside a group, 24 to 208 MiB: f32 +0.2 to -3.4%, made -5 to -12%; f16 +0.8 to -3.4%, made -1.5 to -7%.  Up to 16 MiB
-// from +2% to -4%, which is what runs of one side differ by there.  The limit is the largest size measured where no form loses more than that.
-static bool stays_cached(int64_t bytes) { return bytes <= int64_t(208) << 20; }
+// ordinary loads instead of non-temporal ones.  Compression of one tensor of 64 samples with non-temporal loads (us) and how it changes with
+// ordinary ones; "made": a pass writes the tensor in front, behind 768 MiB of other traffic; "in turn": four tensors.
+//               24 MiB       48 MiB       80 MiB       144 MiB      176 MiB      208 MiB
+// f32, made     23.3 -0.4%   28.4 +0.1%   42.2 -1.2%   61.5 -1.2%   73.1 +4.2%   83.0 +9.6%
+// f32, in turn  23.5 +2.5%   28.9 +1.0%   42.7 -1.5%   63.0 -0.5%   73.1 +0.2%   83.1 -0.6%
+// f16, made     23.4 +1.5%   34.9 -1.0%   44.7 -2.7%   65.1 -4.0%   75.8 +2.8%   87.6 +6.6%
+// f16, in turn  23.3 +0.3%   34.2 +0.3%   44.4 -1.3%   65.1 -2.8%   76.0 -3.5%   87.0 -4.4%
+// Samples that end inside a group, made: f32 -4.1, -3.9, -4.7, -4.4, +3.0, +7.4 %; f16 -3.6, -5.6, -7.0, -10.1, -6.6, -4.2 %.  With a pass over the tensor
+// behind its compression f32 -4.6, -3.8, -3.4, -1.4, +2.1, +5.6 %.  The statistics by themselves, in turn, are behind: f32 from 64 MiB on 7 to 28 %, f16 6 to 19 %.
+// The limit is the largest size at which the compression of a tensor that was just made does not lose; below 80 MiB f32 in turn loses up to 3 %.
+// Tensor sets keep non-temporal loads at any size: between a tensor's statistics and its codes lie those of the others.
+static bool stays_cached(int64_t bytes) { return bytes <= int64_t(144) << 20; }
 
 // Launches with a table of CAPACITY items; ragged samples come as single tensors only.
 template <int CAPACITY>

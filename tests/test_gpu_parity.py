@@ -1140,16 +1140,16 @@ def test_arguments_exactly_at_their_limits_are_accepted():
     assert zr.cpu().tolist() == [2.5, 0.0]
 
 
-# statistics of single tensors up to 208 MiB load through the caches, larger ones do not: both against the extremes themselves, whole
+# statistics of single tensors up to 144 MiB load through the caches, larger ones do not: both against the extremes themselves, whole
 # groups, one element in the last group, and rows that begin off the loads' alignment
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
 @pytest.mark.parametrize("tail", [0, 1, 255])
 @pytest.mark.parametrize("over", [False, True])
 def test_statistics_on_both_sides_of_the_cached_size(over, tail, dtype):
     N, size = 8, torch.finfo(dtype).bits // 8
-    groups = (208 << 20) // (size * N * 256)
+    groups = (144 << 20) // (size * N * 256)
     D = (groups + over) * 256 - (256 - tail if tail else 0)
-    assert (N * D * size > 208 << 20) == over
+    assert (N * D * size > 144 << 20) == over
     g = torch.Generator(device="cuda").manual_seed(tail + 2 * over)
     x = torch.randn((N, D), generator=g, device="cuda").to(dtype)
     gmin, grange = B.group_stats(x)
