@@ -296,6 +296,72 @@ def test_calls_go_to_the_current_stream():
     assert B._stream(None) == torch.cuda.current_stream().cuda_stream
 
 
+def _late(stream, *truth):
+    """Tensors that hold `truth` only once `stream` has come that far: zeros to whatever runs beside it."""
+    late = [torch.zeros_like(t) for t in truth]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        torch.cuda._sleep(20_000_000)     # some milliseconds and more
+        for t, v in zip(late, truth):
+            t.copy_(v)
+    return late
+
+
+def test_device_calls_without_a_stream_run_on_the_current_one():
+    N, D = 4, 2048
+    x = torch.randn(N, D, device=DEV)
+    image, g = torch.randn(2, 3, 16, 16, device=DEV), torch.randn(2, 3, 8, 8, device=DEV)
+
+    def calls(x, grange, w, bits, offsets, packed, header, image, mask, arg, g):
+        stream, head, out = torch.zeros(N * D, dtype=torch.uint8, device=DEV), torch.zeros(N * D // 128, device=DEV), torch.zeros_like(x)
+        results = [*B.group_stats(x), B.sample_sensitivity(grange), *B.allocate_bits_device(w, D, 2 * N * D)]
+        results += [*B.quantize_pack(x, bits, offsets, stream, head, 7), B.unpack_dequantize(packed, header, bits, offsets, out)]
+        results += [*B.compress_mixed(x, None, 2 * N * D, B.ACTQ_WIDTHS_POW2, N * D // 4 + 64, 3, 5, 16)[:2]]
+        results += [*B.relu_forward(image), B.relu_backward(mask, image)]
+        results += [*B.maxpool2d_forward(image, (2, 2), (2, 2)), B.maxpool2d_backward(arg, g, 16, 16, (2, 2), (2, 2))]
+        return results
+
+    _, grange = B.group_stats(x)
+    w = B.sample_sensitivity(grange)
+    bits, offsets, _ = B.allocate_bits_device(w, D, 2 * N * D)
+    packed, header = torch.zeros(N * D, dtype=torch.uint8, device=DEV), torch.zeros(N * D // 128, device=DEV)
+    B.quantize_pack(x, bits, offsets, packed, header, 7)
+    mask, arg = B.relu_forward(image)[1], B.maxpool2d_forward(image, (2, 2), (2, 2))[1]
+    truth = (x, grange, w, bits, offsets, packed, header, image, mask, arg, g)
+    want = calls(*truth)
+    s = torch.cuda.Stream()
+    late = _late(s, *truth)
+    with torch.cuda.stream(s):
+        got = calls(*late)
+    s.synchronize()
+    assert len(got) == len(want)
+    for k, (a, b) in enumerate(zip(got, want)):
+        assert torch.equal(a, b), k
+
+
+@pytest.mark.parametrize("layer", ["linear", "relu", "pool"])
+def test_native_functions_run_on_the_current_stream_in_both_directions(layer):
+    m = {"relu": lambda: L.QReLU(), "pool": lambda: L.QMaxPool2d(2), "linear": lambda: L.QLinear(300, 5, device=DEV)}[layer]()
+    x = torch.randn((9, 300) if layer == "linear" else (2, 3, 16, 16), device=DEV)
+
+    def step(x, g):
+        L._tags = itertools.count(11)
+        x = x.detach().requires_grad_()
+        y = m(x)
+        assert "FnBackward" not in y.grad_fn.name()     # the native one (a function in Python is named after its class)
+        return [y.detach(), *torch.autograd.grad(y, [x, *m.parameters()], g)]
+
+    g = torch.randn(m(x).shape, device=DEV)
+    want = step(x, g)
+    s = torch.cuda.Stream()
+    late = _late(s, x, g)
+    with torch.cuda.stream(s):
+        got = step(*late)
+    s.synchronize()
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
 @pytest.mark.parametrize("layer", ["linear", "linear without bias", "linear fixed width", "relu", "pool"])
 def test_native_functions_equal_those_in_python(layer, dtype, monkeypatch):
