@@ -220,10 +220,6 @@ def _stream(stream) -> int:
     return _raw_stream()
 
 
-def _view2d(x):
-    return int(x.shape[0]), int(x.numel() // x.shape[0])
-
-
 def version() -> int:
     return lib().actq_version()
 
@@ -370,7 +366,6 @@ class TensorDesc(ctypes.Structure):
 def tensor_table(entries):
     """Host-side descriptor array from dicts with any of the keys x, out, gmin, grange, header, bits,
     offsets (device tensors) and D.  All tensors must be [N, D] views with the same N."""
-    torch = _torch()
     table = (TensorDesc * len(entries))()
     for slot, e in zip(table, entries):
         for key in ("x", "out", "gmin", "grange", "header", "bits", "offsets"):

@@ -3075,7 +3075,7 @@ static int each_launch(const char* who, uint64_t most, int32_t count, int waves_
 // Samples that end inside a group, made: f32 -4.1, -3.9, -4.7, -4.4, +3.0, +7.4 %; f16 -3.6, -5.6, -7.0, -10.1, -6.6, -4.2 %.  With a pass over the tensor
 // behind its compression f32 -4.6, -3.8, -3.4, -1.4, +2.1, +5.6 %.  The statistics by themselves, in turn, are behind: f32 from 64 MiB on 7 to 28 %, f16 6 to 19 %.
 // The limit is the largest size at which the compression of a tensor that was just made does not lose; below 80 MiB f32 in turn loses up to 3 %.
-// Tensor sets keep non-temporal loads at any size: between a tensor's statistics and its codes lie those of the others.
+// Tensor sets keep non-temporal loads: the statistics of all their tensors run in front of the first codes, and sets that fit the cache as a whole are not measured.
 static bool stays_cached(int64_t bytes) { return bytes <= int64_t(144) << 20; }
 
 // Launches with a table of CAPACITY items; ragged samples come as single tensors only.
@@ -3387,7 +3387,7 @@ int launch_sample_sensitivity(const float* grange, int64_t N, int64_t ng, int32_
     // one lane per group up to 1024 lanes, whole wavefronts
     const int64_t lanes = (ng + kWave - 1) / kWave * kWave;
     const unsigned block = static_cast<unsigned>(lanes < kSensMaxBlock ? lanes : kSensMaxBlock);
-    launch(sample_sensitivity_kernel, dim3(gx, gy), block, static_cast<hipStream_t>(stream), 
+    launch(sample_sensitivity_kernel, dim3(gx, gy), block, static_cast<hipStream_t>(stream),
         grange, static_cast<uint32_t>(N), static_cast<uint32_t>(ng), gx, static_cast<float>(G) / 6.0f, grad2, w);
     return check_launch("actq_sample_sensitivity");
 }
