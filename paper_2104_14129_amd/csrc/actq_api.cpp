@@ -362,7 +362,7 @@ static int make_pool_shape(const char* who, int32_t H, int32_t W, int32_t kh, in
     if (kh <= 0 || kw <= 0 || static_cast<int64_t>(kh) * kw > 256)
         return fail(ACTQ_EINVAL, "%s: window %d x %d must have 1..256 positions (8-bit context)", who, kh, kw);
     if (sh <= 0 || sw <= 0 || dh <= 0 || dw <= 0) return fail(ACTQ_EINVAL, "%s: strides and dilations must be positive", who);
-    if (ph < 0 || pw < 0 || 2 * ph > kh || 2 * pw > kw)
+    if (ph < 0 || pw < 0 || ph > kh / 2 || pw > kw / 2)
         return fail(ACTQ_EINVAL, "%s: padding must be between 0 and half the window size", who);
     const int64_t eh = static_cast<int64_t>(dh) * (kh - 1) + 1, ew = static_cast<int64_t>(dw) * (kw - 1) + 1;
     if (H + 2 * static_cast<int64_t>(ph) < eh || W + 2 * static_cast<int64_t>(pw) < ew)

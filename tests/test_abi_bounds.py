@@ -188,6 +188,12 @@ def test_pooling_geometry_refused(change):
     assert rc == E and (oh, ow) == (-7, -7), change
 
 
+@pytest.mark.parametrize("ph,pw", [(2 ** 31 - 1, 0), (0, 2 ** 31 - 1), (2 ** 31 - 1, 2 ** 31 - 1), (2 ** 30, 0), (0, 2 ** 30 + 1)])
+def test_paddings_whose_double_overflows_are_refused(ph, pw):
+    rc, oh, ow = _size(kh=2, kw=2, sh=1, sw=1, ph=ph, pw=pw)
+    assert rc == B.ACTQ_EINVAL and (oh, ow) == (-7, -7) and "padding" in B.last_error()
+
+
 def test_pooling_geometry_at_its_limits():
     assert _size(kh=2, kw=2, ph=1, pw=1) == (0, 5, 5)                          # padding of exactly half the window
     assert _size(kh=16, kw=16, ph=0, pw=0, H=16, W=17, sh=1, sw=1) == (0, 1, 2)    # 256 positions
