@@ -376,6 +376,7 @@ Compressed compress_activation(const Tensor& x, const std::optional<Tensor>& gra
     r.header = empty_on(x, {groups * 2}, c.hf == ACTQ_HDR_BF16 ? at::kShort : at::kFloat);
     Tensor scratch;   // released when the last call that uses it has been issued, in the order of the stream
     if (c.bits) {
+        TORCH_CHECK_VALUE(c.offsets && c.bits->numel() == v.N && c.offsets->numel() == v.N, "bits and offsets must have N entries");
         r.bits = *c.bits;
         r.offsets = *c.offsets;
     } else {
@@ -394,7 +395,7 @@ Compressed compress_activation(const Tensor& x, const std::optional<Tensor>& gra
         call(api.sample_sensitivity, grange, v.N, v.groups, kG, g2, w, stream);
         call(api.allocate_bits_device, w, nullptr, v.D, v.N, kG, c.budget, c.widths, bp, op, result, stream);
     }
-    const Memory bp = {r.bits.data_ptr()}, op = {r.offsets.data_ptr()};
+    const Memory bp = on_gpu(r.bits, at::kByte, "bits"), op = on_gpu(r.offsets, at::kLong, "offsets");
     call(api.quantize_pack, xp, dt, v.N, v.D, kG, bp, op, c.seed, c.tag, c.noise_bits, r.packed.data_ptr(), static_cast<uint64_t>(c.capacity),
          r.header.data_ptr(), static_cast<actq_header_format>(c.hf), stream);
     return r;

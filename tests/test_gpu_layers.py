@@ -434,6 +434,20 @@ def test_saved_tensors_of_the_wrong_size_are_refused(layer, which, cut, native, 
     assert which in given_back
 
 
+def test_the_native_linear_function_checks_fixed_widths():
+    x, weight = torch.randn(4, 512, device=DEV), torch.randn(3, 512, device=DEV)
+    bits, offsets = torch.full((4,), 2, dtype=torch.uint8, device=DEV), torch.arange(4, device=DEV) * 128
+
+    def forward(bits, offsets):
+        return B.host().linear(x, weight, None, 0, 0x116, 2048, 1, 1, 16, B.ACTQ_HDR_F32, bits, offsets)
+
+    assert torch.equal(forward(bits, offsets), F.linear(x, weight))
+    for wrong, kind in [((bits[:3], offsets), ValueError), ((bits, offsets[:3]), ValueError), ((bits, None), ValueError),
+                        ((bits.int(), offsets), TypeError), ((bits, offsets.int()), TypeError), ((bits.cpu(), offsets), ValueError)]:
+        with pytest.raises(kind):
+            forward(*wrong)
+
+
 def test_the_binding_refuses_wrong_arguments():
     x = torch.randn(4, 512, device=DEV)
     bits, offs = torch.full((4,), 2, dtype=torch.uint8, device=DEV), torch.arange(4, device=DEV) * 128
