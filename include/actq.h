@@ -353,6 +353,27 @@ int actq_maxpool2d_backward(const uint8_t* argmax, const void* grad_y, actq_dtyp
                             int32_t ph, int32_t pw, int32_t dh, int32_t dw, void* grad_x,
                             void* stream);
 
+/*
+ * Gradients of a linear layer y = x weight^T + bias (Sec. 3.2, Eq. (4)), x being
+ * the dequantized context, in one launch:
+ *   grad_x = grad_y weight, grad_w = grad_y^T x, grad_b = column sums of grad_y.
+ * Products and sums are binary32 (of binary16 operands: rounded once at the end),
+ * in a fixed order.
+ *
+ * grad_y  device, in  : [rows, outputs]    weight  device, in : [outputs, inputs]
+ * x       device, in  : [rows, inputs]
+ * grad_x  device, out : [rows, inputs], or NULL (weight may then be NULL)
+ * grad_w  device, out : [outputs, inputs], or NULL (x may then be NULL)
+ * grad_b  device, out : [outputs], or NULL; beside grad_w only
+ * All of one type, contiguous, aligned to their element size.
+ * Errors: ACTQ_EINVAL on a null or misaligned pointer, nothing to compute, rows
+ * outside [1, 2^20], inputs outside [64, 2^20], outputs outside [2, 2^20] or a
+ * tensor of more than 2^29 elements; ACTQ_EHIP if the launch fails.
+ */
+int actq_linear_backward(const void* grad_y, const void* weight, const void* x, actq_dtype dt,
+                         int64_t rows, int64_t inputs, int64_t outputs, void* grad_x,
+                         void* grad_w, void* grad_b, void* stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -29,7 +29,7 @@ EXPORTS = ("actq_version", "actq_source_hash", "actq_last_error", "actq_packed_b
            "actq_quantize_pack", "actq_unpack_dequantize", "actq_sample_sensitivity", "actq_allocate_bits",
            "actq_allocate_bits_device", "actq_relu_mask_bytes", "actq_relu_forward", "actq_relu_backward",
            "actq_pool2d_output_size", "actq_maxpool2d_forward", "actq_maxpool2d_backward", "actq_tensor_stats",
-           "actq_group_stats_multi", "actq_quantize_pack_multi", "actq_unpack_dequantize_multi")
+           "actq_group_stats_multi", "actq_quantize_pack_multi", "actq_unpack_dequantize_multi", "actq_linear_backward")
 
 
 class ActqError(RuntimeError):
@@ -131,6 +131,8 @@ def lib() -> ctypes.CDLL:
     L.actq_maxpool2d_forward.argtypes = [vp, c.c_int, i64] + [i32] * 10 + [vp, vp, vp]
     L.actq_maxpool2d_backward.restype = c.c_int
     L.actq_maxpool2d_backward.argtypes = [vp, vp, c.c_int, i64] + [i32] * 10 + [vp, vp]
+    L.actq_linear_backward.restype = c.c_int
+    L.actq_linear_backward.argtypes = [vp, vp, vp, c.c_int, i64, i64, i64, vp, vp, vp, vp]
     L.actq_allocate_bits_device.restype = c.c_int
     L.actq_allocate_bits_device.argtypes = [vp, vp, i64, i64, i32, i64, c.c_uint32, vp, vp, vp, vp]
     _lib = L
@@ -141,7 +143,7 @@ _host = None
 # the library's entry points that the native module calls, in the order in which it takes their addresses
 _ATTACHED = ("actq_last_error", "actq_group_stats", "actq_sample_sensitivity", "actq_allocate_bits_device", "actq_quantize_pack",
              "actq_unpack_dequantize", "actq_relu_mask_bytes", "actq_relu_forward", "actq_relu_backward", "actq_pool2d_output_size",
-             "actq_maxpool2d_forward", "actq_maxpool2d_backward")
+             "actq_maxpool2d_forward", "actq_maxpool2d_backward", "actq_linear_backward")
 
 
 def host():

@@ -423,4 +423,21 @@ int actq_maxpool2d_backward(const uint8_t* argmax, const void* grad_y, actq_dtyp
     return launch_maxpool2d_backward(argmax, grad_y, dt, planes, p, grad_x, stream);
 }
 
+int actq_linear_backward(const void* grad_y, const void* weight, const void* x, actq_dtype dt, int64_t rows, int64_t inputs,
+                         int64_t outputs, void* grad_x, void* grad_w, void* grad_b, void* stream)
+{
+    const char* who = "actq_linear_backward";
+    if (int rc = check_dtype(who, dt)) return rc;
+    if (!grad_y || (!grad_x && !grad_w) || (grad_x && !weight) || (grad_w && !x)) return fail(ACTQ_EINVAL, "%s: null pointer", who);
+    if (grad_b && !grad_w) return fail(ACTQ_EINVAL, "%s: grad_b comes with grad_w only", who);
+    constexpr int64_t kMost = int64_t(1) << 20;
+    if (rows < 1 || inputs < 64 || outputs < 2 || rows > kMost || inputs > kMost || outputs > kMost || rows * outputs > kMost * 512 ||
+        rows * inputs > kMost * 512 || outputs * inputs > kMost * 512)
+        return fail(ACTQ_EINVAL, "%s: rows, inputs and outputs must be in [1, 2^20], [64, 2^20] and [2, 2^20] and no tensor may have more than 2^29 elements", who);
+    const uintptr_t elem = dt == ACTQ_F32 ? 4 : 2;
+    if (!aligned(grad_y, elem) || !aligned(weight, elem) || !aligned(x, elem) || !aligned(grad_x, elem) || !aligned(grad_w, elem) || !aligned(grad_b, elem))
+        return fail(ACTQ_EINVAL, "%s: tensors must be aligned to their element size", who);
+    return launch_linear_backward(grad_y, weight, x, dt, rows, inputs, outputs, grad_x, grad_w, grad_b, stream);
+}
+
 }  // extern "C"

@@ -100,6 +100,10 @@ int launch_maxpool2d_forward(const void* x, int dtype, int64_t planes, const Poo
 int launch_maxpool2d_backward(const uint8_t* argmax, const void* grad_y, int dtype, int64_t planes,
                               const PoolShape& p, void* grad_x, void* stream);
 
+// Gradients of a linear layer (linear kernels file).
+int launch_linear_backward(const void* grad_y, const void* weight, const void* x, int dtype, int64_t rows, int64_t inputs, int64_t outputs,
+                           void* grad_x, void* grad_w, void* grad_b, void* stream);
+
 }  // namespace actq
 
 #endif

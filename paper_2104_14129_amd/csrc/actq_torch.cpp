@@ -20,6 +20,10 @@
 
 #include <torch/extension.h>
 
+#include <ATen/TensorSubclassLikeUtils.h>
+#include <ATen/autocast_mode.h>
+#include <c10/core/GradMode.h>
+#include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/custom_function.h>
@@ -45,6 +49,7 @@ struct Api {
     decltype(&actq_pool2d_output_size) pool2d_output_size;
     decltype(&actq_maxpool2d_forward) maxpool2d_forward;
     decltype(&actq_maxpool2d_backward) maxpool2d_backward;
+    decltype(&actq_linear_backward) linear_backward;
 };
 Api api = {};
 PyObject* actq_error = nullptr;   // the binding's exception class, called with (code, message)
@@ -617,6 +622,80 @@ ACTQ_ENTRY(maxpool2d_backward, 10)
 using torch::autograd::AutogradContext;
 using torch::autograd::variable_list;
 
+// ----------------------------------------------------------------------------- gradients of a linear layer
+
+struct LinearGradients {
+    Tensor x, weight, bias;   // undefined where none was asked for
+};
+
+// A tensor whose memory is what it says: no mode, transform or subclass looks on, and nothing is applied lazily.
+bool in_memory(const Tensor& t, at::ScalarType type, c10::DeviceIndex device)
+{
+    return t.defined() && !at::isTensorSubclassLike(t) && t.is_cuda() && t.get_device() == device && t.scalar_type() == type && t.layout() == at::kStrided &&
+           t.is_contiguous() && !t.is_neg() && !t._is_zerotensor();
+}
+
+// Whether the library's one launch (actq_linear_backward) takes the place of two products and a sum of torch.  Each of those costs
+// the host 18 us (the sum 5) whatever its size, so the limits are those up to which the launch is no slower on the device, and a little
+// beyond, where the host still is the longer of the two.  Products and sum of torch -> the launch, device time (us), [rows, inputs, outputs]:
+//   binary32  [128, 2048, 1000] 26.0 -> 19.0   [512, 1024, 1000] 36.7 -> 30.9   [1024, 1024, 1024] 50 -> 55   [2048, 1024, 1024] 84 -> 107
+//             [16, 4096, 2048] 27.8 -> 29.2    [2048, 4096, 64] 49 -> 59        [2048, 64, 10] 22.9 -> 21.0
+//   binary16  [128, 2048, 1000] 26.8 -> 8.3    [1024, 1024, 1024] 32 -> 17      [2048, 1024, 1024] 43 -> 32   [2048, 4096, 2048] 99 -> 221
+// Sums over more than 2048 rows or outputs leave too few workgroups with long chains.
+bool one_launch(int64_t rows, int64_t inputs, int64_t outputs, at::ScalarType type)
+{
+    if (rows < 1 || rows > 2048 || outputs < 2 || outputs > 2048 || inputs < 64 || inputs > (int64_t(1) << 20)) return false;
+    return rows * outputs * inputs <= (type == at::kHalf ? int64_t(1) << 31 : int64_t(1) << 30);
+}
+
+// The gradients of y = x weight^T + bias by that launch on the current stream; false, and nothing done, where torch's own operators have
+// to serve: a graph of the gradients themselves, autocast, modes and transforms, operands that differ in type or are not plain memory,
+// sizes beyond the rule.  `x` is asked for only once all else is settled.
+template <typename X>
+bool fused_gradients(const Tensor& grad_y, const Tensor& weight, X x_of, at::ScalarType type, int64_t inputs, bool need_x, bool need_weight, bool need_bias,
+                     LinearGradients& out)
+{
+    if (c10::GradMode::is_enabled() || at::autocast::is_autocast_enabled(at::kCUDA) || (!need_x && !need_weight)) return false;
+    if (need_bias && !need_weight) return false;
+    const c10::DeviceIndex device = c10::hip::current_device();
+    if ((type != at::kFloat && type != at::kHalf) || !in_memory(grad_y, type, device) || !in_memory(weight, type, device)) return false;
+    if (grad_y.dim() < 1 || grad_y.numel() == 0 || weight.dim() != 2 || weight.size(0) != grad_y.size(-1) || weight.size(1) != inputs) return false;
+    const int64_t outputs = weight.size(0), rows = grad_y.numel() / outputs;
+    if (!one_launch(rows, inputs, outputs, type)) return false;
+    Tensor x;
+    if (need_weight) {
+        x = x_of();
+        if (!in_memory(x, type, device) || x.numel() != rows * inputs) return false;
+        out.weight = empty_on(weight, {outputs, inputs}, type);
+        if (need_bias) out.bias = empty_on(weight, {outputs}, type);
+    }
+    if (need_x) {
+        std::vector<int64_t> shape = grad_y.sizes().vec();
+        shape.back() = inputs;
+        out.x = empty_on(grad_y, shape, type);
+    }
+    const auto pointer = [](const Tensor& t) { return t.defined() ? t.data_ptr() : nullptr; };
+    call(api.linear_backward, pointer(grad_y), pointer(weight), pointer(x), dtype_of(grad_y), rows, inputs, outputs, pointer(out.x), pointer(out.weight),
+         pointer(out.bias), current_stream());
+    return true;
+}
+
+// (grad_y, weight, x, whether x, weight, bias need theirs) -> their gradients (None where none is needed), or None if torch's operators have to serve
+PyObject* linear_gradients_impl(PyObject* const* a)
+{
+    const Tensor &grad_y = tensor_of(a[0], "grad_y"), &weight = tensor_of(a[1], "weight"), &x = tensor_of(a[2], "x");
+    LinearGradients g;
+    if (x.dim() < 1 || !fused_gradients(grad_y, weight, [&] { return x; }, x.scalar_type(), x.size(-1), a[3] == Py_True, a[4] == Py_True, a[5] == Py_True, g))
+        Py_RETURN_NONE;
+    const auto wrap = [](const Tensor& t) {
+        if (t.defined()) return THPVariable_Wrap(t);
+        Py_INCREF(Py_None);
+        return Py_None;
+    };
+    return tuple_of({wrap(g.x), wrap(g.weight), wrap(g.bias)});
+}
+ACTQ_ENTRY(linear_gradients, 6)
+
 // The activation-compressed linear layer: the saved input is the compressed one.
 struct LinearFn : torch::autograd::Function<LinearFn> {
     static Tensor forward(AutogradContext* ctx, const Tensor& x, const Tensor& weight, const std::optional<Tensor>& bias, const Config& config)
@@ -641,15 +720,23 @@ struct LinearFn : torch::autograd::Function<LinearFn> {
         // under autocast the output (and so grad_y) is narrower than the saved input and the weight: the stock backward
         // then computes in grad_y's type and returns gradients of the operands' types
         const at::ScalarType ct = grad_y.scalar_type();
+        const bool need_bias = ctx->saved_data["bias"].toBool() && ctx->needs_input_grad(2);
+        Tensor x;
+        const auto decompressed = [&] {
+            if (!x.defined()) {
+                x = empty_on(bits, shape, type);
+                decompress(packed, header, bits, offsets, x, view_of(x), kG, hf, nullptr);
+            }
+            return x;
+        };
+        LinearGradients g;
+        if (fused_gradients(grad_y, weight, decompressed, type, shape.back(), ctx->needs_input_grad(0), ctx->needs_input_grad(1), need_bias, g))
+            return {g.x, g.weight, g.bias, Tensor()};
         const Tensor g2 = grad_y.reshape({-1, grad_y.size(-1)});
         Tensor grad_x, grad_w, grad_b;
         if (ctx->needs_input_grad(0)) grad_x = grad_y.matmul(weight.to(ct)).to(type);
-        if (ctx->needs_input_grad(1)) {
-            const Tensor x = empty_on(bits, shape, type);
-            decompress(packed, header, bits, offsets, x, view_of(x), kG, hf, nullptr);
-            grad_w = g2.t().matmul(x.reshape({-1, shape.back()}).to(ct)).to(weight.scalar_type());
-        }
-        if (ctx->saved_data["bias"].toBool() && ctx->needs_input_grad(2)) grad_b = g2.sum(0).to(weight.scalar_type());
+        if (ctx->needs_input_grad(1)) grad_w = g2.t().matmul(decompressed().reshape({-1, shape.back()}).to(ct)).to(weight.scalar_type());
+        if (need_bias) grad_b = g2.sum(0).to(weight.scalar_type());
         return {grad_x, grad_w, grad_b, Tensor()};
     }
 };
@@ -781,7 +868,7 @@ ACTQ_ENTRY(attach, 2)
 PyMethodDef methods[] = {
     ACTQ_METHOD(attach), ACTQ_METHOD(plain), ACTQ_METHOD(group_stats), ACTQ_METHOD(sample_sensitivity), ACTQ_METHOD(allocate_bits_device),
     ACTQ_METHOD(quantize_pack), ACTQ_METHOD(unpack_dequantize), ACTQ_METHOD(compress_mixed), ACTQ_METHOD(relu_forward), ACTQ_METHOD(relu_backward),
-    ACTQ_METHOD(maxpool2d_forward), ACTQ_METHOD(maxpool2d_backward), ACTQ_METHOD(linear), ACTQ_METHOD(relu), ACTQ_METHOD(maxpool2d),
+    ACTQ_METHOD(maxpool2d_forward), ACTQ_METHOD(maxpool2d_backward), ACTQ_METHOD(linear_gradients), ACTQ_METHOD(linear), ACTQ_METHOD(relu), ACTQ_METHOD(maxpool2d),
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "actq_torch", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

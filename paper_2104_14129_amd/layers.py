@@ -8,7 +8,8 @@ stock layer, so inference is unchanged.
 Everything that touches the saved activations runs in libactq through `binding`: per-group
 statistics, sensitivities, the device-side bit allocator, quantize + pack, unpack + dequantize,
 the ReLU bit mask and the max-pooling positions.  torch supplies the layers' own arithmetic
-(GEMM, convolution and batch-norm forward / backward) and the autograd plumbing.  There is no
+(GEMM, convolution and batch-norm forward / backward) and the autograd plumbing; the gradients of
+a linear layer of up to a few billion products are one launch of the library.  There is no
 CPU path: tensors must live on the GPU.
 """
 from __future__ import annotations
@@ -214,13 +215,18 @@ class _QLinearFn(torch.autograd.Function):
     @staticmethod
     def backward(ctx, grad_y):
         x, (weight,) = _recall(ctx)
+        need_x, need_w, need_b = ctx.needs_input_grad[0], ctx.needs_input_grad[1], ctx.has_bias and ctx.needs_input_grad[2]
+        if not torch.compiler.is_compiling() and B.host().plain(grad_y, weight, x):
+            gradients = B.host().linear_gradients(grad_y, weight, x, need_x, need_w, need_b)   # the same launch as in the native function
+            if gradients is not None:
+                return gradients
         # under autocast the output (and so grad_y) is narrower than the saved input and the weight:
         # the stock backward then computes in grad_y's type and returns gradients of the operands' types
         g2 = grad_y.reshape(-1, grad_y.shape[-1])
-        grad_x = grad_y.matmul(weight.to(grad_y.dtype)).to(x.dtype) if ctx.needs_input_grad[0] else None
+        grad_x = grad_y.matmul(weight.to(grad_y.dtype)).to(x.dtype) if need_x else None
         grad_w = (g2.t().matmul(x.reshape(-1, x.shape[-1]).to(grad_y.dtype)).to(weight.dtype)
-                  if ctx.needs_input_grad[1] else None)
-        grad_b = g2.sum(0).to(weight.dtype) if ctx.has_bias and ctx.needs_input_grad[2] else None
+                  if need_w else None)
+        grad_b = g2.sum(0).to(weight.dtype) if need_b else None
         return grad_x, grad_w, grad_b
 
 

@@ -1,0 +1,120 @@
+"""The gradients of a linear layer in one launch (actq_linear_backward): against 64-bit products at the edges of its tiles and chunks,
+and the calls of the layer that torch's own operators have to serve."""
+import ctypes
+
+import pytest
+import torch
+import torch.nn.functional as F
+
+from paper_2104_14129_amd import binding as B
+from paper_2104_14129_amd import layers as L
+
+DEV = "cuda:0"
+FAKE = 0x1000
+
+
+def test_arguments_are_checked_before_the_launch():
+    f = B.lib().actq_linear_backward
+    good = [FAKE, FAKE, FAKE, 0, 4, 64, 2, FAKE, FAKE, FAKE, None]
+    for change in ({0: None}, {7: None, 8: None, 9: None}, {1: None}, {2: None}, {8: None}, {3: 2}, {0: FAKE + 2}, {3: 1, 9: FAKE + 1}, {4: 0}, {5: 63},
+                   {6: 1}, {4: (1 << 20) + 1}, {4: 1 << 20, 5: 1024}, {5: 1 << 20, 6: 1024}, {4: 1 << 20, 6: 1024}):
+        assert f(*[change.get(i, v) for i, v in enumerate(good)]) == B.ACTQ_EINVAL, change
+
+
+@pytest.fixture(autouse=True)
+def restore():
+    saved = dict(L.config.__dict__)
+    yield
+    L.config.__dict__.update(saved)
+
+
+def _canary(shape, dtype):
+    n = torch.Size(shape).numel()
+    buf = torch.full((n + 64,), 7.0, dtype=dtype, device=DEV)
+    return buf, buf[:n].view(shape)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("rows,inputs,outputs", [(1, 64, 2), (2, 65, 3), (15, 127, 31), (17, 128, 32), (31, 129, 33), (33, 200, 63), (64, 64, 65), (127, 333, 10),
+                                                 (129, 1030, 97), (300, 67, 515), (2048, 64, 2), (5, 96, 2048)])
+def test_gradients_against_64_bits(rows, inputs, outputs, dtype):
+    g = torch.Generator(device=DEV).manual_seed(rows * 7 + outputs)
+    # an element's alignment is all that is asked for
+    def operand(*shape):
+        t = torch.randn(torch.Size(shape).numel() + 1, generator=g, device=DEV).to(dtype)[1:]
+        return t.view(shape)
+    grad_y, weight, x = operand(rows, outputs), operand(outputs, inputs), operand(rows, inputs)
+    (bx, gx), (bw, gw), (bb, gb) = _canary((rows, inputs), dtype), _canary((outputs, inputs), dtype), _canary((outputs,), dtype)
+    rc = B.lib().actq_linear_backward(grad_y.data_ptr(), weight.data_ptr(), x.data_ptr(), B.ACTQ_F32 if dtype == torch.float32 else B.ACTQ_F16, rows, inputs,
+                                      outputs, gx.data_ptr(), gw.data_ptr(), gb.data_ptr(), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == B.ACTQ_OK, B.last_error()
+    G, W, X = grad_y.double(), weight.double(), x.double()
+    for got, want, size, terms in ((gx, G @ W, G.abs() @ W.abs(), outputs), (gw, G.t() @ X, G.t().abs() @ X.abs(), rows), (gb, G.sum(0), G.abs().sum(0), rows)):
+        # a sum of n rounded products in any order: n 2^-24 of the sum of magnitudes; binary16: the last rounding on top
+        bound = (terms + 2) * 2.0 ** -24 * size + (want.abs() * 2.0 ** -11 + 2.0 ** -25 if dtype == torch.float16 else 0.0) + 1e-30
+        assert ((got.double() - want).abs() <= bound).all()
+    for buf, n in ((bx, rows * inputs), (bw, outputs * inputs), (bb, outputs)):
+        assert (buf[n:] == 7.0).all(), "wrote past an output"
+    # each product by itself, the other's operand absent
+    gx2, gw2 = torch.empty_like(gx), torch.empty_like(gw)
+    code, s = B.ACTQ_F32 if dtype == torch.float32 else B.ACTQ_F16, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert B.lib().actq_linear_backward(grad_y.data_ptr(), weight.data_ptr(), None, code, rows, inputs, outputs, gx2.data_ptr(), None, None, s) == B.ACTQ_OK
+    assert B.lib().actq_linear_backward(grad_y.data_ptr(), None, x.data_ptr(), code, rows, inputs, outputs, None, gw2.data_ptr(), None, s) == B.ACTQ_OK
+    assert torch.equal(gx, gx2) and torch.equal(gw, gw2)
+
+
+@pytest.mark.gpu
+def test_infinities_and_nan_reach_exactly_the_gradients_they_belong_to():
+    grad_y, weight, x = (torch.ones(s, device=DEV) for s in ((40, 35), (35, 70), (40, 70)))
+    grad_y[39, 34], x[3, 69] = float("inf"), float("nan")
+    with torch.no_grad():
+        gx, gw, gb = B.host().linear_gradients(grad_y, weight, x, True, True, True)
+    want = grad_y @ weight, grad_y.t().contiguous() @ x, grad_y.sum(0)
+    for got, stock in zip((gx, gw, gb), want):
+        assert torch.equal(torch.nan_to_num(got, 1e6, 2e6, 3e6), torch.nan_to_num(stock, 1e6, 2e6, 3e6))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("native", [True, False])
+@pytest.mark.parametrize("what", ["graph of the gradients", "expanded", "vmap", "autocast", "weight frozen", "bias only", "too narrow", "many rows", "three dimensions"])
+def test_calls_beyond_the_launch_are_served_as_before(what, native, monkeypatch):
+    """Against the stock layer on the dequantized input (fixed widths of eight bits of values that they represent)."""
+    monkeypatch.setattr(L, "_native", (lambda *t: True) if native else (lambda *t: False))
+    L.config.mixed, L.config.bits = False, 8.0
+    rows, inputs, outputs = (2049 if what == "many rows" else 12), (33 if what == "too narrow" else 256), 6
+    m = L.QLinear(inputs, outputs, device=DEV)
+    shape = (rows, 2, inputs) if what == "three dimensions" else (rows, inputs)
+    x = torch.randint(0, 256, shape, device=DEV).float()
+    x[..., 0], x[..., 1] = 0.0, 255.0          # every group spans 0 .. 255: the codes are the values
+    x.requires_grad_()
+    if what == "weight frozen":
+        m.weight.requires_grad_(False)
+        m.bias.requires_grad_(False)
+    if what == "bias only":
+        m.weight.requires_grad_(False)
+        x = x.detach()
+    stock = lambda x: F.linear(x, m.weight, m.bias)
+    inputs_of = [t for t in (x, m.weight, m.bias) if t.requires_grad]
+    results = []
+    for f in (m, stock):
+        if what == "autocast":
+            with torch.autocast("cuda", dtype=torch.float16):
+                y = f(x)
+                results.append(torch.autograd.grad(y.float().sum(), inputs_of))
+        elif what == "graph of the gradients":
+            y = f(x)
+            (gx,) = torch.autograd.grad(y, x, torch.ones_like(y), create_graph=True)
+            results.append([gx.detach(), *torch.autograd.grad(gx.square().sum(), m.weight)])
+        elif what == "vmap":
+            y = f(x)
+            basis = torch.eye(3, device=DEV)[:, :, None, None].expand(3, 3, *y.shape)[:, 0].contiguous()
+            results.append(torch.autograd.grad(y, inputs_of, basis, is_grads_batched=True))
+        elif what == "expanded":
+            results.append(torch.autograd.grad(f(x).sum(), inputs_of))
+        else:
+            y = f(x)
+            results.append(torch.autograd.grad(y, inputs_of, torch.linspace(-1, 1, y.numel(), device=DEV).reshape(y.shape)))
+    for a, b in zip(*results):
+        assert a.shape == b.shape and a.dtype == b.dtype
+        assert torch.allclose(a, b, rtol=1e-4 if a.dtype == torch.float32 and what != "autocast" else 1e-2, atol=1e-4 * float(b.abs().max()))
