@@ -1598,6 +1598,8 @@ constexpr int kAllocList = 1024;      // items with undecided steps the large ke
 // turn: each item is tested by itself then.  Log-normal sensitivities, all listed -> tested (us): 150,000 with all widths 400 -> 248 where the
 // list overflows and 214 -> 230 where it does not, 200,000 490 -> 302, 400,000 with {1, 2, 4, 8} 965 -> 594.
 constexpr int64_t kAllocFilter = 131072;
+constexpr int kSearchRounds = 5;      // of the large kernel's search over its table, at most
+constexpr int kSearchWaves = 8;       // wavefronts that search, eight prices each [16: slower, they share the SIMDs]
 constexpr int kAllocQuads = 4;        // quadruples of consecutive items per thread kept in registers: 16,384 items in all
 
 // What the budget is compared with.
@@ -1874,11 +1876,16 @@ __device__ Threshold select_price(const Each& each, uint64_t n, uint64_t lo, uin
 }
 
 // The sensitivity finite and not negative (see valid_sensitivity_bits), 0 < D < 2^34.
-__device__ __forceinline__ bool valid_item(float w, int64_t D)
+__device__ __forceinline__ bool valid_weight(float w)
 {
     constexpr int kZeroOrPositive = 0x1E0;   // either zero, positive subnormal, positive normal
+    return __builtin_amdgcn_classf(w, kZeroOrPositive);
+}
+
+__device__ __forceinline__ bool valid_item(float w, int64_t D)
+{
     const uint32_t low = static_cast<uint32_t>(D), high = static_cast<uint32_t>(static_cast<uint64_t>(D) >> 32);
-    return __builtin_amdgcn_classf(w, kZeroOrPositive) & (high < 4u) & ((low | high) != 0u);
+    return valid_weight(w) & (high < 4u) & ((low | high) != 0u);
 }
 
 __device__ __forceinline__ uint64_t stream_bytes(int64_t D, int width)
@@ -2246,14 +2253,21 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_small_kernel(const 
 // Upper 32 bits of the binary64 pattern of w / D, one unit off at most: the reciprocal of D in binary32
 // (relative error below 2^-22 with the rounding of D) is four times finer than a unit, and costs a
 // tenth of a binary64 division.  A valid sensitivity is not negative; -0.0 counts as 0.
-__device__ __forceinline__ uint32_t ratio_of(float w, int64_t D)
+__device__ __forceinline__ double reciprocal_of(int64_t D)
 {
     uint32_t low = static_cast<uint32_t>(D), high = static_cast<uint32_t>(static_cast<uint64_t>(D) >> 32);
     asm("" : "+v"(low), "+v"(high));   // two words to the compiler, which makes one long conversion of the 64 bits
     const float d = __builtin_fmaf(static_cast<float>(high), 4294967296.0f, static_cast<float>(low));
-    const double q = static_cast<double>(w) * static_cast<double>(__builtin_amdgcn_rcpf(d));
+    return static_cast<double>(__builtin_amdgcn_rcpf(d));
+}
+
+__device__ __forceinline__ uint32_t ratio_by(float w, double reciprocal)
+{
+    const double q = static_cast<double>(w) * reciprocal;
     return static_cast<uint32_t>(static_cast<uint64_t>(__double_as_longlong(q)) >> 32) & 0x7fffffffu;
 }
+
+__device__ __forceinline__ uint32_t ratio_of(float w, int64_t D) { return ratio_by(w, reciprocal_of(D)); }
 
 // Upper 32 bits of (price with the upper 32 bits `t` and zeros below) / c_r.
 __device__ __forceinline__ uint32_t ratio_at(uint64_t price, double inverse)
@@ -2310,10 +2324,14 @@ typedef int64_t i64x4_a8 __attribute__((ext_vector_type(4), aligned(8)));
 // The items in a bin with undecided steps are listed, one per thread, and from there on they are the small kernel's problem:
 // exact prices in registers, a histogram over the bracket, the bin that holds the threshold, its few moves ranked.  More of
 // them than the list holds are priced again in every turn of select_price, which the ties end.
-// 2049 items of the ResNet-50's sizes with all widths 23.1 -> 14.4 us, 13,568 29.5 -> 19.8 ({1, 2, 4, 8}: 27.1 -> 19.1), 40,960
-// 82.2 -> 57.9; 13,568 of sensitivity one 43.7 -> 42.8, of zero 126 -> 119.  Before: the undecided moves walked and priced by the
-// threads that hold their items, minima, maxima and three barriers more around a histogram of theirs, the table in 64 bits
-// (an LDS addition of 64 bits takes twice as long), the bins classified a second time, every round's work done for M items or 16,384.
+// What bounds it is instructions: sixteen wavefronts share four SIMDs, so a phase costs four times the instructions of one wavefront,
+// whether they do different work or the same.  Hence items of one size in a row are looked at together, sums are in 32 bits where
+// they fit, the search gives a lane a price and a step (one wavefront with the steps one behind the other: 4.8 -> 3.2 thousand
+// cycles), bins are classified by scalar comparisons (3.9 -> 1.9), a list takes one LDS operation per wavefront, and the bin and the rank of the
+// threshold are found by one wavefront for all (6.8 -> 4.4).  Thousands of cycles of 34 for 13,568 items with all widths: loads 2.4, ratios and totals 6.6,
+// table 3.2, prefix sums 1.1, search 3.2, bins 1.9, list 3.4, exact prices 2.4, threshold 4.4, units and scan 3.4, stores 2.
+// 2049 items of the ResNet-50's sizes with all widths 14.1 -> 12.5 us, 13,568 19.5 -> 16.1 ({1, 2, 4, 8}: 18.7 -> 15.7; sizes drawn at random 21.0 -> 18.3),
+// 40,960 59.1 -> 53.4, 150,000 240 -> 228; 13,568 of sensitivity one 42.4 -> 34.2, of zero 118 -> 112; none of 828 problems slower.
 __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float* __restrict__ w, AllocArgs a,
                                                                     uint8_t* __restrict__ bits,
                                                                     uint64_t* __restrict__ offsets,
@@ -2330,16 +2348,22 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
     __shared__ uint64_t rank_key[kWave], rank_amount[kWave];
     __shared__ SelectLds sel;
     __shared__ uint64_t wave_a[kAllocWavesMax], wave_b[kAllocWavesMax], wave_c[kAllocWavesMax];
-    __shared__ uint32_t wave_lo[kAllocWavesMax], wave_hi[kAllocWavesMax], wave_or[kAllocWavesMax], wave_scan[kAllocWavesMax];
+    __shared__ uint32_t wave_scan[kAllocWavesMax];
     __shared__ uint64_t wave_round[2][kAllocWavesMax], wave_bytes[kAllocQuads * kAllocWavesMax];
     __shared__ uint32_t list_count, rank_count;       // items: fewer than 2^31
     __shared__ uint64_t move_count;                   // moves: up to 7 * 2^31
-    __shared__ uint32_t bracket_lo, bracket_hi;
+    __shared__ uint32_t wave_lo[kAllocWavesMax], wave_hi[kAllocWavesMax], wave_or[kAllocWavesMax];
+    __shared__ uint64_t all_cheaper;
+    __shared__ uint32_t last_short[kSearchRounds], first_enough[kSearchRounds];
+    __shared__ Threshold found;                       // by one wavefront for all: sixteen that do the same take turns on four SIMDs
+    __shared__ uint32_t found_digit;
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int waves = kAllocWavesMax;
     const int steps = a.lad.count - 1;
     const int64_t M = a.M;
+    // the lines of the arguments that the search needs are on their way before it
+    asm volatile("" : : "s"(a.lad.price[0]), "s"(a.inverse[0]));
     const auto item = [&](int j) { return (j / kQ) * kRound + tid * kQ + j % kQ; };
     const auto elements = [&](int64_t i) { return a.D_items ? a.D_items[i] : a.D; };
 
@@ -2368,6 +2392,11 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
         list_count = 0;
         rank_count = 0;
         move_count = 0;
+        all_cheaper = 0;
+    }
+    if (tid < kSearchRounds) {
+        last_short[tid] = 0;
+        first_enough[tid] = ~0u;
     }
 #pragma unroll
     for (int k = 0; k < kAllocQuads; ++k) {
@@ -2399,6 +2428,7 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
         all_sizes |= static_cast<uint32_t>(Di);
         return counted;
     };
+    uint32_t alike_rounds = 0;   // quadruples of one size in the whole wavefront
     // rounds in which this wavefront has items: the others cost it nothing
     const auto in_round = [&](int k) { return k * kRound + wave * (kWave * kQ) < M; };
 #pragma unroll
@@ -2409,6 +2439,27 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
                 ratio[j] = kNone;
                 size[j] = 0;
             }
+            continue;
+        }
+        // Quadruples of one size in the whole wavefront (a layer's samples are neighbours): the size is looked at once
+        // (four items 108 -> 52 instructions, the bound of this phase: one compute unit issues for all of them).  An invalid item
+        // keeps its size here: it leaves the kernel no search that could use it.
+        const int64_t D = size[k * kQ];
+        const bool alike = size[k * kQ + 1] == D && size[k * kQ + 2] == D && size[k * kQ + 3] == D && item(k * kQ) + kQ <= M;
+        if (__all(alike)) {
+            const bool size_ok = valid_item(1.0f, D);
+            const double reciprocal = reciprocal_of(D);
+#pragma unroll
+            for (int j = k * kQ; j < (k + 1) * kQ; ++j) {
+                const uint32_t u = ratio_by(weight[j], reciprocal), less1 = u - 1u;
+                const uint32_t top = valid_weight(weight[j]) & size_ok ? u : 0x80000000u;
+                lo_less1 = less1 < lo_less1 ? less1 : lo_less1;
+                hi_ratio = top > hi_ratio ? top : hi_ratio;
+                ratio[j] = u;
+            }
+            my_elems += static_cast<uint64_t>(D) * kQ;
+            all_sizes |= static_cast<uint32_t>(D);
+            alike_rounds |= 1u << k;
             continue;
         }
 #pragma unroll
@@ -2462,6 +2513,8 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
     // 2^scale divides every size
     const int scale = sizes ? __builtin_ctz(sizes) : 31;
     const bool narrow = (elems >> scale) >> 32 == 0;
+    // and sums of freed bits are below 2^32 in these units: fewer than eight bits per element
+    const bool short_sums = (elems >> scale) >> 29 == 0;
     uint32_t* const table32 = reinterpret_cast<uint32_t*>(table);
 
     Threshold t = {0, 0, 0};
@@ -2471,8 +2524,10 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
     int shift = span ? 32 - __builtin_clz(span) - 12 : 0;
     shift = shift > 0 ? shift : 0;
     if ((span >> shift) > static_cast<uint32_t>(kAllocBins - 2)) ++shift;
+    // a positive ratio is 2^-183 at least, its pattern far above the 2^20 that a bin holds at most
+    const uint32_t origin = first_ratio - (1u << shift);
     const auto bin_of = [&](uint32_t u) {   // an empty slot's ratio gives some bin, too
-        const uint32_t bin = u == 0 ? 0u : 1u + ((u - first_ratio) >> shift);
+        const uint32_t bin = __builtin_elementwise_sub_sat(u, origin) >> shift;
         return bin < static_cast<uint32_t>(kAllocBins) ? bin : static_cast<uint32_t>(kAllocBins - 1);
     };
     const auto class_of = [&](uint32_t bin) { return static_cast<uint32_t>(reinterpret_cast<const uint8_t*>(step_class)[bin]); };
@@ -2481,7 +2536,7 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
     uint64_t rungs = 0, tied = 0;
     if (v.search) {
         const auto add_item = [&](uint32_t bin, int64_t D) {
-            if (narrow) __hip_atomic_fetch_add(&table32[bin], static_cast<uint32_t>(static_cast<uint64_t>(D) >> scale), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (narrow) __hip_atomic_fetch_add(&table32[bin], __builtin_amdgcn_alignbit(static_cast<uint32_t>(static_cast<uint64_t>(D) >> 32), static_cast<uint32_t>(D), scale), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             else __hip_atomic_fetch_add(&table[bin], static_cast<uint64_t>(D), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         };
 #pragma unroll
@@ -2490,7 +2545,7 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
 #pragma unroll
             for (int j = k * kQ; j < (k + 1) * kQ; ++j) {
                 ratio[j] = bin_of(ratio[j]);   // bins from here on
-                if (size[j] != 0) add_item(ratio[j], size[j]);
+                add_item(ratio[j], size[j]);         // an empty slot adds nothing
             }
         }
         further([&](int64_t, float wi, int64_t Di) { add_item(bin_of(ratio_of(wi, Di)), Di); });
@@ -2513,87 +2568,87 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
         else to_prefix(table, wave_round[0]);
         __syncthreads();
 
-        // ---- the bracket: wavefront 0 evaluates both bounds of the bits freed below 64 prices at a time
-        if (wave == 0) {
+        // ---- the bracket: both bounds of the bits freed below 64 prices at a time, eight per wavefront, a lane per price and step
+        // lane r of eight: step r
+        double inverse = 0.0;
+        uint32_t dw = 0;
+#pragma unroll
+        for (int r = 0; r < kMaxSteps; ++r) {
+            inverse = (lane & 7) == r ? a.inverse[r] : inverse;
+            dw = (lane & 7) == r && r < steps ? static_cast<uint32_t>(a.lad.width[r] - a.lad.width[r + 1]) : dw;
+        }
+        {
             // price patterns' upper halves; nothing positive is cheaper than `start`, nothing is dearer than `end`
             const uint64_t lowest = static_cast<uint64_t>(first_ratio) << 32, highest = static_cast<uint64_t>(last_ratio + 1) << 32;
             const uint32_t p_lo = static_cast<uint32_t>(static_cast<uint64_t>(__double_as_longlong(__longlong_as_double(static_cast<long long>(lowest)) * a.lad.price[0])) >> 32);
             const uint32_t p_hi = static_cast<uint32_t>(static_cast<uint64_t>(__double_as_longlong(__longlong_as_double(static_cast<long long>(highest)) * ladder_price(a.lad, steps - 1))) >> 32);
             const uint32_t start = last_ratio ? (p_lo > 4u ? p_lo - 4u : 0u) : 0u, end = last_ratio ? p_hi + 4u : 4u;
+            const uint32_t candidate = static_cast<uint32_t>(8 * wave + (lane >> 3));
+            const auto price_at = [](uint32_t from, uint32_t width, uint32_t k) {
+                return from + static_cast<uint32_t>(static_cast<uint64_t>(width) * k >> 6);
+            };
             uint32_t lo = 0, hi = end, left = start, right = end;
-            for (int round = 0; round < 4; ++round) {
+            for (int round = 0; round < kSearchRounds; ++round) {
                 const uint32_t width = right - left;
-                const uint32_t p = left + static_cast<uint32_t>(static_cast<uint64_t>(width) * static_cast<uint32_t>(lane) / 63u);
-                uint64_t most = 0, least = 0;   // bits freed by the moves cheaper than p: upper and lower bound
-                const auto add_steps = [&](auto from, auto to) {   // the look-ups of all these steps are in flight together
-                    uint32_t b_least[kMaxSteps], b_most[kMaxSteps];
-#pragma unroll
-                    for (int r = from; r < to; ++r) {
-                        const uint32_t u = ratio_at(static_cast<uint64_t>(p) << 32, a.inverse[r]);   // 0 for a step that does not exist
-                        // items of ratio < u - 2 only: whole bins before the one that holds it
-                        const uint32_t x = u > 2u ? u - 2u : 0u;
-                        const uint32_t bl = x <= first_ratio ? 1u : 1u + ((x - first_ratio) >> shift);
-                        b_least[r] = x == 0 ? 0u : (bl < static_cast<uint32_t>(kAllocBins) ? bl : static_cast<uint32_t>(kAllocBins));
-                        // every item of ratio <= u + 2: whole bins up to the one that holds it
-                        const uint32_t y = u + 2u;
-                        const uint32_t bm = y < first_ratio ? 1u : 2u + ((y - first_ratio) >> shift);
-                        b_most[r] = bm < static_cast<uint32_t>(kAllocBins) ? bm : static_cast<uint32_t>(kAllocBins);
+                if (wave < kSearchWaves) {
+                    const uint32_t u = ratio_at(static_cast<uint64_t>(price_at(left, width, candidate)) << 32, inverse);   // 0 for a step that does not exist
+                    // items of ratio < u - 2 only: whole bins before the one that holds it
+                    const uint32_t x = u > 2u ? u - 2u : 0u;
+                    const uint32_t bl = x <= first_ratio ? 1u : 1u + ((x - first_ratio) >> shift);
+                    const uint32_t b_least = x == 0 ? 0u : (bl < static_cast<uint32_t>(kAllocBins) ? bl : static_cast<uint32_t>(kAllocBins));
+                    // every item of ratio <= u + 2: whole bins up to the one that holds it
+                    const uint32_t y = u + 2u;
+                    const uint32_t bm = y < first_ratio ? 1u : 2u + ((y - first_ratio) >> shift);
+                    const uint32_t b_most = bm < static_cast<uint32_t>(kAllocBins) ? bm : static_cast<uint32_t>(kAllocBins);
+                    // bits freed by the moves cheaper than the price: lower and upper bound, over the steps; lanes whose price is too low and high enough
+                    uint64_t not_yet, enough;
+                    if (short_sums) {
+                        uint32_t least = dw * table32[b_least], most = dw * table32[b_most];
+                        least += dpp_u32<kDppXor1>(least);
+                        most += dpp_u32<kDppXor1>(most);
+                        least += dpp_u32<kDppXor2>(least);
+                        most += dpp_u32<kDppXor2>(most);
+                        least += dpp_u32<kDppHalfMirror>(least);
+                        most += dpp_u32<kDppHalfMirror>(most);
+                        const uint32_t need = static_cast<uint32_t>((v.need + ((uint64_t(1) << scale) - 1)) >> scale);
+                        not_yet = __ballot(most < need);
+                        enough = __ballot(least >= need);
+                    } else {
+                        uint64_t least = static_cast<uint64_t>(dw) * (narrow ? static_cast<uint64_t>(table32[b_least]) << scale : table[b_least]);
+                        uint64_t most = static_cast<uint64_t>(dw) * (narrow ? static_cast<uint64_t>(table32[b_most]) << scale : table[b_most]);
+                        least += dpp_u64<kDppXor1>(least);
+                        most += dpp_u64<kDppXor1>(most);
+                        least += dpp_u64<kDppXor2>(least);
+                        most += dpp_u64<kDppXor2>(most);
+                        least += dpp_u64<kDppHalfMirror>(least);
+                        most += dpp_u64<kDppHalfMirror>(most);
+                        not_yet = __ballot(most < v.need);
+                        enough = __ballot(least >= v.need);
                     }
-                    const auto look_up = [&](const auto* entry) {
-                        typedef typename std::remove_const<typename std::remove_reference<decltype(*entry)>::type>::type V;
-                        V e_least[kMaxSteps], e_most[kMaxSteps];
-#pragma unroll
-                        for (int r = from; r < to; ++r) {
-                            e_least[r] = entry[b_least[r]];
-                            e_most[r] = entry[b_most[r]];
-                        }
-#pragma unroll
-                        for (int r = from; r < to; ++r) {
-                            const uint32_t dw = static_cast<uint32_t>(a.lad.width[r] - a.lad.width[r + 1]);
-                            const uint32_t counted = r < steps ? dw : 0u;
-                            least += static_cast<uint64_t>(counted) * e_least[r];
-                            most += static_cast<uint64_t>(counted) * e_most[r];
-                        }
-                    };
-                    if (narrow) look_up(table32);
-                    else look_up(table);
-                };
-                add_steps(std::integral_constant<int, 0>(), std::integral_constant<int, 3>());
-                if (steps > 3) add_steps(std::integral_constant<int, 3>(), std::integral_constant<int, kMaxSteps>());
-                if (narrow) {
-                    least <<= scale;
-                    most <<= scale;
+                    if (lane == 0) {
+                        if (not_yet) __hip_atomic_fetch_max(&last_short[round], 1u + 8u * wave + static_cast<uint32_t>(63 - __builtin_clzll(not_yet)) / 8u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        if (enough) __hip_atomic_fetch_min(&first_enough[round], 8u * wave + static_cast<uint32_t>(__builtin_ctzll(enough)) / 8u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
                 }
-                const uint64_t not_yet = __ballot(most < v.need), enough = __ballot(least >= v.need);
-                if (not_yet) lo = left + static_cast<uint32_t>(static_cast<uint64_t>(width) * static_cast<uint32_t>(63 - __builtin_clzll(not_yet)) / 63u);
-                if (enough) hi = left + static_cast<uint32_t>(static_cast<uint64_t>(width) * static_cast<uint32_t>(__builtin_ctzll(enough)) / 63u);
+                __syncthreads();
+                const uint32_t before = read_lane(last_short[round], 0), from = read_lane(first_enough[round], 0);
+                if (before != 0) lo = price_at(left, width, before - 1u);
+                if (from != ~0u) hi = price_at(left, width, from);
                 left = lo > start ? lo : start;
                 right = hi;
-                // finer than a bin the table cannot tell
-                if (((right - left) >> shift) == 0u || right - left > width / 2u) break;
+                // Finer than a bin the table cannot tell.  With few items per bin the turn that would leave one bin instead of four costs more
+                // than their items; with many the list would not hold them (150,000 items 240 -> 455 us).
+                if (((right - left) >> shift) < (M <= kAllocQuads * kRound ? 4u : 1u) || right - left > width / 2u) break;
             }
-            if (lane == 0) {
-                bracket_lo = lo;
-                bracket_hi = hi;
-            }
+            price_lo = lo;
+            price_hi = hi;
         }
-        __syncthreads();
 
         // ---- what the bracket decides, per bin
-        price_lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(bracket_lo)));
-        price_hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(bracket_hi)));
         BinBracket bins;
         uint64_t my_below = 0;   // bits freed by moves that are cheaper than the bracket
         {
-            // lane r: step r
-            double inverse = 0.0;
-            uint32_t dw = 0;
-#pragma unroll
-            for (int r = 0; r < kMaxSteps; ++r) {
-                inverse = lane == r ? a.inverse[r] : inverse;
-                dw = lane == r && r < steps ? static_cast<uint32_t>(a.lad.width[r] - a.lad.width[r + 1]) : dw;
-            }
-            const bool step = lane < steps;
+            const bool step = lane < steps;   // lane r: step r
             // a ladder with fewer steps: the unused ones are never cheaper (`above` is not looked at)
             const uint32_t below = step ? ratio_at(static_cast<uint64_t>(price_lo) << 32, inverse) : 0u;
             const uint32_t above = step ? ratio_at(static_cast<uint64_t>(price_hi) << 32, inverse) + 2u : 0u;
@@ -2614,18 +2669,24 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
                 my_below = static_cast<uint64_t>(dw) * (narrow ? static_cast<uint64_t>(table32[bin_below]) << scale : table[bin_below]);
         }
         {
-            uint32_t classes = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint32_t bin = static_cast<uint32_t>(4 * tid + k);
-                uint32_t first = 0, last = 0;
-#pragma unroll
-                for (int r = 0; r < kMaxSteps; ++r) {
-                    first += bin < bins.below[r] ? 1u : 0u;
-                    last += bin < bins.above[r] ? 1u : 0u;
+            // a wavefront has 256 neighbouring bins, and most boundaries lie outside of them: scalar comparisons
+            const uint32_t base = static_cast<uint32_t>(wave) * (4 * kWave), own = 4u * static_cast<uint32_t>(lane);
+            uint32_t first = 0, last = 0;   // four bins, a byte each
+            const auto count_bins = [&](uint32_t& counts, uint32_t boundary) {   // the bins before it
+                if (boundary <= base) return;
+                if (boundary >= base + 4 * kWave) {
+                    counts += 0x01010101u;
+                    return;
                 }
-                classes |= (first | (first < last ? 8u : 0u)) << (8 * k);
+                const uint32_t before = __builtin_elementwise_sub_sat(boundary - base, own);
+                counts += before >= 4u ? 0x01010101u : 0x01010101u & ((1u << (8u * before)) - 1u);
+            };
+#pragma unroll
+            for (int r = 0; r < kMaxSteps; ++r) {
+                count_bins(first, bins.below[r]);
+                count_bins(last, bins.above[r]);
             }
+            const uint32_t classes = first | ((last - first + 0x07070707u) & 0x08080808u);   // first <= last < 8
             step_class[tid] = classes;
         }
         __syncthreads();
@@ -2639,9 +2700,11 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
 #pragma unroll
             for (int j = k * kQ; j < (k + 1) * kQ; ++j) {
                 const uint32_t cls = class_of(ratio[j]);
-                undecided |= size[j] != 0 && (cls & 8u) ? 1u << j : 0u;
+                undecided |= (cls >> 3) << j;
                 rungs |= static_cast<uint64_t>(cls & 7u) << (4 * j);
             }
+            const int64_t live = M - item(k * kQ);   // an invalid size has left no search: the slots with items are those of the first M
+            if (live < kQ) undecided &= live > 0 ? (1u << (k * kQ + static_cast<int>(live))) - 1u : (1u << (k * kQ)) - 1u;
         }
         const auto steps_freed = [&](int64_t Di, int from, int to) {   // bits freed by going from rung `from` to rung `to`
             return static_cast<uint64_t>(Di) * static_cast<uint64_t>(ladder_width(a, from) - ladder_width(a, to));
@@ -2658,8 +2721,19 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
                 rungs = (rungs & ~(uint64_t(15) << (4 * j))) | (static_cast<uint64_t>(first) << (4 * j));
             }
         }
+        // places in the list: one LDS operation per wavefront
+        const auto places = [&](uint32_t mask, uint32_t* total) {
+            const uint32_t own = static_cast<uint32_t>(__builtin_popcount(mask)), upto = wave_inclusive_scan(own, lane);
+            const uint32_t of_wave = read_lane(upto, kWave - 1);
+            uint32_t from = 0;
+            if (of_wave != 0) {
+                if (lane == 0) from = __hip_atomic_fetch_add(total, of_wave, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                from = read_lane(from, 0);
+            }
+            return from + upto - own;
+        };
+        listed_at = places(undecided, &list_count);
         if (undecided != 0) {
-            listed_at = __hip_atomic_fetch_add(&list_count, static_cast<uint32_t>(__builtin_popcount(undecided)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             uint32_t at = listed_at;
             for (uint32_t m = undecided; m != 0; m &= m - 1, ++at)
                 if (at < static_cast<uint32_t>(kAllocList)) list_item[at] = static_cast<uint32_t>(item(__builtin_ctz(m)));
@@ -2717,21 +2791,29 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
                     }
                 }
             }
-            {
+            if (__ballot(my_below != 0) != 0) {
                 const uint64_t b = wave_reduce(my_below, Add());
-                if (lane == 0) wave_a[wave] = b;
+                if (lane == 0) __hip_atomic_fetch_add(&all_cheaper, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             }
             __syncthreads();
-            const uint64_t cheaper_than_all = combine_waves(wave_a, waves, 0, Add());
-            uint64_t below;
-            const uint32_t digit = winning_bin(hist, v.need, cheaper_than_all, lane, below);
+            if (wave == 0) {
+                uint64_t below_bin;
+                const uint32_t of_need = winning_bin(hist, v.need, all_cheaper, lane, below_bin);
+                if (lane == 0) {
+                    found_digit = of_need;
+                    found.below = below_bin;
+                }
+            }
+            __syncthreads();
+            const uint32_t digit = read_lane(found_digit, 0);
+            const uint64_t below = read_lane(found.below, 0);
             // the moves in the bin that holds the threshold
             uint32_t chosen = 0;
 #pragma unroll
             for (int r = 0; r < kMaxSteps; ++r)
                 chosen |= (here >> r & 1u) && ((static_cast<uint32_t>(key[r] >> 32) - price_lo) >> fine) == digit ? 1u << r : 0u;
+            uint32_t at = places(chosen, &rank_count);
             if (chosen != 0) {
-                uint32_t at = __hip_atomic_fetch_add(&rank_count, static_cast<uint32_t>(__builtin_popcount(chosen)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 #pragma unroll
                 for (int r = 0; r < kMaxSteps; ++r)
                     if (chosen >> r & 1u) {
@@ -2745,7 +2827,15 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
             __syncthreads();
             const int n = __builtin_amdgcn_readfirstlane(static_cast<int>(rank_count));
             if (n <= kWave) {
-                rank_moves(rank_key, rank_amount, n, v.need, below, lane, t.price, t.below, t.ties);
+                if (wave == 0) {
+                    Threshold own;
+                    rank_moves(rank_key, rank_amount, n, v.need, below, lane, own.price, own.below, own.ties);
+                    if (lane == 0) found = own;
+                }
+                __syncthreads();
+                t.price = read_lane(found.price, 0);
+                t.below = read_lane(found.below, 0);
+                t.ties = read_lane(found.ties, 0);
             } else {
                 const auto each = [&](auto f) {
 #pragma unroll
@@ -2901,47 +2991,67 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
             }
     };
     // groups of an item: below 2^26, so that a quadruple's units stay below 2^31
-    const auto groups_of = [](int64_t D) { return static_cast<uint32_t>((static_cast<uint64_t>(D) + (kGroup - 1)) >> 8); };
-    // the byte sums of all rounds in registers go through one barrier
-    {
-        uint64_t upto[kAllocQuads];
+    const auto groups_of = [](int64_t D) {
+        const uint64_t up = static_cast<uint64_t>(D) + (kGroup - 1);
+        return __builtin_amdgcn_alignbit(static_cast<uint32_t>(up >> 32), static_cast<uint32_t>(up), 8);
+    };
+    // The sums of all rounds in registers go through one barrier.  In 32 bits where all groups together allow it (a scan of a wavefront in
+    // 64 bits takes eight times as many instructions).
+    if (invalid) {   // invalid input: stay memory-safe, with the sizes as they are where they can be
+        alike_rounds = 0;
+#pragma unroll
+        for (int j = 0; j < kCached; ++j) {
+            const int64_t i = item(j);
+            int64_t Di = i < M ? elements(i) : 0;
+            if (Di <= 0 || Di >= (int64_t(1) << 34)) Di = i < M ? 1 : 0;
+            size[j] = Di;
+        }
+    }
+    const auto store_rounds = [&](auto zero) {
+        typedef decltype(zero) V;   // units: 32 bytes of the stream
+        V upto[kAllocQuads];
         uint32_t units[kCached], own[kAllocQuads], widths[kAllocQuads];
+        V* const of_waves = reinterpret_cast<V*>(wave_bytes);
 #pragma unroll
         for (int k = 0; k < kAllocQuads; ++k) {
             own[k] = 0;
             widths[k] = 0;
             upto[k] = 0;
             if (in_round(k)) {
+                uint32_t groups[kQ];
+                groups[0] = groups_of(size[k * kQ]);
+                if (alike_rounds >> k & 1u) {
+                    groups[1] = groups[2] = groups[3] = groups[0];
+                } else {
+#pragma unroll
+                    for (int q = 1; q < kQ; ++q) groups[q] = groups_of(size[k * kQ + q]);
+                }
 #pragma unroll
                 for (int q = 0; q < kQ; ++q) {
                     const int j = k * kQ + q;
-                    if (invalid) {   // invalid input: stay memory-safe, with the sizes as they are where they can be
-                        const int64_t i = item(j);
-                        int64_t Di = i < M ? elements(i) : 0;
-                        if (Di <= 0 || Di >= (int64_t(1) << 34)) Di = i < M ? 1 : 0;
-                        size[j] = Di;
-                    }
                     const uint32_t b = static_cast<uint32_t>(ladder_width(a, static_cast<int>(rungs >> (4 * j)) & 15));
-                    units[j] = groups_of(size[j]) * b;
+                    units[j] = groups[q] * b;
                     own[k] += units[j];
                     widths[k] |= b << (8 * q);
                 }
-                upto[k] = wave_inclusive_scan(static_cast<uint64_t>(own[k]), lane);
+                upto[k] = wave_inclusive_scan(static_cast<V>(own[k]), lane);
             }
-            if (lane == kWave - 1) wave_bytes[k * kAllocWavesMax + wave] = upto[k];
+            if (lane == kWave - 1) of_waves[k * kAllocWavesMax + wave] = upto[k];
         }
         __syncthreads();
-        const uint64_t of_wave = wave_bytes[lane];   // row k of the lanes: round k
-        const uint64_t scan = row_inclusive_scan(of_wave);
+        const V of_wave = of_waves[lane];   // row k of the lanes: round k
+        const V scan = row_inclusive_scan(of_wave);
 #pragma unroll
         for (int k = 0; k < kAllocQuads; ++k) {
-            const uint64_t off = byte_carry + 32u * (read_lane(scan, 16 * k + wave) - read_lane(of_wave, 16 * k + wave) + upto[k] - own[k]);
-            byte_carry += 32u * read_lane(scan, 16 * k + 15);
+            const uint64_t off = byte_carry + 32u * static_cast<uint64_t>(read_lane(scan, 16 * k + wave) - read_lane(of_wave, 16 * k + wave) + upto[k] - own[k]);
+            byte_carry += 32u * static_cast<uint64_t>(read_lane(scan, 16 * k + 15));
             if (!in_round(k)) continue;
             const uint32_t quad[kQ] = {units[k * kQ], units[k * kQ + 1], units[k * kQ + 2], units[k * kQ + 3]};
             store_quad(item(k * kQ), widths[k], quad, off);
         }
-    }
+    };
+    if (!invalid && (elems >> 8) + static_cast<uint64_t>(M) < (uint64_t(1) << 29)) store_rounds(uint32_t(0));
+    else store_rounds(uint64_t(0));
     // items beyond the registers, round by round
     for (int64_t base = kAllocQuads * kRound; base < M; base += kRound) {
         int64_t D4[kQ];

@@ -679,6 +679,31 @@ def test_device_allocator_of_items_of_one_size(M, widths, law):
             assert np.array_equal(offs, np.concatenate([[0], np.cumsum(per)[:-1]])) and total == int(per.sum())
 
 
+# Runs of neighbours of one size (looked at once per quadruple where a wavefront has nothing else), of lengths that divide a quadruple and not;
+# element counts on both sides of where the search (2^29 in units of the sizes' common power of two) and the offsets (2^29 groups) go over to
+# 64 bits; an invalid item inside a run.
+@pytest.mark.parametrize("law", ["log-normal", "wide", "few"])
+@pytest.mark.parametrize("M,run,sizes", [(2049, 4, (256, 25088)), (4097, 7, (256, 25088, 802816)), (13568, 256, (802816, 25088, 100352)), (16384, 300, (512, 1536)),
+                                         (4096, 4096, (131071,)), (4096, 4096, (131073,)), (4096, 1024, (2 ** 25, 2 ** 25 - 1)), (4096, 8, (2 ** 25 + 512, 2 ** 25 + 256)),
+                                         (16385, 5, (2 ** 23, 2 ** 23 + 1)), (5000, 1, (1, 2 ** 34 - 1))])
+def test_device_allocator_of_neighbours_of_one_size(M, run, sizes, law):
+    rng = np.random.default_rng(M + run)
+    w = rng.lognormal(0, 2, M).astype(np.float32) if law == "log-normal" else _spread(rng, M, law)
+    D = np.array([sizes[(i // run) % len(sizes)] for i in range(M)], dtype=np.int64)
+    for mean, widths in ((1.2, 0x1FE), (2.0, 0x116), (6.7, 0x1FE)):
+        budget = int(mean * float(D.sum()))
+        want = B.allocate_bits(w, D, budget, widths)
+        got, offs, total, status = _device_alloc(w, D, budget, widths, False)
+        assert status == 0 and np.array_equal(got, want), (mean, np.flatnonzero(got != want)[:6])
+        per = ((D + 255) // 256) * 32 * want.astype(np.int64)
+        assert np.array_equal(offs, np.concatenate([[0], np.cumsum(per)[:-1]])) and total == int(per.sum())
+    for bad_w, bad_d in ((np.nan, 0), (-1.0, 0), (1.0, -5), (1.0, 2 ** 34)):
+        w2, D2 = w.copy(), D.copy()
+        w2[M // 2], D2[M // 2] = bad_w, bad_d or D[M // 2]
+        got, offs, total, status = _device_alloc(w2, D2, 2 * int(D.sum()), 0x116, False)
+        assert status == B.ACTQ_EINVAL and (got == 1).all()
+
+
 def test_device_allocator_with_more_than_2_to_the_32_equal_moves():
     """2^30 items of sensitivity 0 with four steps each: 2^32 undecided moves, all at the price of the threshold.  The
     first items go down to one bit until the budget holds, the others keep eight."""
