@@ -2040,7 +2040,8 @@ __device__ __forceinline__ uint64_t quotient_bits(double a, double d, double y)
 // 32-bit multiples of the common size, one histogram that leaves a handful of moves, and those ranked from registers.  Many (nearly)
 // equal prices go on to select_among.  Kernel durations with a thread per move and the prices in LDS, and so, items of one size:
 // 4 with {1, 2, 4, 8} 4.8 -> 3.6 us, 128 5.3 -> 3.7, 256 with all widths 7.7 -> 4.4, 1024 16.1 -> 7.6, 2048 23.0 -> 12.5;
-// per-item sizes: 300 with all widths 8.8 -> 5.6, 1024 17.2 -> 12.0.
+// per-item sizes: 300 with all widths 8.8 -> 5.6, 1024 17.2 -> 12.0.  (Call to call, with the arguments as one batch: 4 items 3.1, 128 3.6, 256 with
+// all widths 4.0, 1024 6.9.)
 template <bool UNIFORM, int ITEMS>
 __global__ __launch_bounds__(kAllocBlock) void allocate_bits_small_kernel(const float* __restrict__ w, SmallAllocArgs a,
                                                                           uint8_t* __restrict__ bits,
@@ -2059,6 +2060,10 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_small_kernel(const 
     const int tid = threadIdx.x, lane = tid & (kWave - 1), threads = blockDim.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = threads >> 6;
     const int M = a.M, steps = a.steps;
+    // 180 bytes of arguments, as one batch: left alone they are eleven loads, each waited for where it is first used (128 items 4.07 -> 3.66 us)
+    asm volatile("" : : "s"(w), "s"(a.M), "s"(a.steps), "s"(a.width_nibbles), "s"(a.need), "s"(a.status), "s"(a.search), "s"(a.loose), "s"(a.unit_bytes), "s"(a.D),
+                 "s"(a.reciprocal), "s"(a.D_items), "s"(a.price[0]), "s"(a.price[1]), "s"(a.price[2]), "s"(a.price[3]), "s"(a.price[4]), "s"(a.price[5]),
+                 "s"(a.price[6]), "s"(bits), "s"(offsets), "s"(result));
     const int first = tid * ITEMS;   // the thread's items, consecutive ones
     const auto width_of = [&](int k) { return static_cast<int>((a.width_nibbles >> (4 * k)) & 15u); };
     float wi[ITEMS];
@@ -2452,7 +2457,7 @@ __global__ __launch_bounds__(kAllocBlock) void allocate_bits_kernel(const float*
 #pragma unroll
             for (int j = k * kQ; j < (k + 1) * kQ; ++j) {
                 const uint32_t u = ratio_by(weight[j], reciprocal), less1 = u - 1u;
-                const uint32_t top = valid_weight(weight[j]) & size_ok ? u : 0x80000000u;
+                const uint32_t top = (valid_weight(weight[j]) & size_ok) ? u : 0x80000000u;
                 lo_less1 = less1 < lo_less1 ? less1 : lo_less1;
                 hi_ratio = top > hi_ratio ? top : hi_ratio;
                 ratio[j] = u;
