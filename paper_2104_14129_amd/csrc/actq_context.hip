@@ -405,6 +405,45 @@ struct RowPool {
     int64_t elems;                // elements of the tensor that is read
 };
 
+// Where a lane of a row kernel is, for its BRIEF form: the workgroup's first lane is located by the scalar unit, and a lane counts rows and
+// elements from there in 32 bits (a plane has fewer than 2^31 elements, and a workgroup reaches little further than one).  64-bit element
+// numbers of its own cost every lane two dozen multiplications, which the vector ALU takes four times as long for as for additions.
+struct RowLane {
+    uint32_t plane0, strip0, row0;   // of the workgroup's first lane: its plane, its row over all planes and inside its plane (scalars)
+    uint32_t at, c;                  // lanes from the start of row strip0; the lane's stretch of its row
+    uint32_t down, planes;           // rows and planes below those of the workgroup's first lane
+    int32_t row;                     // inside the lane's plane
+    bool live;
+};
+
+__device__ __forceinline__ RowLane row_lane(uint32_t total, uint32_t chunks, FastDiv by_chunks, uint32_t rows, FastDiv by_rows)
+{
+    RowLane l;
+    const uint32_t first = blockIdx.x * kBlock;
+    l.strip0 = fastdiv(first, by_chunks);
+    const uint32_t c0 = first - l.strip0 * chunks;
+    l.plane0 = fastdiv(l.strip0, by_rows);
+    l.row0 = l.strip0 - l.plane0 * rows;
+    const uint32_t last = total - 1 - first;   // every lane takes part in the shifts: those past the end as the last one
+    l.live = threadIdx.x <= last;
+    l.at = c0 + (l.live ? threadIdx.x : last);
+    l.down = fastdiv(l.at, by_chunks);
+    l.c = l.at - __umul24(l.down, chunks);     // at most 256 rows; W is below 2^22
+    const uint32_t below = l.row0 + l.down;
+    l.planes = fastdiv(below, by_rows);
+    l.row = static_cast<int32_t>(below - l.planes * rows);
+    return l;
+}
+
+// Row `row` of the lane's plane as a row of the planes from plane0 on, where a plane has `height` rows for `rows` rows times `scale` of
+// the lanes' (the difference is a few rows either way, so that 24 bits hold it).
+__device__ __forceinline__ uint32_t row_from_plane0(const RowLane& l, uint32_t scale, int32_t height, uint32_t rows)
+{
+    return scale * (l.row0 + l.down) + static_cast<uint32_t>(__mul24(static_cast<int>(l.planes), height - static_cast<int32_t>(scale * rows)));
+}
+
+__device__ __forceinline__ uint32_t elements_up_to_32_bits(int64_t elems) { return elems > 0xffffffffll ? 0xffffffffu : static_cast<uint32_t>(elems); }
+
 // Stretches of E elements and of NO elements and positions.
 template <typename T, int S>
 struct RowVec;
@@ -468,24 +507,58 @@ __device__ __forceinline__ int64_t read_lane_i64(int64_t v, int lane)
 
 // What a word of memory becomes in the kernels: positions are words as they are, gradients binary32 patterns.
 struct PositionWord {
+    typedef uint8_t memory;
     static __device__ __forceinline__ uint32_t of(uint8_t v) { return v; }
 };
 template <typename T>
 struct GradientWord {
+    typedef T memory;
     static __device__ __forceinline__ uint32_t of(T v) { return __float_as_uint(static_cast<float>(v)); }
 };
 
-// The word `own` of the lane to the left (LEFT) or right.  The wavefront's edge lane takes it from memory,
-// element `at` of p, if its neighbour exists (`inside`).
-template <bool LEFT, typename WORD, typename V, typename M>
-__device__ __forceinline__ V neighbour(V own, bool inside, const M* p, int64_t at)
+// The aligned 32-bit word around an element that the wavefront's edge lane needs of its neighbour, and where the element is in it.
+struct Edge {
+    uint32_t word, shift;
+};
+
+// Of element `at` of p (a scalar) if the edge lane (LEFT: the first) has a neighbour to that side (`inside`), of element 0 otherwise.
+template <bool LEFT, typename M>
+__device__ __forceinline__ Edge edge_element(const M* p, uint32_t at, bool inside)
 {
     constexpr int kEdge = LEFT ? 0 : kWave - 1;
-    const int64_t edge_at = read_lane_i64(at, kEdge);
+    const uint32_t edge_at = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(at), kEdge));
+    const uintptr_t address = reinterpret_cast<uintptr_t>(p + (__builtin_amdgcn_readlane(static_cast<int>(inside), kEdge) != 0 ? edge_at : 0u));
+    return {load_uniform(reinterpret_cast<const uint32_t*>(address & ~uintptr_t(3))), 8 * static_cast<uint32_t>(address & 3u)};
+}
+
+// The word `own` of the lane to the left (LEFT) or right; the edge lane's is made of `edge`.
+template <bool LEFT, typename WORD, typename V>
+__device__ __forceinline__ V neighbour(V own, const Edge& edge)
+{
+    const uint32_t bits = edge.word >> edge.shift;
+    typename WORD::memory element;
+    __builtin_memcpy(&element, &bits, sizeof(element));
+    const V from_edge = WORD::of(element), shifted = static_cast<V>(from_lane(own, LEFT));
+    return (threadIdx.x & (kWave - 1)) == (LEFT ? 0 : kWave - 1) ? from_edge : shifted;
+}
+
+// The same with the element asked for here, behind a branch: a trip to memory of its own, but the forms that ask in front of their loads or without a
+// branch are up to 5 % slower at stride 2 (binary16 [16384, 112, 112] forward 93 -> 98 us, binary32 3x3 / 2 / 0 backward 163 -> 170).
+template <bool LEFT, typename WORD, typename V, typename M, typename I>
+__device__ __forceinline__ V neighbour(V own, bool inside, const M* p, I at)
+{
+    constexpr int kEdge = LEFT ? 0 : kWave - 1;
     V from_edge = 0;
-    if (__builtin_amdgcn_readlane(static_cast<int>(inside), kEdge) != 0) from_edge = WORD::of(load_uniform_element(p + edge_at));
-    const V shifted = static_cast<V>(from_lane(own, LEFT));
-    return (threadIdx.x & (kWave - 1)) == kEdge ? from_edge : shifted;
+    if constexpr (sizeof(I) == 8) {
+        const int64_t edge_at = read_lane_i64(at, kEdge);
+        if (__builtin_amdgcn_readlane(static_cast<int>(inside), kEdge) != 0) from_edge = WORD::of(load_uniform_element(p + edge_at));
+        const V shifted = static_cast<V>(from_lane(own, LEFT));
+        return (threadIdx.x & (kWave - 1)) == kEdge ? from_edge : shifted;
+    } else {
+        Edge edge = {0, 0};
+        if (__builtin_amdgcn_readlane(static_cast<int>(inside), kEdge) != 0) edge = edge_element<LEFT>(p, at, true);
+        return neighbour<LEFT, WORD>(own, edge);
+    }
 }
 
 // The first `count` (1 .. N - 1) of N values or positions, as pieces of 4, 2 and 1: at most three stores.
@@ -548,6 +621,7 @@ struct Carrier;
 template <int S>
 struct Carrier<float, S> {
     typedef uint32_t raw;
+    typedef raw memory;
     typedef uint32_t type;
     static __device__ __forceinline__ type of(raw u) { return u; }
     static __device__ __forceinline__ float value(type u) { return __uint_as_float(u); }
@@ -556,6 +630,7 @@ struct Carrier<float, S> {
 template <>
 struct Carrier<_Float16, 1> {
     typedef uint16_t raw;
+    typedef raw memory;
     typedef uint16_t type;
     static __device__ __forceinline__ type of(raw u) { return u; }
     static __device__ __forceinline__ _Float16 value(type u)
@@ -569,6 +644,7 @@ struct Carrier<_Float16, 1> {
 template <>
 struct Carrier<_Float16, 2> {
     typedef uint16_t raw;
+    typedef raw memory;
     typedef uint32_t type;
     static __device__ __forceinline__ type of(raw u)
     {
@@ -592,7 +668,8 @@ struct Carrier<_Float16, 2> {
 // replaces the running maximum; one to the left or above wins in its original's place, and the
 // position moves to the original (which is the first of the equal values inside the image).
 // PH, PW: padding of the rows and of the columns.  NT: non-temporal stores.
-template <typename T, int K, int PH, int PW, int S, bool NT>
+// BRIEF: fewer instructions around the window and all loads in flight before the first comparison (see forward_brief).
+template <typename T, int K, int PH, int PW, int S, bool NT, bool BRIEF>
 __global__ __launch_bounds__(kBlock) void maxpool2d_forward_rows_kernel(const T* __restrict__ x, Pool g, RowPool q,
                                                                         T* __restrict__ y, uint8_t* __restrict__ argmax)
 {
@@ -604,31 +681,60 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_forward_rows_kernel(const T*
     typedef typename RowVec<T, S>::codes vec_codes;
     constexpr int E = 16 / sizeof(T), NO = E / S;
     constexpr bool kLeft = PW == 1, kRight = K == 3 && (PW == 0 || S == 1);   // columns needed from the neighbours
-    const uint32_t idx = blockIdx.x * kBlock + threadIdx.x;
-    const bool live = idx < q.total;
-    const uint32_t id = live ? idx : q.total - 1;   // every lane takes part in the shift
-    const uint32_t strip = fastdiv(id, q.by_chunks);           // output row over all planes
-    const uint32_t c = id - strip * q.chunks;
-    const uint32_t plane = fastdiv(strip, q.by_rows);
-    const int32_t i = static_cast<int32_t>(strip - plane * q.rows);
-    int64_t at[K];   // the lane's first element of every window row
-#pragma unroll
-    for (int a = 0; a < K; ++a) {
-        const int32_t r = min(max(S * i - PH + a, 0), g.H - 1);
-        at[a] = (static_cast<int64_t>(plane) * g.H + r) * g.W + static_cast<int64_t>(E) * c;
-    }
+    typedef typename std::conditional<BRIEF, uint32_t, int64_t>::type Index;
+    uint32_t c;
+    int32_t i;
+    bool live;
+    Index at[K], o;   // the lane's first element of every window row, and its first output
     const raw* xr = reinterpret_cast<const raw*>(x);
     raw* yr = reinterpret_cast<raw*>(y);
+    int64_t elems = q.elems;   // from xr on
+    if constexpr (BRIEF) {
+        const RowLane l = row_lane(q.total, q.chunks, q.by_chunks, q.rows, q.by_rows);
+        c = l.c;
+        i = l.row;
+        live = l.live;
+        const uint32_t W = static_cast<uint32_t>(g.W);
+        at[0] = (row_from_plane0(l, S, g.H, q.rows) - PH) * W + E * c;
+#pragma unroll
+        for (int a = 1; a < K; ++a) at[a] = at[a - 1] + W;
+        if (PH == 1) {   // only the row above the first and the one below the last are outside
+            at[0] += i == 0 ? W : 0u;
+            at[K - 1] -= S * i - PH + K - 1 >= g.H ? W : 0u;
+        }
+        o = NO * l.at - __umul24(l.down, NO * q.chunks - static_cast<uint32_t>(g.OW));   // columns that the lanes of a row cover beyond its own: few
+        const int64_t base = static_cast<int64_t>(l.plane0) * (static_cast<int64_t>(g.H) * g.W), out_base = static_cast<int64_t>(l.strip0) * g.OW;
+        xr += base;
+        elems -= base;
+        yr += out_base;
+        argmax += out_base;
+    } else {
+        const uint32_t idx = blockIdx.x * kBlock + threadIdx.x;
+        live = idx < q.total;
+        const uint32_t id = live ? idx : q.total - 1;   // every lane takes part in the shift
+        const uint32_t strip = fastdiv(id, q.by_chunks);           // output row over all planes
+        c = id - strip * q.chunks;
+        const uint32_t plane = fastdiv(strip, q.by_rows);
+        i = static_cast<int32_t>(strip - plane * q.rows);
+#pragma unroll
+        for (int a = 0; a < K; ++a) {
+            const int32_t r = min(max(S * i - PH + a, 0), g.H - 1);
+            at[a] = (static_cast<int64_t>(plane) * g.H + r) * g.W + static_cast<int64_t>(E) * c;
+        }
+        o = static_cast<int64_t>(strip) * g.OW + NO * static_cast<int32_t>(c);
+    }
     typename C::type v[K][E + 2];   // slot 1 + t: column E c + t; slots 0 and E + 1: the neighbours' columns
-    if (__any(at[K - 1] + E > q.elems)) {
+    if (BRIEF ? __any(at[K - 1] + E > elements_up_to_32_bits(elems)) : __any(at[K - 1] + E > elems)) {
 #pragma unroll
         for (int a = 0; a < K; ++a)
 #pragma unroll
-            for (int t = 0; t < E; ++t) v[a][1 + t] = C::of(xr[min(at[a] + t, q.elems - 1)]);
+            for (int t = 0; t < E; ++t) v[a][1 + t] = C::of(xr[min(static_cast<int64_t>(at[a]) + t, elems - 1)]);
     } else {
         vec_in w[K];
 #pragma unroll
         for (int a = 0; a < K; ++a) w[a] = *reinterpret_cast<const vec_in*>(xr + at[a]);
+        // left alone, the compiler puts the comparisons of a row in front of the next row's load
+        if constexpr (BRIEF && (sizeof(T) == 4 || S == 1)) asm volatile("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[K - 1]));
 #pragma unroll
         for (int a = 0; a < K; ++a)
 #pragma unroll
@@ -637,13 +743,17 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_forward_rows_kernel(const T*
     if (kLeft) {
 #pragma unroll
         for (int a = 0; a < K; ++a) {
-            v[a][0] = neighbour<true, C>(v[a][E], c > 0, xr, at[a] - 1);
+            if constexpr (BRIEF && S == 1) v[a][0] = neighbour<true, C>(v[a][E], edge_element<true>(xr, at[a] - 1, c > 0));
+            else v[a][0] = neighbour<true, C>(v[a][E], c > 0, xr, at[a] - 1);
             v[a][0] = c > 0 ? v[a][0] : v[a][1];   // the padded column
         }
     }
     if (kRight) {
 #pragma unroll
-        for (int a = 0; a < K; ++a) v[a][E + 1] = neighbour<false, C>(v[a][1], c + 1 < q.chunks, xr, at[a] + E);
+        for (int a = 0; a < K; ++a) {
+            if constexpr (BRIEF && S == 1) v[a][E + 1] = neighbour<false, C>(v[a][1], edge_element<false>(xr, at[a] + E, c + 1 < q.chunks));
+            else v[a][E + 1] = neighbour<false, C>(v[a][1], c + 1 < q.chunks, xr, at[a] + E);
+        }
     }
     const int32_t j0 = NO * static_cast<int32_t>(c);
     vec_out out;
@@ -673,7 +783,6 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_forward_rows_kernel(const T*
     }
     const int left = g.OW - j0;   // output columns from j0 on
     if (!live || left <= 0) return;
-    const int64_t o = static_cast<int64_t>(strip) * g.OW + j0;
     if (left >= NO) {
         if (NT) {
             __builtin_nontemporal_store(out, reinterpret_cast<vec_out*>(yr + o));
@@ -691,8 +800,9 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_forward_rows_kernel(const T*
 // Backward.  A lane produces E columns of S input rows, S q + rr.  The output rows whose windows reach
 // them are q (K = 2), q and q + 1 (stride 2, padding 1), q - 1 and q (stride 2, K = 3, padding 0), and
 // q - 1 .. q + 1 (stride 1).  The additions run over ascending output row, then column.
-// NT: non-temporal stores.
-template <typename T, int K, int P, int S, bool NT>
+// NT: non-temporal stores.  BRIEF: fewer instructions around the windows, what the edge lanes need of their neighbours asked for in front of the loads
+// (stride 1) and all loads in flight before the first use (binary16); see backward_brief.
+template <typename T, int K, int P, int S, bool NT, bool BRIEF>
 __global__ __launch_bounds__(kBlock) void maxpool2d_backward_rows_kernel(const uint8_t* __restrict__ argmax,
                                                                          const T* __restrict__ grad_y, Pool g, RowPool q,
                                                                          T* __restrict__ grad_x)
@@ -705,30 +815,71 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_backward_rows_kernel(const u
     constexpr int kFirstRow = K == 3 && (P == 0 || S == 1) ? -1 : 0;   // the first of them, relative to q
     constexpr bool kLeft = K == 3 && (P == 0 || S == 1), kRight = P == 1;
     constexpr uint32_t kNone = 0x100;                                  // no window position
-    const uint32_t idx = blockIdx.x * kBlock + threadIdx.x;
-    const bool live = idx < q.total;
-    const uint32_t id = live ? idx : q.total - 1;
-    const uint32_t strip = fastdiv(id, q.by_chunks);           // stretch of S input rows over all planes
-    const uint32_t c = id - strip * q.chunks;
-    const uint32_t plane = fastdiv(strip, q.by_rows);
-    const int32_t stretch = static_cast<int32_t>(strip - plane * q.rows);
-    const int32_t j0 = NO * static_cast<int32_t>(c);
+    typedef typename std::conditional<BRIEF, uint32_t, int64_t>::type Index;
     uint32_t gy[MR][NO + 2];     // slot 1 + t: output column j0 + t
     uint32_t code[MR][NO + 2];
-    int64_t at[MR];
+    uint32_t c;
+    int32_t stretch;             // of S input rows
+    bool live;
+    Index at[MR], to;            // the lane's first element of every output row, and of its first input row
     bool row_ok[MR];
+    int64_t elems = q.elems;     // from grad_y and argmax on
+    if constexpr (BRIEF) {
+        const RowLane l = row_lane(q.total, q.chunks, q.by_chunks, q.rows, q.by_rows);
+        c = l.c;
+        stretch = l.row;
+        live = l.live;
+        const uint32_t OW = static_cast<uint32_t>(g.OW);
+        at[0] = (row_from_plane0(l, 1, g.OH, q.rows) + static_cast<uint32_t>(kFirstRow)) * OW + NO * c;
 #pragma unroll
-    for (int u = 0; u < MR; ++u) {
-        const int32_t i = stretch + kFirstRow + u;
-        row_ok[u] = i >= 0 && i < g.OH;
-        at[u] = (static_cast<int64_t>(plane) * g.OH + min(max(i, 0), g.OH - 1)) * g.OW + j0;
+        for (int u = 1; u < MR; ++u) at[u] = at[0] + static_cast<uint32_t>(u) * OW;
+#pragma unroll
+        for (int u = 0; u < MR; ++u) {
+            const int32_t i = stretch + kFirstRow + u;
+            row_ok[u] = i >= 0 && i < g.OH;
+            // a row that does not exist is the one above the first or the one below the last
+            at[u] = row_ok[u] ? at[u] : (kFirstRow + u < 0 ? at[u] + OW : at[u] - OW);
+        }
+        to = row_from_plane0(l, S, g.H, q.rows) * static_cast<uint32_t>(g.W) + E * c;
+        const int64_t base = static_cast<int64_t>(l.plane0) * (static_cast<int64_t>(g.OH) * g.OW);
+        grad_y += base;
+        argmax += base;
+        elems -= base;
+        grad_x += static_cast<int64_t>(l.plane0) * (static_cast<int64_t>(g.H) * g.W);
+    } else {
+        const uint32_t idx = blockIdx.x * kBlock + threadIdx.x;
+        live = idx < q.total;
+        const uint32_t id = live ? idx : q.total - 1;
+        const uint32_t strip = fastdiv(id, q.by_chunks);           // stretch of S input rows over all planes
+        c = id - strip * q.chunks;
+        const uint32_t plane = fastdiv(strip, q.by_rows);
+        stretch = static_cast<int32_t>(strip - plane * q.rows);
+#pragma unroll
+        for (int u = 0; u < MR; ++u) {
+            const int32_t i = stretch + kFirstRow + u;
+            row_ok[u] = i >= 0 && i < g.OH;
+            at[u] = (static_cast<int64_t>(plane) * g.OH + min(max(i, 0), g.OH - 1)) * g.OW + NO * static_cast<int32_t>(c);
+        }
+        to = (static_cast<int64_t>(plane) * g.H + S * stretch) * g.W + static_cast<int64_t>(E) * c;
     }
-    if (__any(at[MR - 1] + NO > q.elems)) {
+    const int32_t j0 = NO * static_cast<int32_t>(c);
+    const bool left_there = c > 0 && j0 - 1 < g.OW, right_there = c + 1 < q.chunks && j0 + NO < g.OW;
+    Edge edge_gy[MR][2] = {}, edge_code[MR][2] = {};   // to the left, to the right
+    if constexpr (BRIEF && S == 1) {
+#pragma unroll
+        for (int u = 0; u < MR; ++u) {
+            edge_gy[u][0] = edge_element<true>(grad_y, at[u] - 1, left_there);
+            edge_code[u][0] = edge_element<true>(argmax, at[u] - 1, left_there);
+            edge_gy[u][1] = edge_element<false>(grad_y, at[u] + NO, right_there);
+            edge_code[u][1] = edge_element<false>(argmax, at[u] + NO, right_there);
+        }
+    }
+    if (BRIEF ? __any(at[MR - 1] + NO > elements_up_to_32_bits(elems)) : __any(at[MR - 1] + NO > elems)) {
 #pragma unroll
         for (int u = 0; u < MR; ++u)
 #pragma unroll
             for (int t = 0; t < NO; ++t) {
-                const int64_t o = min(at[u] + t, q.elems - 1);
+                const int64_t o = min(static_cast<int64_t>(at[u]) + t, elems - 1);
                 gy[u][1 + t] = GradientWord<T>::of(grad_y[o]);
                 code[u][1 + t] = argmax[o];
             }
@@ -740,6 +891,8 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_backward_rows_kernel(const u
             w[u] = *reinterpret_cast<const vec_out*>(grad_y + at[u]);
             cw[u] = *reinterpret_cast<const vec_codes*>(argmax + at[u]);
         }
+        if constexpr (BRIEF && sizeof(T) == 2 && MR == 3) asm volatile("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(cw[0]), "+v"(cw[1]), "+v"(cw[2]));
+        else if constexpr (BRIEF && sizeof(T) == 2 && MR == 2) asm volatile("" : "+v"(w[0]), "+v"(w[1]), "+v"(cw[0]), "+v"(cw[1]));
 #pragma unroll
         for (int u = 0; u < MR; ++u)
 #pragma unroll
@@ -751,15 +904,18 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_backward_rows_kernel(const u
 #pragma unroll
     for (int u = 0; u < MR; ++u) {
         // the neighbours' columns first, as stored; then what does not exist is no position
-        const bool left_there = c > 0 && j0 - 1 < g.OW, right_there = c + 1 < q.chunks && j0 + NO < g.OW;
         if (kLeft) {
-            gy[u][0] = neighbour<true, GradientWord<T>>(gy[u][NO], left_there, grad_y, at[u] - 1);
-            code[u][0] = neighbour<true, PositionWord>(code[u][NO], left_there, argmax, at[u] - 1);
+            if constexpr (BRIEF && S == 1) gy[u][0] = neighbour<true, GradientWord<T>>(gy[u][NO], edge_gy[u][0]);
+            else gy[u][0] = neighbour<true, GradientWord<T>>(gy[u][NO], left_there, grad_y, at[u] - 1);
+            if constexpr (BRIEF && S == 1) code[u][0] = neighbour<true, PositionWord>(code[u][NO], edge_code[u][0]);
+            else code[u][0] = neighbour<true, PositionWord>(code[u][NO], left_there, argmax, at[u] - 1);
             code[u][0] = row_ok[u] && left_there ? code[u][0] : kNone;
         }
         if (kRight) {
-            gy[u][NO + 1] = neighbour<false, GradientWord<T>>(gy[u][1], right_there, grad_y, at[u] + NO);
-            code[u][NO + 1] = neighbour<false, PositionWord>(code[u][1], right_there, argmax, at[u] + NO);
+            if constexpr (BRIEF && S == 1) gy[u][NO + 1] = neighbour<false, GradientWord<T>>(gy[u][1], edge_gy[u][1]);
+            else gy[u][NO + 1] = neighbour<false, GradientWord<T>>(gy[u][1], right_there, grad_y, at[u] + NO);
+            if constexpr (BRIEF && S == 1) code[u][NO + 1] = neighbour<false, PositionWord>(code[u][1], edge_code[u][1]);
+            else code[u][NO + 1] = neighbour<false, PositionWord>(code[u][1], right_there, argmax, at[u] + NO);
             code[u][NO + 1] = row_ok[u] && right_there ? code[u][NO + 1] : kNone;
         }
 #pragma unroll
@@ -794,7 +950,7 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_backward_rows_kernel(const u
         const vec_in out = rows[rr];
         const int32_t r = S * stretch + rr;
         if (!live || r >= g.H) continue;
-        T* dst = grad_x + (static_cast<int64_t>(plane) * g.H + r) * g.W + static_cast<int64_t>(E) * c;
+        T* dst = grad_x + (to + static_cast<Index>(rr) * static_cast<Index>(g.W));
         if (left >= E) {
             if (NT) __builtin_nontemporal_store(out, reinterpret_cast<vec_in*>(dst));
             else *reinterpret_cast<vec_in*>(dst) = out;
@@ -1133,6 +1289,40 @@ static bool one_sided_row_geometry(const PoolShape& p)
     return (p.kh == 3 && p.ph == 0 && p.pw == 1) || (p.kh == 2 && p.ph == 1 && p.pw == 0);
 }
 
+// Whether a row kernel takes its BRIEF form.  Where no lane has a neighbour in another wavefront (the lanes of a row divide 64), the ordinary form asks for no
+// words at the edges, and there is no trip to memory behind the loads that the loads together could make up for.
+static bool wavefronts_hold_rows(const RowPool& q) { return q.chunks <= kWave && kWave % q.chunks == 0; }
+
+// Forward, the loads together pay from the size on at which HBM sets the pace (a few tensors in turn, us, ordinary -> BRIEF):
+//   binary32  3x3/1/1 [16384, 112, 112] 407 -> 348, [8192, 56, 56] 53.3 -> 46.4, [522, 55, 394] 27.4 -> 23.7; 6 MB -2 to +2 %, lanes that divide 64 (rows of
+//             15, 31, 63, 125) 0 to +9 %
+//             3x3/2/1 [16384, 112, 112] 180 -> 168, [8192, 56, 56] 26.3 -> 24.3, [2048, 57, 57] alike; below, up to +7 % ([3, 23, 23] 2.12 -> 2.27)
+//             3x3/2/0 [4096, 113, 113] 50.5 -> 47.7; 30 MB -2 to +5 %
+//   binary16  3x3/1/1 [16384, 112, 112] 250 -> 230, [65536, 28, 28] 72 -> 68, [4096, 112, 112] 62 -> 58; odd rows -3 to +5 % (100 MB: 27 columns +5, 113 -3)
+//             3x3/2/1 [16384, 112, 112] 94.5 -> 91.6, [4096, 112, 112] 26.8 -> 26.0; 30 MB -2 to +1 %, 6 MB up to +3 %; 3x3/2/0 alike or +1 to +5 %
+static bool forward_brief(int64_t planes, const PoolShape& p, const RowPool& q, int64_t element_bytes)
+{
+    if (p.kh != 3 || p.W >= (1 << 22)) return false;   // 2x2 windows gain nothing; a lane's stretch is found with 24-bit products
+    const int64_t mib = planes * p.H * p.W * element_bytes >> 20;
+    if (element_bytes == 2) return p.ph == 1 && (p.sh == 1 ? mib >= 24 && p.W % 2 == 0 : mib >= 64);
+    return !wavefronts_hold_rows(q) && mib >= (p.ph == 1 ? 24 : 64);
+}
+
+// Backward, the words at the edges in front of the loads spare a trip to memory that small gradients wait for:
+//   3x3/1/1   binary32 [64, 31, 47] 3.51 -> 2.97, [28, 258, 258] 7.51 -> 6.37, [8192, 56, 56] 50.1 -> 46.8, [16384, 112, 112] 397 -> 357; lanes that divide 64
+//             -1 to -3 % up to 14 MB, +3 to +4 % from 25 MB on
+//             binary16 [2, 27, 264] 3.94 -> 3.06, [2197, 50, 50] 13.2 -> 11.2, [4096, 113, 113] 91 -> 85, [16384, 112, 112] 302 -> 272; odd rows of 7 to 27
+//             columns -1 to -10 % up to 14 MB, 0 to +4 % from 25 MB on
+//   stride 2  binary16, 8 to 25 MB -3 to -9 % (8 MB of [225, 225] planes -4, 25 MB -6 to -9), below +-1.5; 30 MB -5 to +6, 100 MB -3 to +5 %
+//             (3x3/2/1: [79, 79] planes +4, [56351, 37, 37] 81.5 -> 84.4).  Binary32 gains nothing at best (3x3/2/1 of 30 MB up to +7 %).
+static bool backward_brief(int64_t planes, const PoolShape& p, const RowPool& q, int64_t element_bytes)
+{
+    if (p.kh != 3 || p.W >= (1 << 22)) return false;
+    const int64_t mib = planes * p.H * p.W * element_bytes >> 20;
+    if (p.sh == 2) return element_bytes == 2 && mib < 24;
+    return mib < 16 || (element_bytes == 2 ? p.W % 2 == 0 || p.W >= 32 : !wavefronts_hold_rows(q));
+}
+
 template <typename T>
 static void maxpool_forward_typed(const T* x, int64_t planes, const PoolShape& p, T* y, uint8_t* argmax, hipStream_t s)
 {
@@ -1152,10 +1342,21 @@ static void maxpool_forward_typed(const T* x, int64_t planes, const PoolShape& p
         // over a few tensors in turn: binary16 2x2/2 27.9 -> 25.8 us on [4096, 112, 112], 3x3/2 54.9 -> 52.8 us on [4096, 160, 160]; with the pass
         // over y, results that would have stayed in the Infinity Cache cost 10 to 20 % more.
         const bool nt = sizeof(T) == 4 ? p.kh == 3 || p.W % 4 == 0 : p.W % 8 == 0;
-#define ACTQ_POOL_ROWS(K, PH, PW, S)                                                                                                         \
-    do {                                                                                                                                     \
-        if (nt) launch(maxpool2d_forward_rows_kernel<T, K, PH, PW, S, true>, blocks, kBlock, s, x, g, rows, y, argmax);                              \
-        else if constexpr (sizeof(T) == 2 || K == 2) launch(maxpool2d_forward_rows_kernel<T, K, PH, PW, S, false>, blocks, kBlock, s, x, g, rows, y, argmax); \
+        const bool brief = forward_brief(planes, p, rows, sizeof(T));
+#define ACTQ_POOL_ROWS(K, PH, PW, S)                                                                                                                    \
+    do {                                                                                                                                                \
+        constexpr bool kBrief = K == 3 && (sizeof(T) == 4 || PH == 1);                                                                                  \
+        const auto with = [&](auto store, auto form) {                                                                                                  \
+            constexpr bool kNt = decltype(store)::value, kForm = decltype(form)::value;                                                                 \
+            if constexpr ((kNt || sizeof(T) == 2 || K == 2) && (kBrief || !kForm))                                                                      \
+                launch(maxpool2d_forward_rows_kernel<T, K, PH, PW, S, kNt, kForm>, blocks, kBlock, s, x, g, rows, y, argmax);                             \
+        };                                                                                                                                              \
+        const auto form = [&](auto store) {                                                                                                             \
+            if (kBrief && brief) with(store, std::true_type());                                                                                         \
+            else with(store, std::false_type());                                                                                                        \
+        };                                                                                                                                              \
+        if (nt) form(std::true_type());                                                                                                                 \
+        else form(std::false_type());                                                                                                                   \
     } while (0)
         if (p.sh == 1) ACTQ_POOL_ROWS(3, 1, 1, 1);
         else if (p.kh == 2 && p.ph == 0) ACTQ_POOL_ROWS(2, 0, 0, 2);
@@ -1206,10 +1407,20 @@ static void maxpool_backward_typed(const uint8_t* argmax, const T* grad_y, int64
             launch(maxpool2d_backward_2x2_kernel<T>, blocks, kBlock, s, argmax, grad_y, g, rows, grad_x);
             return;
         }
-#define ACTQ_POOL_ROWS(K, P, S)                                                                                              \
-    do {                                                                                                                    \
-        if (rule.nt) launch(maxpool2d_backward_rows_kernel<T, K, P, S, true>, blocks, kBlock, s, argmax, grad_y, g, rows, grad_x);    \
-        else launch(maxpool2d_backward_rows_kernel<T, K, P, S, false>, blocks, kBlock, s, argmax, grad_y, g, rows, grad_x);      \
+        const bool brief = backward_brief(planes, p, rows, sizeof(T));
+#define ACTQ_POOL_ROWS(K, P, S)                                                                                                                         \
+    do {                                                                                                                                                \
+        const auto with = [&](auto store, auto form) {                                                                                                  \
+            constexpr bool kNt = decltype(store)::value, kForm = decltype(form)::value;                                                                 \
+            if constexpr (!kForm || (K == 3 && (S == 1 || sizeof(T) == 2)))                                                                   \
+                launch(maxpool2d_backward_rows_kernel<T, K, P, S, kNt, kForm>, blocks, kBlock, s, argmax, grad_y, g, rows, grad_x);                       \
+        };                                                                                                                                              \
+        const auto form = [&](auto store) {                                                                                                             \
+            if (brief) with(store, std::true_type());                                                                                                   \
+            else with(store, std::false_type());                                                                                                        \
+        };                                                                                                                                              \
+        if (rule.nt) form(std::true_type());                                                                                                            \
+        else form(std::false_type());                                                                                                                   \
     } while (0)
         if (p.sh == 1) ACTQ_POOL_ROWS(3, 1, 1);
         else if (p.kh == 2) ACTQ_POOL_ROWS(2, 0, 2);

@@ -386,3 +386,26 @@ def test_results_stored_through_the_caches_equal_those_that_are_not(mib, H, W, k
     n = x.numel() // 2 // 256 * 256      # whole words of the bit stream
     _, mask2 = B.relu_forward(x.view(-1)[:n])
     assert torch.equal(mask[:n // 8], mask2)
+
+
+# The row kernels have a second form, chosen by the size of the image, its rows and its type: a tensor that takes one has to
+# agree with its pieces that take the other (small calls of any extent are compared with the oracle above).  Planes smaller than
+# a workgroup, rows of one and of many wavefronts, rows whose lanes divide a wavefront, and tensors that start between words.
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("k,s,p", [(3, 2, (1, 1)), (3, 2, (0, 0)), (3, 2, (0, 1)), (3, 1, (1, 1))])
+@pytest.mark.parametrize("H,W", [(3, 3), (7, 6), (15, 15), (1, 34), (28, 28), (63, 2), (33, 71), (113, 113), (9, 516)])
+def test_maxpool_of_large_tensors_equals_that_of_their_pieces(H, W, k, s, p, dtype):
+    if H + 2 * p[0] < k or W + 2 * p[1] < k:
+        pytest.skip("the window does not fit")
+    pieces = 8
+    planes = (72 << 20) // (torch.finfo(dtype).bits // 8 * H * W) // pieces * pieces
+    gen = torch.Generator(device="cuda").manual_seed(H * 1000 + W)
+    x = torch.randint(-3, 4, (planes * H * W + 1,), generator=gen, device="cuda").to(dtype)[1:].view(planes, H, W)   # many ties
+    z, arg = B.maxpool2d_forward(x, (k, k), (s, s), p)
+    gz = torch.randn(z.shape, generator=gen, device="cuda").to(dtype)
+    gx = B.maxpool2d_backward(arg, gz, H, W, (k, k), (s, s), p)
+    for i in range(pieces):
+        part = slice(i * planes // pieces, (i + 1) * planes // pieces)
+        z2, arg2 = B.maxpool2d_forward(x[part], (k, k), (s, s), p)
+        assert torch.equal(z[part], z2) and torch.equal(arg[part], arg2), i
+        assert torch.equal(gx[part].view(torch.uint8), B.maxpool2d_backward(arg[part], gz[part], H, W, (k, k), (s, s), p).view(torch.uint8)), i
