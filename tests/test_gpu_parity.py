@@ -475,6 +475,33 @@ def test_dequantizing_samples_of_one_group_takes_little_longer(hf):
     assert us(131072, 256) < 2.25 * us(32768, 1024)
 
 
+@pytest.mark.parametrize("dtype,groups", [(torch.float32, 3), (torch.float32, 5), (torch.float32, 9), (torch.float32, 3193),
+                                          (torch.float16, 5), (torch.float16, 9), (torch.float16, 25), (torch.float16, 3193)])
+@pytest.mark.parametrize("hf", [B.ACTQ_HDR_F32, B.ACTQ_HDR_BF16])
+def test_large_tensors_of_odd_samples_equal_their_pieces(dtype, groups, hf):
+    """Samples of an odd number of whole groups have another order of tiles from 48 MiB on; their pieces have that of every tensor."""
+    D = 256 * groups
+    N = (50 << 20) // (D * torch.finfo(dtype).bits // 8) // 4 * 4
+    gen = torch.Generator(device="cuda:0").manual_seed(groups)
+    bits = (1 + torch.arange(N, device="cuda:0") * 5 % 8).to(torch.uint8)
+    size = bits.long() * (D // 8)
+    offsets = torch.cumsum(size, 0) - size
+    packed = torch.randint(0, 256, (int(size.sum()),), generator=gen, dtype=torch.uint8, device="cuda:0")
+    header = torch.rand(N, groups * 2, generator=gen, device="cuda:0")
+    if hf == B.ACTQ_HDR_BF16:
+        header = header.bfloat16().view(torch.int16)
+    assert N * D * torch.finfo(dtype).bits // 8 >= 48 << 20
+    out = torch.full((N * D + 512,), 7.0, dtype=dtype, device="cuda:0")
+    B.unpack_dequantize(packed, header.view(-1), bits, offsets, out[:N * D].view(N, D), hf=hf)
+    assert (out[N * D:] == 7.0).all()
+    step = (N + 2) // 3 // 4 * 4
+    for n in range(0, N, step):
+        part = slice(n, min(N, n + step))
+        want = torch.empty((part.stop - n, D), dtype=dtype, device="cuda:0")
+        B.unpack_dequantize(packed, header[part].reshape(-1), bits[part], offsets[part], want, hf=hf)
+        assert torch.equal(out[n * D:part.stop * D].view(-1, D).view(torch.uint8), want.view(torch.uint8)), n
+
+
 @pytest.mark.parametrize("hf", [B.ACTQ_HDR_F32, B.ACTQ_HDR_BF16])
 def test_quantizing_samples_of_three_groups_takes_no_longer(hf):
     """binary32, 134 MB of mixed widths.  A tile holds four groups: with the same number of wavefronts 0.75 of the work and the same
