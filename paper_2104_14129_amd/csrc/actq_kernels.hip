@@ -3381,13 +3381,16 @@ int launch_unpack_dequantize(const void* packed, uint64_t capacity, const void* 
 {
     const int64_t ng = (D + kGroup - 1) / kGroup;
     const bool lines = D * element_bytes(out_dtype) % 128 == 0 && reinterpret_cast<uintptr_t>(out) % 128 == 0;
-    // Samples of an odd number of whole groups: their tiles, of which one is short, neither alternate evenly over XCDs that take every eighth (two tiles
-    // per sample, a long and a short one, leave every second XCD nearly idle) nor fill the same 4 KiB of the output.  Large tensors take the runs
-    // of the samples that end inside a group (bfloat16 header, b = 2, us): binary32 [122, 817408] 76.8 -> 71.7, [11393, 2304] 25.9 -> 22.8, [20507, 1280]
-    // 29.0 -> 24.2; binary16 [64, 817408] 23.7 -> 22.8, [22786, 2304] 33.9 -> 25.8, [41015, 1280] 27.1 -> 24.9.  At eight bits -21 to +5 %.  Up to 16 MB
-    // the runs keep too few XCDs busy (+25 % at worst), at 26 MB -16 to +14 %; an even number of groups -5 to +4 %; at most half a tile 0 to +84 %.
-    const int64_t half_tile = (out_dtype == ACTQ_F16 ? kDqGroupsF16 : kDqGroupsF32) / 2;
-    const bool runs = lines && ng % 2 == 1 && ng > half_tile && N * D * element_bytes(out_dtype) >= int64_t(48) << 20;
+    // Samples whose last tile is short.  Where they are an even number of tiles, XCDs that take every eighth tile do not get alike: of two tiles per
+    // sample, a long and a short one, every second XCD gets the short ones and is nearly idle.  Where they are an odd number of groups, hardly a tile
+    // begins where 4 KiB of the output do.  Large tensors of both take the runs of the samples that end inside a group (bfloat16 header, b = 2, us):
+    // binary32 [122, 817408] 76.8 -> 71.7, [11393, 2304] 25.9 -> 22.8, [20507, 1280] 29.0 -> 24.2; binary16 [64, 817408] 23.7 -> 22.7, [22786, 2304] 33.9 -> 25.8,
+    // [41015, 1280] 27.1 -> 24.9; even numbers of groups: binary16 of 10 -22 %, 12 -18, 28 -8, 42 -9, binary32 of 6 -14, 14 -7, 22 -1; of more than six tiles
+    // or of whole ones -5 to +5 %.  At eight bits -21 to +5 %.  Up to 16 MB the runs keep too few XCDs busy (+25 % at worst), at 26 MB -16 to +14 %; samples of
+    // at most half a tile 0 to +84 %.
+    const int64_t per_tile = out_dtype == ACTQ_F16 ? kDqGroupsF16 : kDqGroupsF32, tiles = (ng + per_tile - 1) / per_tile;
+    const bool uneven = ng % 2 == 1 || (ng % per_tile != 0 && tiles % 2 == 0 && tiles <= 6);
+    const bool runs = lines && uneven && ng > per_tile / 2 && N * D * element_bytes(out_dtype) >= int64_t(48) << 20;
     const int layout = D % kGroup == 0 && !runs ? kWholeGroups : (lines ? kRaggedLines : kRagged);
     hipStream_t s = static_cast<hipStream_t>(stream);
     return by_sample_ranges(N, D, out_dtype == ACTQ_F16 ? kDqGroupsF16 : kDqGroupsF32, [&](int64_t n0, int64_t count) {

@@ -475,11 +475,11 @@ def test_dequantizing_samples_of_one_group_takes_little_longer(hf):
     assert us(131072, 256) < 2.25 * us(32768, 1024)
 
 
-@pytest.mark.parametrize("dtype,groups", [(torch.float32, 3), (torch.float32, 5), (torch.float32, 9), (torch.float32, 3193),
-                                          (torch.float16, 5), (torch.float16, 9), (torch.float16, 25), (torch.float16, 3193)])
+@pytest.mark.parametrize("dtype,groups", [(torch.float32, 3), (torch.float32, 5), (torch.float32, 6), (torch.float32, 9), (torch.float32, 3193),
+                                          (torch.float16, 5), (torch.float16, 9), (torch.float16, 10), (torch.float16, 28), (torch.float16, 3193)])
 @pytest.mark.parametrize("hf", [B.ACTQ_HDR_F32, B.ACTQ_HDR_BF16])
-def test_large_tensors_of_odd_samples_equal_their_pieces(dtype, groups, hf):
-    """Samples of an odd number of whole groups have another order of tiles from 48 MiB on; their pieces have that of every tensor."""
+def test_large_tensors_of_uneven_samples_equal_their_pieces(dtype, groups, hf):
+    """Whole groups of which the last tile is short have another order of tiles from 48 MiB on; their pieces have that of every tensor."""
     D = 256 * groups
     N = (50 << 20) // (D * torch.finfo(dtype).bits // 8) // 4 * 4
     gen = torch.Generator(device="cuda:0").manual_seed(groups)
