@@ -65,6 +65,7 @@ constexpr int kDqRaggedRun = 16;        //              ragged samples: consecut
 constexpr int kGsBlock = 256;           // statistics: threads per block [64 .. 1024: alike or slower]
 constexpr int kGsXcdMap = 0;
 constexpr int kGsRun = 16;              //             consecutive workgroups' tiles per XCD [1: 5 % slower; 8, 32 near; not powers of two: slower]
+constexpr int kGsRunHalf = 2;           //             binary16 tensors of whole tiles (group_stats_launch)
 constexpr int kQpXcdMap = 0;            // quantizer [tiles modulo 8: slower]
 constexpr int kQpRun = 16;              //           [1: 3 % slower; 32 alike]
 
@@ -1284,14 +1285,14 @@ __device__ __forceinline__ void sample_width_offset(const MultiCursor& c, uint32
 }
 
 
-// Sec. 4.1: Z = min, R = max - min per group; one tile of four groups per wavefront.  NT: non-temporal loads.
-template <typename T, bool RAGGED, bool NT, int CAPACITY>
+// Sec. 4.1: Z = min, R = max - min per group; one tile of four groups per wavefront.  NT: non-temporal loads.  RUN: consecutive workgroups' tiles per XCD.
+template <typename T, bool RAGGED, bool NT, int CAPACITY, int RUN = kGsRun>
 __global__ __launch_bounds__(kGsBlock) void group_stats_multi_kernel(MultiTable<CAPACITY> t)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const uint32_t wave = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)));
     MultiCursor c;
-    if (!multi_cursor<kGsBlock / kWave, kGsXcdMap, kGsRun, CAPACITY>(t, wave, c)) return;
+    if (!multi_cursor<kGsBlock / kWave, kGsXcdMap, RUN, CAPACITY>(t, wave, c)) return;
     const uint32_t ng = static_cast<uint32_t>((c.D + (kGroup - 1)) >> 8);
     const uint32_t g0 = c.tile * kTileGroups;
     const T* tile = device_pointer<const T>(c.x) + (static_cast<int64_t>(c.n) * static_cast<int64_t>(c.D) + (static_cast<int64_t>(g0) << 8));
@@ -3208,6 +3209,13 @@ static int group_stats_launch(const char* who, const actq_tensor* tensors, int32
             if constexpr (CAPACITY == 1) {
                 if (ragged) {
                     launch(group_stats_multi_kernel<T, true, kNt, 1>, grid, kGsBlock, s, t);
+                    return;
+                }
+                // Binary16, samples of whole tiles: every second workgroup fills a line of 128 bytes of either result, and runs of no more workgroups
+                // read 32 KiB per XCD in turn: [256, 802816] 59.4 -> 57.1 us, [13032, 15360] 58.0 -> 55.6, [257, 56320] 6.7 -> 6.6.  Elsewhere lines are
+                // shared by XCDs, [7551, 23808] 52.8 -> 56.7, and binary32 loses ([128, 802816] 57.8 -> 60.2); sets of tensors -4 to +1 %.
+                if (std::is_same<T, _Float16>::value && tensors[0].D % (kTileGroups * kGroup) == 0) {
+                    launch(group_stats_multi_kernel<_Float16, false, kNt, 1, kGsRunHalf>, grid, kGsBlock, s, t);
                     return;
                 }
             }

@@ -475,6 +475,16 @@ def test_dequantizing_samples_of_one_group_takes_little_longer(hf):
     assert us(131072, 256) < 2.25 * us(32768, 1024)
 
 
+@pytest.mark.parametrize("N,groups", [(1, 4), (31, 4), (33, 4), (1, 124), (5, 508), (517, 8), (1, 516), (3, 6), (100000, 4)])
+def test_statistics_of_whole_tiles_of_binary16(N, groups):
+    """Their tiles go to the XCDs in runs of their own (of 64 tiles in turn); [3, 6] are not whole tiles.  Extremes are exact in binary32."""
+    gen = torch.Generator(device="cuda:0").manual_seed(N + groups)
+    x = torch.randn(N, 256 * groups, generator=gen, device="cuda:0").half()
+    gmin, grange = B.group_stats(x)
+    v = x.view(N, groups, 256).float()
+    assert torch.equal(gmin.view(N, groups), v.amin(2)) and torch.equal(grange.view(N, groups), v.amax(2) - v.amin(2))
+
+
 @pytest.mark.parametrize("dtype,groups", [(torch.float32, 3), (torch.float32, 5), (torch.float32, 6), (torch.float32, 9), (torch.float32, 3193),
                                           (torch.float16, 5), (torch.float16, 9), (torch.float16, 10), (torch.float16, 28), (torch.float16, 3193)])
 @pytest.mark.parametrize("hf", [B.ACTQ_HDR_F32, B.ACTQ_HDR_BF16])
