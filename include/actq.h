@@ -370,6 +370,10 @@ int actq_maxpool2d_backward(const uint8_t* argmax, const void* grad_y, actq_dtyp
  * outside [1, 2^20], inputs outside [64, 2^20], outputs outside [2, 2^20] or a
  * tensor of more than 2^29 elements; ACTQ_EHIP if the launch fails.
  */
+#define ACTQ_LINEAR_MIN_INPUTS 64
+#define ACTQ_LINEAR_MIN_OUTPUTS 2
+#define ACTQ_LINEAR_MAX_EXTENT (1 << 20)
+#define ACTQ_LINEAR_MAX_ELEMENTS (1 << 29)
 int actq_linear_backward(const void* grad_y, const void* weight, const void* x, actq_dtype dt,
                          int64_t rows, int64_t inputs, int64_t outputs, void* grad_x,
                          void* grad_w, void* grad_b, void* stream);

@@ -430,9 +430,9 @@ int actq_linear_backward(const void* grad_y, const void* weight, const void* x, 
     if (int rc = check_dtype(who, dt)) return rc;
     if (!grad_y || (!grad_x && !grad_w) || (grad_x && !weight) || (grad_w && !x)) return fail(ACTQ_EINVAL, "%s: null pointer", who);
     if (grad_b && !grad_w) return fail(ACTQ_EINVAL, "%s: grad_b comes with grad_w only", who);
-    constexpr int64_t kMost = int64_t(1) << 20;
-    if (rows < 1 || inputs < 64 || outputs < 2 || rows > kMost || inputs > kMost || outputs > kMost || rows * outputs > kMost * 512 ||
-        rows * inputs > kMost * 512 || outputs * inputs > kMost * 512)
+    constexpr int64_t kExtent = ACTQ_LINEAR_MAX_EXTENT, kElements = ACTQ_LINEAR_MAX_ELEMENTS;
+    if (rows < 1 || inputs < ACTQ_LINEAR_MIN_INPUTS || outputs < ACTQ_LINEAR_MIN_OUTPUTS || rows > kExtent || inputs > kExtent || outputs > kExtent ||
+        rows * outputs > kElements || rows * inputs > kElements || outputs * inputs > kElements)
         return fail(ACTQ_EINVAL, "%s: rows, inputs and outputs must be in [1, 2^20], [64, 2^20] and [2, 2^20] and no tensor may have more than 2^29 elements", who);
     const uintptr_t elem = dt == ACTQ_F32 ? 4 : 2;
     if (!aligned(grad_y, elem) || !aligned(weight, elem) || !aligned(x, elem) || !aligned(grad_x, elem) || !aligned(grad_w, elem) || !aligned(grad_b, elem))

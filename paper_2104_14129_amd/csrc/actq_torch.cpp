@@ -644,7 +644,9 @@ bool in_memory(const Tensor& t, at::ScalarType type, c10::DeviceIndex device)
 // Sums over more than 2048 rows or outputs leave too few workgroups with long chains.
 bool one_launch(int64_t rows, int64_t inputs, int64_t outputs, at::ScalarType type)
 {
-    if (rows < 1 || rows > 2048 || outputs < 2 || outputs > 2048 || inputs < 64 || inputs > (int64_t(1) << 20)) return false;
+    if (rows < 1 || rows > 2048 || outputs < ACTQ_LINEAR_MIN_OUTPUTS || outputs > 2048 || inputs < ACTQ_LINEAR_MIN_INPUTS || inputs > ACTQ_LINEAR_MAX_EXTENT) return false;
+    // what the library refuses is torch's: a weight of more elements at batch 1, a wide input into two outputs
+    if (rows * inputs > ACTQ_LINEAR_MAX_ELEMENTS || outputs * inputs > ACTQ_LINEAR_MAX_ELEMENTS) return false;
     return rows * outputs * inputs <= (type == at::kHalf ? int64_t(1) << 31 : int64_t(1) << 30);
 }
 
@@ -679,6 +681,13 @@ bool fused_gradients(const Tensor& grad_y, const Tensor& weight, X x_of, at::Sca
          pointer(out.bias), current_stream());
     return true;
 }
+
+// (rows, inputs, outputs, whether binary16) -> whether the rule is for the launch
+PyObject* linear_one_launch_impl(PyObject* const* a)
+{
+    return PyBool_FromLong(one_launch(integer(a[0]), integer(a[1]), integer(a[2]), a[3] == Py_True ? at::kHalf : at::kFloat));
+}
+ACTQ_ENTRY(linear_one_launch, 4)
 
 // (grad_y, weight, x, whether x, weight, bias need theirs) -> their gradients (None where none is needed), or None if torch's operators have to serve
 PyObject* linear_gradients_impl(PyObject* const* a)
@@ -868,7 +877,7 @@ ACTQ_ENTRY(attach, 2)
 PyMethodDef methods[] = {
     ACTQ_METHOD(attach), ACTQ_METHOD(plain), ACTQ_METHOD(group_stats), ACTQ_METHOD(sample_sensitivity), ACTQ_METHOD(allocate_bits_device),
     ACTQ_METHOD(quantize_pack), ACTQ_METHOD(unpack_dequantize), ACTQ_METHOD(compress_mixed), ACTQ_METHOD(relu_forward), ACTQ_METHOD(relu_backward),
-    ACTQ_METHOD(maxpool2d_forward), ACTQ_METHOD(maxpool2d_backward), ACTQ_METHOD(linear_gradients), ACTQ_METHOD(linear), ACTQ_METHOD(relu), ACTQ_METHOD(maxpool2d),
+    ACTQ_METHOD(maxpool2d_forward), ACTQ_METHOD(maxpool2d_backward), ACTQ_METHOD(linear_one_launch), ACTQ_METHOD(linear_gradients), ACTQ_METHOD(linear), ACTQ_METHOD(relu), ACTQ_METHOD(maxpool2d),
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "actq_torch", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

@@ -21,6 +21,20 @@ def test_arguments_are_checked_before_the_launch():
         assert f(*[change.get(i, v) for i, v in enumerate(good)]) == B.ACTQ_EINVAL, change
 
 
+@pytest.mark.parametrize("half", [False, True])
+def test_the_rule_for_the_launch_accepts_nothing_that_the_library_refuses(half):
+    """Sizes are checked before the pointers' alignment: a misaligned pointer tells the two refusals apart, and nothing is launched."""
+    accepted = 0
+    for rows in (1, 2, 3, 4, 17, 128, 256, 257, 1023, 1024, 1025, 1536, 1537, 2047, 2048, 2049, 1 << 20):
+        for inputs in (1, 63, 64, 65, 1000, 4096, 65536, 1 << 17, 300000, 1 << 19, (1 << 20) - 1, 1 << 20, (1 << 20) + 1, 1 << 40):
+            for outputs in (1, 2, 3, 10, 64, 512, 768, 1000, 1024, 1025, 1536, 1792, 2047, 2048, 2049, 1 << 20):
+                if B.host().linear_one_launch(rows, inputs, outputs, half):
+                    accepted += 1
+                    rc = B.lib().actq_linear_backward(FAKE + 1, FAKE, FAKE, B.ACTQ_F16 if half else B.ACTQ_F32, rows, inputs, outputs, FAKE, FAKE, FAKE, None)
+                    assert rc == B.ACTQ_EINVAL and "aligned to their element size" in B.last_error(), (rows, inputs, outputs)
+    assert accepted > 300
+
+
 @pytest.fixture(autouse=True)
 def restore():
     saved = dict(L.config.__dict__)
