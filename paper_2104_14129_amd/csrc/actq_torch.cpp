@@ -628,11 +628,12 @@ struct LinearGradients {
     Tensor x, weight, bias;   // undefined where none was asked for
 };
 
-// A tensor whose memory is what it says: no mode, transform or subclass looks on, and nothing is applied lazily.
+// A tensor whose memory is all there is: no mode, transform or subclass looks on, no tangent of forward-mode differentiation goes with it,
+// and nothing is applied lazily.
 bool in_memory(const Tensor& t, at::ScalarType type, c10::DeviceIndex device)
 {
     return t.defined() && !at::isTensorSubclassLike(t) && t.is_cuda() && t.get_device() == device && t.scalar_type() == type && t.layout() == at::kStrided &&
-           t.is_contiguous() && !t.is_neg() && !t._is_zerotensor();
+           t.is_contiguous() && !t.is_neg() && !t._is_zerotensor() && !t._fw_grad(0).defined();
 }
 
 // Whether the library's one launch (actq_linear_backward) takes the place of two products and a sum of torch.  Each of those costs
@@ -651,7 +652,7 @@ bool one_launch(int64_t rows, int64_t inputs, int64_t outputs, at::ScalarType ty
 }
 
 // The gradients of y = x weight^T + bias by that launch on the current stream; false, and nothing done, where torch's own operators have
-// to serve: a graph of the gradients themselves, autocast, modes and transforms, operands that differ in type or are not plain memory,
+// to serve: a graph of the gradients themselves, tangents, autocast, modes and transforms, operands that differ in type or are not plain memory,
 // sizes beyond the rule.  `x` is asked for only once all else is settled.
 template <typename X>
 bool fused_gradients(const Tensor& grad_y, const Tensor& weight, X x_of, at::ScalarType type, int64_t inputs, bool need_x, bool need_weight, bool need_bias,

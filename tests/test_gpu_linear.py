@@ -4,6 +4,7 @@ import ctypes
 
 import pytest
 import torch
+import torch.autograd.forward_ad as forward_ad
 import torch.nn.functional as F
 
 from paper_2104_14129_amd import binding as B
@@ -91,9 +92,10 @@ def test_infinities_and_nan_reach_exactly_the_gradients_they_belong_to():
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("native", [True, False])
-@pytest.mark.parametrize("what", ["graph of the gradients", "expanded", "vmap", "autocast", "weight frozen", "bias only", "too narrow", "many rows", "three dimensions"])
+@pytest.mark.parametrize("what", ["graph of the gradients", "tangent", "expanded", "vmap", "autocast", "weight frozen", "bias only", "too narrow", "many rows", "three dimensions"])
 def test_calls_beyond_the_launch_are_served_as_before(what, native, monkeypatch):
     """Against the stock layer on the dequantized input (fixed widths of eight bits of values that they represent)."""
+    B.host()   # loaded, as the layers' own check leaves it
     monkeypatch.setattr(L, "_native", (lambda *t: True) if native else (lambda *t: False))
     L.config.mixed, L.config.bits = False, 8.0
     rows, inputs, outputs = (2049 if what == "many rows" else 12), (33 if what == "too narrow" else 256), 6
@@ -120,6 +122,13 @@ def test_calls_beyond_the_launch_are_served_as_before(what, native, monkeypatch)
             y = f(x)
             (gx,) = torch.autograd.grad(y, x, torch.ones_like(y), create_graph=True)
             results.append([gx.detach(), *torch.autograd.grad(gx.square().sum(), m.weight)])
+        elif what == "tangent":
+            y = f(x)
+            g, t = (torch.linspace(a, 1, y.numel(), device=DEV).reshape(y.shape) for a in (-1, -3))
+            with forward_ad.dual_level():
+                pairs = [forward_ad.unpack_dual(d) for d in torch.autograd.grad(y, inputs_of, forward_ad.make_dual(g, t))]
+            assert all(p.tangent is not None for p in pairs)
+            results.append([v.detach() for p in pairs for v in p])
         elif what == "vmap":
             y = f(x)
             basis = torch.eye(3, device=DEV)[:, :, None, None].expand(3, 3, *y.shape)[:, 0].contiguous()
