@@ -357,8 +357,8 @@ int actq_maxpool2d_backward(const uint8_t* argmax, const void* grad_y, actq_dtyp
  * Gradients of a linear layer y = x weight^T + bias (Sec. 3.2, Eq. (4)), x being
  * the dequantized context, in one launch:
  *   grad_x = grad_y weight, grad_w = grad_y^T x, grad_b = column sums of grad_y.
- * Products and sums are binary32 (of binary16 operands: rounded once at the end),
- * in a fixed order.
+ * Products and sums are binary32, those of grad_b binary64, in a fixed order; a
+ * result is rounded to its type once, at the end.
  *
  * grad_y  device, in  : [rows, outputs]    weight  device, in : [outputs, inputs]
  * x       device, in  : [rows, inputs]

@@ -299,7 +299,7 @@ __device__ __forceinline__ void product_tile(const Product<T>& p, uint32_t m0, u
         double total = 0.0;
 #pragma unroll
         for (int k = 0; k < kLinWaves; ++k) total += lds.bias[k][threadIdx.x];
-        if (m < p.M) bias[m] = static_cast<T>(static_cast<float>(total));
+        if (m < p.M) bias[m] = static_cast<T>(total);   // by way of binary32, binary16 would be rounded twice
     }
 }
 

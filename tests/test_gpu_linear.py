@@ -80,6 +80,22 @@ def test_gradients_against_64_bits(rows, inputs, outputs, dtype):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("rows", [3, 35, 64, 129])
+@pytest.mark.parametrize("dtype,terms,want", [
+    # 2^-24 above the middle of two neighbours in binary16 (and a tie in binary32, which falls to the middle), the middle itself, just below it
+    (torch.float16, (1.0, 2.0 ** -11, 2.0 ** -24), 1.0 + 2.0 ** -10), (torch.float16, (1.0, 2.0 ** -11, 0.0), 1.0), (torch.float16, (1.0, 2.0 ** -11, -2.0 ** -24), 1.0),
+    (torch.float16, (-1.0, -2.0 ** -11, -2.0 ** -24), -1.0 - 2.0 ** -10), (torch.float16, (60000.0, 60000.0, 0.0), float("inf")),
+    (torch.float32, (1.0, 2.0 ** -24, 2.0 ** -40), 1.0 + 2.0 ** -23), (torch.float32, (1.0, 2.0 ** -24, 0.0), 1.0)])
+def test_the_bias_gradient_is_rounded_once(dtype, terms, want, rows):
+    grad_y = torch.zeros(rows, 33, dtype=dtype, device=DEV)
+    grad_y[:1], grad_y[rows // 2:rows // 2 + 1], grad_y[-1:] = terms
+    x, weight = torch.zeros(rows, 64, dtype=dtype, device=DEV), torch.zeros(33, 64, dtype=dtype, device=DEV)
+    with torch.no_grad():
+        gb = B.host().linear_gradients(grad_y, weight, x, True, True, True)[2]
+    assert gb.dtype == dtype and gb.tolist() == [want] * 33
+
+
+@pytest.mark.gpu
 def test_infinities_and_nan_reach_exactly_the_gradients_they_belong_to():
     grad_y, weight, x = (torch.ones(s, device=DEV) for s in ((40, 35), (35, 70), (40, 70)))
     grad_y[39, 34], x[3, 69] = float("inf"), float("nan")
