@@ -1343,20 +1343,19 @@ static void maxpool_forward_typed(const T* x, int64_t planes, const PoolShape& p
         // over y, results that would have stayed in the Infinity Cache cost 10 to 20 % more.
         const bool nt = sizeof(T) == 4 ? p.kh == 3 || p.W % 4 == 0 : p.W % 8 == 0;
         const bool brief = forward_brief(planes, p, rows, sizeof(T));
-#define ACTQ_POOL_ROWS(K, PH, PW, S)                                                                                                                    \
-    do {                                                                                                                                                \
-        constexpr bool kBrief = K == 3 && (sizeof(T) == 4 || PH == 1);                                                                                  \
-        const auto with = [&](auto store, auto form) {                                                                                                  \
-            constexpr bool kNt = decltype(store)::value, kForm = decltype(form)::value;                                                                 \
-            if constexpr ((kNt || sizeof(T) == 2 || K == 2) && (kBrief || !kForm))                                                                      \
-                launch(maxpool2d_forward_rows_kernel<T, K, PH, PW, S, kNt, kForm>, blocks, kBlock, s, x, g, rows, y, argmax);                             \
-        };                                                                                                                                              \
-        const auto form = [&](auto store) {                                                                                                             \
-            if (kBrief && brief) with(store, std::true_type());                                                                                         \
-            else with(store, std::false_type());                                                                                                        \
-        };                                                                                                                                              \
-        if (nt) form(std::true_type());                                                                                                                 \
-        else form(std::false_type());                                                                                                                   \
+        // What the rules ask for and a geometry does not have takes the form that it has: every choice launches.
+#define ACTQ_POOL_ROWS(K, PH, PW, S)                                                                                                                   \
+    do {                                                                                                                                               \
+        constexpr bool kBrief = K == 3 && (sizeof(T) == 4 || PH == 1), kOrdinaryStores = sizeof(T) == 2 || K == 2;                                     \
+        const auto with = [&](auto store, auto form) {                                                                                                 \
+            launch(maxpool2d_forward_rows_kernel<T, K, PH, PW, S, decltype(store)::value, decltype(form)::value>, blocks, kBlock, s, x, g, rows, y, argmax);\
+        };                                                                                                                                             \
+        const auto form = [&](auto store) {                                                                                                            \
+            if (kBrief && brief) with(store, std::bool_constant<kBrief>());                                                                            \
+            else with(store, std::false_type());                                                                                                       \
+        };                                                                                                                                             \
+        if (nt || !kOrdinaryStores) form(std::true_type());                                                                                            \
+        else form(std::bool_constant<!kOrdinaryStores>());                                                                                             \
     } while (0)
         if (p.sh == 1) ACTQ_POOL_ROWS(3, 1, 1, 1);
         else if (p.kh == 2 && p.ph == 0) ACTQ_POOL_ROWS(2, 0, 0, 2);
@@ -1408,19 +1407,18 @@ static void maxpool_backward_typed(const uint8_t* argmax, const T* grad_y, int64
             return;
         }
         const bool brief = backward_brief(planes, p, rows, sizeof(T));
-#define ACTQ_POOL_ROWS(K, P, S)                                                                                                                         \
-    do {                                                                                                                                                \
-        const auto with = [&](auto store, auto form) {                                                                                                  \
-            constexpr bool kNt = decltype(store)::value, kForm = decltype(form)::value;                                                                 \
-            if constexpr (!kForm || (K == 3 && (S == 1 || sizeof(T) == 2)))                                                                   \
-                launch(maxpool2d_backward_rows_kernel<T, K, P, S, kNt, kForm>, blocks, kBlock, s, argmax, grad_y, g, rows, grad_x);                       \
-        };                                                                                                                                              \
-        const auto form = [&](auto store) {                                                                                                             \
-            if (brief) with(store, std::true_type());                                                                                                   \
-            else with(store, std::false_type());                                                                                                        \
-        };                                                                                                                                              \
-        if (rule.nt) form(std::true_type());                                                                                                            \
-        else form(std::false_type());                                                                                                                   \
+#define ACTQ_POOL_ROWS(K, P, S)                                                                                                                        \
+    do {                                                                                                                                               \
+        constexpr bool kBrief = K == 3 && (S == 1 || sizeof(T) == 2);                                                                                  \
+        const auto with = [&](auto store, auto form) {                                                                                                 \
+            launch(maxpool2d_backward_rows_kernel<T, K, P, S, decltype(store)::value, decltype(form)::value>, blocks, kBlock, s, argmax, grad_y, g, rows, grad_x);\
+        };                                                                                                                                             \
+        const auto form = [&](auto store) {                                                                                                            \
+            if (kBrief && brief) with(store, std::bool_constant<kBrief>());                                                                            \
+            else with(store, std::false_type());                                                                                                       \
+        };                                                                                                                                             \
+        if (rule.nt) form(std::true_type());                                                                                                           \
+        else form(std::false_type());                                                                                                                  \
     } while (0)
         if (p.sh == 1) ACTQ_POOL_ROWS(3, 1, 1);
         else if (p.kh == 2) ACTQ_POOL_ROWS(2, 0, 2);
