@@ -636,19 +636,32 @@ bool in_memory(const Tensor& t, at::ScalarType type, c10::DeviceIndex device)
            t.is_contiguous() && !t.is_neg() && !t._is_zerotensor() && !t._fw_grad(0).defined();
 }
 
-// Whether the library's one launch (actq_linear_backward) takes the place of two products and a sum of torch.  Each of those costs
-// the host 18 us (the sum 5) whatever its size, so the limits are those up to which the launch is no slower on the device, and a little
-// beyond, where the host still is the longer of the two.  Products and sum of torch -> the launch, device time (us), [rows, inputs, outputs]:
-//   binary32  [128, 2048, 1000] 26.0 -> 19.0   [512, 1024, 1000] 36.7 -> 30.9   [1024, 1024, 1024] 50 -> 55   [2048, 1024, 1024] 84 -> 107
-//             [16, 4096, 2048] 27.8 -> 29.2    [2048, 4096, 64] 49 -> 59        [2048, 64, 10] 22.9 -> 21.0
-//   binary16  [128, 2048, 1000] 26.8 -> 8.3    [1024, 1024, 1024] 32 -> 17      [2048, 1024, 1024] 43 -> 32   [2048, 4096, 2048] 99 -> 221
-// Sums over more than 2048 rows or outputs leave too few workgroups with long chains.
-bool one_launch(int64_t rows, int64_t inputs, int64_t outputs, at::ScalarType type)
+// Whether the library's one launch (actq_linear_backward) takes the place of torch's products and sum.  Each product costs the host 18 us
+// there and the sum 5, whatever their size; but in a step whose host runs ahead the device's time is what counts, so the launch is for the sizes at
+// which it is no slower there.  It loses where a product is few tiles (of 32 x 64) with a long sum, 10 ns per row or output in binary32
+// whatever the tiles, and where it is very many tiles, of which each writes little; and, in binary32, to the library's large products.  Products and sum
+// of torch -> the launch, device time (us), [rows, inputs, outputs]; in brackets: beyond the rule.
+//   binary32  long sums     [128, 1439, 1686] 35 -> 27  ([16, 64, 2048] 15.5 -> 20.8, [16, 576, 1408] 15 -> 17: over the outputs, with few rows)
+//                           [1501, 84, 34] 25 -> 17     ([2048, 64, 16] 18.9 -> 21.4, without the input's gradient [1465, 95, 4] 13.8 -> 16.3)
+//             many tiles    [171, 40958, 22] 41 -> 31   ([1444, 3613, 7] 30 -> 32, [2048, 4096, 64] 50 -> 53, [1038, 15201, 10] 55 -> 78, [8, 131072, 256] 71 -> 101)
+//             products      [128, 2048, 1000] 26 -> 19, [512, 1024, 1000] 37 -> 31  ([512, 2048, 1000] 54 -> 55, [1966, 764, 224] 46 -> 55, [1024, 1024, 1024] 52 -> 57)
+//   binary16                [128, 2048, 1000] 27 -> 8, [1024, 1024, 1024] 31 -> 17  ([301, 3881, 1433] 48 -> 52, [8, 21312, 1160] 65 -> 74, [2048, 16384, 10] 51 -> 108)
+// Without the sum, which torch makes a kernel of 4 to 8 us, less is gained: binary32 [656, 4992, 16] 15 -> 18, [16, 192, 1464] 12.7 -> 16.3, binary16 [36, 566, 1409]
+// 13 -> 15, [1237, 1704, 951] 40 -> 44.  One product alone is torch's: of the input's gradient [128, 2048, 1000] 10.9 -> 15.3, of the weight's [896, 640, 8] 6.4 -> 10.8.
+bool one_launch(int64_t rows, int64_t inputs, int64_t outputs, at::ScalarType type, bool need_x, bool need_bias)
 {
+    if (!need_x && !need_bias) return false;
     if (rows < 1 || rows > 2048 || outputs < ACTQ_LINEAR_MIN_OUTPUTS || outputs > 2048 || inputs < ACTQ_LINEAR_MIN_INPUTS || inputs > ACTQ_LINEAR_MAX_EXTENT) return false;
     // what the library refuses is torch's: a weight of more elements at batch 1, a wide input into two outputs
     if (rows * inputs > ACTQ_LINEAR_MAX_ELEMENTS || outputs * inputs > ACTQ_LINEAR_MAX_ELEMENTS) return false;
-    return rows * outputs * inputs <= (type == at::kHalf ? int64_t(1) << 31 : int64_t(1) << 30);
+    const int64_t columns = (inputs + 63) / 64, tiles_x = (rows + 31) / 32 * columns, tiles_w = (outputs + 31) / 32 * columns, products = rows * inputs * outputs;
+    if (type == at::kHalf) {
+        if (!need_bias) return outputs <= 1280 && tiles_x <= 2048 && tiles_w <= 2048 && products <= int64_t(1) << 30;
+        return tiles_x <= 2560 && tiles_w <= 2560 && products <= int64_t(1) << 31;
+    }
+    if (!need_bias) return rows <= 768 && outputs <= 768 && tiles_x <= 1024 && tiles_w <= 1024 && products <= int64_t(1) << 27;
+    const bool sums = (outputs <= 1280 || rows >= 128) && (rows <= 1024 || outputs >= 32);
+    return sums && tiles_x <= (rows <= 512 ? 4096 : 1500) && tiles_w <= 4096 && products < int64_t(1) << (rows <= 768 ? 29 : 28);
 }
 
 // The gradients of y = x weight^T + bias by that launch on the current stream; false, and nothing done, where torch's own operators have
@@ -658,20 +671,16 @@ template <typename X>
 bool fused_gradients(const Tensor& grad_y, const Tensor& weight, X x_of, at::ScalarType type, int64_t inputs, bool need_x, bool need_weight, bool need_bias,
                      LinearGradients& out)
 {
-    if (c10::GradMode::is_enabled() || at::autocast::is_autocast_enabled(at::kCUDA) || (!need_x && !need_weight)) return false;
-    if (need_bias && !need_weight) return false;
+    if (c10::GradMode::is_enabled() || at::autocast::is_autocast_enabled(at::kCUDA) || !need_weight) return false;
     const c10::DeviceIndex device = c10::hip::current_device();
     if ((type != at::kFloat && type != at::kHalf) || !in_memory(grad_y, type, device) || !in_memory(weight, type, device)) return false;
     if (grad_y.dim() < 1 || grad_y.numel() == 0 || weight.dim() != 2 || weight.size(0) != grad_y.size(-1) || weight.size(1) != inputs) return false;
     const int64_t outputs = weight.size(0), rows = grad_y.numel() / outputs;
-    if (!one_launch(rows, inputs, outputs, type)) return false;
-    Tensor x;
-    if (need_weight) {
-        x = x_of();
-        if (!in_memory(x, type, device) || x.numel() != rows * inputs) return false;
-        out.weight = empty_on(weight, {outputs, inputs}, type);
-        if (need_bias) out.bias = empty_on(weight, {outputs}, type);
-    }
+    if (!one_launch(rows, inputs, outputs, type, need_x, need_bias)) return false;
+    const Tensor x = x_of();
+    if (!in_memory(x, type, device) || x.numel() != rows * inputs) return false;
+    out.weight = empty_on(weight, {outputs, inputs}, type);
+    if (need_bias) out.bias = empty_on(weight, {outputs}, type);
     if (need_x) {
         std::vector<int64_t> shape = grad_y.sizes().vec();
         shape.back() = inputs;
@@ -683,12 +692,12 @@ bool fused_gradients(const Tensor& grad_y, const Tensor& weight, X x_of, at::Sca
     return true;
 }
 
-// (rows, inputs, outputs, whether binary16) -> whether the rule is for the launch
+// (rows, inputs, outputs, whether binary16, whether x and bias need theirs beside the weight) -> whether the rule is for the launch
 PyObject* linear_one_launch_impl(PyObject* const* a)
 {
-    return PyBool_FromLong(one_launch(integer(a[0]), integer(a[1]), integer(a[2]), a[3] == Py_True ? at::kHalf : at::kFloat));
+    return PyBool_FromLong(one_launch(integer(a[0]), integer(a[1]), integer(a[2]), a[3] == Py_True ? at::kHalf : at::kFloat, a[4] == Py_True, a[5] == Py_True));
 }
-ACTQ_ENTRY(linear_one_launch, 4)
+ACTQ_ENTRY(linear_one_launch, 6)
 
 // (grad_y, weight, x, whether x, weight, bias need theirs) -> their gradients (None where none is needed), or None if torch's operators have to serve
 PyObject* linear_gradients_impl(PyObject* const* a)

@@ -29,11 +29,29 @@ def test_the_rule_for_the_launch_accepts_nothing_that_the_library_refuses(half):
     for rows in (1, 2, 3, 4, 17, 128, 256, 257, 1023, 1024, 1025, 1536, 1537, 2047, 2048, 2049, 1 << 20):
         for inputs in (1, 63, 64, 65, 1000, 4096, 65536, 1 << 17, 300000, 1 << 19, (1 << 20) - 1, 1 << 20, (1 << 20) + 1, 1 << 40):
             for outputs in (1, 2, 3, 10, 64, 512, 768, 1000, 1024, 1025, 1536, 1792, 2047, 2048, 2049, 1 << 20):
-                if B.host().linear_one_launch(rows, inputs, outputs, half):
+                if any(B.host().linear_one_launch(rows, inputs, outputs, half, *need) for need in ((True, True), (True, False), (False, True))):
                     accepted += 1
                     rc = B.lib().actq_linear_backward(FAKE + 1, FAKE, FAKE, B.ACTQ_F16 if half else B.ACTQ_F32, rows, inputs, outputs, FAKE, FAKE, FAKE, None)
                     assert rc == B.ACTQ_EINVAL and "aligned to their element size" in B.last_error(), (rows, inputs, outputs)
     assert accepted > 300
+
+
+# Either side of the lines of the rule, [rows, inputs, outputs], gradients of the input and the bias asked for: the sizes beyond them
+# were measured slower on the device than torch's products and sum.
+@pytest.mark.parametrize("half,need,taken,left", [
+    (False, (True, True), [(128, 2048, 1000), (512, 1024, 1000), (127, 64, 1280), (128, 64, 2048), (1024, 64, 10), (2048, 64, 32), (512, 16384, 2), (513, 64 * 88, 2)],
+     [(512, 2048, 1000), (1024, 1024, 1024), (2048, 1024, 256), (2048, 4096, 64), (16, 4096, 2048), (127, 64, 1281), (769, 1024, 512), (1025, 64, 31), (513, 64 * 89, 2), (512, 131072, 256)]),
+    (False, (False, True), [(128, 2048, 1000), (1024, 64, 10)], [(1465, 95, 4), (16, 64, 2048)]),
+    (False, (True, False), [(128, 1024, 768), (768, 64, 10)], [(128, 2048, 1000), (769, 64, 10), (16, 64, 769), (656, 4992, 16)]),
+    (False, (False, False), [], [(128, 2048, 1000), (16, 64, 10)]),
+    (True, (True, True), [(128, 2048, 1000), (1024, 1024, 1024), (2048, 64, 2048), (2048, 2560, 10)], [(2048, 2561, 10), (301, 3881, 1433), (2048, 4096, 64), (2049, 64, 64)]),
+    (True, (True, False), [(128, 2048, 1000), (2048, 64, 1280)], [(36, 566, 1409), (2048, 2560, 10), (1237, 1704, 951)]),
+    (True, (False, False), [], [(128, 2048, 1000), (1, 64, 2)])])
+def test_the_rule_for_the_launch_leaves_what_torch_does_faster(half, need, taken, left):
+    for size in taken:
+        assert B.host().linear_one_launch(*size, half, *need), size
+    for size in left:
+        assert not B.host().linear_one_launch(*size, half, *need), size
 
 
 @pytest.fixture(autouse=True)
