@@ -3389,16 +3389,26 @@ int launch_unpack_dequantize(const void* packed, uint64_t capacity, const void* 
 {
     const int64_t ng = (D + kGroup - 1) / kGroup;
     const bool lines = D * element_bytes(out_dtype) % 128 == 0 && reinterpret_cast<uintptr_t>(out) % 128 == 0;
-    // Samples whose last tile is short.  Where they are an even number of tiles, XCDs that take every eighth tile do not get alike: of two tiles per
-    // sample, a long and a short one, every second XCD gets the short ones and is nearly idle.  Where they are an odd number of groups, hardly a tile
-    // begins where 4 KiB of the output do.  Large tensors of both take the runs of the samples that end inside a group (bfloat16 header, b = 2, us):
-    // binary32 [122, 817408] 76.8 -> 71.7, [11393, 2304] 25.9 -> 22.8, [20507, 1280] 29.0 -> 24.2; binary16 [64, 817408] 23.7 -> 22.7, [22786, 2304] 33.9 -> 25.8,
-    // [41015, 1280] 27.1 -> 24.9; even numbers of groups: binary16 of 10 -22 %, 12 -18, 28 -8, 42 -9, binary32 of 6 -14, 14 -7, 22 -1; of more than six tiles
-    // or of whole ones -5 to +5 %.  At eight bits -21 to +5 %.  Up to 16 MB the runs keep too few XCDs busy (+25 % at worst), at 26 MB -16 to +14 %; samples of
-    // at most half a tile 0 to +84 %.
-    const int64_t per_tile = out_dtype == ACTQ_F16 ? kDqGroupsF16 : kDqGroupsF32, tiles = (ng + per_tile - 1) / per_tile;
-    const bool uneven = ng % 2 == 1 || (ng % per_tile != 0 && tiles % 2 == 0 && tiles <= 6);
-    const bool runs = lines && uneven && ng > per_tile / 2 && N * D * element_bytes(out_dtype) >= int64_t(48) << 20;
+    // Samples of whole groups whose last tile is short.  Where they are an even number of tiles, XCDs that take every eighth tile do not get alike: of two
+    // tiles per sample, a long and a short one, every second XCD gets the short ones and is nearly idle.  Where they are an odd number of groups, hardly a
+    // tile begins where 4 KiB of the output do.  From 48 MiB on such tensors take the order of the samples that end inside a group, runs of sixteen workgroups
+    // per XCD, where that was faster at every width (us; widths the same everywhere or mixed with that mean, either header):
+    //   an even number of tiles up to six, of whose room an eighth (binary32: a quarter) is empty, at any width: binary16 [20507, 2560] 31.3 -> 24.4, at eight
+    //     bits 33.8 -> 27.5, [3627, 7168] 13.1 -> 12.6, at four 13.3 -> 13.4; binary32 [29296, 1280] 40.2 -> 32.9, at eight 38.4 -> 33.9, but at six with the
+    //     binary32 header [78125, 1280] 92 -> 97.  Less empty room, or more tiles: [3385, 7680] 12.2 -> 12.7, binary32 [30048, 3328] at a mean of four 82.1 -> 86.3;
+    //   odd numbers of groups, and binary32 with an eighth empty, at up to 3.25 bits per element: binary16 [32552, 4352] 0.85 to 0.99 of the time, [64, 817408]
+    //     23.7 -> 22.7, at three bits everywhere [5974, 4352] 14.6 -> 15.0; binary32 [11268, 3328] 36.7 -> 31.1, [16276, 2304] 35.8 -> 31.4, at worst
+    //     [18601, 5376] 79.5 -> 81.3.  At four bits and more [43402, 2304] 74 -> 84, binary16 at five [5974, 4352] 15.0 -> 16.3, though mixed widths gain
+    //     up to there.  The widths are on the device; what the stream may take is known;
+    //   long binary32 samples up to 160 MiB: [45, 817408] 0.91 to 0.99 of the time, [122, 817408] with mixed widths 71.8 -> 78.3.
+    // Up to 16 MB the runs keep too few XCDs busy (+25 % at worst), at 26 MB -16 to +14 %; samples of at most half a tile 0 to +84 %.
+    const bool half = out_dtype == ACTQ_F16;
+    const int64_t per_tile = half ? kDqGroupsF16 : kDqGroupsF32, tiles = (ng + per_tile - 1) / per_tile, room = tiles * per_tile, output = N * D * element_bytes(out_dtype);
+    const bool idle = tiles % 2 == 0 && tiles <= 6 && 8 * (room - ng) >= room;
+    const bool at_any_width = idle && (half || 4 * (room - ng) >= room);
+    const bool narrow = capacity <= static_cast<uint64_t>(N) * static_cast<uint64_t>(ng) * 104;   // bytes of a group at 3.25 bits
+    const bool at_narrow_widths = (idle || ng % 2 == 1) && (half || ng <= 128 || output <= int64_t(160) << 20);
+    const bool runs = lines && ng > per_tile / 2 && output >= int64_t(48) << 20 && (at_any_width || (narrow && at_narrow_widths));
     const int layout = D % kGroup == 0 && !runs ? kWholeGroups : (lines ? kRaggedLines : kRagged);
     hipStream_t s = static_cast<hipStream_t>(stream);
     return by_sample_ranges(N, D, out_dtype == ACTQ_F16 ? kDqGroupsF16 : kDqGroupsF32, [&](int64_t n0, int64_t count) {

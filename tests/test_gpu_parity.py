@@ -485,30 +485,39 @@ def test_statistics_of_whole_tiles_of_binary16(N, groups):
     assert torch.equal(gmin.view(N, groups), v.amin(2)) and torch.equal(grange.view(N, groups), v.amax(2) - v.amin(2))
 
 
-@pytest.mark.parametrize("dtype,groups", [(torch.float32, 3), (torch.float32, 5), (torch.float32, 6), (torch.float32, 9), (torch.float32, 3193),
-                                          (torch.float16, 5), (torch.float16, 9), (torch.float16, 10), (torch.float16, 28), (torch.float16, 3193)])
-@pytest.mark.parametrize("hf", [B.ACTQ_HDR_F32, B.ACTQ_HDR_BF16])
-def test_large_tensors_of_uneven_samples_equal_their_pieces(dtype, groups, hf):
-    """Whole groups of which the last tile is short have another order of tiles from 48 MiB on; their pieces have that of every tensor."""
+@pytest.mark.parametrize("dtype,groups", [(torch.float32, 3), (torch.float32, 5), (torch.float32, 6), (torch.float32, 9), (torch.float32, 14), (torch.float32, 129),
+                                          (torch.float32, 3193), (torch.float16, 5), (torch.float16, 9), (torch.float16, 10), (torch.float16, 28), (torch.float16, 3193)])
+@pytest.mark.parametrize("hf", [B.ACTQ_HDR_F32, B.ACTQ_HDR_BF16, B.ACTQ_HDR_TENSOR])
+@pytest.mark.parametrize("widths", [(1, 2, 3, 4), (1, 2, 3, 4, 5, 6, 7, 8)])
+def test_large_tensors_of_uneven_samples_equal_their_pieces(dtype, groups, hf, widths):
+    """Whole groups of which the last tile is short have another order of tiles from 48 MiB on, most of them up to 3.25 bits per element of
+    the stream's room; their pieces, and the same stream in a larger room, have that of every tensor."""
     D = 256 * groups
     N = (50 << 20) // (D * torch.finfo(dtype).bits // 8) // 4 * 4
     gen = torch.Generator(device="cuda:0").manual_seed(groups)
-    bits = (1 + torch.arange(N, device="cuda:0") * 5 % 8).to(torch.uint8)
+    bits = torch.tensor(widths, dtype=torch.uint8, device="cuda:0")[torch.arange(N, device="cuda:0") * 5 % len(widths)]
     size = bits.long() * (D // 8)
     offsets = torch.cumsum(size, 0) - size
-    packed = torch.randint(0, 256, (int(size.sum()),), generator=gen, dtype=torch.uint8, device="cuda:0")
-    header = torch.rand(N, groups * 2, generator=gen, device="cuda:0")
+    room = torch.randint(0, 256, (N * D,), generator=gen, dtype=torch.uint8, device="cuda:0")
+    packed = room[:int(size.sum())]
+    tensor = hf == B.ACTQ_HDR_TENSOR
+    header = torch.rand(1 if tensor else N, 2 if tensor else groups * 2, generator=gen, device="cuda:0")
     if hf == B.ACTQ_HDR_BF16:
         header = header.bfloat16().view(torch.int16)
     assert N * D * torch.finfo(dtype).bits // 8 >= 48 << 20
-    out = torch.full((N * D + 512,), 7.0, dtype=dtype, device="cuda:0")
-    B.unpack_dequantize(packed, header.view(-1), bits, offsets, out[:N * D].view(N, D), hf=hf)
-    assert (out[N * D:] == 7.0).all()
+    outs = []
+    for stream in (packed, room):
+        out = torch.full((N * D + 512,), 7.0, dtype=dtype, device="cuda:0")
+        B.unpack_dequantize(stream, header.view(-1), bits, offsets, out[:N * D].view(N, D), hf=hf)
+        assert (out[N * D:] == 7.0).all()
+        outs.append(out)
+    out = outs[0]
+    assert torch.equal(out.view(torch.uint8), outs[1].view(torch.uint8))
     step = (N + 2) // 3 // 4 * 4
     for n in range(0, N, step):
         part = slice(n, min(N, n + step))
         want = torch.empty((part.stop - n, D), dtype=dtype, device="cuda:0")
-        B.unpack_dequantize(packed, header[part].reshape(-1), bits[part], offsets[part], want, hf=hf)
+        B.unpack_dequantize(packed, (header if tensor else header[part]).reshape(-1), bits[part], offsets[part], want, hf=hf)
         assert torch.equal(out[n * D:part.stop * D].view(-1, D).view(torch.uint8), want.view(torch.uint8)), n
 
 
