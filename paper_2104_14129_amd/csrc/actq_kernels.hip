@@ -3212,11 +3212,13 @@ static int group_stats_launch(const char* who, const actq_tensor* tensors, int32
                     return;
                 }
                 // Binary16, samples of whole tiles: every second workgroup fills a line of 128 bytes of either result, and runs of no more workgroups
-                // read 32 KiB per XCD in turn: [256, 802816] 59.4 -> 57.1 us, [13032, 15360] 58.0 -> 55.6, [257, 56320] 6.7 -> 6.6.  Elsewhere lines are
+                // read 16 KiB per XCD in turn: [256, 802816] 59.4 -> 57.1 us, [13032, 15360] 58.0 -> 55.6, [257, 56320] 6.7 -> 6.6.  Elsewhere lines are
                 // shared by XCDs, [7551, 23808] 52.8 -> 56.7, and binary32 loses ([128, 802816] 57.8 -> 60.2); sets of tensors -4 to +1 %.
-                if (std::is_same<T, _Float16>::value && tensors[0].D % (kTileGroups * kGroup) == 0) {
-                    launch(group_stats_multi_kernel<_Float16, false, kNt, 1, kGsRunHalf>, grid, kGsBlock, s, t);
-                    return;
+                if constexpr (std::is_same<T, _Float16>::value) {
+                    if (tensors[0].D % (kTileGroups * kGroup) == 0) {
+                        launch(group_stats_multi_kernel<T, false, kNt, 1, kGsRunHalf>, grid, kGsBlock, s, t);
+                        return;
+                    }
                 }
             }
             launch(group_stats_multi_kernel<T, false, kNt, CAPACITY>, grid, kGsBlock, s, t);
