@@ -3211,10 +3211,11 @@ static int group_stats_launch(const char* who, const actq_tensor* tensors, int32
                     launch(group_stats_multi_kernel<T, true, kNt, 1>, grid, kGsBlock, s, t);
                     return;
                 }
-                // Binary16, samples of whole tiles: every second workgroup fills a line of 128 bytes of either result, and runs of no more workgroups
-                // read 16 KiB per XCD in turn: [256, 802816] 59.4 -> 57.1 us, [13032, 15360] 58.0 -> 55.6, [257, 56320] 6.7 -> 6.6.  Elsewhere lines are
-                // shared by XCDs, [7551, 23808] 52.8 -> 56.7, and binary32 loses ([128, 802816] 57.8 -> 60.2); sets of tensors -4 to +1 %.
-                if constexpr (std::is_same<T, _Float16>::value) {
+                // Binary16, samples of whole tiles, non-temporal loads: every second workgroup fills a line of 128 bytes of either result, and runs of no more
+                // workgroups read 16 KiB per XCD in turn: [256, 802816] 59.4 -> 57.1 us, [13032, 15360] 58.0 -> 55.6, all 1.5 to 5 % less.  Elsewhere lines are
+                // shared by XCDs, [7551, 23808] 52.8 -> 56.7, and binary32 loses ([128, 802816] 57.8 -> 60.2); sets of tensors -4 to +1 %.  With ordinary loads
+                // runs of two are up to 3 % behind from 100 MB on ([14352, 5120] 23.8 -> 24.5) and 0.05 to 0.1 of 2 us on the smallest tensors.
+                if constexpr (std::is_same<T, _Float16>::value && kNt) {
                     if (tensors[0].D % (kTileGroups * kGroup) == 0) {
                         launch(group_stats_multi_kernel<T, false, kNt, 1, kGsRunHalf>, grid, kGsBlock, s, t);
                         return;

@@ -475,9 +475,11 @@ def test_dequantizing_samples_of_one_group_takes_little_longer(hf):
     assert us(131072, 256) < 2.25 * us(32768, 1024)
 
 
-@pytest.mark.parametrize("N,groups", [(1, 4), (31, 4), (33, 4), (1, 124), (5, 508), (517, 8), (1, 516), (3, 6), (100000, 4)])
+@pytest.mark.parametrize("N,groups", [(1, 4), (31, 4), (33, 4), (1, 124), (5, 508), (517, 8), (1, 516), (3, 6), (73728, 4), (73729, 4), (145, 2052),
+                                      (2049, 148), (1, 294916), (49153, 6)])
 def test_statistics_of_whole_tiles_of_binary16(N, groups):
-    """Their tiles go to the XCDs in runs of their own (of 64 tiles in turn); [3, 6] are not whole tiles.  Extremes are exact in binary32."""
+    """Beyond 144 MiB (73728 samples of four groups) their tiles go to the XCDs in runs of their own (of 64 tiles in turn); six groups are not
+    whole tiles.  Extremes are exact in binary32."""
     gen = torch.Generator(device="cuda:0").manual_seed(N + groups)
     x = torch.randn(N, 256 * groups, generator=gen, device="cuda:0").half()
     gmin, grange = B.group_stats(x)
