@@ -818,15 +818,16 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_backward_rows_kernel(const u
     typedef typename std::conditional<BRIEF, uint32_t, int64_t>::type Index;
     uint32_t gy[MR][NO + 2];     // slot 1 + t: output column j0 + t
     uint32_t code[MR][NO + 2];
-    uint32_t c;
-    int32_t stretch;             // of S input rows
+    uint32_t c, plane = 0;       // plane: the ordinary form's
+    int32_t j0, stretch;         // the lane's first output column; its stretch of S input rows
     bool live;
-    Index at[MR], to;            // the lane's first element of every output row, and of its first input row
+    Index at[MR], to = 0;        // the lane's first element of every output row; of its first input row, BRIEF
     bool row_ok[MR];
     int64_t elems = q.elems;     // from grad_y and argmax on
     if constexpr (BRIEF) {
         const RowLane l = row_lane(q.total, q.chunks, q.by_chunks, q.rows, q.by_rows);
         c = l.c;
+        j0 = NO * static_cast<int32_t>(c);
         stretch = l.row;
         live = l.live;
         const uint32_t OW = static_cast<uint32_t>(g.OW);
@@ -852,20 +853,19 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_backward_rows_kernel(const u
         const uint32_t id = live ? idx : q.total - 1;
         const uint32_t strip = fastdiv(id, q.by_chunks);           // stretch of S input rows over all planes
         c = id - strip * q.chunks;
-        const uint32_t plane = fastdiv(strip, q.by_rows);
+        plane = fastdiv(strip, q.by_rows);
         stretch = static_cast<int32_t>(strip - plane * q.rows);
+        j0 = NO * static_cast<int32_t>(c);
 #pragma unroll
         for (int u = 0; u < MR; ++u) {
             const int32_t i = stretch + kFirstRow + u;
             row_ok[u] = i >= 0 && i < g.OH;
-            at[u] = (static_cast<int64_t>(plane) * g.OH + min(max(i, 0), g.OH - 1)) * g.OW + NO * static_cast<int32_t>(c);
+            at[u] = (static_cast<int64_t>(plane) * g.OH + min(max(i, 0), g.OH - 1)) * g.OW + j0;
         }
-        to = (static_cast<int64_t>(plane) * g.H + S * stretch) * g.W + static_cast<int64_t>(E) * c;
     }
-    const int32_t j0 = NO * static_cast<int32_t>(c);
-    const bool left_there = c > 0 && j0 - 1 < g.OW, right_there = c + 1 < q.chunks && j0 + NO < g.OW;
     Edge edge_gy[MR][2] = {}, edge_code[MR][2] = {};   // to the left, to the right
     if constexpr (BRIEF && S == 1) {
+        const bool left_there = c > 0 && j0 - 1 < g.OW, right_there = c + 1 < q.chunks && j0 + NO < g.OW;
 #pragma unroll
         for (int u = 0; u < MR; ++u) {
             edge_gy[u][0] = edge_element<true>(grad_y, at[u] - 1, left_there);
@@ -904,6 +904,7 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_backward_rows_kernel(const u
 #pragma unroll
     for (int u = 0; u < MR; ++u) {
         // the neighbours' columns first, as stored; then what does not exist is no position
+        const bool left_there = c > 0 && j0 - 1 < g.OW, right_there = c + 1 < q.chunks && j0 + NO < g.OW;
         if (kLeft) {
             if constexpr (BRIEF && S == 1) gy[u][0] = neighbour<true, GradientWord<T>>(gy[u][NO], edge_gy[u][0]);
             else gy[u][0] = neighbour<true, GradientWord<T>>(gy[u][NO], left_there, grad_y, at[u] - 1);
@@ -950,7 +951,9 @@ __global__ __launch_bounds__(kBlock) void maxpool2d_backward_rows_kernel(const u
         const vec_in out = rows[rr];
         const int32_t r = S * stretch + rr;
         if (!live || r >= g.H) continue;
-        T* dst = grad_x + (to + static_cast<Index>(rr) * static_cast<Index>(g.W));
+        T* dst = grad_x;
+        if constexpr (BRIEF) dst += to + static_cast<uint32_t>(rr) * static_cast<uint32_t>(g.W);
+        else dst += (static_cast<int64_t>(plane) * g.H + r) * g.W + static_cast<int64_t>(E) * c;   // at the start it costs 1 to 2 % (binary32 3x3/2/0)
         if (left >= E) {
             if (NT) __builtin_nontemporal_store(out, reinterpret_cast<vec_in*>(dst));
             else *reinterpret_cast<vec_in*>(dst) = out;
