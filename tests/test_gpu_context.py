@@ -388,12 +388,16 @@ def test_results_stored_through_the_caches_equal_those_that_are_not(mib, H, W, k
     assert torch.equal(mask[:n // 8], mask2)
 
 
-# The row kernels have a second form, chosen by the size of the image, its rows and its type: a tensor that takes one has to
-# agree with its pieces that take the other (small calls of any extent are compared with the oracle above).  Planes smaller than
-# a workgroup, rows of one and of many wavefronts, rows whose lanes divide a wavefront, and tensors that start between words.
+# The row kernels have a second form, chosen by the size of the image, its rows and its type: a tensor of 72 MiB has to agree with its
+# pieces of 9 MiB (small calls of any extent are compared with the oracle above).  The whole takes the second form and the pieces the first:
+# forward, 3x3 but binary16 without row padding, but binary32 rows whose lanes divide a wavefront and but binary16 3x3/1/1 on odd rows.
+# The whole takes the first form and the pieces the second: binary16 gradients at stride 2, binary16 3x3/1/1 gradients on odd rows below
+# 32 columns (three lanes to a row of 17 to 23 columns, so that rows cross wavefronts; one, two and four lanes do not) and binary32 ones of
+# rows whose lanes divide a wavefront.  Elsewhere both take the same form, at other places of the tensor.
+# Planes smaller than a workgroup, rows of one and of many wavefronts, and tensors that start between words.
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
 @pytest.mark.parametrize("k,s,p", [(3, 2, (1, 1)), (3, 2, (0, 0)), (3, 2, (0, 1)), (3, 1, (1, 1))])
-@pytest.mark.parametrize("H,W", [(3, 3), (7, 6), (15, 15), (1, 34), (28, 28), (63, 2), (33, 71), (113, 113), (9, 516)])
+@pytest.mark.parametrize("H,W", [(3, 3), (7, 6), (15, 15), (1, 34), (28, 28), (63, 2), (17, 17), (21, 21), (9, 23), (33, 71), (113, 113), (9, 516)])
 def test_maxpool_of_large_tensors_equals_that_of_their_pieces(H, W, k, s, p, dtype):
     if H + 2 * p[0] < k or W + 2 * p[1] < k:
         pytest.skip("the window does not fit")

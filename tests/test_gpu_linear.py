@@ -114,14 +114,15 @@ def test_the_bias_gradient_is_rounded_once(dtype, terms, want, rows):
 
 
 @pytest.mark.gpu
-def test_infinities_and_nan_reach_exactly_the_gradients_they_belong_to():
-    grad_y, weight, x = (torch.ones(s, device=DEV) for s in ((40, 35), (35, 70), (40, 70)))
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+def test_infinities_and_nan_reach_exactly_the_gradients_they_belong_to(dtype):
+    grad_y, weight, x = (torch.ones(s, device=DEV, dtype=dtype) for s in ((40, 35), (35, 70), (40, 70)))
     grad_y[39, 34], x[3, 69] = float("inf"), float("nan")
     with torch.no_grad():
         gx, gw, gb = B.host().linear_gradients(grad_y, weight, x, True, True, True)
     want = grad_y @ weight, grad_y.t().contiguous() @ x, grad_y.sum(0)
     for got, stock in zip((gx, gw, gb), want):
-        assert torch.equal(torch.nan_to_num(got, 1e6, 2e6, 3e6), torch.nan_to_num(stock, 1e6, 2e6, 3e6))
+        assert got.dtype == dtype and torch.equal(torch.nan_to_num(got.float(), 1e6, 2e6, 3e6), torch.nan_to_num(stock.float(), 1e6, 2e6, 3e6))
 
 
 @pytest.mark.gpu
@@ -175,3 +176,48 @@ def test_calls_beyond_the_launch_are_served_as_before(what, native, monkeypatch)
     for a, b in zip(*results):
         assert a.shape == b.shape and a.dtype == b.dtype
         assert torch.allclose(a, b, rtol=1e-4 if a.dtype == torch.float32 and what != "autocast" else 1e-2, atol=1e-4 * float(b.abs().max()))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("native", [True, False])
+@pytest.mark.parametrize("what,launch", [("plain", True), ("binary16", True), ("three dimensions", True), ("no bias", True), ("input needs none", True),
+                                         ("too narrow", False), ("many rows", False), ("long sums", False), ("weight frozen", False), ("weight alone", False),
+                                         ("expanded", False), ("graph of the gradients", False), ("tangent", False)])
+def test_the_launch_serves_the_calls_of_its_rule_and_no_others(what, launch, native, monkeypatch):
+    """Which of the two it was is told by the bits: their sums run in another order."""
+    B.host()
+    monkeypatch.setattr(L, "_native", (lambda *t: True) if native else (lambda *t: False))
+    L.config.mixed, L.config.bits = False, 8.0
+    dtype = torch.float16 if what == "binary16" else torch.float32
+    rows, inputs, outputs = {"too narrow": (40, 63, 200), "many rows": (2049, 256, 40), "long sums": (40, 256, 1300)}.get(what, (40, 512, 200))
+    gen = torch.Generator(device=DEV).manual_seed(rows + inputs)
+    m = L.QLinear(inputs, outputs, bias=what != "no bias", device=DEV, dtype=dtype)
+    x = torch.randint(0, 256, (rows // 2, 2, inputs) if what == "three dimensions" else (rows, inputs), generator=gen, device=DEV).to(dtype)
+    x[..., ::63] = 0.0
+    x[..., 1::63] = 255.0                      # every group spans 0 .. 255: the codes are the values
+    x.requires_grad_(what not in ("input needs none", "weight alone"))
+    m.weight.requires_grad_(what != "weight frozen")
+    if m.bias is not None:
+        m.bias.requires_grad_(what not in ("weight frozen", "weight alone"))
+    y = m(x)
+    grad_y = torch.randn(y.shape, generator=gen, device=DEV).to(dtype)
+    if what == "expanded":
+        grad_y = grad_y[:, :1].expand(y.shape)
+    wanted = [t for t in (x, m.weight, m.bias) if t is not None and t.requires_grad]
+    if what == "tangent":
+        with forward_ad.dual_level():
+            got = [forward_ad.unpack_dual(g).primal for g in torch.autograd.grad(y, wanted, forward_ad.make_dual(grad_y, grad_y))]
+    else:
+        got = torch.autograd.grad(y, wanted, grad_y, create_graph=what == "graph of the gradients")
+    with torch.no_grad():
+        weight, g2, x2, dense = m.weight.detach(), grad_y.reshape(-1, outputs), x.detach().reshape(-1, inputs), grad_y.contiguous()
+        by_torch = {id(x): grad_y.matmul(weight), id(m.weight): g2.t().matmul(x2), id(m.bias): g2.sum(0)}
+        made = [torch.empty_like(t) for t in (x, weight, weight[:, 0].contiguous())]
+        if inputs >= 64:
+            rc = B.lib().actq_linear_backward(dense.data_ptr(), weight.data_ptr(), x2.data_ptr(), B.ACTQ_F16 if dtype == torch.float16 else B.ACTQ_F32, dense.numel() // outputs,
+                                              inputs, outputs, *(t.data_ptr() for t in made), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+            assert rc == B.ACTQ_OK
+        by_launch = dict(zip((id(x), id(m.weight), id(m.bias)), made))
+        assert any(not torch.equal(by_torch[id(t)], by_launch[id(t)]) for t in wanted), "the bits do not tell"
+        for t, g in zip(wanted, got):
+            assert torch.equal(g, (by_launch if launch else by_torch)[id(t)])
