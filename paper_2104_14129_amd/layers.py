@@ -9,7 +9,7 @@ Everything that touches the saved activations runs in libactq through `binding`:
 statistics, sensitivities, the device-side bit allocator, quantize + pack, unpack + dequantize,
 the ReLU bit mask and the max-pooling positions.  torch supplies the layers' own arithmetic
 (GEMM, convolution and batch-norm forward / backward) and the autograd plumbing; the gradients of
-a linear layer of up to a few billion products are one launch of the library.  There is no
+a small linear layer are one launch of the library.  There is no
 CPU path: tensors must live on the GPU.
 """
 from __future__ import annotations
